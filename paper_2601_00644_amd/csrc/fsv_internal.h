@@ -163,6 +163,7 @@ int fsv_check_batch(fsv_ctx *c, const fsv_batch *b, bool need_kv, bool need_samp
 int fsv_launch_build_rows(fsv_ctx *c, const fsv_batch *b, int M, hipStream_t s);
 int fsv_launch_sampler(fsv_ctx *c, const void *logits, int logits_dtype, const fsv_batch *b, const fsv_result *r,
                        int M, bool with_rollback, hipStream_t s);
+int fsv_launch_draft_law(fsv_ctx *c, const float *z, const fsv_batch *b, int all_rows, float *q, hipStream_t s);
 int fsv_launch_rollback(fsv_ctx *c, const fsv_batch *b, const int32_t *accepted, const fsv_result *r, hipStream_t s);
 // path_f32.hip
 int fsv_f32_create(fsv_ctx *c, const fsv_weights *w);

@@ -600,7 +600,7 @@ __global__ void k_pack_q(int H, int Hkv, int hd, const uint16_t *__restrict__ q,
 }
 
 // ---------------------------------------------------------------------------------------------
-// head of the draft model (Sec. IV-A: two-layer MLP + vocabulary projection) and its law
+// head of the draft model (Sec. IV-A: two-layer MLP + vocabulary projection); its law is in sampler.hip
 // ---------------------------------------------------------------------------------------------
 // sum of the split partials of a head projection (slice order), optional silu, stored as the next projection's operand
 template <int SILU>
@@ -624,43 +624,6 @@ __global__ void k_head_act(const float *__restrict__ part, int S, int Mpad, int 
     }
     out[tile_unit(r, k0, KB)] = make_uint4(o[0], o[1], o[2], o[3]);
   }
-}
-
-// q = softmax(z / T_b) of the draft's logits rows, fp32: one block per logits row.  all_rows 0: the laws the verification
-// call takes (draft i+1 of request b from row i < gamma_b, written to q row draft_offsets[b] + i); 1: every row.
-__global__ __launch_bounds__(256) void k_softmax_q(const float *__restrict__ z, int V, const int32_t *__restrict__ row_req,
-                                                   const int32_t *__restrict__ row_idx, const int32_t *__restrict__ off,
-                                                   const float *__restrict__ temperature, int all_rows, float *__restrict__ q) {
-  const int m = blockIdx.x, tid = threadIdx.x, b = row_req[m], i = row_idx[m];
-  const float T = temperature[b];
-  if (!(T > 0.f)) return;                                   // greedy requests need no law
-  if (!all_rows && i >= off[b + 1] - off[b]) return;        // the last row of a request scores no draft
-  const float *zr = z + (size_t)m * V;
-  float *qr = q + (size_t)(all_rows ? m : m - b) * V;
-  __shared__ float s_f[4];
-  __shared__ double s_d[4];
-  float mx = -INFINITY;
-  for (int k = tid; k < V; k += 256) mx = fmaxf(mx, zr[k]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  if ((tid & 63) == 0) s_f[tid >> 6] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(s_f[0], s_f[1]), fmaxf(s_f[2], s_f[3]));
-  const float k2 = kLog2eF / T;
-  double sum = 0.0;
-  for (int k0 = tid; k0 < V; k0 += 256 * 8) {   // eight terms in fp32, the groups in fp64
-    float g = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (k0 + j * 256 < V) g += __builtin_amdgcn_exp2f((zr[k0 + j * 256] - mx) * k2);
-    sum += (double)g;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-  if ((tid & 63) == 0) s_d[tid >> 6] = sum;
-  __syncthreads();
-  const float inv = (float)(1.0 / ((s_d[0] + s_d[1]) + (s_d[2] + s_d[3])));
-  for (int k = tid; k < V; k += 256) qr[k] = __builtin_amdgcn_exp2f((zr[k] - mx) * k2) * inv;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1008,10 +971,7 @@ int fsv_bf16_draft_probs(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl
                          float *logits, hipStream_t s) {
   int rc = fsv_bf16_forward(c, b, plan, M, logits, 1, s);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_softmax_q, dim3(M), dim3(256), 0, s, logits, c->d.vocab, c->row_req, c->row_idx, b->draft_offsets,
-                     b->temperature, all_rows, q_out);
-  FSV_HIP(c, hipGetLastError());
-  return FSV_OK;
+  return fsv_launch_draft_law(c, logits, b, all_rows, q_out, s);
 }
 
 // Copy a set of adapters into library-owned tables [layer][adapter][...] (replacing any earlier set).

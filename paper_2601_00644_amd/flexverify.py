@@ -283,7 +283,10 @@ class Context:
         """(q, logits or None): the draft model's laws for the rows of `batch` on the draft's one-layer KV pools."""
         B, G = batch.batch, batch.rows - batch.batch
         n = batch.rows if rows_mode == DRAFT_Q_ALL else G
-        q = torch.zeros((max(n, 1), self.cfg.vocab), dtype=torch.float32, device="cuda")
+        # rows of greedy requests are left untouched by the call: they come back as zeros
+        t = batch.temperature_host
+        whole = n > 0 and t is not None and bool((t > 0).all())
+        q = (torch.empty if whole else torch.zeros)((max(n, 1), self.cfg.vocab), dtype=torch.float32, device="cuda")
         lg = torch.empty((batch.rows, self.cfg.vocab), dtype=torch.float32, device="cuda") if want_logits else None
         b = batch.struct()
         self._check(lib().fsv_draft_probs(self._h, C.byref(b), int(rows_mode), C.c_void_p(q.data_ptr()),
