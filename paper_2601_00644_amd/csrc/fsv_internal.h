@@ -73,6 +73,7 @@ struct fsv_ctx {
   float *logits = nullptr;  // [max_rows][vocab] fp32 when the caller passes no logits_out
   int strip_pad_bytes = 8192;   // bf16 path: padding between the weight strips of a re-tiled matrix (FSV_STRIP_PAD_KIB overrides)
   int gemm_ncw_force = 0;       // bf16 path: 2..4 = weight strips per GEMM block fixed (FSV_GEMM_NCW, a measurement and test knob)
+  int gemm_wide_force = -1;     // bf16 path: FSV_GEMM_WIDE, a measurement and test knob: 0 = never the many-row kernel, 2..4 = always, with that many row tiles per wave
   float os_lm_head = 1.0f;      // bf16 path: inverse of the power of two the fp16 LM-head matrix carries
   uint32_t *absmax = nullptr;   // bf16 path: one word for the largest weight magnitude of the matrix being converted
   void *buf_a = nullptr, *buf_qkv = nullptr, *buf_q = nullptr, *buf_att = nullptr, *buf_gu = nullptr,
@@ -189,7 +190,7 @@ int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl
 // 1 = SwiGLU to the bf16 operand order, 2 = fp32 rows [M][N]
 int fsv_bf16_gemm_init(fsv_ctx *c);
 int fsv_bf16_gemm(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, void *out, int N, int K, int NTpad, int M,
-                  int splits, int KBo, int f16, float oscale, int ncw, hipStream_t st);
+                  int splits, int KBo, int f16, float oscale, int ncw, int wide, hipStream_t st);
 // path_bf16.hip
 int fsv_bf16_create(fsv_ctx *c, const fsv_weights *w);
 int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, float *logits, int draft, hipStream_t s);

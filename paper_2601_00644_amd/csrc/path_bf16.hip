@@ -656,7 +656,7 @@ gemm_shape shape_of(const fsv_ctx *c, int which) {
 
 // How a projection is cut into blocks: compute waves (weight strips of 32 features) per block and K splits.
 struct gemm_launch {
-  int ncw, splits;
+  int ncw, splits, wide = 0;   // wide: row tiles per wave of the many-row kernel (0 = the weight-streaming kernel)
 };
 
 // K splits so that feature blocks x splits x row blocks comes to about one block per compute unit (a block fills
@@ -676,6 +676,45 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
   return sp;
 }
 
+// The many-row kernel: row tiles per wave (a block covers twice as many) and K splits, by the time they are expected to
+// take.  A block's time is its stages (32 contraction elements) times the time of one plus kWideFixed for its first fills
+// and its result; a stage takes longer the more compute units are busy, because the matrix cores then lower the clock
+// (1.9 GHz with all of them at work against 2.4): base + slope x (busy share)^2, fitted to launches of 16 .. 256 blocks of
+// the 8B projections at 200 .. 2048 rows (within 5 % of all of them: 4 tiles 0.53 .. 0.89 us, 3 tiles 0.40 .. 0.69,
+// 2 tiles 0.32 .. 0.47).  Every split adds a set of partial sums to write and read back at about 5 TB/s.
+constexpr int kWideTiles = 9;   // row tiles from which on the many-row kernel is taken, see pick_launch
+constexpr double kWideBase[5] = {0, 0, 0.32, 0.40, 0.53}, kWideSlope[5] = {0, 0, 0.15, 0.29, 0.36}, kWideFixed = 5.0;   // us
+// The weight-streaming kernel's blocks (128 features x 96 or 128 rows) by the same measure: less work per block, so a
+// launch that fills the chip exactly once with them (500 rows, output projection: 24 us against 33) is theirs.
+constexpr double kNarrowBase[5] = {0, 0, 0, 0.17, 0.19}, kNarrowSlope[5] = {0, 0, 0, 0.06, 0.08};
+
+gemm_launch pick_wide(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow) {
+  const int nchunks = s.K / KCHUNK, nb = fsv_ceil_div(s.NTpad, 8);
+  auto expected = [&](int blocks, int sp, double base, double slope) {
+    const int full = blocks / c->n_cus, rest = blocks % c->n_cus;
+    const double stages = fsv_ceil_div(nchunks, sp) * (KCHUNK / 32), busy = (double)rest / c->n_cus;
+    double us = full * (stages * (base + slope) + kWideFixed);
+    if (rest) us += stages * (base + slope * busy * busy) + kWideFixed;
+    return allow ? us + sp * (double)Mt * 32 * s.N * 8 / 5e6 : us;
+  };
+  const int rb = fsv_ceil_div(Mt, 4), rt = fsv_ceil_div(Mt, rb);   // row blocks of the weight-streaming kernel
+  gemm_launch best{4, pick_splits(c, s, Mt, allow, 4)};
+  double best_us = -1;
+  if (c->gemm_wide_force <= 0)
+    best_us = expected(fsv_ceil_div(s.NTpad, 4) * best.splits * rb, best.splits, kNarrowBase[rt], kNarrowSlope[rt]);
+  for (int mt = 4; mt >= 2; --mt) {
+    if (c->gemm_wide_force > 0 && mt != c->gemm_wide_force) continue;
+    for (int sp = 1; sp <= (allow ? min(8, nchunks) : 1); ++sp) {
+      const double us = expected(nb * sp * fsv_ceil_div(Mt, 2 * mt), sp, kWideBase[mt], kWideSlope[mt]);
+      if (best_us < 0 || us < best_us) {
+        best = gemm_launch{4, sp, mt};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
 // With one row block (up to 128 rows) a projection is bound by streaming its weights, every wave streams its own strip
 // and what counts is that all compute units take part: among four, three and two strips per block take the one with
 // the least serial work per compute unit, rounds of blocks x strips per block x granules per split (8B shapes: q|k|v
@@ -683,6 +722,7 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
 // 256 of two strips).  Ties keep the larger block.  With several row blocks the matrix cores are the bound and a
 // block keeps one compute wave per SIMD.
 gemm_launch pick_launch(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow) {
+  if (c->gemm_wide_force > 0 || (c->gemm_wide_force < 0 && !c->gemm_ncw_force && Mt >= kWideTiles)) return pick_wide(c, s, Mt, allow);
   if (c->gemm_ncw_force) return gemm_launch{c->gemm_ncw_force, pick_splits(c, s, Mt, allow, c->gemm_ncw_force)};
   gemm_launch best{4, pick_splits(c, s, Mt, allow, 4)};
   if (Mt > 4) return best;
@@ -742,7 +782,7 @@ template <int EPI>
 int launch_gemm(fsv_ctx *c, int cls, const void *Wp, const void *Ap, void *out, const gemm_shape &s, int M, gemm_launch gl,
                 hipStream_t st, float oscale = 1.0f) {
   return fsv_bf16_gemm(c, cls, EPI, Wp, Ap, out, s.N, s.K, s.NTpad, M, gl.splits, (EPI == EPI_SWIGLU) ? c->d.d_ffn / 16 : 0,
-                       s.f16, oscale, gl.ncw, st);
+                       s.f16, oscale, gl.ncw, gl.wide, st);
 }
 
 size_t layer_stride(const fsv_ctx *c, int num_pages) {
@@ -768,6 +808,10 @@ int fsv_bf16_create(fsv_ctx *c, const fsv_weights *w) {
   if (const char *e = getenv("FSV_GEMM_NCW")) {   // read before anything is sized by pick_launch
     const int v = atoi(e);
     if (v >= 2 && v <= 4) c->gemm_ncw_force = v;
+  }
+  if (const char *e = getenv("FSV_GEMM_WIDE")) {
+    const int v = atoi(e);
+    if (v == 0 || (v >= 2 && v <= 4)) c->gemm_wide_force = v;
   }
   if ((rc = copy_dev(c, &c->embed, w->embed, (size_t)2 * d.vocab * d.d_model))) return rc;
   if ((rc = copy_dev(c, &c->final_norm, w->final_norm, (size_t)2 * d.d_model))) return rc;
