@@ -186,7 +186,7 @@ int fsv_verify(fsv_ctx *c, const fsv_batch *b, const fsv_result *r, void *stream
   fsv_attn_plan pl;
   int rc = (c->d.dtype == FSV_F32) ? fsv_f32_check(c, b) : fsv_bf16_attn_plan_host(c, b, &pl);
   if (rc) return rc;
-  if ((rc = fsv_launch_build_rows(c, b, M, s))) return rc;
+  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, b, M, s))) return rc;   // (the bf16 path sets its rows up itself)
   rc = (c->d.dtype == FSV_F32) ? fsv_f32_forward(c, b, M, logits, s) : fsv_bf16_forward(c, b, &pl, M, logits, 0, s);
   if (rc) return rc;
   return fsv_launch_sampler(c, logits, FSV_F32, b, r, M, true, s);
@@ -204,7 +204,7 @@ int fsv_prefill(fsv_ctx *c, const fsv_batch *b, float *logits_out, void *stream)
   fsv_attn_plan pl;
   int rc = (c->d.dtype == FSV_F32) ? fsv_f32_check(c, b) : fsv_bf16_attn_plan_host(c, b, &pl);
   if (rc) return rc;
-  if ((rc = fsv_launch_build_rows(c, b, M, s))) return rc;
+  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, b, M, s))) return rc;
   return (c->d.dtype == FSV_F32) ? fsv_f32_forward(c, b, M, logits, s) : fsv_bf16_forward(c, b, &pl, M, logits, 0, s);
 }
 
@@ -308,7 +308,6 @@ int fsv_draft_probs(fsv_ctx *c, const fsv_batch *b, int32_t rows_mode, float *q_
   int rc = fsv_bf16_attn_plan_host(c, b, &pl);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
-  if ((rc = fsv_launch_build_rows(c, b, M, s))) return rc;
   return fsv_bf16_draft_probs(c, b, &pl, M, rows_mode == FSV_DRAFT_Q_ALL, q_out, logits_out ? logits_out : c->logits, s);
 }
 
@@ -335,9 +334,9 @@ int fsv_attention(fsv_ctx *c, int32_t layer, const void *q, const fsv_batch *b, 
   fsv_batch bb = *b;
   bb.last_token = nullptr;
   bb.draft_tokens = nullptr;
-  if ((rc = fsv_launch_build_rows(c, &bb, M, s))) return rc;
+  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, &bb, M, s))) return rc;
   return (c->d.dtype == FSV_F32) ? fsv_f32_attention(c, layer, q, b, M, out, s)
-                                 : fsv_bf16_attention(c, layer, q, b, &pl, M, out, s);
+                                 : fsv_bf16_attention(c, layer, q, &bb, &pl, M, out, s);
 }
 
 int fsv_profile_enable(fsv_ctx *c, uint32_t class_mask) {

@@ -58,36 +58,109 @@ __device__ __host__ inline int attn_parts(int n, int tpw, int w16, int *tp) {
 // length, drafts, first row, (pad), and the physical pages of the part's first two tiles -- a wave fetches it with three
 // scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
 constexpr int kDescInts = 12;
-__global__ void k_attn_plan(int B, int tpw, int group, int w2, int w3, const int32_t *__restrict__ seq_lens,
-                            const int32_t *__restrict__ off, const int32_t *__restrict__ page_table, int max_pages,
-                            int num_pages, int32_t *__restrict__ part_prefix, int32_t *__restrict__ part_desc, int map_cap) {
-  if (blockIdx.x != 0) return;
-  __shared__ int total;
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int b = 0; b < B; ++b) {
-      const int L = seq_lens[b], gamma = off[b + 1] - off[b], nk = L + gamma + 1, n = (nk + 31) >> 5;
-      const int rtc = (group * (gamma + 1) + 31) >> 5;
-      int tp;
-      const int s = attn_parts(n, tpw, rtc <= 1 ? 16 : rtc == 2 ? w2 : w3, &tp);
-      part_prefix[b] = run;
-      for (int p = 0; p < s && run + p < map_cap; ++p) {
-        int32_t *d = part_desc + (size_t)(run + p) * kDescInts;
-        d[0] = b; d[1] = p * tp; d[2] = min(n, (p + 1) * tp) - p * tp; d[3] = s;
-        d[4] = L; d[5] = gamma; d[6] = off[b] + b; d[7] = 0;
-      }
-      run += s;
+// Everything the forward's kernels look up about a call, in one launch: the attention schedule (block 0), and for every row
+// its request, index, position and token and the cos / sin of its rotation angles (the other blocks; the angles depend on the
+// row's position only, not on the layer: tab[(row * half + i) * 2 + {0, 1}], formed and reduced in fp64).
+// Bound by latency: a load of the lengths, a scan or search in LDS, a load of the page ids, the stores.  One thread walking
+// the requests, and a launch each for rows and angles, took 13 + 4.5 + 4.5 us for 16 requests and 82 + 6 + 6 for 128; this
+// takes 6 and 8.
+constexpr int kSetupThreads = 1024, kSetupB = 2048;   // requests whose prefix sums are kept in LDS (more are searched in memory)
+struct setup_args {
+  int B, tpw, group, w2, w3, max_pages, num_pages, map_cap, M, half, V;
+  const int32_t *seq_lens, *off, *page_table, *last_token, *draft;
+  const double *inv_freq;
+  int32_t *part_prefix, *part_desc, *row_req, *row_idx, *row_pos, *row_tok;
+  float *tab;
+};
+__global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
+  __shared__ int32_t s_pre[kSetupB + 1];
+  __shared__ int32_t s_w[kSetupThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, B = p.B;
+  // the last index b with pre[b] + step * b <= x, b in [0, B)
+  auto find = [&](const int32_t *pre, int step, int x) {
+    int lo = 0, hi = B;   // pre[lo] <= x < pre[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (pre[mid] + step * mid <= x) lo = mid; else hi = mid;
     }
-    part_prefix[B] = run;
-    total = min(run, map_cap);
+    return lo;
+  };
+  if (blockIdx.x > 0) {   // ---- rows ----
+    const bool in_lds = B <= kSetupB;
+    if (in_lds) {
+      for (int b = tid; b <= B; b += kSetupThreads) s_pre[b] = p.off[b];
+      __syncthreads();
+    }
+    const int32_t *off = in_lds ? s_pre : p.off;
+    const int t = (int)(blockIdx.x - 1) * kSetupThreads + tid, r = t / p.half, i = t - r * p.half;
+    if (r >= p.M) return;
+    const int b = find(off, 1, r), idx = r - off[b] - b, pos = p.seq_lens[b] + idx;
+    if (i == 0) {
+      p.row_req[r] = b;
+      p.row_idx[r] = idx;
+      p.row_pos[r] = pos;
+      const int tok = (idx == 0) ? (p.last_token ? p.last_token[b] : 0) : (p.draft ? p.draft[r - b - 1] : 0);
+      p.row_tok[r] = min(max(tok, 0), p.V - 1);
+    }
+    if (p.tab) {
+      double sn, cs;
+      sincos((double)pos * p.inv_freq[i], &sn, &cs);
+      reinterpret_cast<float2 *>(p.tab)[t] = make_float2((float)cs, (float)sn);
+    }
+    return;
   }
-  __syncthreads();   // the records written above are read back below by other threads of this block
-  for (int p = threadIdx.x; p < total; p += blockDim.x) {
-    int32_t *d = part_desc + (size_t)p * kDescInts;
-    const int b = d[0], t0 = d[1], npg = (d[4] + d[5] + 1 + 15) >> 4;
-    const int32_t *pt = page_table + (size_t)b * max_pages;
+  // ---- attention schedule ----
+  auto parts_of = [&](int b, int &L, int &gamma, int &n, int &tp) {
+    L = p.seq_lens[b];
+    gamma = p.off[b + 1] - p.off[b];
+    n = (L + gamma + 1 + 31) >> 5;
+    const int rtc = (p.group * (gamma + 1) + 31) >> 5;
+    return attn_parts(n, p.tpw, rtc <= 1 ? 16 : rtc == 2 ? p.w2 : p.w3, &tp);
+  };
+  int run = 0;
+  for (int b0 = 0; b0 < B; b0 += kSetupThreads) {
+    const int b = b0 + tid;
+    int L, gamma, n, tp;
+    const int s = b < B ? parts_of(b, L, gamma, n, tp) : 0;
+    int incl = s;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) d[8 + i] = min(max(pt[min(2 * t0 + i, npg - 1)], 0), num_pages - 1);
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    __syncthreads();   // (s_w of the round before has been read)
+    if (lane == 63) s_w[w] = incl;
+    __syncthreads();
+    int pre = run, tot = 0;
+    for (int i = 0; i < kSetupThreads / 64; ++i) {
+      pre += i < w ? s_w[i] : 0;
+      tot += s_w[i];
+    }
+    if (b < B) {
+      p.part_prefix[b] = pre + incl - s;
+      if (b < kSetupB) s_pre[b] = pre + incl - s;
+    }
+    run += tot;
+  }
+  if (tid == 0) {
+    p.part_prefix[B] = run;
+    if (B <= kSetupB) s_pre[B] = run;
+  }
+  __syncthreads();   // the prefix sums are read back below by other threads of this block
+  const int32_t *pre = B <= kSetupB ? s_pre : p.part_prefix;
+  const int total = min(run, p.map_cap);
+  for (int q = tid; q < total; q += kSetupThreads) {
+    const int b = find(pre, 0, q);
+    int L, gamma, n, tp;
+    const int s = parts_of(b, L, gamma, n, tp), k = q - pre[b], t0 = k * tp, npg = (L + gamma + 1 + 15) >> 4;
+    const int32_t *pt = p.page_table + (size_t)b * p.max_pages;
+    int pg[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pg[i] = min(max(pt[min(2 * t0 + i, npg - 1)], 0), p.num_pages - 1);
+    int4 *d = reinterpret_cast<int4 *>(p.part_desc + (size_t)q * kDescInts);
+    d[0] = make_int4(b, t0, min(n, t0 + tp) - t0, s);
+    d[1] = make_int4(L, gamma, p.off[b] + b, 0);
+    d[2] = make_int4(pg[0], pg[1], pg[2], pg[3]);
   }
 }
 
@@ -455,10 +528,17 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   return FSV_OK;
 }
 
-int launch_attn_plan(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, hipStream_t st) {
-  hipLaunchKernelGGL(k_attn_plan, dim3(1), dim3(64), 0, st, b->batch, pl.tpw, c->group, c->attn_w2, c->attn_w3, b->seq_lens, b->draft_offsets,
-                     b->page_table, c->d.max_pages_per_req, b->num_pages,
-                     c->attn_part_prefix, c->attn_part_map, c->attn_wave_cap / c->d.n_kv_heads + 1);
+int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, hipStream_t st) {
+  setup_args a;
+  a.B = b->batch; a.tpw = pl.tpw; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
+  a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.map_cap = c->attn_wave_cap / c->d.n_kv_heads + 1;
+  a.M = M; a.half = rope ? c->d.head_dim / 2 : 1; a.V = c->d.vocab;   // without the angles: one thread per row
+  a.seq_lens = b->seq_lens; a.off = b->draft_offsets; a.page_table = b->page_table;
+  a.last_token = b->last_token; a.draft = b->draft_tokens; a.inv_freq = (const double *)c->inv_freq;
+  a.part_prefix = c->attn_part_prefix; a.part_desc = c->attn_part_map;
+  a.row_req = c->row_req; a.row_idx = c->row_idx; a.row_pos = c->row_pos; a.row_tok = c->row_tok;
+  a.tab = rope ? (float *)c->rope_tab : nullptr;
+  hipLaunchKernelGGL(k_setup, dim3(1 + fsv_ceil_div(M * a.half, kSetupThreads)), dim3(kSetupThreads), 0, st, a);
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
 }
@@ -511,8 +591,8 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
 
 int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) { return plan_attention(c, b, pl); }
 
-int fsv_bf16_attn_plan_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, hipStream_t st) {
-  return launch_attn_plan(c, b, *pl, st);
+int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, hipStream_t st) {
+  return launch_setup(c, b, *pl, M, rope, st);
 }
 
 int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, hipStream_t st) {

@@ -184,7 +184,8 @@ struct fsv_attn_plan {
 };
 int fsv_bf16_attn_create(fsv_ctx *c);
 int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl);          // host only; may fail
-int fsv_bf16_attn_plan_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, hipStream_t s);
+// row map, attention schedule and (rope) rotation angles of a call, on the device
+int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, hipStream_t s);
 int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, hipStream_t s);
 // gemm_bf16.hip: y = x W^T through the weight-streaming kernel; epi 0 = fp32 split partials [splits][Mpad][N],
 // 1 = SwiGLU to the bf16 operand order, 2 = fp32 rows [M][N]

@@ -456,17 +456,6 @@ __global__ __launch_bounds__(256) void k_kv_copy(int Hkv, int num_pages, const i
 // ---------------------------------------------------------------------------------------------
 // rotary embedding + KV append; consumes the split partials of the QKV projection
 // ---------------------------------------------------------------------------------------------
-// cos / sin of every row's rotation angles, once per call (the angles depend on the row's position only, not on the
-// layer): tab[(row * hd/2 + i) * 2 + {0, 1}].  The angle is formed and reduced in fp64.
-__global__ void k_rope_table(int M, int half, const double *__restrict__ inv_freq, const int32_t *__restrict__ row_pos,
-                             float *__restrict__ tab) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= M * half) return;
-  double sn, cs;
-  sincos((double)row_pos[t / half] * inv_freq[t % half], &sn, &cs);
-  reinterpret_cast<float2 *>(tab)[t] = make_float2((float)cs, (float)sn);
-}
-
 template <int LORA>
 __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, const float *__restrict__ rope_tab,
                                                      const float *__restrict__ part, int S, int Mpad,
@@ -875,12 +864,7 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
   const int nthr = min(1024, max(64, fsv_ceil_div(d.d_model / 8, 64) * 64));  // one 8-wide slice per thread
   int rc;
   const fsv_attn_plan &pl = *plan;
-  if ((rc = fsv_bf16_attn_plan_launch(c, b, plan, s))) return rc;
-  {
-    const int n = M * (d.head_dim / 2);
-    hipLaunchKernelGGL(k_rope_table, dim3(fsv_ceil_div(n, 256)), dim3(256), 0, s, M, d.head_dim / 2,
-                       (const double *)c->inv_freq, c->row_pos, (float *)c->rope_tab);
-  }
+  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, true, s))) return rc;
   // draft model (Sec. IV-A): only the anchor block (the last layer) on the draft's one-layer KV pools, then its own head
   const int l_first = draft ? d.n_layers - 1 : 0;
   // adapters of the evolved target: per-request LoRA pairs on q|k|v and o of every layer but the last
@@ -1084,10 +1068,10 @@ int fsv_bf16_attention(fsv_ctx *c, int layer, const void *q, const fsv_batch *b,
                        hipStream_t s) {
   const fsv_model_desc &d = c->d;
   const fsv_attn_plan &pl = *plan;
+  int rc;
+  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, false, s))) return rc;
   hipLaunchKernelGGL(k_pack_q, dim3(M), dim3(256), 0, s, d.n_heads, d.n_kv_heads, d.head_dim, (const uint16_t *)q,
                      c->row_req, c->row_idx, (uint16_t *)c->buf_q, c->q_plane_units * 8);
-  int rc;
-  if ((rc = fsv_bf16_attn_plan_launch(c, b, plan, s))) return rc;
   if ((rc = fsv_bf16_attn_launch(c, b, &pl, (size_t)layer * layer_stride(c, b->num_pages), s))) return rc;
   const int qd = d.n_heads * d.head_dim;
   const size_t n = (size_t)M * (qd / 8);
