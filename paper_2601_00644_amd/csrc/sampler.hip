@@ -700,6 +700,9 @@ __global__ __launch_bounds__(256) void k_decide(
   };
 
   // ---- phase 1: acceptance ----
+  LT lv_raw{};
+  float qd_in = 0.f, u_in = 0.f;
+  uint32_t cut_in = 0u;
   {
     constexpr int RW = (FSV_MAX_GAMMA + 1 + 3) / 4;   // rows a wave combines at most
     float pm[RW];
@@ -713,6 +716,15 @@ __global__ __launch_bounds__(256) void k_decide(
       pm[j] = live ? pmax[at] : -INFINITY;
       ps[j] = live ? psum[at] : 0.0;
       pa[j] = live ? parg[at] : INT_MAX;
+    }
+    // What draft tid + 1 is tested on: its logit, its draft probability, its uniform.  Issued here, so that the two dependent
+    // round trips (token, then the values it points at) pass while the statistics are combined.
+    if (T > 0.f && tid < gamma) {
+      const int d = min(max(draft[o + tid], 0), V - 1);
+      lv_raw = logits[(size_t)(rs + tid) * V + d];
+      qd_in = q[(size_t)(o + tid) * V + d];
+      u_in = u_acc[o + tid];
+      if (nuc_key) cut_in = nuc_key[rs + tid];
     }
 #pragma unroll
     for (int j = 0; j < RW; ++j) {
@@ -751,17 +763,16 @@ __global__ __launch_bounds__(256) void k_decide(
     return;
   }
   if (tid < gamma) {  // row rs + tid scores draft tid + 1
-    const int r = rs + tid, d = min(max(draft[o + tid], 0), V - 1);
     float lv;
-    if constexpr (sizeof(LT) == 2) lv = __uint_as_float((uint32_t)logits[(size_t)r * V + d] << 16);
-    else lv = logits[(size_t)r * V + d];
-    const bool kept = !nuc_key || okey(lv) >= nuc_key[r];
+    if constexpr (sizeof(LT) == 2) lv = __uint_as_float((uint32_t)lv_raw << 16);
+    else lv = lv_raw;
+    const bool kept = !nuc_key || okey(lv) >= cut_in;
     const double p = kept ? exp(((double)lv - s_m[tid]) * invT) / s_S[tid] : 0.0;
-    const double qd = (double)q[(size_t)(o + tid) * V + d];
+    const double qd = (double)qd_in;
     const double ratio = p / qd;
     double a = (ratio >= 1.0) ? 1.0 : ratio;
     if (!(a == a)) a = 0.0;
-    const double u = (double)u_acc[o + tid];
+    const double u = (double)u_in;
     s_acc[tid] = (u < a) ? 1 : 0;
     s_near[tid] = (fabs(u - a) < 1e-4) ? 1 : 0;
   }
@@ -823,24 +834,58 @@ __global__ __launch_bounds__(256) void k_decide(
   __shared__ double s_w[4];
   __shared__ double s_Z, s_lo;
   __shared__ int s_pick, s_first, s_lastpos;
-  for (int sb = tid; sb < nsb; sb += 256)
-    s_sb[sb] = __longlong_as_double((long long)__hip_atomic_load(
-        reinterpret_cast<const unsigned long long *>(bsum) + (size_t)b * nsb + sb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   if (tid == 0) {
     __hip_atomic_store(&ticket[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
     accepted_len[b] = tau;
     rollback(tau);
+    s_first = INT_MAX;
+    s_lastpos = -1;
   }
-  __syncthreads();
-  if (tid == 0) {
-    double Z = 0.0;
-    for (int sb = 0; sb < nsb; ++sb) Z += s_sb[sb];
-    s_Z = Z;
-  }
+  // Wave 0 takes the sub-block masses, PER consecutive ones per lane, and finds the first sub-block whose running mass exceeds
+  // u times the total (lane sums and their shuffle scan: a fixed order).  One thread adding and comparing them one after the
+  // other cost 3 us of this kernel's serial tail.
+  auto pick_sb = [&](auto mass_of) {
+    constexpr int PER = (FSV_MAX_NSB + 63) / 64;
+    double m_[PER], t = 0.0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) m_[j] = (lane * PER + j < nsb) ? mass_of(lane * PER + j) : 0.0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) t += m_[j];
+    double incl = t;
+#pragma unroll
+    for (int sh = 1; sh < 64; sh <<= 1) {
+      const double up = __shfl_up(incl, sh, 64);
+      if (lane >= sh) incl += up;
+    }
+    const double Z = __shfl(incl, 63, 64), target = (double)u_smp[b] * Z;
+    double pre = __shfl_up(incl, 1, 64), run = (lane == 0) ? 0.0 : pre, lo = 0.0;
+    int pick = -1, last = -1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const double prev = run;
+      run += m_[j];
+      if (m_[j] > 0.0) last = lane * PER + j;
+      if (pick < 0 && m_[j] > 0.0 && run > target) { pick = lane * PER + j; lo = prev; }
+    }
+    const unsigned long long hit = __ballot(pick >= 0), any = __ballot(last >= 0);
+    if (hit) {
+      const int from = (int)__builtin_ctzll(hit);
+      pick = __shfl(pick, from, 64);
+      lo = __shfl(lo, from, 64);
+    } else {   // rounding left no crossing: last sub-block with mass
+      pick = any ? __shfl(last, 63 - (int)__builtin_clzll(any), 64) : 0;
+      lo = INFINITY;
+    }
+    if (lane == 0) { s_Z = Z; s_pick = pick; s_lo = lo; }
+  };
+  if (w == 0)
+    pick_sb([&](int sb) {
+      return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long *>(bsum) + (size_t)b * nsb + sb,
+                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    });
   __syncthreads();
   if (residual && !(s_Z > 0.0)) {
     // p <= q everywhere after rounding: the residual carries no mass, draw from p itself
-    __syncthreads();
     residual = false;
     qrow = nullptr;
     for (int sb = 0; sb < nsb; ++sb) {
@@ -850,31 +895,11 @@ __global__ __launch_bounds__(256) void k_decide(
       block_incl_scan(t, s_w, &tot);
       if (tid == 0) s_sb[sb] = tot;
     }
-    __syncthreads();
-    if (tid == 0) {
-      double Z = 0.0;
-      for (int sb = 0; sb < nsb; ++sb) Z += s_sb[sb];
-      s_Z = Z;
-    }
+    __syncthreads();   // (also: every thread has read s_Z above)
+    if (w == 0) pick_sb([&](int sb) { return s_sb[sb]; });
     __syncthreads();
   }
   const double Z = s_Z, target = (double)u_smp[b] * Z;
-  if (tid == 0) {
-    double run = 0.0, lo = 0.0;
-    int pick = -1, lastpos = 0;
-    for (int sb = 0; sb < nsb; ++sb) {
-      double prev = run;
-      run += s_sb[sb];
-      if (s_sb[sb] > 0.0) lastpos = sb;
-      if (pick < 0 && run > target) { pick = sb; lo = prev; }
-    }
-    if (pick < 0) { pick = lastpos; lo = INFINITY; }  // rounding left no crossing: last id with mass
-    s_pick = pick;
-    s_lo = lo;
-    s_first = INT_MAX;
-    s_lastpos = -1;
-  }
-  __syncthreads();
   const int sb = s_pick;
   const double lo = s_lo;
   double mass[8];
