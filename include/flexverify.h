@@ -312,8 +312,8 @@ int fsv_attention(fsv_ctx *ctx, int32_t layer, const void *q, const fsv_batch *b
  * of the kernel classes whose bit (1u << FSV_K_*) is set in mask (0 = off, 0xffffffff = all; at most
  * 8192 launches are kept, later ones are not recorded).  For the GEMM and attention classes the pair
  * rides on the dispatch itself (start and stop of the kernel); for the other classes it is recorded on
- * the stream before and after the launches and so includes the dispatch gaps.  FSV_K_SAMPLE_NUCLEUS brackets
- * all the cut passes of one call (one per key digit and per kind of cut) as one record.  fsv_profile_read() waits for the recorded
+ * the stream before and after the launches and so includes the dispatch gaps.  FSV_K_SAMPLE_NUCLEUS is
+ * the kernel that finds the top-k / top-p cuts of a call.  fsv_profile_read() waits for the recorded
  * events and returns, per class, the number of launches, their summed duration and the algorithmic
  * bytes the host computed for them (weights for a GEMM, K and V for attention, logits and draft law
  * for the sampling kernels), then clears the records.  Returns the number of classes written (<= cap).

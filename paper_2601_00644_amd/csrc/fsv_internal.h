@@ -62,11 +62,10 @@ struct fsv_ctx {
   double *bsum = nullptr;   // [max_batch][nsb]
   int32_t *sel_ticket = nullptr;   // [max_batch] blocks of a request that have left their masses; zero between calls
   int32_t *acc_scratch = nullptr;  // [max_batch] accepted_len when the caller passes none
-  // nucleus (top-p) selection, per logits row: digit-by-digit state, then the cut key, the kept mass, the near flag
-  uint32_t *nuc_prefix = nullptr, *nuc_key = nullptr, *nuc_cabove = nullptr, *nuc_kkey = nullptr;
-  unsigned long long *nuc_above = nullptr, *nuc_total = nullptr, *nuc_kmass = nullptr;
+  // top-k / top-p cut, per logits row: cut key, kept mass (-1: nothing is cut), whether top_p falls near it
+  uint32_t *nuc_key = nullptr;
   double *nuc_S = nullptr;
-  int32_t *nuc_near = nullptr, *nuc_done = nullptr;   // nuc_done[row]: the windowed pass has settled the row's cut
+  int32_t *nuc_near = nullptr, *nuc_done = nullptr;   // nuc_done: the one-pass form has settled the row
 
   // model workspace (both paths)
   float *x = nullptr;       // [rows_pad][d_model] residual stream, fp32

@@ -11,10 +11,8 @@
 //                 through memory), then the blocks of a request stream the one row its token is drawn from (and the
 //                 draft-law row) into the masses of its 2048-id sub-blocks; the block that finishes last (an integer
 //                 ticket per request) locates the sub-block and the id by inverse CDF, emits the outputs and rolls back
-// plus, when a request asks for a top-k / nucleus (top-p) cut of the target law, between the two: for bf16 logits
-// k_nucleus_top, ONE pass per stage that settles every row whose cut lies within one (first try) or two (second try)
-// binades of the row maximum; for the rows it leaves, and for fp32 logits, k_nucleus: one pass over the row per digit
-// of the cut value (two for bf16 logits, three for fp32) and stage.
+// plus, when a request asks for a top-k / nucleus (top-p) cut of the target law, between the two: k_cut, one block per row
+// that finds the row's cut in two passes over it and a short list of candidates.
 // Rows are addressed as (request, row within the request), so the step needs no row map.  Every floating-point sum is
 // taken in a fixed order (the ticket only decides WHICH block adds the sub-block masses up, in sub-block order); the only
 // other atomics are integer adds into the nucleus histograms, whose result does not depend on their order.
@@ -276,10 +274,8 @@ __global__ __launch_bounds__(256) void k_draft_law(const float *__restrict__ z, 
 // ---- top-k / nucleus (top-p) cut of the target law ----------------------------------------------------------
 // The cut keeps every token whose logit is at least the cut value: for top-k the value of the top_k-th most probable
 // token, for top-p the largest value for which the kept mass reaches top_p of what the top-k cut left (tokens tied at
-// the cut value are all kept, so the set does not depend on an order among ties).  The cut value
-// is found digit by digit on a monotone 32-bit key of the logit: one pass over the row per digit builds a histogram of
-// the mass per digit value (in LDS, in 2^-40 fixed point, so that the sums do not depend on the order of the atomic
-// adds), and a scan from the top picks the digit at which the kept mass crosses top_p of the total.
+// the cut value are all kept, so the set does not depend on an order among ties).  Masses are integers in 2^-40 fixed point
+// throughout, so that no sum depends on the order of its terms.
 __device__ inline uint32_t okey(float f) {  // monotone: a < b  <=>  okey(a) < okey(b)
   const uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -287,254 +283,242 @@ __device__ inline uint32_t okey(float f) {  // monotone: a < b  <=>  okey(a) < o
 
 constexpr int FSV_NUC_BINS = 2048;
 constexpr double kNucScale = 1099511627776.0;  // 2^40
+constexpr int kCutThreads = 1024;
+constexpr int kCutBins = 8192;
+constexpr float kCutBinsPerLog2 = 192.0f;   // bins per factor of two of the probability: they span 42.7 factors of two
+constexpr int kCutList = 2 * kCutThreads;   // candidates the last step can hold
 
-// LEVEL 0: key bits 31..21, LEVEL 1: bits 20..10, LEVEL 2: bits 9..0.  LAST marks the level that fixes the whole key
-// (level 1 for bf16 logits, whose keys have no information below bit 16; level 2 for fp32 logits).  grid = rows.
-// MODE 1 (top-k) selects the key of the top_k-th most probable token by COUNT (a second, integer histogram) and leaves
-// the cut key and the mass at or above it per row; MODE 0 (top-p) selects by mass among the tokens the top-k cut kept
-// (all of them when the row has none) and writes the row's final cut key and kept mass.  A row that asks for neither
-// gets key 0 (nothing is cut); one that asks for top-k only gets the top-k cut as its final one.
-template <typename LT, int LEVEL, bool LAST, int MODE>
-__global__ __launch_bounds__(1024) void k_nucleus(const LT *__restrict__ logits, int V, int nc,
-                                                  const int32_t *__restrict__ off,
-                                                  const float *__restrict__ temperature, const float *__restrict__ top_p,
-                                                  const int32_t *__restrict__ top_k, const float *__restrict__ pmax,
-                                                  uint32_t *__restrict__ st_prefix, unsigned long long *__restrict__ st_above,
-                                                  uint32_t *__restrict__ st_cabove, unsigned long long *__restrict__ st_total,
-                                                  uint32_t *__restrict__ kkey, unsigned long long *__restrict__ kmass,
-                                                  uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
-                                                  int32_t *__restrict__ nuc_near, const int32_t *__restrict__ done, int vec) {
-  constexpr int SHIFT = (LEVEL == 0) ? 21 : (LEVEL == 1 ? 10 : 0), BITS = (LEVEL == 2) ? 10 : 11;
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;   // grid = (largest gamma + 1, requests)
-  if ((int)blockIdx.x > off[b + 1] - off[b]) return;
-  const int r = off[b] + b + blockIdx.x;
-  if (done && done[r]) return;   // k_nucleus_top has settled this row
-  const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
-  const int tk = top_k ? top_k[b] : 0;
-  const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
-  if (MODE == 1) {
-    if (!use_k) {
-      if (LEVEL == 0 && tid == 0) kkey[r] = 0u;
-      return;
-    }
-  } else if (!use_p) {  // no top-p for this row: its final cut is the top-k one, if any
-    if (LEVEL == 0 && tid == 0) {
-      const uint32_t kk = use_k ? kkey[r] : 0u;
-      nuc_key[r] = kk;
-      nuc_S[r] = kk ? (double)kmass[r] / kNucScale : -1.0;
-      nuc_near[r] = 0;
-    }
-    return;
+__device__ inline unsigned long long nuc_mass(float d, exp_scale k) {
+  return (unsigned long long)((double)exp_scaled(d, k) * kNucScale + 0.5);
+}
+
+// What the passes over a row hand to each other, in LDS.
+struct cut_state {
+  float m;                                   // row maximum
+  int n, found, bad;                         // candidates, selection done, a NaN in the row
+  uint32_t bin_lo, bin_hi, kkey, cut;
+  unsigned long long kmass, kept, acc, total;
+  double S;                                  // normaliser from the row statistics, in units of the maximum's probability
+  uint32_t prefix, cabove;                   // digit passes: the digits fixed so far, tokens and mass above them
+  unsigned long long above;
+  uint32_t w32[kCutThreads / 64];
+  unsigned long long w64[kCutThreads / 64], t64[kCutThreads / 64];
+};
+
+// f(first id, eight values) over the block's share of a row, ids beyond the vocabulary as -inf.  Rounds of U loads per
+// thread are issued back to back, without a branch between them (a branch per load makes the wave wait for each load
+// before the next); the U loads of a round lie a U-th of the whole rounds apart, so that the first round is a sample of the
+// vocabulary.  after_round(r, values of the round) is met by every thread of the block after each whole round.
+template <typename LT>
+__device__ inline int whole_rounds(int V, bool vec) { return vec ? V / (4 * kCutThreads * 8) : 0; }
+template <typename LT, typename F, typename G>
+__device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, G &&after_round) {
+  constexpr int U = 4, STEP = kCutThreads * 8;
+  const int R = whole_rounds<LT>(V, vec);
+  for (int r = 0; r < R; ++r) {
+    const int base = r * STEP + tid * 8;
+    float v[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) loader<LT>::load8_fast(row, base + u * R * STEP, v[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) f(base + u * R * STEP, v[u]);
+    after_round(r, v);
   }
-  __shared__ unsigned long long hist[FSV_NUC_BINS];
-  __shared__ uint32_t hcnt[(MODE == 1) ? FSV_NUC_BINS : 1];
-  __shared__ float s_m;
-  for (int i = tid; i < FSV_NUC_BINS; i += 1024) {
+  for (int base = R * U * STEP + tid * 8; base < V; base += STEP) {
+    float v[8];
+    loader<LT>::load8(row, base, V, vec, -INFINITY, v);
+    f(base, v);
+  }
+}
+
+// The general way, digit by digit on the 32-bit key: one pass over the row per digit builds a histogram of the mass (and, for
+// top-k, the count) per digit value in LDS, and a scan from the top picks the digit at which the kept mass (count) crosses.
+// LEVEL 0: key bits 31..21, LEVEL 1: bits 20..10, LEVEL 2: bits 9..0; LAST fixes the whole key (level 1 for bf16 logits,
+// whose keys have no information below bit 16).  MODE 1 selects by count and leaves kkey / kmass, MODE 0 by mass among the
+// keys from lowkey on and leaves cut / kept / acc / total.
+template <typename LT, int LEVEL, bool LAST, int MODE>
+__device__ inline void cut_digit_pass(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lowkey, int tk, float tp,
+                                      unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
+  constexpr int SHIFT = (LEVEL == 0) ? 21 : (LEVEL == 1 ? 10 : 0), BITS = (LEVEL == 2) ? 10 : 11;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < FSV_NUC_BINS; i += kCutThreads) {
     hist[i] = 0ull;
     if (MODE == 1) hcnt[i] = 0u;
   }
-  if (tid < 64) {
-    float mx = -INFINITY;
-    for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) s_m = mx;
-  }
   __syncthreads();
-  const float m = s_m;
-  const exp_scale k = make_exp_scale(kLog2e / (double)T);
-  const uint32_t prefix = (LEVEL > 0) ? st_prefix[r] : 0u;
-  const uint32_t lowkey = (MODE == 0 && use_k) ? kkey[r] : 0u;   // top-p works on what the top-k cut kept
-  const LT *row = logits + (size_t)r * V;
-  auto add8 = [&](int i0, const float (&v)[8]) {
+  const uint32_t prefix = (LEVEL > 0) ? st->prefix : 0u;
+  over_row<LT>(row, V, vec, tid, [&](int i0, const float(&v)[8]) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (i0 + j >= V) continue;   // ids beyond the vocabulary are not tokens (they would count for top-k)
       const uint32_t key = okey(v[j]);
       if (LEVEL > 0 && (key >> (SHIFT + BITS)) != prefix) continue;
       if (MODE == 0 && key < lowkey) continue;
-      const unsigned long long q = (unsigned long long)((double)exp_scaled(v[j] - m, k) * kNucScale + 0.5);
+      const unsigned long long q = nuc_mass(v[j] - m, k);
       const uint32_t bin = (key >> SHIFT) & ((1u << BITS) - 1u);
       if (q) atomicAdd(&hist[bin], q);
       if (MODE == 1) atomicAdd(&hcnt[bin], 1u);
     }
-  };
-  // Rounds of U loads per thread issued back to back, without a branch between them (a branch per load makes the wave
-  // wait for each load before the next, and the pass then runs at one memory round trip per 8192 ids of the row); the
-  // ragged end of the row takes the guarded loads one by one.
-  constexpr int U = 4, STEP = 1024 * 8;
-  int base = tid * 8;
-  if (vec) {
-    for (; base + (U - 1) * STEP + 8 <= V; base += U * STEP) {
-      float v[U][8];
-#pragma unroll
-      for (int u = 0; u < U; ++u) loader<LT>::load8_fast(row, base + u * STEP, v[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u) add8(base + u * STEP, v[u]);
+  }, [](int, const auto &) {});
+  __syncthreads();
+  if (tid < 64) {
+    // lane l owns the 32 digit values below (64 - l) * 32, the highest values in lane 0: masses above each lane's group
+    constexpr int PER = FSV_NUC_BINS / 64;
+    unsigned long long mine = 0ull;
+    uint32_t minec = 0u;
+    const int top = (63 - lane) * PER + PER - 1;
+    for (int i = 0; i < PER; ++i) {
+      mine += hist[top - i];
+      if (MODE == 1) minec += hcnt[top - i];
     }
-  }
-  for (; base < V; base += STEP) {
-    float v[8];
-    loader<LT>::load8(row, base, V, vec != 0, -INFINITY, v);
-    add8(base, v);
+    unsigned long long incl = mine;
+    uint32_t inclc = minec;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long t = __shfl_up(incl, o, 64);
+      const uint32_t tc = __shfl_up(inclc, o, 64);
+      if (lane >= o) { incl += t; inclc += tc; }
+    }
+    const unsigned long long before = ((LEVEL == 0) ? 0ull : st->above) + (incl - mine);   // mass strictly above this lane's group
+    const uint32_t beforec = ((LEVEL == 0) ? 0u : st->cabove) + (inclc - minec);
+    const unsigned long long total = (LEVEL == 0) ? __shfl(incl, 63, 64) : st->total;
+    const double target = (double)tp * (double)total;
+    const bool crosses = (MODE == 1) ? (beforec + minec >= (uint32_t)tk) : ((double)(before + mine) >= target);
+    const unsigned long long ballot = __ballot(crosses);
+    // level 0 always has a crossing (tk < V tokens are counted; the last lane holds the total mass); deeper levels were
+    // chosen because they cross; the guard only keeps the index in range
+    const int pick_lane = ballot ? (int)__builtin_ctzll(ballot) : 63;
+    if (lane == pick_lane) {
+      unsigned long long acc = before;
+      uint32_t accc = beforec;
+      int digit = top - (PER - 1);
+      for (int i = 0; i < PER; ++i) {
+        const unsigned long long hbin = hist[top - i];
+        const bool hit = (MODE == 1) ? (accc + hcnt[top - i] >= (uint32_t)tk) : ((double)(acc + hbin) >= target);
+        if (hit || i == PER - 1) { digit = top - i; break; }
+        acc += hbin;
+        if (MODE == 1) accc += hcnt[top - i];
+      }
+      const uint32_t newprefix = (prefix << BITS) | (uint32_t)digit;
+      st->prefix = newprefix;
+      st->above = acc;
+      st->cabove = accc;
+      if (MODE == 0) st->total = total;
+      if (LAST) {
+        if (MODE == 1) { st->kkey = newprefix << SHIFT; st->kmass = acc + hist[digit]; }
+        else { st->cut = newprefix << SHIFT; st->kept = acc + hist[digit]; st->acc = acc; }
+      }
+    }
   }
   __syncthreads();
-  if (tid >= 64) return;
-  // lane l owns the 32 digit values below (64 - l) * 32, the highest values in lane 0: masses above each lane's group
-  constexpr int PER = FSV_NUC_BINS / 64;
-  unsigned long long mine = 0ull;
-  uint32_t minec = 0u;
-  const int top = (63 - lane) * PER + PER - 1;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    mine += hist[top - i];
-    if (MODE == 1) minec += hcnt[top - i];
-  }
-  unsigned long long incl = mine;
-  uint32_t inclc = minec;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned long long t = __shfl_up(incl, off, 64);
-    const uint32_t tc = __shfl_up(inclc, off, 64);
-    if (lane >= off) { incl += t; inclc += tc; }
-  }
-  const unsigned long long above0 = (LEVEL == 0) ? 0ull : st_above[r];
-  const unsigned long long before = above0 + (incl - mine);  // mass strictly above this lane's group
-  if (MODE == 1) {
-    const uint32_t cabove0 = (LEVEL == 0) ? 0u : st_cabove[r];
-    const uint32_t beforec = cabove0 + (inclc - minec);     // tokens strictly above this lane's group
-    const unsigned long long ballot = __ballot(beforec + minec >= (uint32_t)tk);
-    // level 0 always has a crossing (tk < V tokens are counted); deeper levels were chosen because they cross
-    const int pick_lane = ballot ? (int)__builtin_ctzll(ballot) : 63;
-    if (lane != pick_lane) return;
-    unsigned long long acc = before;
-    uint32_t accc = beforec;
-    int digit = top - (PER - 1);
-    for (int i = 0; i < PER; ++i) {
-      if (accc + hcnt[top - i] >= (uint32_t)tk || i == PER - 1) { digit = top - i; break; }
-      accc += hcnt[top - i];
-      acc += hist[top - i];
-    }
-    const uint32_t newprefix = (prefix << BITS) | (uint32_t)digit;
-    if (!LAST) {
-      st_prefix[r] = newprefix;
-      st_above[r] = acc;
-      st_cabove[r] = accc;
-    } else {
-      kkey[r] = newprefix << SHIFT;
-      kmass[r] = acc + hist[digit];
-    }
-    return;
-  }
-  unsigned long long total = (LEVEL == 0) ? __shfl(incl, 63, 64) : st_total[r];
-  const double target = (double)tp * (double)total;
-  const bool crosses = (double)(before + mine) >= target;
-  const unsigned long long ballot = __ballot(crosses);
-  // rounding cannot leave the ballot empty at level 0 (the last lane holds the total); at deeper levels the digit group
-  // was chosen because it crosses, so some lane does as well; the guard only keeps the index in range
-  const int pick_lane = ballot ? (int)__builtin_ctzll(ballot) : 63;
-  if (lane != pick_lane) return;
-  unsigned long long acc = before;
-  int digit = top - (PER - 1);
-  for (int i = 0; i < PER; ++i) {
-    const unsigned long long hbin = hist[top - i];
-    if ((double)(acc + hbin) >= target || i == PER - 1) { digit = top - i; break; }
-    acc += hbin;
-  }
-  const uint32_t newprefix = (prefix << BITS) | (uint32_t)digit;
-  if (!LAST) {
-    st_prefix[r] = newprefix;
-    st_above[r] = acc;
-    if (LEVEL == 0) st_total[r] = total;
+}
+
+template <typename LT, int MODE>
+__device__ inline void cut_digits(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lowkey, int tk, float tp,
+                                  unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
+  cut_digit_pass<LT, 0, false, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
+  if constexpr (sizeof(LT) == 2) {
+    cut_digit_pass<LT, 1, true, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
   } else {
-    const unsigned long long kept = acc + hist[digit];
-    nuc_key[r] = newprefix << SHIFT;
-    nuc_S[r] = (double)kept / kNucScale;
-    const double lo = target - (double)acc, hi = (double)kept - target;
-    nuc_near[r] = (fmin(lo, hi) < 1e-6 * (double)total) ? 1 : 0;
+    cut_digit_pass<LT, 1, false, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
+    cut_digit_pass<LT, 2, true, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
   }
 }
 
-// The same selection for bf16 logits in ONE pass whenever the cut lies near the top of the row, which is where a top-p
-// or top-k cut lies in practice: only the W highest digit values at and below the row maximum's digit (W = 4: one binade
-// of the logit, tried first; W = 8: two binades, for the rows the first try leaves) get histogram bins, 32 each (a bf16 key has five bits below the digit, so a bin is one key: the second
-// level comes for free).  Every other token is dismissed after a look at its key: the pass needs no exponential and no
-// LDS atomic for it, which is what bounds the full pass.  The row's total mass, against which top_p is measured, is not
-// summed again either: it is the normaliser the statistics pass already left (or, after a top-k cut, the mass that
-// cut kept).  That total differs from the integer sum the full passes form by the rounding of a floating-point sum
-// (1e-7 relative); the rows where that could matter are the ones within 1e-6 of the cut, which are flagged in any case.
-// A row whose cut lies below the window is left to the full passes (done[r] = 0).
-template <int MODE, int W, bool FIRST>
-__global__ __launch_bounds__(1024) void k_nucleus_top(const uint16_t *__restrict__ logits, int V, int nc,
+// First bins at which the running sum of the bins reaches x0 and x1, to bin_lo and bin_hi (kCutBins: never).
+__device__ inline void cut_find_bins(const uint32_t *hist, uint32_t x0, uint32_t x1, cut_state *st) {
+  constexpr int PER = kCutBins / kCutThreads;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tid == 0) st->bin_lo = st->bin_hi = kCutBins;
+  uint32_t h[PER], incl = 0u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    h[i] = hist[PER * tid + i];
+    incl += h[i];
+  }
+  uint32_t run = incl;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
+  }
+  run = incl - run;
+  if (lane == 63) st->w32[w] = incl;
+  __syncthreads();
+  for (int i = 0; i < w; ++i) run += st->w32[i];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const uint32_t before = run;
+    run += h[i];
+    if (before < x0 && x0 <= run) st->bin_lo = PER * tid + i;
+    if (before < x1 && x1 <= run) st->bin_hi = PER * tid + i;
+  }
+  __syncthreads();
+}
+
+// The value a key stands for.
+__device__ inline float okey_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key); }
+
+// top-p alone on bf16 logits, in ONE pass, whenever the cut lies within one binade of the row maximum: only the W = 4 highest
+// values of the key's top 11 bits, at and below the row maximum's, get histogram bins, 32 each (a bf16 key has five bits
+// below, so a bin is one key and needs no list).  Every other token is dismissed by one comparison: no exponential, no LDS
+// add.  top_p is measured against the normaliser of the statistics pass.  Rows it cannot settle, and rows with a top-k cut,
+// go on to k_cut (done[r] = 0).  596 rows x 152064, top-p 0.9: 47 us and 5 for the k_cut that finds nothing left; k_cut
+// alone, two passes, takes 145.
+constexpr int kWindowDigits = 4;
+__global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict__ logits, int V, int nc,
                                                       const int32_t *__restrict__ off,
                                                       const float *__restrict__ temperature,
                                                       const float *__restrict__ top_p, const int32_t *__restrict__ top_k,
                                                       const float *__restrict__ pmax, const double *__restrict__ psum,
-                                                      uint32_t *__restrict__ kkey, unsigned long long *__restrict__ kmass,
                                                       uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
                                                       int32_t *__restrict__ nuc_near, int32_t *__restrict__ done, int vec) {
-  constexpr int FB = 32;
+  constexpr int FB = 32, W = kWindowDigits;
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   if ((int)blockIdx.x > off[b + 1] - off[b]) return;
   const int r = off[b] + b + blockIdx.x;
-  if (!FIRST && done[r]) return;   // settled by the narrower window
   const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
   const int tk = top_k ? top_k[b] : 0;
   const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
-  if (MODE == 1) {
-    if (!use_k) {
-      if (tid == 0) { kkey[r] = 0u; done[r] = 1; }
-      return;
-    }
-  } else if (!use_p) {  // no top-p for this row: its final cut is the top-k one, if any
-    if (tid == 0) {
-      const uint32_t kk = use_k ? kkey[r] : 0u;
-      nuc_key[r] = kk;
-      nuc_S[r] = kk ? (double)kmass[r] / kNucScale : -1.0;
-      nuc_near[r] = 0;
-      done[r] = 1;
-    }
+  if (use_k) {
+    if (tid == 0) done[r] = 0;
+    return;
+  }
+  if (!use_p) {
+    if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; done[r] = 1; }
     return;
   }
   __shared__ unsigned long long hist[W * FB];
-  __shared__ uint32_t hcnt[(MODE == 1) ? W * FB : 1];
   __shared__ float s_m;
   __shared__ double s_total;
-  for (int i = tid; i < W * FB; i += 1024) {
-    hist[i] = 0ull;
-    if (MODE == 1) hcnt[i] = 0u;
-  }
+  for (int i = tid; i < W * FB; i += 1024) hist[i] = 0ull;
   if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
     float mx = -INFINITY;
     for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
 #pragma unroll
     for (int o2 = 32; o2 > 0; o2 >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o2, 64));
     double term = 0.0;
-    if (MODE == 0 && !use_k) {
-      const double invT = 1.0 / (double)T;
-      for (int c = lane; c < nc; c += 64) {
-        const float pm = pmax[(size_t)r * nc + c];
-        term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
-      }
-#pragma unroll
-      for (int o2 = 32; o2 > 0; o2 >>= 1) term += __shfl_xor(term, o2, 64);
+    const double invT = 1.0 / (double)T;
+    for (int c = lane; c < nc; c += 64) {
+      const float pm = pmax[(size_t)r * nc + c];
+      term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
     }
+#pragma unroll
+    for (int o2 = 32; o2 > 0; o2 >>= 1) term += __shfl_xor(term, o2, 64);
     if (lane == 0) {
       s_m = mx;
-      s_total = (MODE == 0) ? (use_k ? (double)kmass[r] : term * kNucScale) : 0.0;
+      s_total = term * kNucScale;
     }
   }
   __syncthreads();
   const float m = s_m;
   const exp_scale k = make_exp_scale(kLog2e / (double)T);
   const uint32_t d0 = okey(m) >> 21;                              // the row's highest digit
-  const uint32_t lowkey = (MODE == 0 && use_k) ? kkey[r] : 0u;   // top-p works on what the top-k cut kept
   const uint16_t *row = logits + (size_t)r * V;
-  // the lowest value inside the window (and, after a top-k cut, inside that cut): the value whose key is the window's
-  // lowest key; keys below 2^31 belong to negative values (the key is the complement of their bits)
-  const uint32_t wlow = (d0 >= (uint32_t)(W - 1)) ? ((d0 - (uint32_t)(W - 1)) << 21) : 0u, klow = max(wlow, lowkey);
-  float vlow = __uint_as_float((klow & 0x80000000u) ? (klow & 0x7FFFFFFFu) : ~klow);
-  if (!(vlow == vlow)) vlow = (klow & 0x80000000u) ? INFINITY : -INFINITY;   // (keys of NaN patterns: only when the row holds them)
+  // the lowest value inside the window: the value whose key is the window's lowest key
+  const uint32_t wlow = (d0 >= (uint32_t)(W - 1)) ? ((d0 - (uint32_t)(W - 1)) << 21) : 0u;
+  float vlow = okey_value(wlow);
+  if (!(vlow == vlow)) vlow = (wlow & 0x80000000u) ? INFINITY : -INFINITY;   // (keys of NaN patterns: only when the row holds them)
   // Eight ids of a thread at a time: a bit per id that falls into the window, then the wave works through the set bits,
   // every lane on its next one, so that the exponential and the atomics are issued about as often as the busiest lane
   // has window tokens among its eight, not once per id.
@@ -557,7 +541,6 @@ __global__ __launch_bounds__(1024) void k_nucleus_top(const uint16_t *__restrict
         const unsigned long long q = (unsigned long long)((double)exp_scaled(val - m, k) * kNucScale + 0.5);
         const uint32_t idx = (d0 - (key >> 21)) * FB + ((key >> 16) & (FB - 1));
         if (q) atomicAdd(&hist[idx], q);
-        if (MODE == 1) atomicAdd(&hcnt[idx], 1u);
       }
     }
   };
@@ -581,54 +564,327 @@ __global__ __launch_bounds__(1024) void k_nucleus_top(const uint16_t *__restrict
   if (tid >= 64) return;
   // lane l < W owns the window's digit d0 - l: the highest keys in lane 0
   unsigned long long mine = 0ull;
-  uint32_t minec = 0u;
   if (lane < W) {
 #pragma unroll
-    for (int f = 0; f < FB; ++f) {
-      mine += hist[lane * FB + f];
-      if (MODE == 1) minec += hcnt[lane * FB + f];
-    }
+    for (int f = 0; f < FB; ++f) mine += hist[lane * FB + f];
   }
   unsigned long long incl = mine;
-  uint32_t inclc = minec;
 #pragma unroll
   for (int o2 = 1; o2 < W; o2 <<= 1) {
     const unsigned long long t = __shfl_up(incl, o2, 64);
-    const uint32_t tc = __shfl_up(inclc, o2, 64);
-    if (lane >= o2) { incl += t; inclc += tc; }
+    if (lane >= o2) incl += t;
   }
   const unsigned long long before = incl - mine;   // mass strictly above this lane's digit
-  const uint32_t beforec = inclc - minec;
   const double total = s_total, target = (double)tp * total;
-  const bool crosses = (MODE == 1) ? (beforec + minec >= (uint32_t)tk) : ((double)(before + mine) >= target);
+  const bool crosses = (double)(before + mine) >= target;
   const unsigned long long ballot = __ballot(crosses && lane < W && lane <= (int)d0);   // digits below zero do not exist
-  if (!ballot || (MODE == 0 && !(total > 0.0))) {   // the cut lies below the window: the full passes take the row
+  if (!ballot || !(total > 0.0)) {   // the cut lies below the window
     if (lane == 0) done[r] = 0;
     return;
   }
   if (lane != (int)__builtin_ctzll(ballot)) return;
   unsigned long long acc = before;
-  uint32_t accc = beforec;
   int fsel = 0;
   for (int f = FB - 1; f >= 0; --f) {
     const unsigned long long hbin = hist[lane * FB + f];
-    const bool hit = (MODE == 1) ? (accc + hcnt[lane * FB + f] >= (uint32_t)tk) : ((double)(acc + hbin) >= target);
-    if (hit || f == 0) { fsel = f; break; }
+    if ((double)(acc + hbin) >= target || f == 0) { fsel = f; break; }
     acc += hbin;
-    if (MODE == 1) accc += hcnt[lane * FB + f];
   }
   const uint32_t cut = ((d0 - (uint32_t)lane) << 21) | ((uint32_t)fsel << 16);
   const unsigned long long kept = acc + hist[lane * FB + fsel];
-  if (MODE == 1) {
-    kkey[r] = cut;
-    kmass[r] = kept;
-  } else {
-    nuc_key[r] = cut;
-    nuc_S[r] = (double)kept / kNucScale;
-    const double lo = target - (double)acc, hi = (double)kept - target;
-    nuc_near[r] = (fmin(lo, hi) < 1e-6 * total) ? 1 : 0;
-  }
+  nuc_key[r] = cut;
+  nuc_S[r] = (double)kept / kNucScale;
+  nuc_near[r] = (fmin(target - (double)acc, (double)kept - target) < 1e-6 * total) ? 1 : 0;
   done[r] = 1;
+}
+
+// The cut of every row that asks for one: cut key, kept mass, and whether top_p falls within 1e-6 of the row's mass of it.
+// grid = rows, one block each (a block fills its compute unit: blocks that only find they have no row would cost a round).
+//
+// The first pass files the tokens under 8192 bins of the exponent (log2 of the probability relative to the maximum, 192 bins
+// per factor of two): their count for top-k, their mass in 32-bit fixed point for top-p; the bins in which the cut can lie
+// follow from the running sum and a bound of its rounding.  The second collects the tokens of those bins (for top-k: of all
+// bins down to it) and adds up, exactly, what lies above.  The list is sorted by key, and its running sum of exact 2^-40
+// masses decides.  A top-k of a few hundred takes one pass: a quarter of the ids, sampled across the vocabulary, is filed,
+// the bin at which these already hold top_k tokens bounds the cut, and everything from that bin on goes to the list at once.
+// For top-p, tokens so improbable that all of them together carry less than 0.9 (1 - top_p) are not filed.
+// A row with NaN or an infinite maximum, or whose list overflows (near-flat laws with many ties), goes digit by digit, as
+// does every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other).
+// Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
+// arithmetic of a single compute unit with few rows.  Measured: top-k 50 then top-p 0.9 on those 204 rows 34 us, against 235
+// for six digit passes; top-p 0.9 alone 54 against 135, on 71 rows of model logits 52 against 73; top-k 50 on 596 rows x
+// 152064 bf16 80 against 87 (a one-binade window, then digits).
+template <typename LT>
+__global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logits, int V, int nc, const int32_t *__restrict__ off,
+                                                     const float *__restrict__ temperature, const float *__restrict__ top_p,
+                                                     const int32_t *__restrict__ top_k, const float *__restrict__ pmax,
+                                                     const double *__restrict__ psum, uint32_t *__restrict__ nuc_key,
+                                                     double *__restrict__ nuc_S, int32_t *__restrict__ nuc_near,
+                                                     const int32_t *__restrict__ done, int B, int vec, int digits) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x;
+  if (done && done[r]) return;   // k_cut_window has settled this row
+  int b = -1;   // the row's request: the last one whose first row, off[b] + b, is not beyond r (every wave by itself)
+  for (int b0 = 0; b0 < B; b0 += 64) b += __popcll(__ballot(b0 + lane < B && off[min(b0 + lane, B)] + b0 + lane <= r));
+  const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
+  const int tk = top_k ? top_k[b] : 0;
+  const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
+  if (!use_k && !use_p) {
+    if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; }
+    return;
+  }
+  // 32 KiB of bins; later the list's running sums (16), or the digit passes' masses (16) and counts (8)
+  __shared__ unsigned long long s_raw[kCutBins / 2];
+  __shared__ __align__(16) uint32_t lkey[kCutList];
+  __shared__ uint32_t lrank[256];
+  __shared__ cut_state st;
+  uint32_t *hist = reinterpret_cast<uint32_t *>(s_raw);
+  for (int i = tid; i < kCutBins; i += kCutThreads) hist[i] = 0u;
+  if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
+    float mx = -INFINITY;
+    for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    const double invT = 1.0 / (double)T;
+    double term = 0.0;
+    for (int c = lane; c < nc; c += 64) {
+      const float pm = pmax[(size_t)r * nc + c];
+      term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
+    if (lane == 0) { st.m = mx; st.S = term; st.n = 0; st.found = 0; st.bad = 0; }
+  }
+  __syncthreads();
+  const float m = st.m;
+  const double S = st.S;
+  const exp_scale k = make_exp_scale(kLog2e / (double)T);
+  const LT *row = logits + (size_t)r * V;
+  // The bin of a token is a chain of correctly rounded, monotone steps, so that no token is filed above one with a larger
+  // logit; -inf (and NaN, which leaves the fast way) ends in the last bin.
+  auto bin_of = [&](float v) { return min((uint32_t)(fmaxf((v - m) * k.hi, -150.0f) * -kCutBinsPerLog2), (uint32_t)(kCutBins - 1)); };
+  auto put = [&](float v) {
+    const int at = atomicAdd(&st.n, 1);
+    if (at < kCutList) lkey[at] = okey(v);
+  };
+  bool fast = !digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9;   // block-uniform
+
+  if (fast) {
+    double tot = 0.0;     // top-p alone on fp32 logits: the row's mass as an integer sum (exact in a double: < 2^53 per thread)
+    double above = 0.0;   // likewise the mass above the candidates
+    bool bad = false;
+    const bool one_pass = use_k && whole_rounds<LT>(V, vec != 0) > 0 && 6l * tk <= kCutList;
+    if (one_pass) {
+      // Once the bin that bounds the cut is known, a token is dismissed by comparing it with a value a little below that
+      // bin's lower edge (extra candidates do no harm): most groups of eight by one branch.
+      float vlim = -INFINITY;
+      bool sampled = false;
+      over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+        if (!sampled) {   // block-uniform
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            bad |= !(v[j] <= m);
+            const uint32_t bin = bin_of(v[j]);
+            if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
+          }
+          return;
+        }
+        bool any = false;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) any |= !(v[j] < vlim);
+        if (any) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            bad |= !(v[j] <= m);
+            if (v[j] >= vlim) put(v[j]);
+          }
+        }
+      }, [&](int round, const auto &v) {
+        if (round != 0) return;
+        __syncthreads();
+        cut_find_bins(hist, (uint32_t)tk, (uint32_t)tk, &st);
+        const float depth = (float)(min(st.bin_lo, (uint32_t)(kCutBins - 2)) + 1) / (kCutBinsPerLog2 * k.hi);
+        vlim = (m - depth * 1.00001f) - 5e-7f * (fabsf(m) + depth);
+        sampled = true;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (v[u][j] >= vlim) put(v[u][j]);
+      });
+      if (__any(bad) && lane == 0) st.bad = 1;
+      __syncthreads();
+      fast = !st.bad;
+    } else {
+      // ---- pass 1: bins ----
+      const float scale = (float)(2147483648.0 / S), drop = (float)(0.9 * (1.0 - (double)tp) * S / V);
+      if (use_k) {
+        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            bad |= !(v[j] <= m);
+            const uint32_t bin = bin_of(v[j]);
+            if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
+          }
+        }, [](int, const auto &) {});
+      } else {   // (a NaN has made the normaliser one, or carries no mass)
+        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float e = exp_scaled(v[j] - m, k);
+            if constexpr (sizeof(LT) == 4) tot += floor((double)e * kNucScale + 0.5);
+            if (e >= drop) atomicAdd(&hist[bin_of(v[j])], (uint32_t)fmaf(e, scale, 0.5f));
+          }
+        }, [](int, const auto &) {});
+      }
+      if (__any(bad) && lane == 0) st.bad = 1;
+      __syncthreads();
+      // the running sums are within half a unit per token of the masses they stand for, the normaliser within 1e-6
+      const double target32 = (double)tp * 2147483648.0, slack = (double)V + 2147483648.0 * 2e-6;
+      const uint32_t x0 = use_k ? (uint32_t)tk : (uint32_t)fmax(1.0, target32 - slack), x1 = use_k ? (uint32_t)tk : (uint32_t)(target32 + slack);
+      cut_find_bins(hist, x0, x1, &st);
+      const uint32_t lo = use_k ? 0u : st.bin_lo, hi = st.bin_hi;
+      fast = !st.bad && hi < kCutBins - 1;
+      // ---- pass 2: candidates, and the mass above them ----
+      if (fast)
+        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const uint32_t bin = bin_of(v[j]);
+            if (bin > hi) continue;
+            if (bin < lo) above += floor((double)exp_scaled(v[j] - m, k) * kNucScale + 0.5);
+            else put(v[j]);
+          }
+        }, [](int, const auto &) {});
+    }
+    // sums over the block: the mass above, and (fp32) the total
+    unsigned long long ta = (unsigned long long)above, tt = (unsigned long long)tot;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      ta += __shfl_xor(ta, o, 64);
+      tt += __shfl_xor(tt, o, 64);
+    }
+    if (lane == 0) { st.w64[w] = ta; st.t64[w] = tt; }
+    __syncthreads();
+    unsigned long long A = 0ull, all = 0ull;
+    for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
+    double total = (sizeof(LT) == 4) ? (double)all : S * kNucScale;   // bf16 logits: the statistics' normaliser (within 1e-7)
+    const int n = st.n;
+    fast = fast && n <= kCutList && n > 0;
+
+    // ---- the list, in descending order of the keys ----
+    if (fast) {
+      if (n <= 256) {
+        // by rank: four threads per candidate, each against a quarter of the list (a short sort by exchanges takes 36 barriers, 6 us)
+        const int i = tid & 255, part = tid >> 8;
+        for (int x = n + tid; x < 256; x += kCutThreads) lkey[x] = 0u;
+        if (tid < 256) lrank[tid] = 0u;
+        __syncthreads();
+        const uint32_t mine = lkey[i];
+        uint32_t rank = 0u;
+#pragma unroll 4
+        for (int x = part * 64; x < part * 64 + 64; x += 4) {
+          const uint4 kx = *reinterpret_cast<const uint4 *>(lkey + x);
+          rank += (kx.x > mine || (kx.x == mine && x < i)) + (kx.y > mine || (kx.y == mine && x + 1 < i)) +
+                  (kx.z > mine || (kx.z == mine && x + 2 < i)) + (kx.w > mine || (kx.w == mine && x + 3 < i));
+        }
+        atomicAdd(&lrank[i], rank);
+        __syncthreads();
+        if (tid < 256) lkey[lrank[tid]] = mine;
+        __syncthreads();
+      } else {
+        int P2 = 512;
+        while (P2 < n) P2 <<= 1;
+        for (int i = n + tid; i < P2; i += kCutThreads) lkey[i] = 0u;
+        for (int size = 2; size <= P2; size <<= 1)
+          for (int gap = size >> 1; gap > 0; gap >>= 1) {
+            __syncthreads();
+            if (tid < P2 / 2) {
+              const int i = 2 * tid - (tid & (gap - 1)), j = i + gap;
+              const uint32_t x = lkey[i], y = lkey[j];
+              if ((x < y) == ((i & size) == 0)) { lkey[i] = y; lkey[j] = x; }
+            }
+          }
+        __syncthreads();
+      }
+      // running mass up to and with each candidate, two consecutive ones per thread
+      unsigned long long q[2], mle[2];
+      uint32_t key[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int i = 2 * tid + u;
+        key[u] = i < n ? lkey[i] : 0u;
+        q[u] = i < n ? nuc_mass(okey_value(key[u]) - m, k) : 0ull;
+      }
+      unsigned long long incl = q[0] + q[1];
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+      }
+      if (lane == 63) st.t64[w] = incl;   // (read by everyone before the sort)
+      __syncthreads();
+      unsigned long long pre = A;
+      for (int i = 0; i < w; ++i) pre += st.t64[i];
+      mle[1] = pre + incl;
+      mle[0] = mle[1] - q[1];
+      const uint32_t prev = tid > 0 && 2 * tid - 1 < n ? lkey[2 * tid - 1] : 0u, next = 2 * tid + 2 < n ? lkey[2 * tid + 2] : 0u;
+      // first / last of its key, u = 0, 1
+      const bool is0 = 2 * tid < n, is1 = 2 * tid + 1 < n;
+      const bool first0 = is0 && (tid == 0 || prev != key[0]), last0 = is0 && (!is1 || key[1] != key[0]);
+      const bool first1 = is1 && key[1] != key[0], last1 = is1 && (2 * tid + 2 >= n || next != key[1]);
+      if (use_k) {
+        const uint32_t kk = lkey[min(tk, n) - 1];
+        if (last0 && key[0] == kk) { st.kkey = kk; st.kmass = mle[0]; }
+        if (last1 && key[1] == kk) { st.kkey = kk; st.kmass = mle[1]; }
+        if (tid == 0) st.found = n >= tk ? 1 : 0;
+        __syncthreads();
+      }
+      if (use_p) {
+        if (use_k) total = (double)st.kmass;
+        const double target = (double)tp * total;
+        const bool ok = !use_k || st.found;
+        __syncthreads();   // found has been read
+        if (tid == 0) st.found = 0;
+        __syncthreads();
+        // the first candidate with which the running mass reaches the target, and the group of equal keys around it
+        if (ok && is0 && (double)mle[0] >= target && !((double)(mle[0] - q[0]) >= target)) { st.cut = key[0]; st.found = 1; }
+        if (ok && is1 && (double)mle[1] >= target && !((double)mle[0] >= target)) { st.cut = key[1]; st.found = 1; }
+        __syncthreads();
+        const uint32_t cut = st.cut;
+        if (first0 && key[0] == cut) st.acc = mle[0] - q[0];
+        if (first1 && key[1] == cut) st.acc = mle[1] - q[1];
+        if (last0 && key[0] == cut) st.kept = mle[0];
+        if (last1 && key[1] == cut) st.kept = mle[1];
+        __syncthreads();
+      }
+      fast = st.found != 0;
+      if (fast && tid == 0) {
+        const double target = (double)tp * total;
+        nuc_key[r] = use_p ? st.cut : st.kkey;
+        nuc_S[r] = (double)(use_p ? st.kept : st.kmass) / kNucScale;
+        nuc_near[r] = (use_p && fmin(target - (double)st.acc, (double)st.kept - target) < 1e-6 * total) ? 1 : 0;
+      }
+    }
+    if (fast) return;
+    __syncthreads();   // the bins and the list make room for the digit passes
+  }
+  unsigned long long *h64 = s_raw;
+  uint32_t *hcnt = reinterpret_cast<uint32_t *>(s_raw + FSV_NUC_BINS);
+  if (use_k) cut_digits<LT, 1>(row, V, vec != 0, m, k, 0u, tk, tp, h64, hcnt, &st);
+  const uint32_t kkey = use_k ? st.kkey : 0u;
+  if (use_p) cut_digits<LT, 0>(row, V, vec != 0, m, k, kkey, tk, tp, h64, hcnt, &st);
+  if (tid == 0) {
+    if (use_p) {
+      const double total = (double)st.total, target = (double)tp * total;
+      nuc_key[r] = st.cut;
+      nuc_S[r] = (double)st.kept / kNucScale;
+      nuc_near[r] = (fmin(target - (double)st.acc, (double)st.kept - target) < 1e-6 * total) ? 1 : 0;
+    } else {
+      nuc_key[r] = kkey;
+      nuc_S[r] = kkey ? (double)st.kmass / kNucScale : -1.0;
+      nuc_near[r] = 0;
+    }
+  }
 }
 
 #define FSV_MAX_GAMMA 16
@@ -967,7 +1223,7 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
     hipLaunchKernelGGL((k_row_stats<LT>), dim3(fsv_ceil_div(nc, 4), gmax + 1, B), dim3(256), 0, s, logits, V, nc,
                        b->draft_offsets, b->temperature, c->pmax, c->psum, c->parg, lvec, 0);
   }
-  // Top-k / top-p cut: only when some request asks for it; one pass over every logits row per key digit and stage.
+  // Top-k / top-p cut: only when some request asks for it.
   bool any_k = false, any_p = false;
   for (int i = 0; i < B; ++i) {
     const bool sampled = !b->temperature_host || b->temperature_host[i] > 0.f;
@@ -976,51 +1232,17 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   }
   const bool nucleus = any_k || any_p;
   if (nucleus) {
-    const int levels = (sizeof(LT) == 2) ? 2 : 3;
-    const int passes = (any_k ? levels : 0) + 1 + (any_p ? levels - 1 : 0);
-    fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT) * passes);
-    // bf16 logits: one windowed pass settles the rows whose cut lies near the top of the row (all of them in practice);
-    // the full passes then find every row done and return at once.  fp32 logits take the full passes.
-    // (FSV_NUCLEUS_FULL=1 in the environment sends every row through the digit-by-digit passes: a test compares the two)
+    fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT) * 2);
+    // (FSV_NUCLEUS_FULL=1 in the environment sends every row through the digit passes: a test compares the two)
     const char *full_env = getenv("FSV_NUCLEUS_FULL");
-    const bool windowed = sizeof(LT) == 2 && !(full_env && full_env[0] == '1');
-    int32_t *done = windowed ? c->nuc_done : nullptr;
-#define FSV_NUC(LEVEL, LAST, MODE)                                                                                     \
-  hipLaunchKernelGGL((k_nucleus<LT, LEVEL, LAST, MODE>), dim3(gmax + 1, B), dim3(1024), 0, s, logits, V, nc,             \
-                     b->draft_offsets, b->temperature, b->top_p, b->top_k, c->pmax, c->nuc_prefix, c->nuc_above,          \
-                     c->nuc_cabove, c->nuc_total, c->nuc_kkey, c->nuc_kmass, c->nuc_key, c->nuc_S, c->nuc_near, done, lvec)
-#define FSV_NUC_TOP1(MODE, WV, FIRSTV)                                                                                 \
-  hipLaunchKernelGGL((k_nucleus_top<MODE, WV, FIRSTV>), dim3(gmax + 1, B), dim3(1024), 0, s, (const uint16_t *)logits,  \
-                     V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, c->pmax, c->psum, c->nuc_kkey,        \
-                     c->nuc_kmass, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, lvec)
-#define FSV_NUC_TOP(MODE)                                                                                              \
-  if (windowed) {                                                                                               \
-    FSV_NUC_TOP1(MODE, 4, true);                                                                                       \
-    FSV_NUC_TOP1(MODE, 8, false);                                                                                      \
-  }
-    if (any_k) {
-      FSV_NUC_TOP(1);
-      FSV_NUC(0, false, 1);
-      if (sizeof(LT) == 2) {
-        FSV_NUC(1, true, 1);
-      } else {
-        FSV_NUC(1, false, 1);
-        FSV_NUC(2, true, 1);
-      }
-    }
-    FSV_NUC_TOP(0);
-    FSV_NUC(0, false, 0);   // also settles the rows that take the top-k cut (or none) as their final one
-    if (any_p) {
-      if (sizeof(LT) == 2) {
-        FSV_NUC(1, true, 0);
-      } else {
-        FSV_NUC(1, false, 0);
-        FSV_NUC(2, true, 0);
-      }
-    }
-#undef FSV_NUC_TOP
-#undef FSV_NUC_TOP1
-#undef FSV_NUC
+    const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
+    // bf16 logits and no top-k: the cut lies within one binade of the maximum more often than not, which is one pass
+    const bool window = sizeof(LT) == 2 && !any_k && !digits;
+    if (window)
+      hipLaunchKernelGGL(k_cut_window, dim3(gmax + 1, B), dim3(1024), 0, s, (const uint16_t *)logits, V, nc, b->draft_offsets, b->temperature,
+                         b->top_p, b->top_k, c->pmax, c->psum, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, lvec);
+    hipLaunchKernelGGL(k_cut<LT>, dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, c->pmax,
+                       c->psum, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, lvec, digits);
   }
   {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_DECIDE, (double)B * V * (sizeof(LT) + 4));
@@ -1116,11 +1338,8 @@ bool carve_static(fsv_ctx &c, unsigned char *base) {
   c.pmax = (float *)take(4 * R * NC); c.psum = (double *)take(8 * R * NC); c.parg = (int32_t *)take(4 * R * NC);
   c.bsum = (double *)take(8 * B * NSB);
   c.acc_scratch = (int32_t *)take(4 * B);
-  c.nuc_prefix = (uint32_t *)take(4 * R); c.nuc_key = (uint32_t *)take(4 * R);
-  c.nuc_above = (unsigned long long *)take(8 * R); c.nuc_total = (unsigned long long *)take(8 * R);
-  c.nuc_S = (double *)take(8 * R); c.nuc_near = (int32_t *)take(4 * R);
-  c.nuc_cabove = (uint32_t *)take(4 * R); c.nuc_kkey = (uint32_t *)take(4 * R); c.nuc_done = (int32_t *)take(4 * R);
-  c.nuc_kmass = (unsigned long long *)take(8 * R);
+  c.nuc_key = (uint32_t *)take(4 * R); c.nuc_S = (double *)take(8 * R); c.nuc_near = (int32_t *)take(4 * R);
+  c.nuc_done = (int32_t *)take(4 * R);
   c.sel_ticket = (int32_t *)take(4 * B);   // starts at zero with the array and is left at zero by every call
   return off <= FSV_STATIC_BYTES;
 }
