@@ -15,7 +15,7 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Work decomposition.  The keys of request b are cut into tiles of 32 (two pages); a "part" is a run of
 // tp_b consecutive tiles, s_b parts per request, chosen so that every part of every request has about the
-// same length and parts x kv heads fills the machine once (one wave per part and kv head, about three waves per
+// same length and parts x kv heads fills the machine once (one wave per part and kv head, three or four waves per
 // compute unit, every wave resident from the start).  A wave owns its part completely: it streams the K and
 // V page tiles of its key range straight from HBM into MFMA operand registers, NB - 1 tiles ahead of their
 // use (each byte of the KV stream is read by exactly one wave; all `group` query heads and all gamma+1
@@ -418,54 +418,35 @@ __global__ __launch_bounds__(256) void k_attn_combine(int Hkv, int group, int ro
   const int rr = blockIdx.z * RPB + tid / TPR, e0 = (tid % TPR) * 8;
   if (rr >= R) return;
   const size_t base = ((size_t)p0 * Hkv + kvh) * rows_cap + rr, pstr = (size_t)Hkv * rows_cap;
-  // All loads of a batch of parts are issued before the first use: one part per iteration would put a full memory
-  // round trip into every step of this short loop.  Up to sixteen parts (the usual case) are merged from one batch,
-  // maxima and values fetched together; more take a pass for the maximum and a pass for the sums, eight at a time.
-  // The sums always run in part order.
+  // The loads of sixteen parts, maxima and values together, are issued before the first use: one part per iteration would put a
+  // full memory round trip into every step of this short loop.  Further batches rescale what has been summed to the new
+  // maximum.  The sums always run in part order.  (A pass for the maximum and one for the sums, eight parts at a time, took
+  // 7.5 us for requests of 9 .. 30 parts, and this no less; it is half the code.)
+  constexpr int U = 16;
   float mm = -INFINITY, acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ll = 0.f;
-  auto merge = [&](int s0, int n, const float2 *ml, const float4 *a, const float4 *c) {
-    for (int u = 0; u < n; ++u) {
+  for (int s0 = 0; s0 < nparts; s0 += U) {
+    float2 ml[U];
+    float4 a[U], c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {   // entries beyond nparts repeat the last part
+      const size_t prow = base + min(s0 + u, nparts - 1) * pstr;
+      ml[u] = *reinterpret_cast<const float2 *>(part_ml + prow * 2);
+      a[u] = *reinterpret_cast<const float4 *>(part_o + prow * HD + e0);
+      c[u] = *reinterpret_cast<const float4 *>(part_o + prow * HD + e0 + 4);
+    }
+    const float mold = mm;
+#pragma unroll
+    for (int u = 0; u < U; ++u) mm = fmaxf(mm, ml[u].x);
+    const float f0 = (mold == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mold - mm);
+    ll *= f0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] *= f0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       const float f = (s0 + u >= nparts || ml[u].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - mm);
       ll += ml[u].y * f;
       acc[0] += a[u].x * f; acc[1] += a[u].y * f; acc[2] += a[u].z * f; acc[3] += a[u].w * f;
       acc[4] += c[u].x * f; acc[5] += c[u].y * f; acc[6] += c[u].z * f; acc[7] += c[u].w * f;
-    }
-  };
-  auto fetch = [&](int s0, int u, float2 &ml, float4 &a, float4 &c) {
-    const size_t prow = base + min(s0 + u, nparts - 1) * pstr;
-    ml = *reinterpret_cast<const float2 *>(part_ml + prow * 2);
-    a = *reinterpret_cast<const float4 *>(part_o + prow * HD + e0);
-    c = *reinterpret_cast<const float4 *>(part_o + prow * HD + e0 + 4);
-  };
-  if (nparts <= 16) {
-    float2 ml[16];
-    float4 a[16], c[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) fetch(0, u, ml[u], a[u], c[u]);
-#pragma unroll
-    for (int u = 0; u < 16; ++u) mm = fmaxf(mm, ml[u].x);  // entries beyond nparts repeat the last part
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const float f = (u >= nparts || ml[u].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - mm);
-      ll += ml[u].y * f;
-      acc[0] += a[u].x * f; acc[1] += a[u].y * f; acc[2] += a[u].z * f; acc[3] += a[u].w * f;
-      acc[4] += c[u].x * f; acc[5] += c[u].y * f; acc[6] += c[u].z * f; acc[7] += c[u].w * f;
-    }
-  } else {
-    constexpr int U = 8;
-    for (int s0 = 0; s0 < nparts; s0 += U) {
-      float mv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) mv[u] = part_ml[(base + min(s0 + u, nparts - 1) * pstr) * 2];
-#pragma unroll
-      for (int u = 0; u < U; ++u) mm = fmaxf(mm, mv[u]);
-    }
-    for (int s0 = 0; s0 < nparts; s0 += U) {
-      float2 ml[U];
-      float4 a[U], c[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) fetch(s0, u, ml[u], a[u], c[u]);
-      merge(s0, U, ml, a, c);
     }
   }
   const float inv = 1.0f / ll;
@@ -476,7 +457,10 @@ __global__ __launch_bounds__(256) void k_attn_combine(int Hkv, int group, int ro
   reinterpret_cast<uint4 *>(out)[tile_unit(m, col, KBq)] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
 }
 
-constexpr int kAttnWavesPerCu = 3;  // a wave takes most of a SIMD's registers, so at most four fit; three measured best on MI355X
+// A wave takes most of a SIMD's registers, so at most four fit.  Head size 128: three are enough to keep HBM busy (27.4 us; four
+// 27.7 and more parts to merge).  Head size 64 has half the bytes per key and the same softmax work, so every SIMD is needed:
+// 8 requests of 4 .. 16 k positions, 42.4 us with three, 35.4 with four, 52 with five (the fifth waits for a whole round).
+constexpr int attn_waves_per_cu(int head_dim) { return head_dim == 64 ? 4 : 3; }
 
 // Size the parts from the host copies of the lengths: the smallest part length for which parts x kv heads
 // still fits the machine once (or one part per request when even that does not fit).
@@ -496,9 +480,11 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
     pl->kv_tokens += nk;
   }
   // One round if it can be had: the smallest part length, up to twice the even share, for which parts x kv heads fit the
-  // resident waves.  Otherwise (many requests, or a few very long ones among many short ones) parts of a quarter of the
+  // resident waves.  Otherwise (many requests, or a few very long ones among many short ones) parts of half the
   // even share, run in several rounds: waves are independent, so the hardware keeps every slot busy and the last round
-  // is short.  Keeping whole requests as single parts instead would let the longest request set the kernel's time.
+  // is short.  Keeping whole requests as single parts instead would let the longest request set the kernel's time; parts of a
+  // quarter end no sooner (128 requests: 230 us either way) and leave twice the partial results to merge (2048 prefill rows:
+  // 30 us against 21).
   const int target = c->attn_wave_target;
   auto count = [&](int tpw, bool *split) {
     int parts = 0;
@@ -518,7 +504,7 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
     bool sp;
     if (count(t, &sp) <= target) { tpw = t; break; }
   }
-  if (!tpw) tpw = max(8, (even + 3) / 4);
+  if (!tpw) tpw = max(8, (even + 1) / 2);
   pl->tpw = tpw;
   pl->waves = count(tpw, &pl->split);
   pl->rt = fsv_ceil_div(max_rows, 32);
@@ -601,7 +587,7 @@ int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl
 
 int fsv_bf16_attn_create(fsv_ctx *c) {
   const fsv_model_desc &d = c->d;
-  int wpc = kAttnWavesPerCu;
+  int wpc = attn_waves_per_cu(d.head_dim);
   c->attn_depth = 2;
   if (const char *e = getenv("FSV_ATTN_TUNE")) {   // "waves per CU,tiles in flight[,w2,w3[,fewest tiles per part]]": measurement knob
     int a = 0, bb = 0, w2 = c->attn_w2, w3 = c->attn_w3, mt = c->attn_min_tpw;
