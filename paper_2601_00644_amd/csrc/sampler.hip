@@ -919,9 +919,10 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
 
 // Acceptance tests, masses and token selection of one request.  grid = (ceil(sub-blocks / 4), requests).
 //
-// Phase 1, every block: the acceptance tests.  Wave w combines the per-chunk statistics of rows w, w+4, ... (one chunk per
-//   lane: row max with the lowest id attaining it, then the sum of the rescaled chunk sums over a fixed shuffle tree; the
-//   loads of all of a wave's rows are issued together); then thread i tests draft i+1 from two gathered scalars, and
+// Phase 1, every block: the acceptance tests.  Sixteen lanes combine the per-chunk statistics of a row (up to three chunks per
+//   lane: row max with the lowest id attaining it, then the sum of the rescaled chunk sums over a fixed shuffle tree), all rows
+//   of the request side by side (four rows per wave one after the other took 3 us longer at 16 drafts); then thread i tests
+//   draft i+1 from two gathered scalars, and
 //   thread 0 takes the accepted prefix.  Every block of the request repeats this (a few KB from L2) instead of waiting
 //   for a launch of its own.
 // Phase 2: wave w of block x takes sub-block 4x + w of the row the emitted token is drawn from (the residual
@@ -960,19 +961,23 @@ __global__ __launch_bounds__(256) void k_decide(
   float qd_in = 0.f, u_in = 0.f;
   uint32_t cut_in = 0u;
   {
-    constexpr int RW = (FSV_MAX_GAMMA + 1 + 3) / 4;   // rows a wave combines at most
-    float pm[RW];
-    double ps[RW];
-    int pa[RW];
+    constexpr int CPL = (FSV_MAX_NSB / FSV_SPC + 15) / 16;   // chunks per lane
+    const int l16 = tid & 15;
+    float pm[CPL];
+    double ps[CPL];
+    int pa[CPL];
+    auto load_row = [&](int i) {
 #pragma unroll
-    for (int j = 0; j < RW; ++j) {
-      const int i = w + 4 * j;
-      const bool live = i <= gamma && lane < nc;
-      const size_t at = (size_t)(rs + min(i, gamma)) * nc + min(lane, nc - 1);
-      pm[j] = live ? pmax[at] : -INFINITY;
-      ps[j] = live ? psum[at] : 0.0;
-      pa[j] = live ? parg[at] : INT_MAX;
-    }
+      for (int j = 0; j < CPL; ++j) {
+        const int c = l16 + 16 * j;
+        const bool live = i <= gamma && c < nc;
+        const size_t at = (size_t)(rs + min(i, gamma)) * nc + min(c, nc - 1);
+        pm[j] = live ? pmax[at] : -INFINITY;
+        ps[j] = live ? psum[at] : 0.0;
+        pa[j] = live ? parg[at] : INT_MAX;
+      }
+    };
+    load_row(tid >> 4);
     // What draft tid + 1 is tested on: its logit, its draft probability, its uniform.  Issued here, so that the two dependent
     // round trips (token, then the values it points at) pass while the statistics are combined.
     if (T > 0.f && tid < gamma) {
@@ -982,23 +987,28 @@ __global__ __launch_bounds__(256) void k_decide(
       u_in = u_acc[o + tid];
       if (nuc_key) cut_in = nuc_key[rs + tid];
     }
+    for (int i = tid >> 4; i <= gamma; i += 16) {   // (a second trip for the first sixteen threads only when gamma is 16)
+      if (i >= 16) load_row(i);
+      float mx = pm[0];
+      int ai = pa[0];
 #pragma unroll
-    for (int j = 0; j < RW; ++j) {
-      const int i = w + 4 * j;
-      if (i > gamma) continue;   // wave-uniform
-      float mx = pm[j];
-      int ai = pa[j];
+      for (int j = 1; j < CPL; ++j)
+        if (pm[j] > mx || (pm[j] == mx && pa[j] < ai)) { mx = pm[j]; ai = pa[j]; }
 #pragma unroll
-      for (int sh = 32; sh > 0; sh >>= 1) {
-        const float om = __shfl_xor(mx, sh, 64);
-        const int oi = __shfl_xor(ai, sh, 64);
+      for (int sh = 8; sh > 0; sh >>= 1) {
+        const float om = __shfl_xor(mx, sh, 16);
+        const int oi = __shfl_xor(ai, sh, 16);
         if (om > mx || (om == mx && oi < ai)) { mx = om; ai = oi; }
       }
       double term = 0.0;
-      if (T > 0.f && lane < nc) term = ps[j] * ((pm[j] == mx) ? 1.0 : exp(((double)pm[j] - (double)mx) * invT));
+      if (T > 0.f) {
 #pragma unroll
-      for (int sh = 32; sh > 0; sh >>= 1) term += __shfl_xor(term, sh, 64);
-      if (lane == 0) {
+        for (int j = 0; j < CPL; ++j)
+          if (l16 + 16 * j < nc) term += ps[j] * ((pm[j] == mx) ? 1.0 : exp(((double)pm[j] - (double)mx) * invT));
+      }
+#pragma unroll
+      for (int sh = 8; sh > 0; sh >>= 1) term += __shfl_xor(term, sh, 16);
+      if (l16 == 0) {
         s_m[i] = (double)mx;
         // a row cut to its most probable tokens is normalised by the kept mass; its cut key masks the tokens outside
         s_S[i] = (nuc_S && nuc_S[rs + i] >= 0.0) ? nuc_S[rs + i] : term;
