@@ -889,18 +889,9 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
 
 #define FSV_MAX_GAMMA 16
 
-template <typename LT>
-__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, bool lvec, bool qvec,
-                                       float m, exp_scale k, double invS, bool residual, bool fast, uint32_t cutkey,
-                                       double (&mass)[8]) {
-  float lv[8], qv[8];
-  if (fast) {  // the caller has checked alignment and range for the whole sub-block
-    loader<LT>::load8_fast(lrow, i0, lv);
-    if (residual) loader<float>::load8_fast(qrow, i0, qv);
-  } else {
-    loader<LT>::load8(lrow, i0, V, lvec, -INFINITY, lv);
-    if (residual) loader<float>::load8(qrow, i0, V, qvec, 0.f, qv);
-  }
+// Eight ids' masses from their logits and draft probabilities: p, or (residual) max(0, p - q); their sum in id order.
+__device__ inline double masses_of(const float (&lv)[8], const float (&qv)[8], float m, exp_scale k, double invS, bool residual,
+                                   uint32_t cutkey, double (&mass)[8]) {
   double t = 0.0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -913,6 +904,15 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
     t += p;
   }
   return t;
+}
+
+template <typename LT>
+__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, bool lvec, bool qvec,
+                                       float m, exp_scale k, double invS, bool residual, uint32_t cutkey, double (&mass)[8]) {
+  float lv[8], qv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  loader<LT>::load8(lrow, i0, V, lvec, -INFINITY, lv);
+  if (residual) loader<float>::load8(qrow, i0, V, qvec, 0.f, qv);
+  return masses_of(lv, qv, m, k, invS, residual, cutkey, mass);
 }
 
 #define FSV_MAX_NSB 160
@@ -1066,13 +1066,23 @@ __global__ __launch_bounds__(256) void k_decide(
   {
     const int sb = blockIdx.x * 4 + w;
     if (sb < nsb) {
-      double tot = 0.0;
-      const bool fast = lvec && qvec && (sb + 1) * FSV_SBK <= V;  // wave-uniform
+      constexpr int PARTS = FSV_SBK / 512;
+      double tot = 0.0, mass[8];
+      if (lvec && qvec && (sb + 1) * FSV_SBK <= V) {   // wave-uniform; all loads of the sub-block before the first use
+        float lv[PARTS][8], qv[PARTS][8];
 #pragma unroll
-      for (int part = 0; part < FSV_SBK / 512; ++part) {
-        double mass[8];
-        tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, lvec != 0, qvec != 0, (float)m, k, invS,
-                                 residual, fast, cutkey, mass);
+        for (int part = 0; part < PARTS; ++part) loader<LT>::load8_fast(lrow, sb * FSV_SBK + part * 512 + lane * 8, lv[part]);
+        if (residual) {
+#pragma unroll
+          for (int part = 0; part < PARTS; ++part) loader<float>::load8_fast(qrow, sb * FSV_SBK + part * 512 + lane * 8, qv[part]);
+        }
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) tot += masses_of(lv[part], qv[part], (float)m, k, invS, residual, cutkey, mass);
+      } else {
+#pragma unroll 1
+        for (int part = 0; part < PARTS; ++part)
+          tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, lvec != 0, qvec != 0, (float)m, k, invS,
+                                   residual, cutkey, mass);
       }
 #pragma unroll
       for (int sh = 32; sh > 0; sh >>= 1) tot += __shfl_xor(tot, sh, 64);
@@ -1099,13 +1109,11 @@ __global__ __launch_bounds__(256) void k_decide(
   __shared__ double s_sb[FSV_MAX_NSB];
   __shared__ double s_w[4];
   __shared__ double s_Z, s_lo;
-  __shared__ int s_pick, s_first, s_lastpos;
+  __shared__ int s_pick, s_wfirst[4], s_wlast[4];
   if (tid == 0) {
     __hip_atomic_store(&ticket[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
     accepted_len[b] = tau;
     rollback(tau);
-    s_first = INT_MAX;
-    s_lastpos = -1;
   }
   // Wave 0 takes the sub-block masses, PER consecutive ones per lane, and finds the first sub-block whose running mass exceeds
   // u times the total (lane sums and their shuffle scan: a fixed order).  One thread adding and comparing them one after the
@@ -1157,7 +1165,7 @@ __global__ __launch_bounds__(256) void k_decide(
     for (int sb = 0; sb < nsb; ++sb) {
       double mass[8], tot;
       double t = thread_masses<LT>(lrow, qrow, sb * FSV_SBK + tid * 8, V, lvec != 0, qvec != 0, (float)m, k, invS,
-                                   false, false, cutkey, mass);
+                                   false, cutkey, mass);
       block_incl_scan(t, s_w, &tot);
       if (tid == 0) s_sb[sb] = tot;
     }
@@ -1170,24 +1178,31 @@ __global__ __launch_bounds__(256) void k_decide(
   const double lo = s_lo;
   double mass[8];
   const int i0 = sb * FSV_SBK + tid * 8;
-  double t = thread_masses<LT>(lrow, qrow, i0, V, lvec != 0, qvec != 0, (float)m, k, invS, residual, false, cutkey, mass);
+  double t = thread_masses<LT>(lrow, qrow, i0, V, lvec != 0, qvec != 0, (float)m, k, invS, residual, cutkey, mass);
   double incl = block_incl_scan(t, s_w, nullptr);
+  // the first thread whose running mass crosses, and the last id with mass: a ballot per wave (LDS atomics of all 256 threads
+  // on one address cost 3 us here)
   const bool crosses = (lo + incl) > target;  // false for every thread when lo == inf
-  if (crosses) atomicMin(&s_first, tid);
   int lp = -1;
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     if (mass[j] > 0.0) lp = i0 + j;
-  if (lp >= 0) atomicMax(&s_lastpos, lp);
+  const unsigned long long cb = __ballot(crosses), pb = __ballot(lp >= 0);
+  const int wave_lp = __shfl(lp, pb ? 63 - (int)__builtin_clzll(pb) : 0, 64);
+  if (lane == 0) {
+    s_wfirst[w] = cb ? w * 64 + (int)__builtin_ctzll(cb) : INT_MAX;
+    s_wlast[w] = pb ? wave_lp : -1;
+  }
   __syncthreads();
-  if (s_first == INT_MAX) {
+  const int first = min(min(s_wfirst[0], s_wfirst[1]), min(s_wfirst[2], s_wfirst[3]));
+  if (first == INT_MAX) {
     if (tid == 0) {
-      next_token[b] = max(s_lastpos, 0);
+      next_token[b] = max(max(max(s_wlast[0], s_wlast[1]), max(s_wlast[2], s_wlast[3])), 0);
       flags[b] = (s_flags & (residual ? ~0u : ~4u)) | 2u;
     }
     return;
   }
-  if (tid == s_first) {
+  if (tid == first) {
     double run = lo + (incl - t), margin = 0.0;
     int pick = -1;
 #pragma unroll
