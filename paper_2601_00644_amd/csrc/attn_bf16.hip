@@ -58,7 +58,8 @@ __device__ __host__ inline int attn_parts(int n, int tpw, int w16, int *tp) {
 // length, drafts, first row, (pad), and the physical pages of the part's first two tiles -- a wave fetches it with three
 // scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
 constexpr int kDescInts = 12;
-// Everything the forward's kernels look up about a call, in one launch: the attention schedule (block 0), and for every row
+// Everything the forward's kernels look up about a call, in one launch: the attention schedule (block 0), for the stand-alone
+// attention the query operand (the last blocks; 6 us as a launch of its own, two bytes per lane), and for every row
 // its request, index, position and token and the cos / sin of its rotation angles (the other blocks; the angles depend on the
 // row's position only, not on the layer: tab[(row * half + i) * 2 + {0, 1}], formed and reduced in fp64).
 // Bound by latency: a load of the lengths, a scan or search in LDS, a load of the page ids, the stores.  One thread walking
@@ -71,6 +72,11 @@ struct setup_args {
   const double *inv_freq;
   int32_t *part_prefix, *part_desc, *row_req, *row_idx, *row_pos, *row_tok;
   float *tab;
+  // stand-alone attention: the caller's rotated queries [M][heads][hd] (bf16), to be put into the query operand
+  int row_blocks = 0, H = 0, Hkv = 0, hd = 0, q_vec = 0;
+  const uint16_t *q = nullptr;
+  uint16_t *qp = nullptr;
+  size_t q_plane = 0;
 };
 __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
   __shared__ int32_t s_pre[kSetupB + 1];
@@ -85,6 +91,32 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     }
     return lo;
   };
+  if ((int)blockIdx.x > p.row_blocks) {   // ---- queries, eight features per thread ----
+    const bool in_lds = B <= kSetupB;
+    if (in_lds) {
+      for (int b = tid; b <= B; b += kSetupThreads) s_pre[b] = p.off[b];
+      __syncthreads();
+    }
+    const int32_t *off = in_lds ? s_pre : p.off;
+    const int per = p.H * (p.hd / 8), t = (int)(blockIdx.x - 1 - p.row_blocks) * kSetupThreads + tid, r = t / per;
+    if (r >= p.M) return;
+    const int hh = (t - r * per) / (p.hd / 8), e = ((t - r * per) % (p.hd / 8)) * 8;
+    const int b = find(off, 1, r), rr = (r - off[b] - b) * p.group + hh % p.group;
+    const uint16_t *src = p.q + (size_t)r * p.H * p.hd + hh * p.hd + e;
+    uint4 v;
+    if (p.q_vec) {
+      v = *reinterpret_cast<const uint4 *>(src);
+    } else {
+      uint32_t w4[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w4[j] = (uint32_t)src[2 * j] | ((uint32_t)src[2 * j + 1] << 16);
+      v = make_uint4(w4[0], w4[1], w4[2], w4[3]);
+    }
+    const size_t o = q_elem_off(b, hh / p.group, rr, e, p.Hkv, p.hd);
+    *reinterpret_cast<uint4 *>(p.qp + o) = v;
+    *reinterpret_cast<uint4 *>(p.qp + p.q_plane + o) = make_uint4(0, 0, 0, 0);   // the caller's queries are bf16 already
+    return;
+  }
   if (blockIdx.x > 0) {   // ---- rows ----
     const bool in_lds = B <= kSetupB;
     if (in_lds) {
@@ -164,13 +196,20 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
   }
 }
 
+// Four fp16 values as floats, for the stand-alone entry point's row-major result (a 16-byte store at any 4-byte boundary).
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline void store_row4(float *p, uint32_t lo, uint32_t hi) {
+  *reinterpret_cast<f32x4_u *>(p) = (f32x4_u){h2f((uint16_t)(lo & 0xffffu)), h2f((uint16_t)(lo >> 16)), h2f((uint16_t)(hi & 0xffffu)),
+                                              h2f((uint16_t)(hi >> 16))};
+}
+
 template <int HD, int RT, int NB>
 __global__ __launch_bounds__(64) void k_attention(
     int Hkv, int group, int rows_cap, const uint4 *__restrict__ qp, size_t q_plane_units,
     const int32_t *__restrict__ part_desc,
     const int32_t *__restrict__ page_table, int max_pages, int num_pages, const uint16_t *__restrict__ kpool,
     const uint16_t *__restrict__ vpool, uint32_t layer_bytes, float *__restrict__ part_o, float *__restrict__ part_ml,
-    uint16_t *__restrict__ out, int KBq) {
+    uint16_t *__restrict__ out, int KBq, float *__restrict__ out32) {
   constexpr int KS = HD / 16, VC = HD / 32, TILEB = 16 * HD * 2;  // TILEB: bytes of one (page, kv head) tile
   constexpr uint32_t OOB = 0xFFFF0000u;                            // offset no descriptor here reaches
   constexpr int kStream = 2;  // non-temporal: K/V bytes are used once and should not displace the queries and partials in L2
@@ -386,7 +425,8 @@ __global__ __launch_bounds__(64) void k_attention(
           // the output is a convex combination of cached values: bounded, so it is handed on in fp16
           const uint32_t lo = f2h2(o[rt][c][4 * g] * inv, o[rt][c][4 * g + 1] * inv);
           const uint32_t hi = f2h2(o[rt][c][4 * g + 2] * inv, o[rt][c][4 * g + 3] * inv);
-          *reinterpret_cast<uint2 *>(out + tile_unit(m, col + e0, KBq) * 8 + 4 * h) = make_uint2(lo, hi);
+          if (out32) store_row4(out32 + (size_t)m * KBq * 16 + col + e0 + 4 * h, lo, hi);
+          else *reinterpret_cast<uint2 *>(out + tile_unit(m, col + e0, KBq) * 8 + 4 * h) = make_uint2(lo, hi);
         }
     } else {
       const size_t prow = (size_t)gw * rows_cap + rr;
@@ -409,7 +449,7 @@ __global__ __launch_bounds__(256) void k_attn_combine(int Hkv, int group, int ro
                                                       const int32_t *__restrict__ part_prefix,
                                                       const float *__restrict__ part_o,
                                                       const float *__restrict__ part_ml, uint16_t *__restrict__ out,
-                                                      int KBq) {
+                                                      int KBq, float *__restrict__ out32) {
   constexpr int TPR = HD / 8, RPB = 256 / TPR;  // threads per row (eight features each), rows per block
   const int b = blockIdx.y, kvh = blockIdx.x, tid = threadIdx.x;
   const int p0 = part_prefix[b], nparts = part_prefix[b + 1] - p0;
@@ -454,7 +494,13 @@ __global__ __launch_bounds__(256) void k_attn_combine(int Hkv, int group, int ro
 #pragma unroll
   for (int j = 0; j < 4; ++j) pk[j] = f2h2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
   const int m = rs + rr / group, col = (kvh * group + rr % group) * HD + e0;
-  reinterpret_cast<uint4 *>(out)[tile_unit(m, col, KBq)] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+  if (out32) {
+    float *dst = out32 + (size_t)m * KBq * 16 + col;
+    store_row4(dst, pk[0], pk[1]);
+    store_row4(dst + 4, pk[2], pk[3]);
+  } else {
+    reinterpret_cast<uint4 *>(out)[tile_unit(m, col, KBq)] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+  }
 }
 
 // A wave takes most of a SIMD's registers, so at most four fit.  Head size 128: three are enough to keep HBM busy (27.4 us; four
@@ -514,7 +560,7 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   return FSV_OK;
 }
 
-int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, hipStream_t st) {
+int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, const void *q, hipStream_t st) {
   setup_args a;
   a.B = b->batch; a.tpw = pl.tpw; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
   a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.map_cap = c->attn_wave_cap / c->d.n_kv_heads + 1;
@@ -524,12 +570,19 @@ int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M,
   a.part_prefix = c->attn_part_prefix; a.part_desc = c->attn_part_map;
   a.row_req = c->row_req; a.row_idx = c->row_idx; a.row_pos = c->row_pos; a.row_tok = c->row_tok;
   a.tab = rope ? (float *)c->rope_tab : nullptr;
-  hipLaunchKernelGGL(k_setup, dim3(1 + fsv_ceil_div(M * a.half, kSetupThreads)), dim3(kSetupThreads), 0, st, a);
+  a.row_blocks = fsv_ceil_div(M * a.half, kSetupThreads);
+  int q_blocks = 0;
+  if (q) {
+    a.H = c->d.n_heads; a.Hkv = c->d.n_kv_heads; a.hd = c->d.head_dim; a.q_vec = ((uintptr_t)q % 16 == 0) ? 1 : 0;
+    a.q = (const uint16_t *)q; a.qp = (uint16_t *)c->buf_q; a.q_plane = c->q_plane_units * 8;
+    q_blocks = fsv_ceil_div(M * a.H * (a.hd / 8), kSetupThreads);
+  }
+  hipLaunchKernelGGL(k_setup, dim3(1 + a.row_blocks + q_blocks), dim3(kSetupThreads), 0, st, a);
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
 }
 
-int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, size_t layer_off, hipStream_t st) {
+int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, size_t layer_off, float *out32, hipStream_t st) {
   const fsv_model_desc &d = c->d;
   const int group = c->group, KBq = d.n_heads * d.head_dim / 16;
   const int rows_cap = group * (d.max_gamma + 1);
@@ -544,7 +597,7 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
   hipExtLaunchKernelGGL((k_attention<HDV, RTV, NBV>), dim3(pl.waves), dim3(64), 0, st, ps.start(), ps.stop(), 0,   \
                         d.n_kv_heads, group, rows_cap,                                                             \
                      (const uint4 *)c->buf_q, c->q_plane_units, c->attn_part_map, b->page_table, d.max_pages_per_req, b->num_pages,  \
-                     kl, vl, layer_bytes, po, pml, out, KBq)
+                     kl, vl, layer_bytes, po, pml, out, KBq, out32)
     const bool deep = c->attn_depth >= 3;   // tiles in flight per wave: 2 (one ahead) or 3 (two ahead)
     if (d.head_dim == 128) {
       if (pl.rt <= 1) { if (deep) FSV_ATTN_LAUNCH(128, 1, 3); else FSV_ATTN_LAUNCH(128, 1, 2); }
@@ -564,10 +617,10 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
     dim3 cg(d.n_kv_heads, b->batch, fsv_ceil_div(pl.rt * 32, rpb));
     if (d.head_dim == 128)
       hipLaunchKernelGGL((k_attn_combine<128>), cg, dim3(256), 0, st, d.n_kv_heads, group, rows_cap, b->draft_offsets,
-                         c->attn_part_prefix, po, pml, out, KBq);
+                         c->attn_part_prefix, po, pml, out, KBq, out32);
     else
       hipLaunchKernelGGL((k_attn_combine<64>), cg, dim3(256), 0, st, d.n_kv_heads, group, rows_cap, b->draft_offsets,
-                         c->attn_part_prefix, po, pml, out, KBq);
+                         c->attn_part_prefix, po, pml, out, KBq, out32);
     FSV_HIP(c, hipGetLastError());
   }
   return FSV_OK;
@@ -577,12 +630,12 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
 
 int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) { return plan_attention(c, b, pl); }
 
-int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, hipStream_t st) {
-  return launch_setup(c, b, *pl, M, rope, st);
+int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, const void *q, hipStream_t st) {
+  return launch_setup(c, b, *pl, M, rope, q, st);
 }
 
-int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, hipStream_t st) {
-  return launch_attention(c, b, *pl, layer_off, st);
+int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, float *out32, hipStream_t st) {
+  return launch_attention(c, b, *pl, layer_off, out32, st);
 }
 
 int fsv_bf16_attn_create(fsv_ctx *c) {

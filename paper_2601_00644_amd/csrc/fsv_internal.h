@@ -183,9 +183,11 @@ struct fsv_attn_plan {
 };
 int fsv_bf16_attn_create(fsv_ctx *c);
 int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl);          // host only; may fail
-// row map, attention schedule and (rope) rotation angles of a call, on the device
-int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, hipStream_t s);
-int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, hipStream_t s);
+// row map, attention schedule and (rope) rotation angles of a call, on the device; q: rotated queries to put into the query
+// operand (the stand-alone attention), or NULL
+int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, const void *q, hipStream_t s);
+// out32: row-major fp32 result [M][heads * hd], or NULL = the operand of the output projection (buf_att)
+int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, float *out32, hipStream_t s);
 // gemm_bf16.hip: y = x W^T through the weight-streaming kernel; epi 0 = fp32 split partials [splits][Mpad][N],
 // 1 = SwiGLU to the bf16 operand order, 2 = fp32 rows [M][N]
 int fsv_bf16_gemm_init(fsv_ctx *c);

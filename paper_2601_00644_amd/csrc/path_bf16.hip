@@ -93,22 +93,6 @@ __global__ void k_pack_act(const uint16_t *__restrict__ x, int M, int Mpad, int 
   out[tile_unit(m, k0, K / 16)] = v;
 }
 
-// operand order fp16 (the attention output) -> row-major fp32 [M][K]
-__global__ void k_unpack_act(const uint4 *__restrict__ in, int M, int K, float *__restrict__ y) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int K8 = K / 8;
-  if (t >= (size_t)M * K8) return;
-  const int m = t / K8, k0 = (t % K8) * 8;
-  uint4 v = in[tile_unit(m, k0, K / 16)];
-  uint32_t w[4] = {v.x, v.y, v.z, v.w};
-  float *dst = y + (size_t)m * K + k0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    dst[2 * j] = h2f((uint16_t)(w[j] & 0xffffu));
-    dst[2 * j + 1] = h2f((uint16_t)(w[j] >> 16));
-  }
-}
-
 // y[m][src(n')] = sum_s part[s][m][n']   (fixed order over s)
 __global__ void k_reduce_part(const float *__restrict__ part, int S, int Mpad, int M, int N, int mode, int F,
                               float *__restrict__ y) {
@@ -575,19 +559,6 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
   }
 }
 
-// row-major rotated queries [M][H][hd] -> query operand (stand-alone attention entry point)
-__global__ void k_pack_q(int H, int Hkv, int hd, const uint16_t *__restrict__ q, const int32_t *__restrict__ row_req,
-                         const int32_t *__restrict__ row_idx, uint16_t *__restrict__ qp, size_t q_plane) {
-  const int r = blockIdx.x, group = H / Hkv;
-  const int b = row_req[r], i_row = row_idx[r];
-  for (int idx = threadIdx.x; idx < H * hd; idx += blockDim.x) {
-    const int hh = idx / hd, e = idx % hd;
-    const size_t o = q_elem_off(b, hh / group, i_row * group + hh % group, e, Hkv, hd);
-    qp[o] = q[(size_t)r * H * hd + idx];
-    qp[q_plane + o] = 0;  // the caller's queries are bf16 already
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // head of the draft model (Sec. IV-A: two-layer MLP + vocabulary projection); its law is in sampler.hip
 // ---------------------------------------------------------------------------------------------
@@ -864,7 +835,7 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
   const int nthr = min(1024, max(64, fsv_ceil_div(d.d_model / 8, 64) * 64));  // one 8-wide slice per thread
   int rc;
   const fsv_attn_plan &pl = *plan;
-  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, true, s))) return rc;
+  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, true, nullptr, s))) return rc;
   // draft model (Sec. IV-A): only the anchor block (the last layer) on the draft's one-layer KV pools, then its own head
   const int l_first = draft ? d.n_layers - 1 : 0;
   // adapters of the evolved target: per-request LoRA pairs on q|k|v and o of every layer but the last
@@ -913,7 +884,7 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
         hipLaunchKernelGGL(k_rope_append<0>, rg, dim3(256), 0, s, FSV_ROPE_ARGS, nullptr, 0, 0, nullptr, nullptr, nullptr);
 #undef FSV_ROPE_ARGS
     }
-    if ((rc = fsv_bf16_attn_launch(c, b, &pl, lo, s))) return rc;
+    if ((rc = fsv_bf16_attn_launch(c, b, &pl, lo, nullptr, s))) return rc;
     if ((rc = launch_gemm<EPI_PARTIAL>(c, FSV_K_GEMM_O, L.w_o, c->buf_att, part, so, M, glo, s, L.os_o))) return rc;
     {
       fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
@@ -1066,18 +1037,9 @@ int fsv_bf16_linear(fsv_ctx *c, int which, int layer, const void *x, int M, floa
 
 int fsv_bf16_attention(fsv_ctx *c, int layer, const void *q, const fsv_batch *b, const fsv_attn_plan *plan, int M, float *out,
                        hipStream_t s) {
-  const fsv_model_desc &d = c->d;
-  const fsv_attn_plan &pl = *plan;
   int rc;
-  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, false, s))) return rc;
-  hipLaunchKernelGGL(k_pack_q, dim3(M), dim3(256), 0, s, d.n_heads, d.n_kv_heads, d.head_dim, (const uint16_t *)q,
-                     c->row_req, c->row_idx, (uint16_t *)c->buf_q, c->q_plane_units * 8);
-  if ((rc = fsv_bf16_attn_launch(c, b, &pl, (size_t)layer * layer_stride(c, b->num_pages), s))) return rc;
-  const int qd = d.n_heads * d.head_dim;
-  const size_t n = (size_t)M * (qd / 8);
-  hipLaunchKernelGGL(k_unpack_act, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const uint4 *)c->buf_att, M, qd, out);
-  FSV_HIP(c, hipGetLastError());
-  return FSV_OK;
+  if ((rc = fsv_bf16_setup_launch(c, b, plan, M, false, q, s))) return rc;
+  return fsv_bf16_attn_launch(c, b, plan, (size_t)layer * layer_stride(c, b->num_pages), out, s);
 }
 
 int fsv_bf16_kv_copy(fsv_ctx *c, void *k_pool, void *v_pool, int num_pages, const int32_t *pt_row, int pos0, int n,
