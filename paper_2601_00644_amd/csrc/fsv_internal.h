@@ -24,6 +24,22 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 #define FSV_SPC 4
 #define FSV_CHUNK (FSV_SBK * FSV_SPC)
 
+// Sum of eight values over the wave, all eight at once: every exchange halves the values a lane still carries, so it takes
+// ten shuffles instead of forty-eight.  Lane l ends with the sum of value 4 l5 + 2 l4 + l3 (l5 .. l3: bits of l).
+__device__ inline float wave_sum8(float (&v)[8], int lane) {
+#pragma unroll
+  for (int cnt = 4, off = 32; cnt >= 1; cnt >>= 1, off >>= 1)
+#pragma unroll
+    for (int i = 0; i < cnt; ++i) {
+      const float send = (lane & off) ? v[i] : v[i + cnt], keep = (lane & off) ? v[i + cnt] : v[i];
+      v[i] = keep + __shfl_xor(send, off, 64);
+    }
+  float r = v[0];
+#pragma unroll
+  for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+  return r;
+}
+
 struct fsv_prof_rec {
   int cls;
   double bytes;

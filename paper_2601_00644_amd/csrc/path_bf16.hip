@@ -136,7 +136,8 @@ template <typename F>
 __device__ inline void lora_shrink(const uint16_t *__restrict__ A, int rank, int K, int tid, int nthreads, F &&slice,
                                    float (*s_part)[64], float *s_t) {
   const int w = tid >> 6, nw = nthreads >> 6;
-  for (int j0 = 0; j0 < rank; j0 += 8) {
+#pragma unroll 2
+  for (int j0 = 0; j0 < rank; j0 += 8) {   // (ranks are multiples of eight)
     float part[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int k0 = tid * 8; k0 < K; k0 += nthreads * 8) {
       float xv[8];
@@ -150,11 +151,8 @@ __device__ inline void lora_shrink(const uint16_t *__restrict__ A, int rank, int
           part[j] += __uint_as_float(w4[u] << 16) * xv[2 * u] + __uint_as_float(w4[u] & 0xffff0000u) * xv[2 * u + 1];
       }
     }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float t = wave_sum(part[j]);
-      if ((tid & 63) == 0) s_part[w][j0 + j] = t;
-    }
+    const float t = wave_sum8(part, tid & 63);   // lane l: rank j0 + 4 l5 + 2 l4 + l3
+    if ((tid & 7) == 0) s_part[w][j0 + ((tid >> 5) & 1) * 4 + ((tid >> 4) & 1) * 2 + ((tid >> 3) & 1)] = t;
   }
   __syncthreads();
   if (tid < rank) {
@@ -179,11 +177,6 @@ __global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, float eps, co
   float *xr = x + (size_t)r * d;
   __shared__ float s_ss[16];
   __shared__ float s_part[(LQ || LO) ? 16 : 1][64], s_t[64];
-  int ad = -1;
-  if (LQ || LO) {
-    ad = lo.adapter[lo.row_req[r]];
-    if (ad < 0 || ad >= lo.n) ad = -1;   // block-uniform: the row's request has no adapter
-  }
   // sum of the split slices (in slice order) on top of the residual, or the embedding row
   auto gather = [&](int k0, float(&v)[8]) {
     if (EMBED) {
@@ -242,6 +235,11 @@ __global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, float eps, co
     if (live) {
       graw = *reinterpret_cast<const uint4 *>(gain + k0);
       gather(k0, v);
+    }
+    int ad = -1;   // two dependent lookups: behind the loads just issued
+    if (LQ || LO) {
+      ad = lo.adapter[lo.row_req[r]];
+      if (ad < 0 || ad >= lo.n) ad = -1;   // block-uniform: the row's request has no adapter
     }
     if (LO && ad >= 0) {
       // output projection of an adapted request: v += s B_o (A_o att), att = this row of the attention output

@@ -20,22 +20,6 @@ __global__ void k_embed(int d, const float *__restrict__ E, const int32_t *__res
   for (int k = threadIdx.x; k < d; k += blockDim.x) x[(size_t)r * d + k] = src[k];
 }
 
-// Sum of eight values over the wave, all eight at once: every exchange halves the values a lane still carries, so it takes
-// ten shuffles instead of forty-eight.  Lane l ends with the sum of value 4 l5 + 2 l4 + l3 (l5 .. l3: bits of l).
-__device__ inline float wave_sum8(float (&v)[8], int lane) {
-#pragma unroll
-  for (int cnt = 4, off = 32; cnt >= 1; cnt >>= 1, off >>= 1)
-#pragma unroll
-    for (int i = 0; i < cnt; ++i) {
-      const float send = (lane & off) ? v[i] : v[i + cnt], keep = (lane & off) ? v[i + cnt] : v[i];
-      v[i] = keep + __shfl_xor(send, off, 64);
-    }
-  float r = v[0];
-#pragma unroll
-  for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
-  return r;
-}
-
 // y[m][n] (+)= sum_k a[m][k] w[n][k]; one wave per output column and eight rows, lanes stride over k.
 // NORM: the rows are RMS-normalised on the way, y = (sum a g w) / sqrt(mean(a^2) + eps): a wave reads whole rows anyway, so
 // the sum of squares costs an operation per element and saves a launch and a pass.  SWIGLU: columns n and n + N of w are gate
