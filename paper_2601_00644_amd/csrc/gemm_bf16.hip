@@ -287,7 +287,7 @@ __global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restric
 // an opaque statement, because the compiler makes every later LDS read wait for all such loads it knows of; the waits below
 // are explicit.  (One wait state between writing M0 and the load that reads it.)
 __device__ __forceinline__ void load_to_lds(uint32_t dst, uint32_t lane_off, const char *src) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_off), "s"(src) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
 }
 
 template <int N>
