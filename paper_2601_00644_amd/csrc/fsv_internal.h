@@ -27,14 +27,12 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 // Sum of eight values over the wave, all eight at once: every exchange halves the values a lane still carries, so it takes
 // ten shuffles instead of forty-eight.  Lane l ends with the sum of value 4 l5 + 2 l4 + l3 (l5 .. l3: bits of l).
 __device__ inline float wave_sum8(float (&v)[8], int lane) {
-#pragma unroll
-  for (int cnt = 4, off = 32; cnt >= 1; cnt >>= 1, off >>= 1)
-#pragma unroll
-    for (int i = 0; i < cnt; ++i) {
-      const float send = (lane & off) ? v[i] : v[i + cnt], keep = (lane & off) ? v[i + cnt] : v[i];
-      v[i] = keep + __shfl_xor(send, off, 64);
-    }
-  float r = v[0];
+  auto fold = [lane](float lo, float hi, int off) {   // every index a constant: an array indexed by a loop would leave the registers
+    const float send = (lane & off) ? lo : hi, keep = (lane & off) ? hi : lo;
+    return keep + __shfl_xor(send, off, 64);
+  };
+  const float a0 = fold(v[0], v[4], 32), a1 = fold(v[1], v[5], 32), a2 = fold(v[2], v[6], 32), a3 = fold(v[3], v[7], 32);
+  float r = fold(fold(a0, a2, 16), fold(a1, a3, 16), 8);
 #pragma unroll
   for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
   return r;

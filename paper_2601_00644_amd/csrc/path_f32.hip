@@ -25,7 +25,7 @@ __global__ void k_embed(int d, const float *__restrict__ E, const int32_t *__res
 // the sum of squares costs an operation per element and saves a launch and a pass.  SWIGLU: columns n and n + N of w are gate
 // and up, y = silu(gate) up, for the same reason.
 // Bound by latency at the sizes this path is for (5 rows, 256 .. 4096 columns): one round of loads and ten shuffles per eight
-// rows.  Measured there: 3.7 .. 8.4 us per projection against 7.6 .. 15.3 us row by row plus 4.2 us per norm and 3.4 for SwiGLU.
+// rows.  Measured there: 3.4 .. 5.0 us per projection against 7.6 .. 15.3 us row by row plus 4.2 us per norm and 3.4 for SwiGLU.
 template <bool NORM, bool SWIGLU>
 __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, const float *__restrict__ a, const float *__restrict__ g,
                                                 const float *__restrict__ w, float *__restrict__ y, int accumulate, int vec) {
