@@ -116,12 +116,14 @@ __global__ void k_rope_append(int H, int Hkv, int hd, double theta, int num_page
   }
 }
 
-// One block per (row, query head): scores into LDS (sixteen lanes per key, a page of keys per step of the block), softmax, then
+// One block per (row, query head): scores into LDS (sixteen lanes per key, two pages of keys per step of the block), softmax, then
 // the weighted sum of values with the keys dealt to groups of threads, added up in group order.  The page ids are in LDS before
 // the loops, so that every loop's loads are independent.
-// Bound by latency; 133 keys of 64: 12 us, against 38 us for one wave that went from key to key.
-constexpr int ATT = 256;
-__global__ __launch_bounds__(ATT) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_attention(int H, int Hkv, int hd, int max_pages, int num_pages, int page_size, int key_cap,
+// Bound by latency; 133 keys of 64: 8.7 us, against 38 us for one wave that went from key to key.  Eight waves per block
+// and no integer division per key: 12 -> 8.7 us, 162 -> 112 us for a two-layer call of 16 rows at 1000 positions, 1030 -> 907 us
+// for a prefill of 1024 rows (sixteen waves: the single call 9.8 against 10 us before the division went, the prefill 12 % slower).
+constexpr int ATT = 512;
+__global__ __launch_bounds__(ATT) void k_attention(int H, int Hkv, int hd, int max_pages, int num_pages, int page_size, int key_cap,
                                                   const float *__restrict__ qbuf, const int32_t *__restrict__ row_req,
                                                   const int32_t *__restrict__ row_pos, const int32_t *__restrict__ page_table,
                                                   const float *__restrict__ kpool, const float *__restrict__ vpool,
@@ -134,8 +136,10 @@ __global__ __launch_bounds__(ATT) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   float *s_part = reinterpret_cast<float *>(s_pg + key_cap / page_size + 1);
   for (int p = tid; p < npg; p += ATT) s_pg[p] = min(max(page_table[(size_t)b * max_pages + p], 0), num_pages - 1);
   __syncthreads();
+  const float inv_page = 1.0f / (float)page_size;
   auto row_of = [&](const float *pool, int j) {
-    return pool + layer_off + (((size_t)s_pg[j / page_size] * Hkv + kvh) * page_size + j % page_size) * hd;
+    const int p = (int)(((float)j + 0.5f) * inv_page);   // exact: j + 1/2 is 1/2 of a key away from a page's edge, keys stay below 2^15
+    return pool + layer_off + (((size_t)s_pg[p] * Hkv + kvh) * page_size + (j - p * page_size)) * hd;
   };
   const float *q = qbuf + ((size_t)r * H + h) * hd;
   const float scale = 1.0f / sqrtf((float)hd);
@@ -198,7 +202,8 @@ __global__ __launch_bounds__(ATT) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
   if (lane == 0) s_red[w] = mx;
   __syncthreads();
-  mx = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+#pragma unroll
+  for (int i = 0; i < ATT / 64; ++i) mx = fmaxf(mx, s_red[i]);
   float den = 0.f;
   for (int j = tid; j < nkeys; j += ATT) {
     const float p = expf(sc[j] - mx);
@@ -208,10 +213,16 @@ __global__ __launch_bounds__(ATT) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   den = wave_sum(den);
   __syncthreads();   // (s_red has been read, the scores are probabilities)
   if (lane == 0) s_red[w] = den;
+  auto total = [&]() {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < ATT / 64; ++i) t += s_red[i];
+    return t;
+  };
   float *dst = out + ((size_t)r * H + h) * hd;
   if (hd > ATT) {   // block-uniform; a thread has several features
     __syncthreads();
-    den = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+    den = total();
     for (int e = tid; e < hd; e += ATT) {
       float acc = 0.f;
 #pragma unroll 4
@@ -228,7 +239,7 @@ __global__ __launch_bounds__(ATT) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
     s_part[tid] = acc;
   }
   __syncthreads();
-  den = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
+  den = total();
   if (tid < hd) {
     float acc = 0.f;
     for (int i = 0; i < groups; ++i) acc += s_part[i * hd + tid];
@@ -274,7 +285,7 @@ void launch_linear(int M, int N, int K, const float *a, const float *w, float *y
   else hipLaunchKernelGGL((k_linear<false, false>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);
 }
 
-// LDS of k_attention for key_cap keys: 69.1 KiB at the 16384 that fsv_f32_check admits
+// LDS of k_attention for key_cap keys: 70.0 KiB at the 16384 that fsv_f32_check admits
 size_t attention_lds(const fsv_model_desc &d, int key_cap) {
   return sizeof(float) * ((size_t)key_cap + key_cap / d.page_size + 1 + ATT);
 }

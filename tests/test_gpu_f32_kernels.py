@@ -1,5 +1,5 @@
 """The fp32 path's kernels off their usual sizes: row counts around the blocks of eight, contraction lengths that do not take
-16-byte loads, unaligned inputs, head sizes around the blocks of 256 threads, key counts around the pages.  Single kernels
+16-byte loads, unaligned inputs, head sizes around the blocks of 512 threads, key counts around the pages.  Single kernels
 against fp64, the whole forward (normalised and SwiGLU projections) against the oracle."""
 import numpy as np
 import pytest
@@ -36,7 +36,7 @@ def test_linear(M, d, F, shift):
     ctx.close()
 
 
-@pytest.mark.parametrize("hd,heads,kv", [(2, 4, 2), (34, 3, 1), (64, 4, 4), (254, 2, 1), (256, 2, 2), (300, 2, 1)])
+@pytest.mark.parametrize("hd,heads,kv", [(2, 4, 2), (34, 3, 1), (64, 4, 4), (254, 2, 1), (256, 2, 2), (300, 2, 1), (512, 1, 1), (514, 2, 1)])
 def test_attention(hd, heads, kv):
     cfg = synth.ModelCfg("f32att", 1, 32, heads, kv, hd, 32, 64, "f32")
     L, gam = np.array([0, 15, 16, 130, 700], np.int32), np.array([0, 1, 3, 2, 4], np.int32)
