@@ -1181,8 +1181,9 @@ __global__ __launch_bounds__(256) void k_decide(
   double t = thread_masses<LT>(lrow, qrow, i0, V, lvec != 0, qvec != 0, (float)m, k, invS, residual, cutkey, mass);
   double incl = block_incl_scan(t, s_w, nullptr);
   // the first thread whose running mass crosses, and the last id with mass: a ballot per wave (LDS atomics of all 256 threads
-  // on one address cost 3 us here)
-  const bool crosses = (lo + incl) > target;  // false for every thread when lo == inf
+  // on one address cost 3 us here).  Only a thread and an id that hold mass can be taken: lane sums, their scan and the sums
+  // id by id are rounded differently, so lo may already lie a rounding above the target.
+  const bool crosses = t > 0.0 && (lo + incl) > target;  // false for every thread when lo == inf
   int lp = -1;
 #pragma unroll
   for (int j = 0; j < 8; ++j)
@@ -1209,12 +1210,12 @@ __global__ __launch_bounds__(256) void k_decide(
     for (int j = 0; j < 8; ++j) {
       double prev = run;
       run += mass[j];
-      if (pick < 0 && run > target) {
+      if (pick < 0 && mass[j] > 0.0 && run > target) {
         pick = i0 + j;
         margin = fmin(target - prev, run - target) / Z;
       }
     }
-    if (pick < 0) { pick = lp >= 0 ? lp : i0; margin = 0.0; }
+    if (pick < 0) { pick = lp; margin = 0.0; }
     next_token[b] = pick;
     uint32_t f = s_flags;
     if (!residual) f &= ~4u;

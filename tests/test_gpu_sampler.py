@@ -337,3 +337,39 @@ def test_windowed_and_full_nucleus_passes_agree(monkeypatch):
     assert bool((same | (near != 0)).all())
     assert int((near != 0).sum()) <= B // 4
     ctx.close()
+
+
+# Residual masses 2^-17 - q of one id in each of the first twelve 2048-id sub-blocks, for which half the total lies between two
+# roundings of the same running mass: the mass of the first six sub-blocks added one after the other, and as lane sums and
+# their scan (the two ways the selection meets it).
+_GAPS = [
+    "0x1.13e4bep-44 0x1.6a26e2p-44 0x1.482808p-47 0x1.bc071cp-44 0x1.bfd1bcp-45 0x1.b60d74p-55 0x1.eca9fap-54 0x1.ee9b76p-45 "
+    "0x1.2f4528p-55 0x1.1d6c38p-44 0x1.21e25cp-46 0x1.72b1e2p-43",
+    "0x1.d63cfep-48 0x1.3b78c2p-49 0x1.95acfap-46 0x1.bfae74p-50 0x1.6a15bap-45 0x1.a4c9d4p-55 0x1.1e52b6p-52 0x1.b9cb40p-53 "
+    "0x1.4dc476p-51 0x1.1532f0p-44 0x1.4b9ee6p-54 0x1.76637ap-47",
+    "0x1.188aa2p-55 0x1.873d84p-47 0x1.fc9fa8p-52 0x1.39fbeep-46 0x1.44d676p-46 0x1.c70d20p-54 0x1.3043d2p-52 0x1.2b8a42p-48 "
+    "0x1.37370cp-53 0x1.93c33ep-51 0x1.80f2b0p-51 0x1.70ffa6p-45",
+]
+
+
+@pytest.mark.parametrize("place", [0, 9, 1000, 2047])
+def test_emitted_id_has_mass_when_the_target_falls_between_two_roundings(place):
+    V, B = 1 << 17, len(_GAPS)
+    fv, ctx = _ctx(V, B, 16)
+    p = 2.0 ** -17                                   # equal logits: every probability is exactly this
+    q = torch.full((B, V), p, dtype=torch.float32)   # no residual
+    for b, law in enumerate(_GAPS):
+        for sb, x in enumerate(law.split()):
+            q[b, sb * 2048 + place] = float.fromhex(x)
+    d = V - 1                                        # the draft, rejected: p / q = 1/2 < u
+    q[:, d] = 2.0 * p
+    off = np.arange(B + 1, dtype=np.int32)
+    case = synth.SamplerCase(torch.zeros((2 * B, V)), q, np.full(B, d, np.int32), off, np.full(B, 0.75, np.float32),
+                             np.full(B, 0.5, np.float32), np.ones(B, np.float32))
+    tau, nxt, flags = _run(fv, ctx, case)
+    assert list(tau) == [0] * B
+    for b in range(B):
+        assert float(q[b, int(nxt[b])]) < p, (b, int(nxt[b]))      # an id of zero residual was emitted
+        assert int(nxt[b]) in (5 * 2048 + place, 6 * 2048 + place)  # either side of the edge the target sits on
+        assert (int(flags[b]) & 6) == 6                             # residual draw, flagged as close to an edge
+    ctx.close()
