@@ -459,13 +459,17 @@ __device__ inline void cut_find_bins(const uint32_t *hist, uint32_t x0, uint32_t
 // The value a key stands for.
 __device__ inline float okey_value(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key); }
 
-// top-p alone on bf16 logits, in ONE pass, whenever the cut lies within one binade of the row maximum: only the W = 4 highest
-// values of the key's top 11 bits, at and below the row maximum's, get histogram bins, 32 each (a bf16 key has five bits
-// below, so a bin is one key and needs no list).  Every other token is dismissed by one comparison: no exponential, no LDS
-// add.  top_p is measured against the normaliser of the statistics pass.  Rows it cannot settle, and rows with a top-k cut,
-// go on to k_cut (done[r] = 0).  596 rows x 152064, top-p 0.9: 47 us and 5 for the k_cut that finds nothing left; k_cut
-// alone, two passes, takes 145.
-constexpr int kWindowDigits = 4;
+// The cuts on bf16 logits, in ONE pass, whenever they lie near the row maximum: only the W highest values of the key's top 11
+// bits, at and below the row maximum's, get histogram bins, 32 each (a bf16 key has five bits below, so a bin is one key and
+// needs no list): W = 4 is one binade of the logit, tried first, W = 8 two, for the rows the first leaves (done[r] = 0).  Every
+// other token is dismissed by one comparison: no exponential, no LDS add.  top_p is measured against the normaliser of the
+// statistics pass, or the mass the top-k cut kept.  Rows neither settles go on to k_cut (done[r] = 2 keeps the second window off
+// a row that would most likely fail there: under a normal law of the logits the mass below two binades is about 0.25 .. 0.55 of
+// the square of the mass below one; the lower factor, since a vain second window costs 65 us and k_cut for few rows 60).
+// Measured for 584 rows x 152064, logits N(0, 3), all launches of a cut: T = 0.7, top-p 0.9 54 us (first window); T = 1.0 128 and
+// T = 0.8, top-p 0.95 127 (second; 199 and 188 with the first window and k_cut alone); T = 1.0, top-p 0.99 257 (k_cut after the
+// first); top-k 50 58, 1000 99, 5000 130 (k_cut alone: 76, 141, 363); top-k 50 then top-p 0.9 61.
+template <int W, bool FIRST>
 __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict__ logits, int V, int nc,
                                                       const int32_t *__restrict__ off,
                                                       const float *__restrict__ temperature,
@@ -473,25 +477,26 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
                                                       const float *__restrict__ pmax, const double *__restrict__ psum,
                                                       uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
                                                       int32_t *__restrict__ nuc_near, int32_t *__restrict__ done, int vec) {
-  constexpr int FB = 32, W = kWindowDigits;
+  constexpr int FB = 32;
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   if ((int)blockIdx.x > off[b + 1] - off[b]) return;
   const int r = off[b] + b + blockIdx.x;
+  if (!FIRST && done[r]) return;   // settled by the narrower window, or left to k_cut
   const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
   const int tk = top_k ? top_k[b] : 0;
   const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
-  if (use_k) {
-    if (tid == 0) done[r] = 0;
-    return;
-  }
-  if (!use_p) {
+  if (!use_k && !use_p) {
     if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; done[r] = 1; }
     return;
   }
   __shared__ unsigned long long hist[W * FB];
+  __shared__ uint32_t hcnt[W * FB];
   __shared__ float s_m;
   __shared__ double s_total;
-  for (int i = tid; i < W * FB; i += 1024) hist[i] = 0ull;
+  for (int i = tid; i < W * FB; i += 1024) {
+    hist[i] = 0ull;
+    hcnt[i] = 0u;
+  }
   if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
     float mx = -INFINITY;
     for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
@@ -541,16 +546,31 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
         const unsigned long long q = (unsigned long long)((double)exp_scaled(val - m, k) * kNucScale + 0.5);
         const uint32_t idx = (d0 - (key >> 21)) * FB + ((key >> 16) & (FB - 1));
         if (q) atomicAdd(&hist[idx], q);
+        if (use_k) atomicAdd(&hcnt[idx], 1u);
       }
     }
   };
   constexpr int U = 4, STEP = 1024 * 8;
+  // Most of the first round inside the window (logits far from zero, close together): a top-k that k_cut finds in one pass is
+  // left to it.
+  const bool sample = FIRST && use_k && vec && V >= U * STEP && 6l * tk <= kCutList;
   int base = tid * 8;
   if (vec) {
     for (; base + (U - 1) * STEP + 8 <= V; base += U * STEP) {
       float v[U][8];
 #pragma unroll
       for (int u = 0; u < U; ++u) loader<uint16_t>::load8_fast(row, base + u * STEP, v[u]);
+      if (sample && base < STEP) {
+        int seen = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) seen += v[u][j] >= vlow ? 1 : 0;
+        if (__syncthreads_count(seen > 4) > 512) {
+          if (tid == 0) done[r] = 2;
+          return;
+        }
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) add8(base + u * STEP, v[u], std::true_type{});
     }
@@ -564,38 +584,75 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   if (tid >= 64) return;
   // lane l < W owns the window's digit d0 - l: the highest keys in lane 0
   unsigned long long mine = 0ull;
+  uint32_t minec = 0u;
   if (lane < W) {
 #pragma unroll
-    for (int f = 0; f < FB; ++f) mine += hist[lane * FB + f];
+    for (int f = 0; f < FB; ++f) {
+      mine += hist[lane * FB + f];
+      minec += hcnt[lane * FB + f];
+    }
   }
   unsigned long long incl = mine;
+  uint32_t inclc = minec;
 #pragma unroll
   for (int o2 = 1; o2 < W; o2 <<= 1) {
     const unsigned long long t = __shfl_up(incl, o2, 64);
-    if (lane >= o2) incl += t;
+    const uint32_t tc = __shfl_up(inclc, o2, 64);
+    if (lane >= o2) { incl += t; inclc += tc; }
   }
   const unsigned long long before = incl - mine;   // mass strictly above this lane's digit
-  const double total = s_total, target = (double)tp * total;
-  const bool crosses = (double)(before + mine) >= target;
-  const unsigned long long ballot = __ballot(crosses && lane < W && lane <= (int)d0);   // digits below zero do not exist
-  if (!ballot || !(total > 0.0)) {   // the cut lies below the window
-    if (lane == 0) done[r] = 0;
+  const uint32_t beforec = inclc - minec;
+  const bool digit = lane < W && lane <= (int)d0;   // digits below zero do not exist
+  double total = s_total, target = 0.0;
+  uint32_t cut = 0u;
+  unsigned long long kept = 0ull, acc = 0ull;   // mass down to and with the cut, and above it
+  // the key in the chosen lane's digit, from the top, at which the running count or mass crosses; to every lane
+  auto select = [&](unsigned long long lanes, bool by_count) {
+    const int from = (int)__builtin_ctzll(lanes);
+    acc = before;
+    uint32_t accc = beforec;
+    int fsel = 0;
+    if (lane == from) {
+      for (int f = FB - 1; f >= 0; --f) {
+        const unsigned long long hbin = hist[lane * FB + f];
+        const bool hit = by_count ? (accc + hcnt[lane * FB + f] >= (uint32_t)tk) : ((double)(acc + hbin) >= target);
+        if (hit || f == 0) { fsel = f; break; }
+        acc += hbin;
+        accc += hcnt[lane * FB + f];
+      }
+      kept = acc + hist[lane * FB + fsel];
+    }
+    cut = ((d0 - (uint32_t)from) << 21) | ((uint32_t)__shfl(fsel, from, 64) << 16);
+    kept = __shfl(kept, from, 64);
+    acc = __shfl(acc, from, 64);
+  };
+  bool settled = total > 0.0;   // (not with a NaN or an infinite maximum)
+  if (settled && use_k) {
+    const unsigned long long ballot = __ballot(digit && beforec + minec >= (uint32_t)tk);
+    settled = ballot != 0ull;
+    if (settled) {
+      select(ballot, true);
+      total = (double)kept;   // top-p works on what the top-k cut kept
+    }
+  }
+  if (settled && use_p) {
+    target = (double)tp * total;
+    const unsigned long long ballot = __ballot(digit && (double)(before + mine) >= target);
+    settled = ballot != 0ull;
+    if (settled) select(ballot, false);
+  }
+  const unsigned long long inside = __shfl(incl, W - 1, 64);
+  if (lane != 0) return;
+  if (!settled) {   // a cut lies below the window, or the row is out of the ordinary (2: nothing for the wider window either)
+    const double outside = 1.0 - (double)inside / total;
+    const bool wider = total > 0.0 && (use_k || 0.25 * outside * outside <= 1.0 - (double)tp);
+    done[r] = (FIRST && wider) ? 0 : 2;
     return;
   }
-  if (lane != (int)__builtin_ctzll(ballot)) return;
-  unsigned long long acc = before;
-  int fsel = 0;
-  for (int f = FB - 1; f >= 0; --f) {
-    const unsigned long long hbin = hist[lane * FB + f];
-    if ((double)(acc + hbin) >= target || f == 0) { fsel = f; break; }
-    acc += hbin;
-  }
-  const uint32_t cut = ((d0 - (uint32_t)lane) << 21) | ((uint32_t)fsel << 16);
-  const unsigned long long kept = acc + hist[lane * FB + fsel];
+  done[r] = 1;
   nuc_key[r] = cut;
   nuc_S[r] = (double)kept / kNucScale;
-  nuc_near[r] = (fmin(target - (double)acc, (double)kept - target) < 1e-6 * total) ? 1 : 0;
-  done[r] = 1;
+  nuc_near[r] = (use_p && fmin(target - (double)acc, (double)kept - target) < 1e-6 * total) ? 1 : 0;
 }
 
 // The cut of every row that asks for one: cut key, kept mass, and whether top_p falls within 1e-6 of the row's mass of it.
@@ -622,7 +679,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
                                                      double *__restrict__ nuc_S, int32_t *__restrict__ nuc_near,
                                                      const int32_t *__restrict__ done, int B, int vec, int digits) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x;
-  if (done && done[r]) return;   // k_cut_window has settled this row
+  if (done && done[r] == 1) return;   // k_cut_window has settled this row
   int b = -1;   // the row's request: the last one whose first row, off[b] + b, is not beyond r (every wave by itself)
   for (int b0 = 0; b0 < B; b0 += 64) b += __popcll(__ballot(b0 + lane < B && off[min(b0 + lane, B)] + b0 + lane <= r));
   const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
@@ -1262,11 +1319,16 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
     // (FSV_NUCLEUS_FULL=1 in the environment sends every row through the digit passes: a test compares the two)
     const char *full_env = getenv("FSV_NUCLEUS_FULL");
     const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
-    // bf16 logits and no top-k: the cut lies within one binade of the maximum more often than not, which is one pass
-    const bool window = sizeof(LT) == 2 && !any_k && !digits;
-    if (window)
-      hipLaunchKernelGGL(k_cut_window, dim3(gmax + 1, B), dim3(1024), 0, s, (const uint16_t *)logits, V, nc, b->draft_offsets, b->temperature,
-                         b->top_p, b->top_k, c->pmax, c->psum, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, lvec);
+    // bf16 logits: the cuts lie within one or two binades of the maximum more often than not, which is one pass
+    const bool window = sizeof(LT) == 2 && !digits;
+#define FSV_WINDOW(W, FIRST)                                                                                                           \
+  hipLaunchKernelGGL((k_cut_window<W, FIRST>), dim3(gmax + 1, B), dim3(1024), 0, s, (const uint16_t *)logits, V, nc, b->draft_offsets, \
+                     b->temperature, b->top_p, b->top_k, c->pmax, c->psum, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, lvec)
+    if (window) {
+      FSV_WINDOW(4, true);
+      FSV_WINDOW(8, false);
+    }
+#undef FSV_WINDOW
     hipLaunchKernelGGL(k_cut<LT>, dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, c->pmax,
                        c->psum, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, lvec, digits);
   }
