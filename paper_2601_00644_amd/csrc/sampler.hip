@@ -726,7 +726,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   bool fast = !digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9;   // block-uniform
 
   if (fast) {
-    double tot = 0.0;     // top-p alone on fp32 logits: the row's mass as an integer sum (exact in a double: < 2^53 per thread)
+    double tot = 0.0;     // top-p alone: the row's mass as an integer sum (exact in a double: < 2^53 per thread)
     double above = 0.0;   // likewise the mass above the candidates
     bool bad = false;
     const bool one_pass = use_k && whole_rounds<LT>(V, vec != 0) > 0 && 6l * tk <= kCutList;
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const float e = exp_scaled(v[j] - m, k);
-            if constexpr (sizeof(LT) == 4) tot += floor((double)e * kNucScale + 0.5);
+            tot += floor((double)e * kNucScale + 0.5);
             if (e >= drop) atomicAdd(&hist[bin_of(v[j])], (uint32_t)fmaf(e, scale, 0.5f));
           }
         }, [](int, const auto &) {});
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
           }
         }, [](int, const auto &) {});
     }
-    // sums over the block: the mass above, and (fp32) the total
+    // sums over the block: the mass above, and the total
     unsigned long long ta = (unsigned long long)above, tt = (unsigned long long)tot;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     __syncthreads();
     unsigned long long A = 0ull, all = 0ull;
     for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
-    double total = (sizeof(LT) == 4) ? (double)all : S * kNucScale;   // bf16 logits: the statistics' normaliser (within 1e-7)
+    double total = (double)all;
     const int n = st.n;
     fast = fast && n <= kCutList && n > 0;
 

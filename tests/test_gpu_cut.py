@@ -67,3 +67,46 @@ def test_fast_cut_equals_the_digit_passes(kind, V, dtype, monkeypatch):
         else:
             assert ((a == b).all(0) | near).all(), (top_p, top_k)
     ctx.close()
+
+
+def test_bf16_top_p_is_measured_against_the_exact_mass(monkeypatch):
+    """bf16 rows whose cut lies more than two binades below the maximum: top_p steps by its last bit across the kept mass at the
+    end of several groups of equal logits.  The cut has to change at the step at which the digit passes, which sum the row's
+    mass as integers, change it; a normaliser rounded to fp32 terms is off by such steps."""
+    from paper_2601_00644_amd import flexverify as fv
+    V, T, steps = 40000, 1.5, 24
+    z = (torch.randn(V, generator=torch.Generator().manual_seed(3)) * 3.0).to(torch.bfloat16)
+    v = z.float().sort(descending=True).values.numpy()
+    e = np.exp((v.astype(np.float64) - float(v[0])) / T)
+    c = np.cumsum(e) / e.sum()
+    ends = np.flatnonzero(v[1:] != v[:-1])
+    ends = ends[(c[ends] > 0.97) & (c[ends] < 0.995)][::3][:8]
+    assert len(ends) == 8 and v[ends[0]] < v[0] / 4          # below the second binade
+    rows, tops = [], []
+    rng = np.random.default_rng(4)
+    for n in ends:
+        nxt = np.flatnonzero(v == v[n + 1])                   # the group that the next step of top_p adds
+        tail = np.concatenate([[n], nxt])
+        row = v[np.concatenate([rng.permutation(np.setdiff1d(np.arange(V), tail)), tail])]
+        bits = np.float32(c[n]).view(np.uint32).astype(np.int64) + np.arange(-steps, steps + 1)
+        tops.append(bits.astype(np.uint32).view(np.float32))
+        rows += [row] * len(bits)
+    tops = np.concatenate(tops)
+    B = len(tops)
+    t = lambda a: torch.as_tensor(a).cuda()
+    off, temps = np.zeros(B + 1, np.int32), np.full(B, T, np.float32)
+    ctx = fv.Context(synth.ModelCfg("sampler", 0, 0, 0, 0, 0, 0, V, "bf16"), None, B, 16, sampler_only=True)
+    batch = fv.DeviceBatch(None, None, t(off), None, None, None, t(np.full(B, 1.0 - 2.0 ** -24, np.float32)), t(temps), None, None, None, 0,
+                           None, off, temps)
+    batch.top_p_host, batch.top_p = tops, t(tops)
+    lg = torch.as_tensor(np.stack(rows)).to(torch.bfloat16).cuda()
+    out = []
+    for full in ("0", "1"):
+        monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
+        res = fv.DeviceResult.alloc(B)
+        ctx.sample(lg, batch, res)
+        out.append(torch.stack([res.next_token, res.flags]).cpu().numpy())
+    ctx.close()
+    ids = out[1][0].reshape(8, -1)
+    assert all(len(set(r.tolist())) > 1 for r in ids)         # every sweep crosses its edge
+    assert (out[0] == out[1]).all(), int((out[0] != out[1]).any(0).sum())
