@@ -296,10 +296,12 @@ __device__ inline unsigned long long nuc_mass(float d, exp_scale k) {
 struct cut_state {
   float m;                                   // row maximum
   int n, found, bad;                         // candidates, selection done, a NaN in the row
-  uint32_t bin_lo, bin_hi, kkey, cut;
+  uint32_t bin_lo, bin_hi, before, upto;     // bins the cut can lie in, running sum before the first and up to the last
+  uint32_t kkey, cut;
   unsigned long long kmass, kept, acc, total;
   double S;                                  // normaliser from the row statistics, in units of the maximum's probability
-  uint32_t prefix, cabove;                   // digit passes: the digits fixed so far, tokens and mass above them
+  uint32_t lo, hi, cabove;                   // narrowing passes: the interval of keys left, tokens and mass above it
+  int last;                                  // it is one key
   unsigned long long above;
   uint32_t w32[kCutThreads / 64];
   unsigned long long w64[kCutThreads / 64], t64[kCutThreads / 64];
@@ -331,98 +333,122 @@ __device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, 
   }
 }
 
-// The general way, digit by digit on the 32-bit key: one pass over the row per digit builds a histogram of the mass (and, for
-// top-k, the count) per digit value in LDS, and a scan from the top picks the digit at which the kept mass (count) crosses.
-// LEVEL 0: key bits 31..21, LEVEL 1: bits 20..10, LEVEL 2: bits 9..0; LAST fixes the whole key (level 1 for bf16 logits,
-// whose keys have no information below bit 16).  MODE 1 selects by count and leaves kkey / kmass, MODE 0 by mass among the
-// keys from lowkey on and leaves cut / kept / acc / total.
-template <typename LT, int LEVEL, bool LAST, int MODE>
-__device__ inline void cut_digit_pass(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lowkey, int tk, float tp,
-                                      unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
-  constexpr int SHIFT = (LEVEL == 0) ? 21 : (LEVEL == 1 ? 10 : 0), BITS = (LEVEL == 2) ? 10 : 11;
-  const int tid = threadIdx.x, lane = tid & 63;
-  for (int i = tid; i < FSV_NUC_BINS; i += kCutThreads) {
-    hist[i] = 0ull;
-    if (MODE == 1) hcnt[i] = 0u;
-  }
-  __syncthreads();
-  const uint32_t prefix = (LEVEL > 0) ? st->prefix : 0u;
-  over_row<LT>(row, V, vec, tid, [&](int i0, const float(&v)[8]) {
+// The general way: passes over the row that narrow an interval of keys, 2048 bins of equal width each time, until a bin is a
+// single key (16 bits wide for bf16 logits, whose keys have no information below).  A pass builds a histogram of the mass (and,
+// for top-k, the count) per bin in LDS, and a scan from the top picks the bin at which the kept mass (count) crosses.  From the
+// whole range these are digits of 11, 11 and 10 bits.  `whole` = false (by mass): the cut is expected in [lo, hi], the first pass
+// adds up the mass above, st->total is known; false is returned if the cut does not lie there.  These passes also keep the lowest
+// and highest key of each bin (in hcnt): tied tokens, and a bin of one token, need no further pass.
+// COUNT selects by count and leaves kkey / kmass; by mass, among the keys from lowkey on, leaves cut / kept / acc / total.
+template <typename LT, bool COUNT>
+__device__ inline bool cut_narrow(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lo, uint32_t hi, bool whole, uint32_t lowkey,
+                                  int tk, float tp, unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
+  constexpr int LAST = (sizeof(LT) == 2) ? 16 : 0;   // widest bin that holds one key
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  for (bool first = true;; first = false) {
+    const uint32_t span = hi - lo;
+    int shift = span ? 32 - __clz((int)span) - 11 : 0;
+    if (shift < 0) shift = 0;
+    if ((hi >> shift) - (lo >> shift) >= (uint32_t)FSV_NUC_BINS) ++shift;   // (an interval that does not begin on a bin's edge)
+    const uint32_t base = lo >> shift, from = max(lo, lowkey);
+    const bool ends = !COUNT && !whole && shift > LAST, sum_above = first && !whole;
+    for (int i = tid; i < FSV_NUC_BINS; i += kCutThreads) {
+      hist[i] = 0ull;
+      if (COUNT) hcnt[i] = 0u;
+      if (ends) { hcnt[i] = ~0u; hcnt[FSV_NUC_BINS + i] = 0u; }
+    }
+    __syncthreads();
+    double above = 0.0;   // exact: a whole number below 2^53
+    over_row<LT>(row, V, vec, tid, [&](int i0, const float(&v)[8]) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      if (i0 + j >= V) continue;   // ids beyond the vocabulary are not tokens (they would count for top-k)
-      const uint32_t key = okey(v[j]);
-      if (LEVEL > 0 && (key >> (SHIFT + BITS)) != prefix) continue;
-      if (MODE == 0 && key < lowkey) continue;
-      const unsigned long long q = nuc_mass(v[j] - m, k);
-      const uint32_t bin = (key >> SHIFT) & ((1u << BITS) - 1u);
-      if (q) atomicAdd(&hist[bin], q);
-      if (MODE == 1) atomicAdd(&hcnt[bin], 1u);
-    }
-  }, [](int, const auto &) {});
-  __syncthreads();
-  if (tid < 64) {
-    // lane l owns the 32 digit values below (64 - l) * 32, the highest values in lane 0: masses above each lane's group
-    constexpr int PER = FSV_NUC_BINS / 64;
-    unsigned long long mine = 0ull;
-    uint32_t minec = 0u;
-    const int top = (63 - lane) * PER + PER - 1;
-    for (int i = 0; i < PER; ++i) {
-      mine += hist[top - i];
-      if (MODE == 1) minec += hcnt[top - i];
-    }
-    unsigned long long incl = mine;
-    uint32_t inclc = minec;
+      for (int j = 0; j < 8; ++j) {
+        if (i0 + j >= V) continue;   // ids beyond the vocabulary are not tokens (they would count for top-k)
+        const uint32_t key = okey(v[j]);
+        if (key - from > hi - from) {
+          if (!COUNT && sum_above && key > hi) above += floor((double)exp_scaled(v[j] - m, k) * kNucScale + 0.5);
+          continue;
+        }
+        const unsigned long long q = nuc_mass(v[j] - m, k);
+        const uint32_t bin = (key >> shift) - base;
+        if (q) atomicAdd(&hist[bin], q);
+        if (COUNT) atomicAdd(&hcnt[bin], 1u);
+        if (ends) { atomicMin(&hcnt[bin], key); atomicMax(&hcnt[FSV_NUC_BINS + bin], key); }
+      }
+    }, [](int, const auto &) {});
+    if (sum_above) {
+      unsigned long long ta = (unsigned long long)above;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long t = __shfl_up(incl, o, 64);
-      const uint32_t tc = __shfl_up(inclc, o, 64);
-      if (lane >= o) { incl += t; inclc += tc; }
+      for (int o = 32; o > 0; o >>= 1) ta += __shfl_xor(ta, o, 64);
+      if (lane == 0) st->w64[w] = ta;
     }
-    const unsigned long long before = ((LEVEL == 0) ? 0ull : st->above) + (incl - mine);   // mass strictly above this lane's group
-    const uint32_t beforec = ((LEVEL == 0) ? 0u : st->cabove) + (inclc - minec);
-    const unsigned long long total = (LEVEL == 0) ? __shfl(incl, 63, 64) : st->total;
-    const double target = (double)tp * (double)total;
-    const bool crosses = (MODE == 1) ? (beforec + minec >= (uint32_t)tk) : ((double)(before + mine) >= target);
-    const unsigned long long ballot = __ballot(crosses);
-    // level 0 always has a crossing (tk < V tokens are counted; the last lane holds the total mass); deeper levels were
-    // chosen because they cross; the guard only keeps the index in range
-    const int pick_lane = ballot ? (int)__builtin_ctzll(ballot) : 63;
-    if (lane == pick_lane) {
-      unsigned long long acc = before;
-      uint32_t accc = beforec;
-      int digit = top - (PER - 1);
+    __syncthreads();
+    if (tid < 64) {
+      // lane l owns the 32 bins below (64 - l) * 32, the highest keys in lane 0: masses above each lane's group
+      constexpr int PER = FSV_NUC_BINS / 64;
+      unsigned long long mine = 0ull, above0 = first ? 0ull : st->above;
+      uint32_t minec = 0u;
+      const int top = (63 - lane) * PER + PER - 1;
+#pragma unroll 8
       for (int i = 0; i < PER; ++i) {
-        const unsigned long long hbin = hist[top - i];
-        const bool hit = (MODE == 1) ? (accc + hcnt[top - i] >= (uint32_t)tk) : ((double)(acc + hbin) >= target);
-        if (hit || i == PER - 1) { digit = top - i; break; }
-        acc += hbin;
-        if (MODE == 1) accc += hcnt[top - i];
+        mine += hist[top - i];
+        if (COUNT) minec += hcnt[top - i];
       }
-      const uint32_t newprefix = (prefix << BITS) | (uint32_t)digit;
-      st->prefix = newprefix;
-      st->above = acc;
-      st->cabove = accc;
-      if (MODE == 0) st->total = total;
-      if (LAST) {
-        if (MODE == 1) { st->kkey = newprefix << SHIFT; st->kmass = acc + hist[digit]; }
-        else { st->cut = newprefix << SHIFT; st->kept = acc + hist[digit]; st->acc = acc; }
+      if (sum_above)
+        for (int i = 0; i < kCutThreads / 64; ++i) above0 += st->w64[i];
+      unsigned long long incl = mine;
+      uint32_t inclc = minec;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long t = __shfl_up(incl, o, 64);
+        const uint32_t tc = __shfl_up(inclc, o, 64);
+        if (lane >= o) { incl += t; inclc += tc; }
+      }
+      const unsigned long long before = above0 + (incl - mine);   // mass strictly above this lane's group
+      const uint32_t beforec = (first ? 0u : st->cabove) + (inclc - minec);
+      const unsigned long long total = (first && whole) ? __shfl(incl, 63, 64) : st->total;
+      const double target = (double)tp * (double)total;
+      const bool crosses = COUNT ? (beforec + minec >= (uint32_t)tk) : ((double)(before + mine) >= target);
+      const unsigned long long ballot = __ballot(crosses);
+      if (sum_above && (!ballot || (double)above0 >= target)) {
+        if (lane == 0) st->found = 0;
+      } else {
+        // the whole range always has a crossing (tk < V tokens are counted; the last lane holds the total mass), a bin is chosen
+        // because it crosses; the guard only keeps the index in range
+        const int pick_lane = ballot ? (int)__builtin_ctzll(ballot) : 63;
+        if (lane == pick_lane) {
+          unsigned long long acc = before;
+          uint32_t accc = beforec;
+          int bin = top - (PER - 1);
+#pragma unroll 1
+          for (int i = 0; i < PER; ++i) {
+            const unsigned long long hbin = hist[top - i];
+            const bool hit = COUNT ? (accc + hcnt[top - i] >= (uint32_t)tk) : ((double)(acc + hbin) >= target);
+            if (hit || i == PER - 1) { bin = top - i; break; }
+            acc += hbin;
+            if (COUNT) accc += hcnt[top - i];
+          }
+          const uint32_t edge = (base + (uint32_t)bin) << shift;
+          st->found = 1;
+          st->lo = ends ? hcnt[bin] : edge;
+          st->hi = ends ? hcnt[FSV_NUC_BINS + bin] : min(hi, edge + ((1u << shift) - 1u));
+          st->above = acc;
+          st->cabove = accc;
+          st->last = (shift <= LAST || (ends && st->lo == st->hi)) ? 1 : 0;
+          if (!COUNT) st->total = total;
+          if (st->last) {
+            const uint32_t key = ends ? st->lo : edge;
+            if (COUNT) { st->kkey = key; st->kmass = acc + hist[bin]; }
+            else { st->cut = key; st->kept = acc + hist[bin]; st->acc = acc; }
+          }
+        }
       }
     }
+    __syncthreads();
+    if (!st->found || st->last) break;
+    lo = st->lo;
+    hi = st->hi;
   }
-  __syncthreads();
-}
-
-template <typename LT, int MODE>
-__device__ inline void cut_digits(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lowkey, int tk, float tp,
-                                  unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
-  cut_digit_pass<LT, 0, false, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
-  if constexpr (sizeof(LT) == 2) {
-    cut_digit_pass<LT, 1, true, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
-  } else {
-    cut_digit_pass<LT, 1, false, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
-    cut_digit_pass<LT, 2, true, MODE>(row, V, vec, m, k, lowkey, tk, tp, hist, hcnt, st);
-  }
+  return st->found != 0;
 }
 
 // First bins at which the running sum of the bins reaches x0 and x1, to bin_lo and bin_hi (kCutBins: never).
@@ -450,8 +476,8 @@ __device__ inline void cut_find_bins(const uint32_t *hist, uint32_t x0, uint32_t
   for (int i = 0; i < PER; ++i) {
     const uint32_t before = run;
     run += h[i];
-    if (before < x0 && x0 <= run) st->bin_lo = PER * tid + i;
-    if (before < x1 && x1 <= run) st->bin_hi = PER * tid + i;
+    if (before < x0 && x0 <= run) { st->bin_lo = PER * tid + i; st->before = before; }
+    if (before < x1 && x1 <= run) { st->bin_hi = PER * tid + i; st->upto = run; }
   }
   __syncthreads();
 }
@@ -662,15 +688,17 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
 // per factor of two): their count for top-k, their mass in 32-bit fixed point for top-p; the bins in which the cut can lie
 // follow from the running sum and a bound of its rounding.  The second collects the tokens of those bins (for top-k: of all
 // bins down to it) and adds up, exactly, what lies above.  The list is sorted by key, and its running sum of exact 2^-40
-// masses decides.  A top-k of a few hundred takes one pass: a quarter of the ids, sampled across the vocabulary, is filed,
-// the bin at which these already hold top_k tokens bounds the cut, and everything from that bin on goes to the list at once.
-// For top-p, tokens so improbable that all of them together carry less than 0.9 (1 - top_p) are not filed.
-// A row with NaN or an infinite maximum, or whose list overflows (near-flat laws with many ties), goes digit by digit, as
-// does every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other).
+// masses decides.  A top-k of a few hundred takes one pass: the first round of loads (32768 ids, sampled across the vocabulary)
+// is filed, the bin at which these already hold top_k tokens bounds the cut, and everything from that bin on goes to the list
+// at once.  For top-p, tokens so improbable that all of them together do not matter to the sums are not filed.
+// When the list cannot hold the candidates (near-flat laws, many ties), top-p goes on with passes that narrow the keys of those
+// bins (cut_narrow).  Rows with NaN or an infinite maximum, a top-k beyond the list, a top-p too close to 1 for the sums of the
+// first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
 // Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
-// arithmetic of a single compute unit with few rows.  Measured: top-k 50 then top-p 0.9 on those 204 rows 34 us, against 235
-// for six digit passes; top-p 0.9 alone 54 against 135, on 71 rows of model logits 52 against 73; top-k 50 on 596 rows x
-// 152064 bf16 80 against 87 (a one-binade window, then digits).
+// arithmetic of a single compute unit with few rows.  Measured on 166 rows x 128256 fp32, N(0, 3), T = 0.8, against passes by
+// digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
+// passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
+// (74); logits rounded to whole numbers, top-p 0.99 110 (110).
 template <typename LT>
 __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logits, int V, int nc, const int32_t *__restrict__ off,
                                                      const float *__restrict__ temperature, const float *__restrict__ top_p,
@@ -723,7 +751,14 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     const int at = atomicAdd(&st.n, 1);
     if (at < kCutList) lkey[at] = okey(v);
   };
-  bool fast = !digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9;   // block-uniform
+  // The first pass sums in units of 2^-31 of the row's mass.  A running sum is within half a unit per token of the mass it stands
+  // for, the normaliser within 1e-6.
+  const double slack = 0.5 * V + 2147483648.0 * 2e-6, room = (1.0 - (double)tp) * 2147483648.0 - 2.0 * slack;
+  // a top-k beyond the list, or (top-p alone) no room between top_p and the whole for the sums' error: the general way at once
+  bool fast = !digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9 && (use_k ? tk <= kCutList : room > 6.0 * slack);   // block-uniform
+
+  bool crowded = false;           // top-p alone, too many candidates for the list:
+  uint32_t klo = 0u, khi = ~0u;   // the keys of the bins the cut can lie in
 
   if (fast) {
     double tot = 0.0;     // top-p alone: the row's mass as an integer sum (exact in a double: < 2^53 per thread)
@@ -773,7 +808,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       fast = !st.bad;
     } else {
       // ---- pass 1: bins ----
-      const float scale = (float)(2147483648.0 / S), drop = (float)(0.9 * (1.0 - (double)tp) * S / V);
+      const float scale = (float)(2147483648.0 / S), drop = (float)(0.9 * room / 2147483648.0 * S / V);
       if (use_k) {
         over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
 #pragma unroll
@@ -795,14 +830,21 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       }
       if (__any(bad) && lane == 0) st.bad = 1;
       __syncthreads();
-      // the running sums are within half a unit per token of the masses they stand for, the normaliser within 1e-6
-      const double target32 = (double)tp * 2147483648.0, slack = (double)V + 2147483648.0 * 2e-6;
+      const double target32 = (double)tp * 2147483648.0;
       const uint32_t x0 = use_k ? (uint32_t)tk : (uint32_t)fmax(1.0, target32 - slack), x1 = use_k ? (uint32_t)tk : (uint32_t)(target32 + slack);
       cut_find_bins(hist, x0, x1, &st);
       const uint32_t lo = use_k ? 0u : st.bin_lo, hi = st.bin_hi;
       fast = !st.bad && hi < kCutBins - 1;
+      if (fast && !use_k) {
+        // the values at the bins' edges, a little outside, as in the one-pass form
+        const float d_lo = (float)lo / (kCutBinsPerLog2 * k.hi), d_hi = (float)(hi + 1) / (kCutBinsPerLog2 * k.hi);
+        khi = okey((m - d_lo * 0.99999f) + 5e-7f * (fabsf(m) + d_lo));
+        klo = okey((m - d_hi * 1.00001f) - 5e-7f * (fabsf(m) + d_hi));
+        // a token of these bins has at most the mass of the first one's upper edge: at least this many of them
+        crowded = (float)(st.upto - st.before) * __builtin_amdgcn_exp2f((float)lo / kCutBinsPerLog2) > scale * (float)kCutList;
+      }
       // ---- pass 2: candidates, and the mass above them ----
-      if (fast)
+      if (fast && !crowded)
         over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -826,7 +868,9 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
     double total = (double)all;
     const int n = st.n;
-    fast = fast && n <= kCutList && n > 0;
+    crowded |= n > kCutList && fast && !use_k;   // block-uniform
+    if (crowded && tid == 0) st.total = all;
+    fast = fast && !crowded && n <= kCutList && n > 0;
 
     // ---- the list, in descending order of the keys ----
     if (fast) {
@@ -923,13 +967,17 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       }
     }
     if (fast) return;
-    __syncthreads();   // the bins and the list make room for the digit passes
+    __syncthreads();   // the bins and the list make room for the passes below
   }
-  unsigned long long *h64 = s_raw;
   uint32_t *hcnt = reinterpret_cast<uint32_t *>(s_raw + FSV_NUC_BINS);
-  if (use_k) cut_digits<LT, 1>(row, V, vec != 0, m, k, 0u, tk, tp, h64, hcnt, &st);
+  if (use_k) cut_narrow<LT, true>(row, V, vec != 0, m, k, 0u, ~0u, true, 0u, tk, tp, s_raw, hcnt, &st);
   const uint32_t kkey = use_k ? st.kkey : 0u;
-  if (use_p) cut_digits<LT, 0>(row, V, vec != 0, m, k, kkey, tk, tp, h64, hcnt, &st);
+  if (use_p) {
+    // (a second trip over the whole range if the interval the bins left does not hold the cut)
+    while (!cut_narrow<LT, false>(row, V, vec != 0, m, k, crowded ? klo : 0u, crowded ? khi : ~0u, !crowded, kkey, tk, tp, s_raw, hcnt, &st) &&
+           crowded)
+      crowded = false;
+  }
   if (tid == 0) {
     if (use_p) {
       const double total = (double)st.total, target = (double)tp * total;
