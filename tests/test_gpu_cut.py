@@ -69,6 +69,77 @@ def test_fast_cut_equals_the_digit_passes(kind, V, dtype, monkeypatch):
     ctx.close()
 
 
+def _cut_rank(v, T, top_k, top_p):
+    """(tokens kept, least distance of the kept mass from top_p) by the definition, in fp64: v the logits in descending order."""
+    e = np.exp((v.astype(np.float64) - float(v[0])) / float(T))
+    n = len(v)
+    if top_k:
+        n = int(np.searchsorted(-v, -v[top_k - 1], side="right"))
+    if top_p is None:
+        return n, 1.0
+    c = np.cumsum(e[:n]) / e[:n].sum()
+    ends = np.flatnonzero(np.append(v[1:n] != v[:n - 1], True))       # last token of each group of equal logits
+    at = int(np.searchsorted(c[ends], float(top_p)))
+    lo = c[ends[at - 1]] if at else 0.0
+    return int(ends[at]) + 1, min(float(top_p) - lo, float(c[ends[at]]) - float(top_p))
+
+
+def _between(v, T, top_k, rank):
+    """A top_p that falls half way into the mass of the group of equal logits that holds `rank`."""
+    e = np.exp((v.astype(np.float64) - float(v[0])) / float(T))
+    n = int(np.searchsorted(-v, -v[top_k - 1], side="right")) if top_k else len(v)
+    a, b = np.searchsorted(-v[:n], -v[rank]), np.searchsorted(-v[:n], -v[rank], side="right")
+    c = np.cumsum(e[:n]) / e[:n].sum()
+    return np.float32(0.5 * ((c[a - 1] if a else 0.0) + c[b - 1]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [64, 8191, 32768, 98312, 100003])
+@pytest.mark.parametrize("law,T", [("normal", 0.7), ("normal", 1.0), ("normal", 3.0), ("offset", 0.8), ("flat", 1.0), ("ties", 0.8)])
+def test_last_token_kept(law, T, V, dtype):
+    """The cut itself: the id V - 2 holds the last token kept, V - 3 the one before it, V - 1 the first one cut, the others lie
+    anywhere, and with u = 1 - 2^-24 the emitted id is the last one that has mass.  One token too many or too few emits another."""
+    from paper_2601_00644_amd import flexverify as fv
+    g = torch.Generator().manual_seed(V + len(law))
+    z = torch.randn(V, generator=g)
+    z = {"normal": z * 3.0, "offset": z * 3.0 + 20.0, "flat": z * 1e-2, "ties": (z * 2.0).round()}[law].to(dtype)
+    v = z.float().sort(descending=True).values.numpy()
+    cuts = [(k, None) for k in (1, 2, 50, 341, 342, 1000, 2047, 2048, 2049, V // 2, V - 1) if k < V]
+    cuts += [(0, _between(v, T, 0, r)) for r in (0, 1, 60, 900, 2500, V // 3) if r < V]
+    cuts += [(k, _between(v, T, k, r)) for k, r in ((50, 0), (50, 20), (1000, 700), (2500, 1800), (30000, 20000)) if k < V]
+    e = np.exp((v.astype(np.float64) - float(v[0])) / T)
+    rng, rows, used = np.random.default_rng(V), [], []
+    for k, p in cuts:
+        if p is not None and not 0.0 < p < 1.0:
+            continue
+        n, margin = _cut_rank(v, np.float32(T), k, p)
+        # the draw has to be able to tell: a margin well above the masses' fixed point, the last token's mass above 2^-23 of the
+        # whole, a token beyond the cut to emit by mistake
+        if margin < 1e-6 or n >= V - 1 or n < 3 or e[n - 1] < 2.0 ** -23 * e[:n].sum():
+            continue
+        tail = [n - 2, n - 1, n]
+        rest = rng.permutation(np.setdiff1d(np.arange(V), tail))
+        rows.append(v[np.concatenate([rest, tail])])
+        used.append((k, p))
+    B = len(rows)
+    assert B >= 4
+    t = lambda a: torch.as_tensor(a).cuda()
+    off = np.zeros(B + 1, np.int32)
+    temps = np.full(B, T, np.float32)
+    ctx = fv.Context(synth.ModelCfg("sampler", 0, 0, 0, 0, 0, 0, V, "bf16"), None, B, 16, sampler_only=True)
+    batch = fv.DeviceBatch(None, None, t(off), None, None, None, t(np.full(B, 1.0 - 2.0 ** -24, np.float32)), t(temps), None, None, None, 0,
+                           None, off, temps)
+    batch.top_k_host = np.array([k for k, _ in used], np.int32)
+    batch.top_p_host = np.array([1.0 if p is None else p for _, p in used], np.float32)
+    batch.top_k, batch.top_p = t(batch.top_k_host), t(batch.top_p_host)
+    res = fv.DeviceResult.alloc(B)
+    lg = torch.as_tensor(np.stack(rows)).to(dtype).cuda()
+    ctx.sample(lg, batch, res)
+    got = res.next_token.cpu().numpy().tolist()
+    ctx.close()
+    assert got == [V - 2] * B, [(u, a) for u, a in zip(used, got) if a != V - 2]
+
+
 def test_bf16_top_p_is_measured_against_the_exact_mass(monkeypatch):
     """bf16 rows whose cut lies more than two binades below the maximum: top_p steps by its last bit across the kept mass at the
     end of several groups of equal logits.  The cut has to change at the step at which the digit passes, which sum the row's
