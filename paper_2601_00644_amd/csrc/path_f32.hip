@@ -122,13 +122,14 @@ __global__ void k_rope_append(int H, int Hkv, int hd, double theta, int num_page
 // Bound by latency; 133 keys of 64: 8.7 us, against 38 us for one wave that went from key to key.  Eight waves per block
 // and no integer division per key: 12 -> 8.7 us, 162 -> 112 us for a two-layer call of 16 rows at 1000 positions, 1030 -> 907 us
 // for a prefill of 1024 rows (sixteen waves: the single call 9.8 against 10 us before the division went, the prefill 12 % slower).
-constexpr int ATT = 512;
+constexpr int ATT_SUMS = 512;   // (feature, group of keys) pairs, whatever the block: a row's result does not depend on its batch
+template <int ATT>
 __global__ __launch_bounds__(ATT) void k_attention(int H, int Hkv, int hd, int max_pages, int num_pages, int page_size, int key_cap,
                                                   const float *__restrict__ qbuf, const int32_t *__restrict__ row_req,
                                                   const int32_t *__restrict__ row_pos, const int32_t *__restrict__ page_table,
                                                   const float *__restrict__ kpool, const float *__restrict__ vpool,
                                                   size_t layer_off, float *__restrict__ out) {
-  extern __shared__ float sc[];   // [key_cap] scores, then [key_cap / page_size + 1] page ids, then [ATT] partial sums
+  extern __shared__ float sc[];   // [key_cap] scores, then [key_cap / page_size + 1] page ids, then [ATT_SUMS] partial sums
   __shared__ float s_red[ATT / 64];
   const int r = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int b = row_req[r], nkeys = min(row_pos[r] + 1, key_cap), kvh = h / (H / Hkv), npg = (nkeys + page_size - 1) / page_size;
@@ -231,12 +232,13 @@ __global__ __launch_bounds__(ATT) void k_attention(int H, int Hkv, int hd, int m
     }
     return;
   }
-  const int groups = ATT / hd, g = tid / hd, e = tid - g * hd;
-  if (g < groups) {
+  const int groups = ATT_SUMS / hd;
+  for (int i = tid; i < groups * hd; i += ATT) {
+    const int g = i / hd, e = i - g * hd;
     float acc = 0.f;
 #pragma unroll 8
     for (int j = g; j < nkeys; j += groups) acc = fmaf(sc[j], row_of(vpool, j)[e], acc);
-    s_part[tid] = acc;
+    s_part[i] = acc;
   }
   __syncthreads();
   den = total();
@@ -286,8 +288,23 @@ void launch_linear(int M, int N, int K, const float *a, const float *w, float *y
 }
 
 // LDS of k_attention for key_cap keys: 70.0 KiB at the 16384 that fsv_f32_check admits
+constexpr int ATT_WIDE = 512, ATT_NARROW = 128;   // threads per block
 size_t attention_lds(const fsv_model_desc &d, int key_cap) {
-  return sizeof(float) * ((size_t)key_cap + key_cap / d.page_size + 1 + ATT);
+  return sizeof(float) * ((size_t)key_cap + key_cap / d.page_size + 1 + ATT_SUMS);
+}
+
+void launch_attention(const fsv_model_desc &d, const fsv_ctx *c, const fsv_batch *b, int M, int keys, const float *q, size_t lo, float *out,
+                      hipStream_t s) {
+#define FSV_F32_ATT(T)                                                                                                              \
+  hipLaunchKernelGGL(k_attention<T>, dim3(M, d.n_heads), dim3(T), attention_lds(d, keys), s, d.n_heads, d.n_kv_heads, d.head_dim, \
+                     d.max_pages_per_req, b->num_pages, d.page_size, keys, q, c->row_req, c->row_pos, b->page_table,                \
+                     (const float *)b->k_pool, (const float *)b->v_pool, lo, out)
+  // Many blocks of few keys run in rounds, and eight waves of a block then have less to do than it takes to start them: 4096 blocks
+  // of 24 keys 34 us with 512 threads, 20 with 128, of 40 keys 38 and 27.  Up to 1024 blocks both take the same up to 64 keys, and
+  // 128 threads fall behind beyond (1024 blocks of 254 keys 27 us and 32), as they do where a thread has several features.
+  if (keys <= 64 && d.head_dim <= ATT_NARROW && (long)M * d.n_heads >= 2048) FSV_F32_ATT(ATT_NARROW);
+  else FSV_F32_ATT(ATT_WIDE);
+#undef FSV_F32_ATT
 }
 
 }  // namespace
@@ -311,7 +328,7 @@ int fsv_f32_create(fsv_ctx *c, const fsv_weights *w) {
     if ((rc = dev_copy(c, &L.w_down, w->w_down[l], f * d.d_model * d.d_ffn))) return rc;
   }
   if (attention_lds(d, min(16384, d.max_pages_per_req * d.page_size)) > 64 * 1024)   // beyond what a launch may take unasked
-    FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attention), hipFuncAttributeMaxDynamicSharedMemorySize,
+    FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attention<ATT_WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)attention_lds(d, 16384)));
   const size_t R = c->max_rows;
   FSV_HIP(c, hipMalloc(&c->buf_qkv, f * R * qkvd));
@@ -343,7 +360,6 @@ int fsv_f32_forward(fsv_ctx *c, const fsv_batch *b, int M, float *logits, hipStr
   float *x = c->x, *qkv = (float *)c->buf_qkv, *qb = (float *)c->buf_q;
   float *att = (float *)c->buf_att, *act = (float *)c->buf_act;
   const int keys = max_keys_of(b);   // fsv_f32_check has bounded it
-  const size_t lds = attention_lds(d, keys);
   hipLaunchKernelGGL(k_embed, dim3(M), dim3(256), 0, s, d.d_model, (const float *)c->embed, c->row_tok, x);
   for (int l = 0; l < d.n_layers; ++l) {
     const fsv_layer_w &L = c->layers[l];
@@ -352,9 +368,7 @@ int fsv_f32_forward(fsv_ctx *c, const fsv_batch *b, int M, float *logits, hipStr
     hipLaunchKernelGGL(k_rope_append, dim3(M), dim3(256), 0, s, d.n_heads, d.n_kv_heads, d.head_dim,
                        (double)d.rope_theta, b->num_pages, d.max_pages_per_req, qkv, c->row_req, c->row_pos,
                        b->page_table, qb, (float *)b->k_pool, (float *)b->v_pool, lo, d.page_size);
-    hipLaunchKernelGGL(k_attention, dim3(M, d.n_heads), dim3(ATT), lds, s, d.n_heads, d.n_kv_heads, d.head_dim,
-                       d.max_pages_per_req, b->num_pages, d.page_size, keys, qb, c->row_req, c->row_pos, b->page_table,
-                       (const float *)b->k_pool, (const float *)b->v_pool, lo, att);
+    launch_attention(d, c, b, M, keys, qb, lo, att, s);
     launch_linear(M, d.d_model, qd, att, (const float *)L.w_o, x, 1, s);
     launch_linear(M, d.d_ffn, d.d_model, x, (const float *)L.w_gate_up, act, 0, s, (const float *)L.mlp_norm, d.rms_eps, true);
     launch_linear(M, d.d_model, d.d_ffn, act, (const float *)L.w_down, x, 1, s);
@@ -384,11 +398,8 @@ int fsv_f32_linear(fsv_ctx *c, int which, int layer, const void *x, int M, float
 int fsv_f32_attention(fsv_ctx *c, int layer, const void *q, const fsv_batch *b, int M, float *out, hipStream_t s) {
   const fsv_model_desc &d = c->d;
   const int keys = max_keys_of(b);   // fsv_f32_check has bounded it
-  const size_t lds = attention_lds(d, keys);
   const size_t lo = (size_t)layer * layer_stride(c, b->num_pages);
-  hipLaunchKernelGGL(k_attention, dim3(M, d.n_heads), dim3(ATT), lds, s, d.n_heads, d.n_kv_heads, d.head_dim,
-                     d.max_pages_per_req, b->num_pages, d.page_size, keys, (const float *)q, c->row_req, c->row_pos, b->page_table,
-                     (const float *)b->k_pool, (const float *)b->v_pool, lo, out);
+  launch_attention(d, c, b, M, keys, (const float *)q, lo, out, s);
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
 }

@@ -78,3 +78,38 @@ def test_forward_of_odd_sizes(rows):
     rms = np.sqrt((ref ** 2).mean(1, keepdims=True))
     assert (np.abs(got - ref) <= 1e-4 * np.maximum(np.abs(ref), rms)).all()      # the fp32 path's bar
     ctx.close()
+
+
+@pytest.mark.parametrize("hd,heads,kv", [(2, 16, 2), (34, 12, 3), (64, 16, 4), (128, 8, 2)])
+def test_attention_of_many_blocks_with_few_keys(hd, heads, kv):
+    """2048 blocks or more of up to 64 keys take smaller blocks: the bits of the same rows in a call that takes the larger ones,
+    and (one request of each length) the fp64 result."""
+    cfg = synth.ModelCfg("f32few", 1, 32, heads, kv, hd, 32, 64, "f32")
+    B = 2048 // heads
+    L = np.array([0, 1, 14, 15, 16, 31, 62, 63], np.int32)[np.arange(B) % 8]
+    gam, off = np.zeros(B, np.int32), np.zeros(B + 1, np.int32)
+    pt, n = synth.make_page_table(L, gam, 16, "permuted", 1)
+    fv, ctx = _ctx(cfg, synth.make_weights(cfg, 1), max_batch=B, max_gamma=0, max_pages_per_req=pt.shape[1])
+    kp, vp = fv.alloc_pools(cfg, n)
+    g = torch.Generator().manual_seed(hd)
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
+    q = torch.randn((B, heads, hd), generator=g)
+    kv_of = {b: [torch.randn((1, int(L[b]) + 1, kv, hd), generator=g) for _ in range(2)] for b in range(B)}
+    for b, (k, v) in kv_of.items():
+        ctx.kv_import(kp, vp, n, t(pt)[b], 0, k.cuda(), v.cuda())
+
+    def run(rows):
+        o = np.zeros(len(rows) + 1, np.int32)
+        return ctx.attention(0, q[rows].cuda(), fv.DeviceBatch(t(L[rows]), None, t(o), None, None, None, None, None, t(pt[rows]), kp, vp, n,
+                                                               np.ascontiguousarray(L[rows]), o)).cpu().view(-1, heads, hd)
+
+    out = run(np.arange(B))                     # B * heads = 2048 blocks
+    assert torch.equal(run(np.arange(B - 1)), out[:B - 1])     # fewer: the larger blocks
+    for b in range(8):
+        k, v = (x[0].double() for x in kv_of[b])
+        for h in range(heads):
+            s = (k[:, h * kv // heads] @ q[b, h].double()) / hd ** 0.5
+            ref = torch.softmax(s, -1) @ v[:, h * kv // heads]
+            bound = (4 + s.abs().max() + hd / 16 + len(s) / 64) * 2.0 ** -22
+            assert (out[b, h].double() - ref).abs().max() <= bound * max(1.0, float(v.abs().max())), (b, h)
+    ctx.close()
