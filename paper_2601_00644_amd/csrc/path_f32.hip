@@ -23,30 +23,36 @@ __global__ void k_embed(int d, const float *__restrict__ E, const int32_t *__res
 // y[m][n] (+)= sum_k a[m][k] w[n][k]; one wave per output column and eight rows, lanes stride over k.
 // NORM: the rows are RMS-normalised on the way, y = (sum a g w) / sqrt(mean(a^2) + eps): a wave reads whole rows anyway, so
 // the sum of squares costs an operation per element and saves a launch and a pass.  SWIGLU: columns n and n + N of w are gate
-// and up, y = silu(gate) up, for the same reason.
+// and up, y = silu(gate) up, for the same reason.  ROWS = 1 for a call of one row: seven repeated rows cost nothing on a small
+// matrix, but 131 MB of head take 34 us with them and 19 without (26 before rows were taken by eight).
 // Bound by latency at the sizes this path is for (5 rows, 256 .. 4096 columns): one round of loads and ten shuffles per eight
 // rows.  Measured there: 3.4 .. 5.0 us per projection against 7.6 .. 15.3 us row by row plus 4.2 us per norm and 3.4 for SwiGLU.
-template <bool NORM, bool SWIGLU>
+template <bool NORM, bool SWIGLU, int ROWS>
 __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, const float *__restrict__ a, const float *__restrict__ g,
                                                 const float *__restrict__ w, float *__restrict__ y, int accumulate, int vec) {
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (n >= N) return;
+  // the same sums in the same order for one row as for eight: a row's result does not depend on its batch
+  auto sums_of = [lane](float(&v)[ROWS]) {
+    if constexpr (ROWS == 1) return wave_sum(v[0]);
+    else return wave_sum8(v, lane);
+  };
   const float *wr = w + (size_t)n * K, *wu = wr + (SWIGLU ? (size_t)N * K : 0);
-  for (int m0 = blockIdx.y * 8; m0 < M; m0 += gridDim.y * 8) {
-    const float *ar[8];
+  for (int m0 = blockIdx.y * ROWS; m0 < M; m0 += gridDim.y * ROWS) {
+    const float *ar[ROWS];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ar[i] = a + (size_t)min(m0 + i, M - 1) * K;   // (rows beyond M repeat the last; not stored)
-    float acc[8], up[8], ss[8];
+    for (int i = 0; i < ROWS; ++i) ar[i] = a + (size_t)min(m0 + i, M - 1) * K;   // (rows beyond M repeat the last; not stored)
+    float acc[ROWS], up[ROWS], ss[ROWS];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = up[i] = ss[i] = 0.f;
+    for (int i = 0; i < ROWS; ++i) acc[i] = up[i] = ss[i] = 0.f;
     auto add = [&](int i, float av, float wv, float uv, float gv) {
       const float x = NORM ? av * gv : av;
       acc[i] = fmaf(x, wv, acc[i]);
       if (SWIGLU) up[i] = fmaf(x, uv, up[i]);
       if (NORM) ss[i] = fmaf(av, av, ss[i]);
     };
-    const int m = m0 + ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-    const bool mine = !(lane & 7) && m < M;
+    const int m = m0 + (ROWS == 1 ? 0 : ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1));
+    const bool mine = !(lane & (ROWS == 1 ? 63 : 7)) && m < M;
     const size_t o = (size_t)min(m, M - 1) * N + n;
     const float before = (accumulate && mine) ? y[o] : 0.f;   // fetched with the first operands
     if (vec) {
@@ -54,11 +60,11 @@ __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, 
         const float4 w4 = *reinterpret_cast<const float4 *>(wr + k);
         const float4 u4 = SWIGLU ? *reinterpret_cast<const float4 *>(wu + k) : w4;
         const float4 g4 = NORM ? *reinterpret_cast<const float4 *>(g + k) : w4;
-        float4 a4[8];
+        float4 a4[ROWS];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a4[i] = *reinterpret_cast<const float4 *>(ar[i] + k);
+        for (int i = 0; i < ROWS; ++i) a4[i] = *reinterpret_cast<const float4 *>(ar[i] + k);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < ROWS; ++i) {
           add(i, a4[i].x, w4.x, u4.x, g4.x);
           add(i, a4[i].y, w4.y, u4.y, g4.y);
           add(i, a4[i].z, w4.z, u4.z, g4.z);
@@ -69,12 +75,12 @@ __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, 
       for (int k = lane; k < K; k += 64) {
         const float w1 = wr[k], u1 = SWIGLU ? wu[k] : 0.f, g1 = NORM ? g[k] : 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) add(i, ar[i][k], w1, u1, g1);
+        for (int i = 0; i < ROWS; ++i) add(i, ar[i][k], w1, u1, g1);
       }
     }
-    float r = wave_sum8(acc, lane);
-    const float u = SWIGLU ? wave_sum8(up, lane) : 0.f;
-    const float rinv = NORM ? 1.0f / sqrtf(wave_sum8(ss, lane) / (float)K + eps) : 1.0f;
+    float r = sums_of(acc);
+    const float u = SWIGLU ? sums_of(up) : 0.f;
+    const float rinv = NORM ? 1.0f / sqrtf(sums_of(ss) / (float)K + eps) : 1.0f;
     if (!mine) continue;
     r *= rinv;
     if (SWIGLU) r = r / (1.0f + expf(-r)) * (u * rinv);
@@ -282,9 +288,15 @@ void launch_linear(int M, int N, int K, const float *a, const float *w, float *y
   // row blocks side by side only as far as the columns alone leave the chip idle; the rest in turn, the weight row still in L1
   const int nb = fsv_ceil_div(N, 4);
   const dim3 grid(nb, max(1, min(fsv_ceil_div(M, 8), 2048 / nb)));
-  if (swiglu) hipLaunchKernelGGL((k_linear<true, true>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);
-  else if (gain) hipLaunchKernelGGL((k_linear<true, false>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);
-  else hipLaunchKernelGGL((k_linear<false, false>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);
+#define FSV_F32_LIN(NORM, SWIGLU)                                                                                                    \
+  do {                                                                                                                              \
+    if (M == 1) hipLaunchKernelGGL((k_linear<NORM, SWIGLU, 1>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);       \
+    else hipLaunchKernelGGL((k_linear<NORM, SWIGLU, 8>), grid, dim3(256), 0, s, M, N, K, eps, a, gain, w, y, acc, vec);              \
+  } while (0)
+  if (swiglu) FSV_F32_LIN(true, true);
+  else if (gain) FSV_F32_LIN(true, false);
+  else FSV_F32_LIN(false, false);
+#undef FSV_F32_LIN
 }
 
 // LDS of k_attention for key_cap keys: 70.0 KiB at the 16384 that fsv_f32_check admits

@@ -80,6 +80,28 @@ def test_forward_of_odd_sizes(rows):
     ctx.close()
 
 
+def test_one_row_alone_gives_the_bits_it_gives_in_a_batch():
+    """A call of one row takes its own form of the projections: same sums, same order."""
+    cfg = synth.MODELS["minif32"]
+    w = synth.make_weights(cfg, 5, std=0.1)
+    fv, ctx = _ctx(cfg, w, max_batch=9, max_gamma=0, max_pages_per_req=2)
+    toks = np.random.default_rng(1).integers(0, cfg.vocab, 9).astype(np.int32)
+    pt = np.arange(18, dtype=np.int32).reshape(9, 2)
+    t = lambda a: torch.as_tensor(a).cuda()
+
+    def prefill(rows):
+        kp, vp = fv.alloc_pools(cfg, 18)
+        n = len(rows)
+        L, off = np.zeros(n, np.int32), np.zeros(n + 1, np.int32)
+        return ctx.prefill(fv.DeviceBatch(t(L), t(toks[rows]), t(off), None, None, None, None, None, t(pt[rows]), kp, vp, 18, L, off),
+                           want_logits=True).cpu()
+
+    together = prefill(np.arange(9))
+    for r in (0, 4, 8):
+        assert torch.equal(prefill(np.array([r]))[0], together[r])
+    ctx.close()
+
+
 @pytest.mark.parametrize("hd,heads,kv", [(2, 16, 2), (34, 12, 3), (64, 16, 4), (128, 8, 2)])
 def test_attention_of_many_blocks_with_few_keys(hd, heads, kv):
     """2048 blocks or more of up to 64 keys take smaller blocks: the bits of the same rows in a call that takes the larger ones,
