@@ -648,22 +648,30 @@ constexpr double kNarrowBase[5] = {0, 0, 0, 0.17, 0.19}, kNarrowSlope[5] = {0, 0
 
 gemm_launch pick_wide(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow) {
   const int nchunks = s.K / KCHUNK, nb = fsv_ceil_div(s.NTpad, 8);
-  auto expected = [&](int blocks, int sp, double base, double slope) {
-    const int full = blocks / c->n_cus, rest = blocks % c->n_cus;
-    const double stages = fsv_ceil_div(nchunks, sp) * (KCHUNK / 32), busy = (double)rest / c->n_cus;
+  // blocks in rounds over `units` of them at a time
+  auto expected = [&](int blocks, int units, int sp, double base, double slope) {
+    const int full = blocks / units, rest = blocks % units;
+    const double stages = fsv_ceil_div(nchunks, sp) * (KCHUNK / 32), busy = (double)rest / units;
     double us = full * (stages * (base + slope) + kWideFixed);
     if (rest) us += stages * (base + slope * busy * busy) + kWideFixed;
     return allow ? us + sp * (double)Mt * 32 * s.N * 8 / 5e6 : us;
+  };
+  // A feature block stays on one XCD (unless the splits are dealt out to them), so with a count that is no multiple of eight some
+  // XCDs get a block more: their rounds set the time.  5024 features x 512, 1450 rows, 240 blocks, 36 of them on the 32 units of
+  // an XCD: 25 us, the weight-streaming kernel 21.  That kernel's blocks are short enough to count them over the whole chip.
+  auto expected_wide = [&](int sp, int mb, double base, double slope) {
+    const int busiest = sp % 8 == 0 ? nb * (sp / 8) * mb : fsv_ceil_div(nb, 8) * sp * mb;
+    return expected(busiest, max(1, c->n_cus / 8), sp, base, slope);
   };
   const int rb = fsv_ceil_div(Mt, 4), rt = fsv_ceil_div(Mt, rb);   // row blocks of the weight-streaming kernel
   gemm_launch best{4, pick_splits(c, s, Mt, allow, 4)};
   double best_us = -1;
   if (c->gemm_wide_force <= 0)
-    best_us = expected(fsv_ceil_div(s.NTpad, 4) * best.splits * rb, best.splits, kNarrowBase[rt], kNarrowSlope[rt]);
+    best_us = expected(fsv_ceil_div(s.NTpad, 4) * best.splits * rb, c->n_cus, best.splits, kNarrowBase[rt], kNarrowSlope[rt]);
   for (int mt = 4; mt >= 2; --mt) {
     if (c->gemm_wide_force > 0 && mt != c->gemm_wide_force) continue;
     for (int sp = 1; sp <= (allow ? min(8, nchunks) : 1); ++sp) {
-      const double us = expected(nb * sp * fsv_ceil_div(Mt, 2 * mt), sp, kWideBase[mt], kWideSlope[mt]);
+      const double us = expected_wide(sp, fsv_ceil_div(Mt, 2 * mt), kWideBase[mt], kWideSlope[mt]);
       if (best_us < 0 || us < best_us) {
         best = gemm_launch{4, sp, mt};
         best_us = us;
