@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void k_kv_copy(int Hkv, int num_pages, const i
   constexpr int U8 = HD / 8, UPT = 2 * HD;          // 16-byte units per (position, head) row and per tile
   constexpr int PER = KV_HG * UPT / 256;            // units a thread moves per tensor
   constexpr int PITCH = HD + 2;                     // LDS row pitch in elements: rows of a tile fall on different banks
-  __shared__ uint16_t s_v[KV_HG][16][PITCH];
+  __shared__ __align__(16) uint16_t s_v[KV_HG][16][PITCH];   // (also read and written in 32-bit words)
   const int l = blockIdx.y, h0 = blockIdx.z * KV_HG, nh = min(KV_HG, Hkv - h0), tid = threadIdx.x;
   const int lp = (pos0 >> 4) + blockIdx.x, t_first = max(pos0 - lp * 16, 0), t_last = min(pos0 + n - lp * 16, 16) - 1;
   const int page = min(max(pt[lp], 0), num_pages - 1);
