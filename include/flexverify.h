@@ -296,7 +296,7 @@ int fsv_kv_export(fsv_ctx *ctx, const void *k_pool, const void *v_pool, int32_t 
  * Single kernels of the step, exposed for parity tests and roofline measurements.
  * fsv_linear: y[M][N] (fp32, DEVICE) = x[M][K] (model dtype, row-major, DEVICE) times the re-tiled
  *   weight matrix `which` of `layer` (FSV_W_* below; layer ignored for FSV_W_LM_HEAD), through the
- *   same weight-streaming GEMM kernel fsv_verify uses.  M <= max_rows.
+ *   same GEMM kernels, chosen by the same rule, that fsv_verify uses.  M <= max_rows.
  * fsv_attention: out[M][n_heads*head_dim] (fp32, DEVICE) for queries q[M][n_heads][head_dim] (model
  *   dtype, already rotated) over the paged KV of `layer`; row i of request b attends to positions
  *   0 .. seq_lens[b] + i.  Uses from batch: batch, num_pages, seq_lens(+_host), draft_offsets(+_host),
@@ -312,8 +312,9 @@ int fsv_attention(fsv_ctx *ctx, int32_t layer, const void *q, const fsv_batch *b
  * of the kernel classes whose bit (1u << FSV_K_*) is set in mask (0 = off, 0xffffffff = all; at most
  * 8192 launches are kept, later ones are not recorded).  For the GEMM and attention classes the pair
  * rides on the dispatch itself (start and stop of the kernel); for the other classes it is recorded on
- * the stream before and after the launches and so includes the dispatch gaps.  FSV_K_SAMPLE_NUCLEUS is
- * the kernel that finds the top-k / top-p cuts of a call.  fsv_profile_read() waits for the recorded
+ * the stream before and after the launches and so includes the dispatch gaps.  FSV_K_SAMPLE_NUCLEUS covers
+ * the launches that find the top-k / top-p cuts of a call (one, or three on bf16 logits), its bytes every
+ * logits row once.  fsv_profile_read() waits for the recorded
  * events and returns, per class, the number of launches, their summed duration and the algorithmic
  * bytes the host computed for them (weights for a GEMM, K and V for attention, logits and draft law
  * for the sampling kernels), then clears the records.  Returns the number of classes written (<= cap).

@@ -64,7 +64,7 @@ constexpr int kDescInts = 12;
 // row's position only, not on the layer: tab[(row * half + i) * 2 + {0, 1}], formed and reduced in fp64).
 // Bound by latency: a load of the lengths, a scan or search in LDS, a load of the page ids, the stores.  One thread walking
 // the requests, and a launch each for rows and angles, took 13 + 4.5 + 4.5 us for 16 requests and 82 + 6 + 6 for 128; this
-// takes 6 and 8.
+// takes 4.7 and 6.3.
 constexpr int kSetupThreads = 1024, kSetupB = 2048;   // requests whose prefix sums are kept in LDS (more are searched in memory)
 struct setup_args {
   int B, tpw, group, w2, w3, max_pages, num_pages, map_cap, M, half, V;
@@ -458,9 +458,9 @@ __global__ __launch_bounds__(256) void k_attn_combine(int Hkv, int group, int ro
   const int rr = blockIdx.z * RPB + tid / TPR, e0 = (tid % TPR) * 8;
   if (rr >= R) return;
   const size_t base = ((size_t)p0 * Hkv + kvh) * rows_cap + rr, pstr = (size_t)Hkv * rows_cap;
-  // The loads of sixteen parts, maxima and values together, are issued before the first use: one part per iteration would put a
-  // full memory round trip into every step of this short loop.  Further batches rescale what has been summed to the new
-  // maximum.  The sums always run in part order.  (A pass for the maximum and one for the sums, eight parts at a time, took
+  // Sixteen parts at a time: their maxima and sums are fetched together, their values behind them as far as the registers go (114;
+  // all sixteen would take 160): one part per iteration would put a full memory round trip into every step of this short loop.
+  // Further batches rescale what has been summed to the new maximum.  The sums always run in part order.  (A pass for the maximum and one for the sums, eight parts at a time, took
   // 7.5 us for requests of 9 .. 30 parts, and this no less; it is half the code.)
   constexpr int U = 16;
   float mm = -INFINITY, acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ll = 0.f;

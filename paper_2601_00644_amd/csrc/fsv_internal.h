@@ -102,7 +102,7 @@ struct fsv_ctx {
   int attn_min_tpw = 5;         // fewest key tiles a part is given: with a single 2048-position request, parts of 5 tiles
                                 // (13 per kv head, merged from one batch of loads) beat parts of 2 (33 per head) by 4 % of the call
   int attn_w2 = 26, attn_w3 = 36;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
-  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 8-int record per part
+  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 12-int record per part
 
   // LoRA adapters of the evolved target (bf16 path): tables [layer < n_layers - 1][adapter][...], library-owned
   int lora_n = 0, lora_rank = 0;
@@ -202,7 +202,7 @@ int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl); 
 int fsv_bf16_setup_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, bool rope, const void *q, hipStream_t s);
 // out32: row-major fp32 result [M][heads * hd], or NULL = the operand of the output projection (buf_att)
 int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, size_t layer_off, float *out32, hipStream_t s);
-// gemm_bf16.hip: y = x W^T through the weight-streaming kernel; epi 0 = fp32 split partials [splits][Mpad][N],
+// gemm_bf16.hip: y = x W^T, through the many-row kernel with `wide` row tiles per wave or (wide 0) the weight-streaming one; epi 0 = fp32 split partials [splits][Mpad][N],
 // 1 = SwiGLU to the bf16 operand order, 2 = fp32 rows [M][N]
 int fsv_bf16_gemm_init(fsv_ctx *c);
 int fsv_bf16_gemm(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, void *out, int N, int K, int NTpad, int M,

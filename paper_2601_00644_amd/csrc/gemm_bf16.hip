@@ -1,5 +1,6 @@
-// Weight-streaming 16-bit GEMM (bf16 or fp16 operands, fp32 sums) of the FSV_BF16 path: the dense projections of the target forward (Alg. 2
-// step 2) for a few dozen to a few hundred rows, where streaming the weight matrix from HBM is the bound.
+// The two 16-bit GEMM kernels (bf16 or fp16 operands, fp32 sums) of the FSV_BF16 path: the dense projections of the target forward (Alg. 2
+// step 2).  First the weight-streaming one, for a few dozen to a few hundred rows, where streaming the weight matrix from HBM is
+// the bound; k_gemm_wide, for more rows, is described where it begins.
 // Built with -mllvm -amdgpu-mfma-vgpr-form (accumulators in architectural registers, the weight chunks in
 // flight in accumulation registers).
 //
@@ -536,7 +537,7 @@ int init_e(fsv_ctx *c) {
 
 }  // namespace
 
-// Raise the dynamic LDS limit of every instantiation (up to 96 KiB) on the current device; called once per context
+// Raise the dynamic LDS limit of every instantiation (up to 96 KiB, the many-row kernel 140 .. 160 KiB) on the current device; called once per context
 // from its creation, with error checking, so that no launch depends on a lazily set process-wide flag.
 int fsv_bf16_gemm_init(fsv_ctx *c) {
   int rc;

@@ -638,9 +638,13 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
 // take.  A block's time is its stages (32 contraction elements) times the time of one plus kWideFixed for its first fills
 // and its result; a stage takes longer the more compute units are busy, because the matrix cores then lower the clock
 // (1.9 GHz with all of them at work against 2.4): base + slope x (busy share)^2, fitted to launches of 16 .. 256 blocks of
-// the 8B projections at 200 .. 2048 rows (within 5 % of all of them: 4 tiles 0.53 .. 0.89 us, 3 tiles 0.40 .. 0.69,
-// 2 tiles 0.32 .. 0.47).  Every split adds a set of partial sums to write and read back at about 5 TB/s.
-constexpr int kWideTiles = 9;   // row tiles from which on the many-row kernel is taken, see pick_launch
+// the 8B projections at 200 .. 2048 rows (4 tiles 0.53 .. 0.89 us, 3 tiles 0.40 .. 0.69, 2 tiles 0.32 .. 0.47).  Of the launches in
+// profiles/gemm_two_kernels_sweep.txt (three tile counts, five projections) 85 % lie within 10 % of it above 700 rows, two thirds
+// at 257 .. 700; the shortest launches run up to 60 % longer than expected.  Every split adds a set of
+// partial sums to write and read back at about 5 TB/s.
+// kWideTiles: row tiles from which on the many-row kernel is considered.  Below, the weight-streaming kernel is taken unseen; at
+// 129 .. 224 rows two row tiles would be faster where the matrix fills the chip (gate|up, 129 rows: 67 us and 57).
+constexpr int kWideTiles = 9;
 constexpr double kWideBase[5] = {0, 0, 0.32, 0.40, 0.53}, kWideSlope[5] = {0, 0, 0.15, 0.29, 0.36}, kWideFixed = 5.0;   // us
 // The weight-streaming kernel's blocks (128 features x 96 or 128 rows) by the same measure: less work per block, so a
 // launch that fills the chip exactly once with them (500 rows, output projection: 24 us against 33) is theirs.

@@ -12,10 +12,12 @@
 //                 draft-law row) into the masses of its 2048-id sub-blocks; the block that finishes last (an integer
 //                 ticket per request) locates the sub-block and the id by inverse CDF, emits the outputs and rolls back
 // plus, when a request asks for a top-k / nucleus (top-p) cut of the target law, between the two: k_cut, one block per row
-// that finds the row's cut in two passes over it and a short list of candidates.
+// that finds the row's cut in one or two passes over it and a short list of candidates; on bf16 logits two launches of
+// k_cut_window before it, which settle the rows whose cut lies near their maximum in one pass.
 // Rows are addressed as (request, row within the request), so the step needs no row map.  Every floating-point sum is
-// taken in a fixed order (the ticket only decides WHICH block adds the sub-block masses up, in sub-block order); the only
-// other atomics are integer adds into the nucleus histograms, whose result does not depend on their order.
+// taken in a fixed order (the ticket only decides WHICH block adds the sub-block masses up: three consecutive ones per lane, then
+// a scan over the lanes); the only other atomics are on integers in the histograms of the cuts, whose result does not depend on
+// their order.
 #include <limits.h>
 #include <math.h>
 #include <stdlib.h>
@@ -1032,8 +1034,8 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
 //   for a launch of its own.
 // Phase 2: wave w of block x takes sub-block 4x + w of the row the emitted token is drawn from (the residual
 //   max(0, p - q) after a rejection, p itself when every draft passed): four passes of 512 ids, mass to bsum.
-// Phase 3: the blocks of a request take a ticket; the one that draws the last ticket adds the sub-block masses up in
-//   sub-block order, finds the sub-block and the id by inverse CDF, writes every output of the request (accepted length,
+// Phase 3: the blocks of a request take a ticket; the one that draws the last ticket adds the sub-block masses up (lane sums
+//   and their scan), finds the sub-block and the id by inverse CDF, writes every output of the request (accepted length,
 //   token, flags, rollback) and clears the ticket for the next call.
 template <typename LT>
 __global__ __launch_bounds__(256) void k_decide(
@@ -1363,7 +1365,8 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   }
   const bool nucleus = any_k || any_p;
   if (nucleus) {
-    fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT) * 2);
+    // bytes: every row once, what no form can do without; how many passes a row takes is decided on the device
+    fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT));
     // (FSV_NUCLEUS_FULL=1 in the environment sends every row through the digit passes: a test compares the two)
     const char *full_env = getenv("FSV_NUCLEUS_FULL");
     const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
