@@ -194,6 +194,13 @@ __global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits
       }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    } else if (LAW) {   // a NaN makes the whole law NaN, also where nothing else in its chunk carries mass
+      bool nan = false;
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) nan |= v[p][j] != v[p][j];
+      if (__any(nan)) sum = __longlong_as_double(0x7FF8000000000000ll);
     }
   } else {
 #pragma unroll

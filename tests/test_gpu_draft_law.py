@@ -42,3 +42,28 @@ def test_law_is_the_softmax_of_the_logits(vocab, greedy):
             bound = (4 + (z[r].max() - z[r]) / float(T[b])) * 2.0 ** -22
             assert ((q[qi] - want).abs() <= want * bound + 1e-30).all()
     ctx.close()
+
+
+@pytest.mark.parametrize("vocab,at", [(8193, 8192), (8200, 8195), (16384, 100), (16388, 16387)])
+def test_a_nan_logit_makes_the_law_nan(vocab, at):
+    """As softmax does, also where the NaN is alone in its chunk of 8192 ids (8193: the last id has one to itself)."""
+    from paper_2601_00644_amd import flexverify as fv
+    cfg = dataclasses.replace(synth.MODELS["mini64"], vocab=vocab)
+    w = synth.make_weights(cfg, 3, std=0.05)
+    gam, L = np.array([2, 1], np.int32), np.array([4, 18], np.int32)
+    off = np.array([0, 2, 3], np.int32)
+    pt, n = synth.make_page_table(L, gam, 16, "interleaved", 1)
+    ctx = fv.Context(cfg, {k: t.cuda() for k, t in w.items()}, max_batch=2, max_gamma=8, max_pages_per_req=pt.shape[1])
+    head = synth.make_draft_head(cfg, 256, 256, 4, std=0.2)
+    head["wv"][at] = float("nan")
+    ctx.draft_attach({k: t.cuda() for k, t in head.items()})
+    kp, vp = fv.alloc_draft_pools(cfg, n)
+    T = np.array([0.7, 1.0], np.float32)
+    t = lambda a: torch.as_tensor(a).cuda()
+    batch = fv.DeviceBatch(t(L), t(np.array([1, 2], np.int32)), t(off), t(np.array([5, 6, 7], np.int32)), None, None, None, t(T), t(pt), kp,
+                           vp, n, L, off, T)
+    for mode in (fv.DRAFT_Q_VERIFY, fv.DRAFT_Q_ALL):
+        q, z = ctx.draft_probs(batch, mode, want_logits=True)
+        assert z[:, at].isnan().all() and int(z.isnan().sum()) == z.shape[0]
+        assert q.isnan().all()
+    ctx.close()
