@@ -372,6 +372,7 @@ __device__ inline bool cut_narrow(const LT *row, int V, bool vec, float m, exp_s
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         if (i0 + j >= V) continue;   // ids beyond the vocabulary are not tokens (they would count for top-k)
+        if (COUNT && v[j] != v[j]) continue;   // nor is a NaN one, which carries no mass
         const uint32_t key = okey(v[j]);
         if (key - from > hi - from) {
           if (!COUNT && sum_above && key > hi) above += floor((double)exp_scaled(v[j] - m, k) * kNucScale + 0.5);
@@ -661,8 +662,8 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
     kept = __shfl(kept, from, 64);
     acc = __shfl(acc, from, 64);
   };
-  bool settled = total > 0.0;   // (not with a NaN or an infinite maximum)
-  if (settled && use_k) {
+  bool settled = true;
+  if (use_k) {
     const unsigned long long ballot = __ballot(digit && beforec + minec >= (uint32_t)tk);
     settled = ballot != 0ull;
     if (settled) {
@@ -670,6 +671,7 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
       total = (double)kept;   // top-p works on what the top-k cut kept
     }
   }
+  settled = settled && (!use_p || total > 0.0);   // (not top-p with a NaN or an infinite maximum)
   if (settled && use_p) {
     target = (double)tp * total;
     const unsigned long long ballot = __ballot(digit && (double)(before + mine) >= target);
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   if (lane != 0) return;
   if (!settled) {   // a cut lies below the window, or the row is out of the ordinary (2: nothing for the wider window either)
     const double outside = 1.0 - (double)inside / total;
-    const bool wider = total > 0.0 && (use_k || 0.25 * outside * outside <= 1.0 - (double)tp);
+    const bool wider = use_k || (total > 0.0 && 0.25 * outside * outside <= 1.0 - (double)tp);
     done[r] = (FIRST && wider) ? 0 : 2;
     return;
   }

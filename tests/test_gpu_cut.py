@@ -95,18 +95,19 @@ def _between(v, T, top_k, rank):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("V", [64, 8191, 32768, 98312, 100003])
-@pytest.mark.parametrize("law,T", [("normal", 0.7), ("normal", 1.0), ("normal", 3.0), ("offset", 0.8), ("flat", 1.0), ("ties", 0.8)])
+@pytest.mark.parametrize("law,T", [("normal", 0.7), ("normal", 1.0), ("normal", 3.0), ("offset", 0.8), ("flat", 1.0), ("ties", 0.8), ("nans", 1.0)])
 def test_last_token_kept(law, T, V, dtype):
     """The cut itself: the id V - 2 holds the last token kept, V - 3 the one before it, V - 1 the first one cut, the others lie
     anywhere, and with u = 1 - 2^-24 the emitted id is the last one that has mass.  One token too many or too few emits another."""
     from paper_2601_00644_amd import flexverify as fv
     g = torch.Generator().manual_seed(V + len(law))
     z = torch.randn(V, generator=g)
-    z = {"normal": z * 3.0, "offset": z * 3.0 + 20.0, "flat": z * 1e-2, "ties": (z * 2.0).round()}[law].to(dtype)
-    v = z.float().sort(descending=True).values.numpy()
-    cuts = [(k, None) for k in (1, 2, 50, 341, 342, 1000, 2047, 2048, 2049, V // 2, V - 1) if k < V]
-    cuts += [(0, _between(v, T, 0, r)) for r in (0, 1, 60, 900, 2500, V // 3) if r < V]
-    cuts += [(k, _between(v, T, k, r)) for k, r in ((50, 0), (50, 20), (1000, 700), (2500, 1800), (30000, 20000)) if k < V]
+    z = {"normal": z * 3.0, "offset": z * 3.0 + 20.0, "flat": z * 1e-2, "ties": (z * 2.0).round(), "nans": z * 3.0}[law].to(dtype)
+    nans = np.full(5 if law == "nans" else 0, np.nan, np.float32)      # neither tokens nor mass
+    v = z.float()[len(nans):].sort(descending=True).values.numpy()
+    cuts = [(k, None) for k in (1, 2, 50, 341, 342, 1000, 2047, 2048, 2049, V // 2, V - 1) if k < len(v)]
+    cuts += [(0, _between(v, T, 0, r)) for r in (0, 1, 60, 900, 2500, V // 3) if r < len(v)]
+    cuts += [(k, _between(v, T, k, r)) for k, r in ((50, 0), (50, 20), (1000, 700), (2500, 1800), (30000, 20000)) if k < len(v)]
     e = np.exp((v.astype(np.float64) - float(v[0])) / T)
     rng, rows, used = np.random.default_rng(V), [], []
     for k, p in cuts:
@@ -115,11 +116,11 @@ def test_last_token_kept(law, T, V, dtype):
         n, margin = _cut_rank(v, np.float32(T), k, p)
         # the draw has to be able to tell: a margin well above the masses' fixed point, the last token's mass above 2^-23 of the
         # whole, a token beyond the cut to emit by mistake
-        if margin < 1e-6 or n >= V - 1 or n < 3 or e[n - 1] < 2.0 ** -23 * e[:n].sum():
+        if margin < 1e-6 or n >= len(v) - 1 or n < 3 or e[n - 1] < 2.0 ** -23 * e[:n].sum():
             continue
         tail = [n - 2, n - 1, n]
-        rest = rng.permutation(np.setdiff1d(np.arange(V), tail))
-        rows.append(v[np.concatenate([rest, tail])])
+        rest = rng.permutation(np.concatenate([v[np.setdiff1d(np.arange(len(v)), tail)], nans]))
+        rows.append(np.concatenate([rest, v[tail]]))
         used.append((k, p))
     B = len(rows)
     assert B >= 4
@@ -134,6 +135,8 @@ def test_last_token_kept(law, T, V, dtype):
     batch.top_k, batch.top_p = t(batch.top_k_host), t(batch.top_p_host)
     res = fv.DeviceResult.alloc(B)
     lg = torch.as_tensor(np.stack(rows)).to(dtype).cuda()
+    if dtype == torch.bfloat16:
+        lg.view(torch.int16)[lg.isnan()] = 0x7FC0      # (the conversion makes them negative, at the lower end of the key order)
     ctx.sample(lg, batch, res)
     got = res.next_token.cpu().numpy().tolist()
     ctx.close()
