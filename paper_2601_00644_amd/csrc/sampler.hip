@@ -728,7 +728,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; }
     return;
   }
-  // 32 KiB of bins; later the list's running sums (16), or the digit passes' masses (16) and counts (8)
+  // 32 KiB of bins; later the narrowing passes' masses (16) and counts (8) or lowest and highest keys (16)
   __shared__ unsigned long long s_raw[kCutBins / 2];
   __shared__ __align__(16) uint32_t lkey[kCutList];
   __shared__ uint32_t lrank[256];
@@ -1376,7 +1376,7 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   if (nucleus) {
     // bytes: every row once, what no form can do without; how many passes a row takes is decided on the device
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT));
-    // (FSV_NUCLEUS_FULL=1 in the environment sends every row through the digit passes: a test compares the two)
+    // (FSV_NUCLEUS_FULL=1 in the environment narrows every row from the whole key range: a test compares the two)
     const char *full_env = getenv("FSV_NUCLEUS_FULL");
     const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
     // bf16 logits: the cuts lie within one or two binades of the maximum more often than not, which is one pass

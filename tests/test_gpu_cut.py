@@ -1,7 +1,7 @@
 """The top-k / top-p cut kernel (fsv_sample) where its fast way can go wrong, against the digit-by-digit way forced with
 FSV_NUCLEUS_FULL=1: vocabularies around the rounds of its loads, ragged and unaligned rows, cuts of every depth, laws whose
-candidates overflow its list, rows with -inf and NaN.  Both ways form the same integer masses; for bf16 logits the fast way
-measures top_p against the statistics' normaliser, which can move a cut only where the call flags it (bit 3)."""
+candidates overflow its list, rows with -inf and NaN.  Both ways form the same integer masses; the windowed pass over bf16
+logits measures top_p against the statistics' normaliser, which can move a cut only where the call flags it (bit 3)."""
 import numpy as np
 import pytest
 import torch
