@@ -96,13 +96,12 @@ struct fsv_ctx {
   void *attn_part = nullptr;    // per-part attention results (O, then (m, l)) of requests with several parts
   size_t attn_part_bytes = 0;
   int n_cus = 0;                // compute units of the device the context was created on
-  int attn_wave_target = 0;     // waves the attention schedule aims at (resident waves of the device)
-  int attn_wave_cap = 0;        // waves the partial buffers hold
-  int attn_depth = 2;           // K/V tiles in flight per attention wave
-  int attn_min_tpw = 5;         // fewest key tiles a part is given: with a single 2048-position request, parts of 5 tiles
-                                // (13 per kv head, merged from one batch of loads) beat parts of 2 (33 per head) by 4 % of the call
-  int attn_w2 = 26, attn_w3 = 36;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
-  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 12-int record per part
+  int attn_wave_target = 0;     // blocks the attention schedule aims at (one per compute unit)
+  int attn_wave_cap = 0;        // blocks the partial buffers hold
+  int32_t *attn_ticket = nullptr;  // [max_batch][kv heads] parts of a (request, kv head) that have left their results; zero between launches
+  int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7
+  int attn_w2 = 20, attn_w3 = 26;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
+  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 24-int record per part
 
   // LoRA adapters of the evolved target (bf16 path): tables [layer < n_layers - 1][adapter][...], library-owned
   int lora_n = 0, lora_rank = 0;
@@ -190,9 +189,9 @@ int fsv_f32_kv_copy(fsv_ctx *c, void *k_pool, void *v_pool, int num_pages, const
 // attn_bf16.hip
 struct fsv_attn_plan {
   int tpw = 0;          // target key tiles per part
-  int waves = 0;        // parts x kv heads
+  int waves = 0;        // parts x kv heads: blocks
   int rt = 1;           // query-row tiles of the widest request
-  bool split = false;   // some request has several parts
+  int nw = 8;           // waves per block
   double kv_tokens = 0;
 };
 int fsv_bf16_attn_create(fsv_ctx *c);

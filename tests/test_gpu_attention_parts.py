@@ -1,0 +1,47 @@
+"""The attention kernel at the edges of its schedule: parts that end at and beside a multiple of eight key tiles, waves without a
+tile, requests of one to three query-row tiles in one call, as many parts as it takes several batches to merge, and the second
+launch after a merge (the tickets it leaves must be those it found)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2601_00644_amd import synth
+from tests.helpers import logits_close
+from tests.test_gpu_bf16_ops import _attention_case, _ctx
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("name", ["mini64", "mini128"])
+@pytest.mark.parametrize("seq_lens,gammas", [
+    ([30, 31, 32, 223, 255, 256, 287], [0, 0, 7, 1, 0, 8, 16]),     # one part: one tile, two, seven, eight, nine
+    ([511, 512, 1023, 1500, 20], [0, 16, 7, 8, 3]),                 # 16, 17, 32 tiles: two and more parts
+    ([5000], [16]),                                                 # ten parts, three row tiles
+    ([9000, 100, 4095], [1, 2, 7]),
+])
+def test_parts(name, seq_lens, gammas):
+    cfg = synth.MODELS[name]
+    L, gm, off, pt, npages, q, ks, vs = _attention_case(cfg, 8, seq_lens, gammas, "permuted")
+    fv, ctx, w, wn = _ctx(cfg, 4, max_batch=8, max_gamma=16, max_pages=pt.shape[1])
+    kp, vp = fv.alloc_pools(cfg, npages)
+    kp.fill_(float("nan"))      # slots no position was written to
+    vp.fill_(float("nan"))
+    ptd = torch.as_tensor(pt).cuda()
+    for b in range(len(L)):
+        k = ks[b].expand(cfg.n_layers, -1, -1, -1).contiguous().cuda()
+        v = vs[b].expand(cfg.n_layers, -1, -1, -1).contiguous().cuda()
+        ctx.kv_import(kp, vp, npages, ptd[b], 0, k, v)
+    batch = fv.DeviceBatch(torch.as_tensor(L).cuda(), None, torch.as_tensor(off).cuda(), None, None, None, None, None,
+                           ptd, kp, vp, npages, L, off)
+    qd = q.cuda()
+    first = ctx.attention(1, qd, batch)
+    assert torch.equal(first, ctx.attention(1, qd, batch))
+    out = first.cpu().numpy().astype(np.float64)
+    for b in range(len(L)):
+        rs, n = int(off[b]) + b, int(gm[b]) + 1
+        ref = oracle.attention(q[rs:rs + n].float().numpy(), ks[b][0].float().numpy(), vs[b][0].float().numpy(), int(L[b]))
+        # the result is stored in fp16 (2^-11), its operands are exact to 2^-16
+        ok, ratio = logits_close(out[rs:rs + n], ref, 2e-3)
+        assert ok, (b, ratio)
+    ctx.close()
