@@ -206,6 +206,10 @@ int fsv_bf16_attn_launch(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl
 int fsv_bf16_gemm_init(fsv_ctx *c);
 int fsv_bf16_gemm(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, void *out, int N, int K, int NTpad, int M,
                   int splits, int KBo, int f16, float oscale, int ncw, int wide, hipStream_t st);
+// gemm_wide.hip: the many-row kernel, mt row tiles per wave
+int fsv_bf16_gemm_wide_init(fsv_ctx *c);
+int fsv_bf16_gemm_wide(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, void *out, int N, int K, int NTpad, int M, int splits,
+                       int KBo, int f16, float oscale, int mt, hipStream_t st);
 // path_bf16.hip
 int fsv_bf16_create(fsv_ctx *c, const fsv_weights *w);
 int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, float *logits, int draft, hipStream_t s);

@@ -645,7 +645,7 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
 // kWideTiles: row tiles from which on the many-row kernel is considered.  Below, the weight-streaming kernel is taken unseen; at
 // 129 .. 224 rows two row tiles would be faster where the matrix fills the chip (gate|up, 129 rows: 67 us and 57).
 constexpr int kWideTiles = 9;
-constexpr double kWideBase[5] = {0, 0, 0.32, 0.40, 0.53}, kWideSlope[5] = {0, 0, 0.15, 0.29, 0.36}, kWideFixed = 5.0;   // us
+constexpr double kWideBase[5] = {0, 0, 0.32, 0.39, 0.53}, kWideSlope[5] = {0, 0, 0.15, 0.25, 0.35}, kWideFixed = 5.0;   // us
 // The weight-streaming kernel's blocks (128 features x 96 or 128 rows) by the same measure: less work per block, so a
 // launch that fills the chip exactly once with them (500 rows, output projection: 24 us against 33) is theirs.
 constexpr double kNarrowBase[5] = {0, 0, 0, 0.17, 0.19}, kNarrowSlope[5] = {0, 0, 0, 0.06, 0.08};
