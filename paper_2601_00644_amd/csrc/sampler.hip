@@ -321,7 +321,7 @@ struct cut_state {
 // before the next); the U loads of a round lie a U-th of the whole rounds apart, so that the first round is a sample of the
 // vocabulary.  after_round(r, values of the round) is met by every thread of the block after each whole round.
 template <typename LT>
-__device__ inline int whole_rounds(int V, bool vec) { return vec ? V / (4 * kCutThreads * 8) : 0; }
+__device__ __host__ inline int whole_rounds(int V, bool vec) { return vec ? V / (4 * kCutThreads * 8) : 0; }
 template <typename LT, typename F, typename G>
 __device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, G &&after_round) {
   constexpr int U = 4, STEP = kCutThreads * 8;
@@ -710,13 +710,76 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
 // digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
 // passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
 // (74); logits rounded to whole numbers, top-p 0.99 110 (110).
+// What k_row_stats leaves for a row, by the waves of one block: the same chunks, the same sums in the same order, but a quarter of a
+// chunk's loads at a time and a second trip (from the cache) for the sums, so that it fits this kernel's registers.
 template <typename LT>
+__device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int V, int nc, bool vec, float T, float *pm, double *ps, int32_t *pa, int w, int lane) {
+  constexpr int P = FSV_CHUNK / 512;
+  for (int c = w; c < nc; c += kCutThreads / 64) {
+    const int base = c * FSV_CHUNK + lane * 8;
+    const bool whole = vec && (c + 1) * FSV_CHUNK <= V;   // wave-uniform
+    auto quarter = [&](int p0, float(&v)[P / 4][8]) {
+      if (whole) {
+#pragma unroll
+        for (int p = 0; p < P / 4; ++p) loader<LT>::load8_fast(row, base + (p0 + p) * 512, v[p]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < P / 4; ++p) loader<LT>::load8(row, base + (p0 + p) * 512, V, vec, -INFINITY, v[p]);
+      }
+    };
+    float mx = -INFINITY, v[P / 4][8];
+    int ai = INT_MAX;
+    double sum = 0.0;
+    for (int p0 = 0; p0 < P; p0 += P / 4) {
+      quarter(p0, v);
+#pragma unroll
+      for (int p = 0; p < P / 4; ++p)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (T > 0.f) mx = fmaxf(mx, v[p][j]);
+          else if (v[p][j] > mx) { mx = v[p][j]; ai = base + (p0 + p) * 512 + j; }   // ids ascend: the first maximum stays
+        }
+    }
+    if (T > 0.f) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      if (mx > -INFINITY) {
+        const float k = (float)(kLog2e / (double)T);
+        for (int p0 = 0; p0 < P; p0 += P / 4) {
+          quarter(p0, v);
+#pragma unroll
+          for (int p = 0; p < P / 4; ++p) {
+            float part = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) part += __builtin_amdgcn_exp2f((v[p][j] - mx) * k);
+            sum += (double)part;
+          }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+      }
+    } else {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const float om = __shfl_xor(mx, o, 64);
+        const int oi = __shfl_xor(ai, o, 64);
+        if (om > mx || (om == mx && oi < ai)) { mx = om; ai = oi; }
+      }
+    }
+    if (lane == 0) { pm[c] = mx; ps[c] = sum; pa[c] = ai; }
+  }
+}
+
+// A top-k of this size takes one pass, which needs nothing from the row statistics (4 x top_k candidates are expected in the list).
+__device__ __host__ inline bool cut_takes_one_pass(int top_k, int V) { return top_k > 0 && top_k < V && 6l * top_k <= kCutList; }
+
+template <typename LT, bool STATS>
 __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logits, int V, int nc, const int32_t *__restrict__ off,
                                                      const float *__restrict__ temperature, const float *__restrict__ top_p,
-                                                     const int32_t *__restrict__ top_k, const float *__restrict__ pmax,
-                                                     const double *__restrict__ psum, uint32_t *__restrict__ nuc_key,
-                                                     double *__restrict__ nuc_S, int32_t *__restrict__ nuc_near,
-                                                     const int32_t *__restrict__ done, int B, int vec, int digits) {
+                                                     const int32_t *__restrict__ top_k, float *pmax, double *psum, int32_t *parg,
+                                                     uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
+                                                     int32_t *__restrict__ nuc_near, const int32_t *__restrict__ done, int B, int vec,
+                                                     int digits) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x;
   if (done && done[r] == 1) return;   // k_cut_window has settled this row
   int b = -1;   // the row's request: the last one whose first row, off[b] + b, is not beyond r (every wave by itself)
@@ -724,7 +787,9 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   const float T = temperature[b], tp = top_p ? top_p[b] : 1.f;
   const int tk = top_k ? top_k[b] : 0;
   const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
+  const LT *row = logits + (size_t)r * V;
   if (!use_k && !use_p) {
+    if (STATS) row_stats_by_block(row, V, nc, vec != 0, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
     if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; }
     return;
   }
@@ -735,26 +800,37 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   __shared__ cut_state st;
   uint32_t *hist = reinterpret_cast<uint32_t *>(s_raw);
   for (int i = tid; i < kCutBins; i += kCutThreads) hist[i] = 0u;
-  if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
-    float mx = -INFINITY;
-    for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    const double invT = 1.0 / (double)T;
-    double term = 0.0;
-    for (int c = lane; c < nc; c += 64) {
-      const float pm = pmax[(size_t)r * nc + c];
-      term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
+  if (tid == 0) { st.n = 0; st.found = 0; st.bad = 0; }
+  const bool one_pass = use_k && !digits && cut_takes_one_pass(tk, V) && whole_rounds<LT>(V, vec != 0) > 0;   // block-uniform
+  float m = 0.f;    // the row's maximum; the one-pass form: first that of its sample, then that of its list, which is the row's
+  double S = 0.0;
+  auto row_max = [&]() __attribute__((always_inline)) {
+    if (STATS) {
+      row_stats_by_block(row, V, nc, vec != 0, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
+      __syncthreads();
     }
+    if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
+      float mx = -INFINITY;
+      for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
-    if (lane == 0) { st.m = mx; st.S = term; st.n = 0; st.found = 0; st.bad = 0; }
-  }
-  __syncthreads();
-  const float m = st.m;
-  const double S = st.S;
+      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      const double invT = 1.0 / (double)T;
+      double term = 0.0;
+      for (int c = lane; c < nc; c += 64) {
+        const float pm = pmax[(size_t)r * nc + c];
+        term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
+      if (lane == 0) { st.m = mx; st.S = term; }
+    }
+    __syncthreads();
+    m = st.m;
+    S = st.S;
+  };
+  if (!one_pass) row_max();
+  else __syncthreads();
   const exp_scale k = make_exp_scale(kLog2e / (double)T);
-  const LT *row = logits + (size_t)r * V;
   // The bin of a token is a chain of correctly rounded, monotone steps, so that no token is filed above one with a larger
   // logit; -inf (and NaN, which leaves the fast way) ends in the last bin.
   auto bin_of = [&](float v) { return min((uint32_t)(fmaxf((v - m) * k.hi, -150.0f) * -kCutBinsPerLog2), (uint32_t)(kCutBins - 1)); };
@@ -766,7 +842,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   // for, the normaliser within 1e-6.
   const double slack = 0.5 * V + 2147483648.0 * 2e-6, room = (1.0 - (double)tp) * 2147483648.0 - 2.0 * slack;
   // a top-k beyond the list, or (top-p alone) no room between top_p and the whole for the sums' error: the general way at once
-  bool fast = !digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9 && (use_k ? tk <= kCutList : room > 6.0 * slack);   // block-uniform
+  bool fast = one_pass || (!digits && fabsf(m) < INFINITY && S >= 0.5 && S < 1e9 && (use_k ? tk <= kCutList : room > 6.0 * slack));   // block-uniform
 
   bool crowded = false;           // top-p alone, too many candidates for the list:
   uint32_t klo = 0u, khi = ~0u;   // the keys of the bins the cut can lie in
@@ -775,19 +851,18 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     double tot = 0.0;     // top-p alone: the row's mass as an integer sum (exact in a double: < 2^53 per thread)
     double above = 0.0;   // likewise the mass above the candidates
     bool bad = false;
-    const bool one_pass = use_k && whole_rounds<LT>(V, vec != 0) > 0 && 6l * tk <= kCutList;
     if (one_pass) {
-      // Once the bin that bounds the cut is known, a token is dismissed by comparing it with a value a little below that
-      // bin's lower edge (extra candidates do no harm): most groups of eight by one branch.
-      float vlim = -INFINITY;
+      // The bins are those of the sample's maximum (a token above it goes to the first).  Once the bin that bounds the cut is known, a
+      // token is dismissed by comparing it with a value a little below that bin's lower edge (extra candidates do no harm): most
+      // groups of eight by one branch.
+      float vlim = -INFINITY, mx = -INFINITY;
       bool sampled = false;
       over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
         if (!sampled) {   // block-uniform
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            bad |= !(v[j] <= m);
-            const uint32_t bin = bin_of(v[j]);
-            if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
+            bad |= v[j] != v[j];
+            mx = fmaxf(mx, v[j]);
           }
           return;
         }
@@ -797,13 +872,29 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         if (any) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            bad |= !(v[j] <= m);
+            bad |= v[j] != v[j];
             if (v[j] >= vlim) put(v[j]);
           }
         }
       }, [&](int round, const auto &v) {
         if (round != 0) return;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        if (lane == 0) st.w32[w] = __float_as_uint(mx);
         __syncthreads();
+        for (int i = 0; i < kCutThreads / 64; ++i) mx = fmaxf(mx, __uint_as_float(st.w32[i]));
+        m = mx;
+        bad |= !(fabsf(m) < INFINITY);
+        if (fabsf(m) < INFINITY) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const uint32_t bin = bin_of(v[u][j]);
+              if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
+            }
+        }
+        __syncthreads();   // (the bins are complete, and w32 has been read)
         cut_find_bins(hist, (uint32_t)tk, (uint32_t)tk, &st);
         const float depth = (float)(min(st.bin_lo, (uint32_t)(kCutBins - 2)) + 1) / (kCutBinsPerLog2 * k.hi);
         vlim = (m - depth * 1.00001f) - 5e-7f * (fabsf(m) + depth);
@@ -918,6 +1009,10 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
           }
         __syncthreads();
       }
+      if (one_pass) {   // the list begins with the row's maximum
+        m = okey_value(lkey[0]);
+        if (!(fabsf(m) < INFINITY)) fast = false;   // block-uniform
+      }
       // running mass up to and with each candidate, two consecutive ones per thread
       unsigned long long q[2], mle[2];
       uint32_t key[2];
@@ -969,7 +1064,12 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         if (last1 && key[1] == cut) st.kept = mle[1];
         __syncthreads();
       }
-      fast = st.found != 0;
+      fast = fast && st.found != 0;
+      if (STATS && fast && one_pass && tid < nc) {   // what k_decide takes from the statistics of a row that is cut: its maximum
+        pmax[(size_t)r * nc + tid] = tid == 0 ? m : -INFINITY;
+        psum[(size_t)r * nc + tid] = 0.0;
+        parg[(size_t)r * nc + tid] = INT_MAX;
+      }
       if (fast && tid == 0) {
         const double target = (double)tp * total;
         nuc_key[r] = use_p ? st.cut : st.kkey;
@@ -979,6 +1079,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     }
     if (fast) return;
     __syncthreads();   // the bins and the list make room for the passes below
+    if (one_pass) row_max();
   }
   uint32_t *hcnt = reinterpret_cast<uint32_t *>(s_raw + FSV_NUC_BINS);
   if (use_k) cut_narrow<LT, true>(row, V, vec != 0, m, k, 0u, ~0u, true, 0u, tk, tp, s_raw, hcnt, &st);
@@ -1360,25 +1461,36 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   int32_t *acc = r->accepted_len ? r->accepted_len : c->acc_scratch;
   int gmax = 0;
   for (int i = 0; i < B; ++i) gmax = max(gmax, b->draft_offsets_host[i + 1] - b->draft_offsets_host[i]);
-  {
+  // Top-k / top-p cut: only when some request asks for it.
+  bool any_k = false, any_p = false;
+  int one_pass_rows = 0, other_rows = 0;   // of the sampled requests: rows that k_cut settles without statistics, and others
+  for (int i = 0; i < B; ++i) {
+    const bool sampled = !b->temperature_host || b->temperature_host[i] > 0.f;
+    any_p |= sampled && b->top_p && b->top_p_host && b->top_p_host[i] < 1.f;
+    const int tk = sampled && b->top_k && b->top_k_host ? b->top_k_host[i] : 0;
+    any_k |= tk > 0 && tk < V;
+    const int rows = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i] + 1;
+    if (cut_takes_one_pass(tk, V)) one_pass_rows += rows; else if (sampled) other_rows += rows;
+  }
+  const bool nucleus = any_k || any_p;
+  // (FSV_NUCLEUS_FULL=1 in the environment narrows every row from the whole key range: a test compares the two)
+  const char *full_env = nucleus ? getenv("FSV_NUCLEUS_FULL") : nullptr;
+  const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
+  // fp32 logits, every sampled request with a top-k that takes k_cut one pass: the statistics are not needed and the rows are read
+  // once; k_cut makes those of the greedy rows among them.  Half of the rows may be greedy while there is a compute unit for every
+  // row, a third otherwise (a block per row streams at 3.3 TB/s, k_row_stats at 5.5).  Whole calls, V = 128256, top-k 50 and top-p 0.9: 204 rows
+  // 69.6 -> 51.2 us, 5 rows 39.5 -> 33.5, 576 rows 156 -> 116; every second request greedy: 192 rows 57.8 -> 45.1, 576 rows 115 (122 without
+  // the statistics); logits rounded to whole numbers, whose lists overflow: 192 rows 68 -> 53.
+  const bool skip_stats = sizeof(LT) == 4 && !digits && other_rows == 0 && one_pass_rows > 0 && (M <= 256 ? 2 * one_pass_rows >= M : 3 * one_pass_rows >= 2 * M) &&
+                          whole_rounds<LT>(V, lvec != 0) > 0 && nc <= kCutThreads;
+  if (!skip_stats) {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_STATS, (double)M * V * sizeof(LT));
     hipLaunchKernelGGL((k_row_stats<LT>), dim3(fsv_ceil_div(nc, 4), gmax + 1, B), dim3(256), 0, s, logits, V, nc,
                        b->draft_offsets, b->temperature, c->pmax, c->psum, c->parg, lvec, 0);
   }
-  // Top-k / top-p cut: only when some request asks for it.
-  bool any_k = false, any_p = false;
-  for (int i = 0; i < B; ++i) {
-    const bool sampled = !b->temperature_host || b->temperature_host[i] > 0.f;
-    any_p |= sampled && b->top_p && b->top_p_host && b->top_p_host[i] < 1.f;
-    any_k |= sampled && b->top_k && b->top_k_host && b->top_k_host[i] > 0 && b->top_k_host[i] < V;
-  }
-  const bool nucleus = any_k || any_p;
   if (nucleus) {
     // bytes: every row once, what no form can do without; how many passes a row takes is decided on the device
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_NUCLEUS, (double)M * V * sizeof(LT));
-    // (FSV_NUCLEUS_FULL=1 in the environment narrows every row from the whole key range: a test compares the two)
-    const char *full_env = getenv("FSV_NUCLEUS_FULL");
-    const int digits = (full_env && full_env[0] == '1') ? 1 : 0;
     // bf16 logits: the cuts lie within one or two binades of the maximum more often than not, which is one pass
     const bool window = sizeof(LT) == 2 && !digits;
 #define FSV_WINDOW(W, FIRST)                                                                                                           \
@@ -1389,8 +1501,16 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
       FSV_WINDOW(8, false);
     }
 #undef FSV_WINDOW
-    hipLaunchKernelGGL(k_cut<LT>, dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, c->pmax,
-                       c->psum, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, lvec, digits);
+#define FSV_CUT(ST)                                                                                                                      \
+  hipLaunchKernelGGL((k_cut<LT, ST>), dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, \
+                     c->pmax, c->psum, c->parg, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, lvec, digits)
+    if constexpr (sizeof(LT) == 4) {
+      if (skip_stats) FSV_CUT(true);
+      else FSV_CUT(false);
+    } else {
+      FSV_CUT(false);
+    }
+#undef FSV_CUT
   }
   {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_DECIDE, (double)B * V * (sizeof(LT) + 4));
