@@ -16,20 +16,20 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Work decomposition.  The keys of request b are cut into tiles of 32 (two pages); a "part" is a run of
 // tp_b consecutive tiles, s_b parts per request, chosen so that every part of every request has about the
-// same length and parts x kv heads comes to one block per compute unit.  A block owns its part completely: its eight
-// waves take every eighth tile each (each byte of the KV stream is read once; all `group` query heads and all gamma+1
+// same length and parts x kv heads comes to one block per compute unit (see plan_attention).  A block owns its part completely: its
+// waves (eight, or four) take every eighth (fourth) tile each (each byte of the KV stream is read once; all `group` query heads and all gamma+1
 // positions share it).  A wave streams the K and V page tiles of its keys straight from HBM into a ring of its own in LDS, forms
 // S^T = K Q^T (rows = keys, so a query row's scores sit in two lanes; the queries lie in LDS, shared by the waves), does the
 // online softmax in registers, and feeds the probabilities back as the B operand of O^T += V^T P^T without
 // any shuffle: the V tile is stored in the key order the score accumulators produce.  The waves' shares are merged through
 // LDS; a request with one part is then done, the others leave (m, l, O) per part and the block that comes last merges them.
 //
-// Why like this: bound by the KV stream where a request has one row tile per wave, by the softmax arithmetic (about 670 cycles of
+// Why like this: bound by the KV stream where a request has one row tile, by the softmax arithmetic (about 670 cycles of
 // it per 32 x 32 tile, which the exponentials and the split into hi + lo take) where it has two or three.  With two waves on a
 // SIMD one's arithmetic runs under the other's matrix products; the loads cost no registers and 64 .. 128 KiB per compute unit are on
 // their way.  One wave per SIMD with K and V in registers, one tile ahead, and the merge as a launch of its own (16 requests of
 // 512 .. 4096 positions, head size 128: 27.3 + 5.9 us; 128 requests of 256 .. 8192: 230 + 14; 2048 prefill rows 128 + 22; 8 requests
-// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 33.2, 239, 127, 38.  Measured and dropped: four waves per block with the
+// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 33.2, 207, 119, 38.  Measured and dropped: four waves per block with the
 // queries in registers (33, 249, 141, 46); two blocks per compute unit whose waves share the tiles, one row tile each, a barrier per
 // item (40, 249, 148, 54: a tile is a chain of 1.2 us and too few are in work); one block per compute unit that goes through the
 // requests of its share, the next one's keys on their way (39, 235, 177, 51: without the rings' place the merge takes 3.3 us a request).
@@ -54,10 +54,10 @@ __device__ __host__ inline int attn_parts(int n, int tpw, int w16, int nw, int *
 }
 
 // part_prefix[b] = parts of requests before b; part_desc[global part] = everything a wave of
-// the attention kernel needs to start, in one 96-byte record: request, first tile, tiles, parts of the request, cached
-// length, drafts, first row, first part of the request, and the physical pages of the part's first eight tiles -- a wave fetches it
-// with three scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
-constexpr int kDescInts = 24;
+// the attention kernel needs to start, in one 112-byte record: request, first tile, tiles, parts of the request, cached
+// length, drafts, first row, first part of the request, the physical pages of the part's first eight tiles, its number (records of a
+// schedule of several rounds are not in order) -- a wave fetches it with a few scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
+constexpr int kDescInts = 28;
 // Everything the forward's kernels look up about a call, in one launch: the attention schedule (block 0), for the stand-alone
 // attention the query operand (the last blocks; 6 us as a launch of its own, two bytes per lane), and for every row
 // its request, index, position and token and the cos / sin of its rotation angles (the other blocks; the angles depend on the
@@ -67,7 +67,7 @@ constexpr int kDescInts = 24;
 // takes 4.7 and 6.3.
 constexpr int kSetupThreads = 1024, kSetupB = 2048;   // requests whose prefix sums are kept in LDS (more are searched in memory)
 struct setup_args {
-  int B, tpw, nw, group, w2, w3, max_pages, num_pages, map_cap, M, half, V;
+  int B, tpw, nw, sorted, group, w2, w3, max_pages, num_pages, map_cap, M, half, V;
   const int32_t *seq_lens, *off, *page_table, *last_token, *draft;
   const double *inv_freq;
   int32_t *part_prefix, *part_desc, *row_req, *row_idx, *row_pos, *row_tok;
@@ -181,19 +181,55 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
   __syncthreads();   // the prefix sums are read back below by other threads of this block
   const int32_t *pre = B <= kSetupB ? s_pre : p.part_prefix;
   const int total = min(run, p.map_cap);
+  // In several rounds the long parts go first, so that the last round is made of short ones: the place of a part is the count of
+  // parts in longer classes (128 of them), then as it comes.  What a part computes does not depend on its place.
+  __shared__ int32_t s_class[128];
+  auto part = [&](int q, int &b, int &k, int &s, int &t0, int &cnt, int &L, int &gamma) {
+    b = find(pre, 0, q);
+    int n, tp;
+    s = parts_of(b, L, gamma, n, tp);
+    k = q - pre[b];
+    t0 = k * tp;
+    cnt = min(n, t0 + tp) - t0;
+  };
+  auto class_of = [&](int cnt) { return 127 - min(127, cnt * 128 / (p.tpw + p.nw)); };
+  if (p.sorted) {
+    if (tid < 128) s_class[tid] = 0;
+    __syncthreads();
+    for (int q = tid; q < total; q += kSetupThreads) {
+      int b, k, s, t0, cnt, L, gamma;
+      part(q, b, k, s, t0, cnt, L, gamma);
+      atomicAdd(&s_class[class_of(cnt)], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {
+      const int c0 = s_class[2 * tid], c1 = s_class[2 * tid + 1];
+      int incl = c0 + c1;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+      }
+      s_class[2 * tid] = incl - c0 - c1;
+      s_class[2 * tid + 1] = incl - c1;
+    }
+    __syncthreads();
+  }
   for (int q = tid; q < total; q += kSetupThreads) {
-    const int b = find(pre, 0, q);
-    int L, gamma, n, tp;
-    const int s = parts_of(b, L, gamma, n, tp), k = q - pre[b], t0 = k * tp, npg = (L + gamma + 1 + 15) >> 4;
+    int b, k, s, t0, cnt, L, gamma;
+    part(q, b, k, s, t0, cnt, L, gamma);
+    const int npg = (L + gamma + 1 + 15) >> 4;
     const int32_t *pt = p.page_table + (size_t)b * p.max_pages;
     int pg[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) pg[i] = min(max(pt[min(2 * t0 + i, npg - 1)], 0), p.num_pages - 1);
-    int4 *d = reinterpret_cast<int4 *>(p.part_desc + (size_t)q * kDescInts);
-    d[0] = make_int4(b, t0, min(n, t0 + tp) - t0, s);
+    const int at = p.sorted ? atomicAdd(&s_class[class_of(cnt)], 1) : q;
+    int4 *d = reinterpret_cast<int4 *>(p.part_desc + (size_t)at * kDescInts);
+    d[0] = make_int4(b, t0, cnt, s);
     d[1] = make_int4(L, gamma, p.off[b] + b, pre[b]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) d[2 + i] = make_int4(pg[4 * i], pg[4 * i + 1], pg[4 * i + 2], pg[4 * i + 3]);
+    d[6] = make_int4(q, 0, 0, 0);
   }
 }
 
@@ -239,7 +275,7 @@ template <int HD, int RT, int NW>
 struct attn_geo {
   static constexpr int KS = HD / 16, VC = HD / 32, TILEB = 16 * HD * 2;   // TILEB: bytes of one (page, kv head) tile
   static constexpr int ITEM = 2 * TILEB, LPI = ITEM / 1024;              // an item: K or V of a key tile (two pages); its loads
-  static constexpr int BUDGET = 160 * 1024;                              // one block per compute unit
+  static constexpr int BUDGET = ((RT == 3 && HD == 128) ? 8 : NW) * 20 * 1024;   // eight waves per compute unit
   static constexpr int QBYTES = RT * KS * 2048;                          // hi and lo planes of the query operand
   static constexpr int LOOK = (BUDGET - QBYTES) / (2 * NW * ITEM), SLOTS = 2 * LOOK;   // key tiles a wave's ring holds
   static constexpr int LDS = SLOTS * NW * ITEM + QBYTES;
@@ -249,7 +285,7 @@ struct attn_geo {
 };
 
 template <int HD, int RT, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attention(
+__global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_attention(
     int Hkv, int group, int rows_cap, const char *__restrict__ qp, size_t q_plane_bytes, const int32_t *__restrict__ part_desc,
     const int32_t *__restrict__ page_table, int max_pages, int num_pages,
     const char *__restrict__ kpool, const char *__restrict__ vpool, float *part_o, float *part_ml, int32_t *__restrict__ ticket,
@@ -264,6 +300,7 @@ __global__ __launch_bounds__(64 * NW) void k_attention(
   const int32_t *desc = part_desc + (size_t)pp * kDescInts;
   const int4 d0 = *reinterpret_cast<const int4 *>(desc), d1 = *reinterpret_cast<const int4 *>(desc + 4);
   const int2 d2 = *reinterpret_cast<const int2 *>(desc + 8 + 2 * w);
+  const int own = desc[24];
   const int b = d0.x, t0 = d0.y + w, nparts = d0.w, L = d1.x, gamma = d1.y, rs = d1.z;
   const int cnt = max(0, (d0.z - w + NW - 1) / NW), total = 2 * cnt;   // key tiles t0, t0 + NW, ... of this wave; items
   const int nk = L + gamma + 1, R = group * (gamma + 1);
@@ -458,6 +495,12 @@ __global__ __launch_bounds__(64 * NW) void k_attention(
       reinterpret_cast<uint4 *>(out)[tile_unit(m, col, KBq)] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
     }
   };
+  auto write_out4 = [&](int rr, int e0, float4 v, float inv) {
+    const uint32_t lo = f2h2(v.x * inv, v.y * inv), hi = f2h2(v.z * inv, v.w * inv);
+    const int i = (int)(((uint32_t)rr * group_inv) >> 16), m = rs + i, col = (kvh * group + rr - i * group) * HD + e0;
+    if (out32) store_row4(out32 + (size_t)m * KBq * 16 + col, lo, hi);
+    else *reinterpret_cast<uint2 *>(out + tile_unit(m, col & ~7, KBq) * 8 + (col & 4)) = make_uint2(lo, hi);
+  };
 #pragma unroll
   for (int rt0 = 0; rt0 < RT; rt0 += MS) {
     if (rt0 >= rtc) continue;
@@ -500,7 +543,7 @@ __global__ __launch_bounds__(64 * NW) void k_attention(
         write_out(rr, e0, acc, 1.0f / lsum);
       } else {
         // device-scope stores: written through to where every XCD sees them
-        const size_t prow = (size_t)gw * rows_cap + rr;
+        const size_t prow = ((size_t)own * Hkv + kvh) * rows_cap + rr;
         if (e0 == 0) store_dev(part_ml + prow * 2, mm, lsum);
 #pragma unroll
         for (int u = 0; u < 4; ++u) store_dev(part_o + prow * HD + e0 + 2 * u, acc[2 * u], acc[2 * u + 1]);
@@ -523,59 +566,54 @@ __global__ __launch_bounds__(64 * NW) void k_attention(
   if (tid == 0) __hip_atomic_store(tk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
   const size_t base = ((size_t)d1.w * Hkv + kvh) * rows_cap, pstr = (size_t)Hkv * rows_cap;   // d1.w: the request's first part
   // U parts of IT rows are fetched together (two features per access): the time is that of a round trip to memory and back
-  constexpr int U = 4, IT = 2;
-  for (int i0 = tid; i0 < R * TPR; i0 += IT * 64 * NW) {
-    float mm[IT], lsum[IT], acc[IT][8];
+  constexpr int U = 8, IT = 2, TPM = HD / 4;   // TPM: threads per row, four features each
+  for (int i0 = tid; i0 < R * TPM; i0 += IT * 64 * NW) {
+    float mm[IT], lsum[IT];
+    float4 acc[IT];
 #pragma unroll
     for (int x = 0; x < IT; ++x) {
       mm[x] = -INFINITY;
       lsum[x] = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[x][j] = 0.f;
+      acc[x] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     for (int s0 = 0; s0 < nparts; s0 += U) {
-      float2 ml[IT][U], v[IT][U][4];
+      float2 ml[IT][U], va[IT][U], vb[IT][U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (s0 + u >= nparts) continue;   // (uniform)
 #pragma unroll
         for (int x = 0; x < IT; ++x) {
           const int i = i0 + x * 64 * NW;
-          if (i >= R * TPR) continue;
-          const size_t prow = base + i / TPR + (s0 + u) * pstr;
+          if (i >= R * TPM) continue;
+          const size_t prow = base + i / TPM + (s0 + u) * pstr;
           ml[x][u] = load_dev(part_ml + prow * 2);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) v[x][u][j] = load_dev(part_o + prow * HD + (i % TPR) * 8 + 2 * j);
+          va[x][u] = load_dev(part_o + prow * HD + (i % TPM) * 4);
+          vb[x][u] = load_dev(part_o + prow * HD + (i % TPM) * 4 + 2);
         }
       }
 #pragma unroll
       for (int x = 0; x < IT; ++x) {
-        if (i0 + x * 64 * NW >= R * TPR) continue;
+        if (i0 + x * 64 * NW >= R * TPM) continue;
         const float mold = mm[x];
 #pragma unroll
         for (int u = 0; u < U; ++u)
           if (s0 + u < nparts) mm[x] = fmaxf(mm[x], ml[x][u].x);
         const float f0 = (mold == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(mold - mm[x]);
         lsum[x] *= f0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[x][j] *= f0;
+        acc[x] = make_float4(acc[x].x * f0, acc[x].y * f0, acc[x].z * f0, acc[x].w * f0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (s0 + u >= nparts) continue;
-          const float fu = (ml[x][u].y == 0.f) ? 0.f : __builtin_amdgcn_exp2f(ml[x][u].x - mm[x]);
-          lsum[x] += ml[x][u].y * fu;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            acc[x][2 * j] += v[x][u][j].x * fu;
-            acc[x][2 * j + 1] += v[x][u][j].y * fu;
-          }
+          const float f = (ml[x][u].y == 0.f) ? 0.f : __builtin_amdgcn_exp2f(ml[x][u].x - mm[x]);
+          lsum[x] += ml[x][u].y * f;
+          acc[x] = make_float4(acc[x].x + va[x][u].x * f, acc[x].y + va[x][u].y * f, acc[x].z + vb[x][u].x * f, acc[x].w + vb[x][u].y * f);
         }
       }
     }
 #pragma unroll
     for (int x = 0; x < IT; ++x) {
       const int i = i0 + x * 64 * NW;
-      if (i < R * TPR) write_out(i / TPR, (i % TPR) * 8, acc[x], 1.0f / lsum[x]);
+      if (i < R * TPM) write_out4(i / TPM, (i % TPM) * 4, acc[x], 1.0f / lsum[x]);
     }
   }
 }
@@ -597,12 +635,18 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
     pl->kv_tokens += nk;
   }
   pl->rt = fsv_ceil_div(max_rows, 32);
-  pl->nw = (d.head_dim == 128 && pl->rt > 2) ? 4 : 8;   // (eight waves' rings and three row tiles of queries exceed the LDS)
+  // Waves per block.  Eight, one block per compute unit, while requests are few: a part then takes an eighth of its tiles' time.  Four, two blocks per
+  // compute unit, from 192 (request, kv head) pairs on, so that a request need not be cut, and one block computes while the other
+  // starts or merges; where the queries leave room for it (not with head size 128 and more than one row tile).  Head size 64, whole call
+  // of the stand-alone entry: 8 requests of 2000 .. 6000 positions 24.8 us with eight, 28.6 with four; 24 of 200 .. 1000 16.6 and 16.6; 54 of 1000
+  // 36.8 and 28.5.  Three row tiles of head size 128: four waves, one block (eight waves' rings and the queries exceed the LDS).
+  const bool two_blocks = d.head_dim == 64 || pl->rt == 1, wide_q = d.head_dim == 128 && pl->rt > 2;
+  pl->nw = wide_q || (two_blocks && b->batch * d.n_kv_heads >= 192) ? 4 : 8;
   // One round if it can be had: the smallest part length, up to twice the even share, for which parts x kv heads fit the
-  // compute units.  Otherwise (many requests, or a few very long ones among many short ones) parts of half the
-  // even share, run in several rounds: blocks are independent, so the hardware keeps every unit busy and the last round
-  // is short.  Keeping whole requests as single parts instead would let the longest request set the kernel's time.
-  const int target = c->attn_wave_target;
+  // compute units.  Otherwise parts of up to five quarters of the even share in several rounds, the long ones first (a block costs 6 us besides
+  // its tiles, so few and long is right as long as the last round is short).  In the order of the requests, and in parts of half the share:
+  // 128 requests of 256 .. 8192 positions 240 us instead of 207, 2048 prefill rows 127 and 119.
+  const int target = c->attn_wave_target * (pl->nw == 4 && !wide_q ? 2 : 1);
   auto count = [&](int tpw) {
     int parts = 0;
     for (int i = 0; i < b->batch; ++i) {
@@ -617,7 +661,8 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   for (int t = even; t <= 2 * even; ++t) {
     if (count(t) <= target) { tpw = t; break; }
   }
-  if (!tpw) tpw = max(8, (even + 1) / 2);
+  pl->sorted = tpw == 0;
+  if (!tpw) tpw = max(8, even * 5 / 4);
   pl->tpw = tpw;
   pl->waves = count(tpw);
   if (pl->waves > c->attn_wave_cap) FSV_FAIL(c, FSV_E_CAPACITY, "%d attention parts > %d the workspace holds", pl->waves, c->attn_wave_cap);
@@ -628,7 +673,7 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
 
 int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, const void *q, hipStream_t st) {
   setup_args a;
-  a.B = b->batch; a.tpw = pl.tpw; a.nw = pl.nw; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
+  a.B = b->batch; a.tpw = pl.tpw; a.nw = pl.nw; a.sorted = pl.sorted; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
   a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.map_cap = c->attn_wave_cap / c->d.n_kv_heads + 1;
   a.M = M; a.half = rope ? c->d.head_dim / 2 : 1; a.V = c->d.vocab;   // without the angles: one thread per row
   a.seq_lens = b->seq_lens; a.off = b->draft_offsets; a.page_table = b->page_table;
@@ -664,13 +709,15 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
                         b->page_table, d.max_pages_per_req, b->num_pages, (const char *)kl, (const char *)vl, po, pml, c->attn_ticket, \
                         out, KBq, out32)
     if (d.head_dim == 128) {
-      if (pl.rt <= 1) FSV_ATTN_LAUNCH(128, 1, 8);
+      if (pl.rt <= 1) { if (pl.nw == 8) FSV_ATTN_LAUNCH(128, 1, 8); else FSV_ATTN_LAUNCH(128, 1, 4); }
       else if (pl.rt == 2) FSV_ATTN_LAUNCH(128, 2, 8);
       else FSV_ATTN_LAUNCH(128, 3, 4);
     } else {
-      if (pl.rt <= 1) FSV_ATTN_LAUNCH(64, 1, 8);
-      else if (pl.rt == 2) FSV_ATTN_LAUNCH(64, 2, 8);
-      else FSV_ATTN_LAUNCH(64, 3, 8);
+#define FSV_ATTN_NW(RTV) do { if (pl.nw == 8) FSV_ATTN_LAUNCH(64, RTV, 8); else FSV_ATTN_LAUNCH(64, RTV, 4); } while (0)
+      if (pl.rt <= 1) FSV_ATTN_NW(1);
+      else if (pl.rt == 2) FSV_ATTN_NW(2);
+      else FSV_ATTN_NW(3);
+#undef FSV_ATTN_NW
     }
 #undef FSV_ATTN_LAUNCH
     FSV_HIP(c, hipGetLastError());
@@ -712,7 +759,8 @@ int fsv_bf16_attn_create(fsv_ctx *c) {
   FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attention<HDV, RTV, NWV>),         \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (attn_geo<HDV, RTV, NWV>::LDS)))
   FSV_ATTN_ATTR(128, 1, 8); FSV_ATTN_ATTR(128, 2, 8); FSV_ATTN_ATTR(128, 3, 4);
-  FSV_ATTN_ATTR(64, 1, 8); FSV_ATTN_ATTR(64, 2, 8); FSV_ATTN_ATTR(64, 3, 8);
+  FSV_ATTN_ATTR(64, 1, 8); FSV_ATTN_ATTR(64, 2, 8); FSV_ATTN_ATTR(64, 3, 8); FSV_ATTN_ATTR(128, 1, 4);
+  FSV_ATTN_ATTR(64, 1, 4); FSV_ATTN_ATTR(64, 2, 4); FSV_ATTN_ATTR(64, 3, 4);
 #undef FSV_ATTN_ATTR
   if ((rc = zalloc((void **)&c->attn_ticket, sizeof(int32_t) * (size_t)d.max_batch * d.n_kv_heads))) return rc;
   if ((rc = zalloc(&c->attn_part, c->attn_part_bytes))) return rc;

@@ -96,12 +96,12 @@ struct fsv_ctx {
   void *attn_part = nullptr;    // per-part attention results (O, then (m, l)) of requests with several parts
   size_t attn_part_bytes = 0;
   int n_cus = 0;                // compute units of the device the context was created on
-  int attn_wave_target = 0;     // blocks the attention schedule aims at (one per compute unit)
+  int attn_wave_target = 0;     // compute units: blocks of eight waves the attention schedule aims at
   int attn_wave_cap = 0;        // blocks the partial buffers hold
   int32_t *attn_ticket = nullptr;  // [max_batch][kv heads] parts of a (request, kv head) that have left their results; zero between launches
   int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7
   int attn_w2 = 20, attn_w3 = 26;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
-  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 24-int record per part
+  int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 28-int record per part
 
   // LoRA adapters of the evolved target (bf16 path): tables [layer < n_layers - 1][adapter][...], library-owned
   int lora_n = 0, lora_rank = 0;
@@ -192,6 +192,7 @@ struct fsv_attn_plan {
   int waves = 0;        // parts x kv heads: blocks
   int rt = 1;           // query-row tiles of the widest request
   int nw = 8;           // waves per block
+  bool sorted = false;  // the parts run in several rounds, long ones first
   double kv_tokens = 0;
 };
 int fsv_bf16_attn_create(fsv_ctx *c);

@@ -19,11 +19,13 @@ pytestmark = pytest.mark.gpu
     ([511, 512, 1023, 1500, 20], [0, 16, 7, 8, 3]),                 # 16, 17, 32 tiles: two and more parts
     ([5000], [16]),                                                 # ten parts, three row tiles
     ([9000, 100, 4095], [1, 2, 7]),
+    ([40 + 37 * i for i in range(100)], [i % 2 for i in range(100)]),        # two kv heads: four waves per block, one round
+    ([3 + 61 * i % 997 for i in range(300)] + [7000], [7] * 300 + [1]),      # several rounds, long parts first
 ])
 def test_parts(name, seq_lens, gammas):
     cfg = synth.MODELS[name]
     L, gm, off, pt, npages, q, ks, vs = _attention_case(cfg, 8, seq_lens, gammas, "permuted")
-    fv, ctx, w, wn = _ctx(cfg, 4, max_batch=8, max_gamma=16, max_pages=pt.shape[1])
+    fv, ctx, w, wn = _ctx(cfg, 4, max_batch=len(L), max_gamma=16, max_pages=pt.shape[1])
     kp, vp = fv.alloc_pools(cfg, npages)
     kp.fill_(float("nan"))      # slots no position was written to
     vp.fill_(float("nan"))
