@@ -7,6 +7,7 @@ namespace fsv_bf16 {
 enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_F32 = 2 };
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // rows of a vocabulary that is no multiple of four
 
 // The barrier as an opaque statement: memory operations do not move across it, and no counter wait is attached.
 #define FSV_BARRIER() asm volatile("s_barrier" ::: "memory")
@@ -45,9 +46,9 @@ __device__ __forceinline__ void store_strip(f32x16_t (&acc)[MT], void *__restric
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int n0 = nt * 32 + 8 * g + 4 * h;
-          if (n0 + 3 < N && (N & 3) == 0) {
-            *reinterpret_cast<float4 *>(dst + n0) =
-                make_float4(acc[mt][4 * g], acc[mt][4 * g + 1], acc[mt][4 * g + 2], acc[mt][4 * g + 3]);
+          if (n0 + 3 < N) {
+            *reinterpret_cast<f32x4_any *>(dst + n0) =
+                (f32x4_any){acc[mt][4 * g], acc[mt][4 * g + 1], acc[mt][4 * g + 2], acc[mt][4 * g + 3]};
           } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r)

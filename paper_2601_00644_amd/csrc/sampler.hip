@@ -48,31 +48,30 @@ __device__ inline float exp_scaled(float d, exp_scale k) {
   return (z > -150.f) ? __builtin_amdgcn_exp2f(z) : 0.f;  // also catches -inf and NaN (a chunk that is all -inf)
 }
 
+// Sixteen bytes at a time from any row: a vocabulary that is no multiple of four or eight leaves the rows at 4- or 2-byte boundaries,
+// and a load of four dwords takes those as they come (one element per load instead: 576 rows x 50257 fp32, top-k 50, 267 us a call;
+// 75 like this, bf16 with top-p 0.9 157 and 77).
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 template <typename LT>
 struct loader;
 
 template <>
 struct loader<uint16_t> {  // bf16 bit patterns
-  // eight ids from a 16-byte aligned, fully in-range address: no bounds logic, so that a run of these loads is
+  // eight ids, all in range: no bounds logic, so that a run of these loads is
   // issued back to back (a branch per load makes the wave wait for each load before the next)
   static __device__ inline void load8_fast(const uint16_t *row, int i0, float (&v)[8]) {
-    uint4 raw = *reinterpret_cast<const uint4 *>(row + i0);
-    uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+    const u32x4_any w = *reinterpret_cast<const u32x4_any *>(row + i0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       v[2 * j] = __uint_as_float(w[j] << 16);
       v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
     }
   }
-  static __device__ inline void load8(const uint16_t *row, int i0, int V, bool vec, float fill, float (&v)[8]) {
-    if (vec && i0 + 8 <= V) {
-      uint4 raw = *reinterpret_cast<const uint4 *>(row + i0);
-      uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v[2 * j] = __uint_as_float(w[j] << 16);
-        v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-      }
+  static __device__ inline void load8(const uint16_t *row, int i0, int V, float fill, float (&v)[8]) {
+    if (i0 + 8 <= V) {
+      load8_fast(row, i0, v);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = (i0 + j < V) ? __uint_as_float((uint32_t)row[i0 + j] << 16) : fill;
@@ -83,17 +82,16 @@ struct loader<uint16_t> {  // bf16 bit patterns
 template <>
 struct loader<float> {
   static __device__ inline void load8_fast(const float *row, int i0, float (&v)[8]) {
-    float4 a = *reinterpret_cast<const float4 *>(row + i0);
-    float4 b = *reinterpret_cast<const float4 *>(row + i0 + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    const f32x4_any a = *reinterpret_cast<const f32x4_any *>(row + i0), b = *reinterpret_cast<const f32x4_any *>(row + i0 + 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = a[j];
+      v[4 + j] = b[j];
+    }
   }
-  static __device__ inline void load8(const float *row, int i0, int V, bool vec, float fill, float (&v)[8]) {
-    if (vec && i0 + 8 <= V) {
-      float4 a = *reinterpret_cast<const float4 *>(row + i0);
-      float4 b = *reinterpret_cast<const float4 *>(row + i0 + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-      v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  static __device__ inline void load8(const float *row, int i0, int V, float fill, float (&v)[8]) {
+    if (i0 + 8 <= V) {
+      load8_fast(row, i0, v);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = (i0 + j < V) ? row[i0 + j] : fill;
@@ -149,8 +147,7 @@ template <typename LT, bool LAW = false>
 __global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits, int V, int nc,
                                                    const int32_t *__restrict__ off,
                                                    const float *__restrict__ temperature, float *__restrict__ pmax,
-                                                   double *__restrict__ psum, int32_t *__restrict__ parg, int vec,
-                                                   int drafts_only = 0) {
+                                                   double *__restrict__ psum, int32_t *__restrict__ parg, int drafts_only = 0) {
   constexpr int P = FSV_CHUNK / 512;  // passes of 64 lanes x 8 ids
   const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.x * 4 + (tid >> 6), bq = blockIdx.z;
   if (c >= nc) return;
@@ -162,12 +159,12 @@ __global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits
   const float T = temperature[bq];
   float v[P][8];
   const int base = c * FSV_CHUNK + lane * 8;
-  if (vec && (c + 1) * FSV_CHUNK <= V) {  // wave-uniform: every chunk but a ragged last one
+  if ((c + 1) * FSV_CHUNK <= V) {  // wave-uniform: every chunk but a ragged last one
 #pragma unroll
     for (int p = 0; p < P; ++p) loader<LT>::load8_fast(row, base + p * 512, v[p]);
   } else {
 #pragma unroll
-    for (int p = 0; p < P; ++p) loader<LT>::load8(row, base + p * 512, V, vec != 0, -INFINITY, v[p]);
+    for (int p = 0; p < P; ++p) loader<LT>::load8(row, base + p * 512, V, -INFINITY, v[p]);
   }
   // A row needs either the argmax (greedy, T = 0) or the sum of exponentials (T > 0), never both; the vocabulary-wide
   // pass is bound by its arithmetic as soon as it carries more than a handful of operations per id.
@@ -233,7 +230,7 @@ __global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits
 constexpr int LAW_IDS = 4096;   // 256 threads x four loads of four ids
 __global__ __launch_bounds__(256) void k_draft_law(const float *__restrict__ z, int V, int nc, const int32_t *__restrict__ off,
                                                    const float *__restrict__ temperature, const float *__restrict__ pmax,
-                                                   const double *__restrict__ psum, int all_rows, float *__restrict__ q, int vec) {
+                                                   const double *__restrict__ psum, int all_rows, float *__restrict__ q) {
   const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.z, o = off[b], i = blockIdx.y;
   if (i > off[b + 1] - o - (all_rows ? 0 : 1)) return;
   const float T = temperature[b];
@@ -242,12 +239,13 @@ __global__ __launch_bounds__(256) void k_draft_law(const float *__restrict__ z, 
   const float *zr = z + (size_t)r * V;
   float *qr = q + (size_t)(all_rows ? r : o + i) * V;
   float v[4][4];
-  const bool fast = vec && (int)(blockIdx.x + 1) * LAW_IDS <= V;   // block-uniform
+  const bool fast = (int)(blockIdx.x + 1) * LAW_IDS <= V;   // block-uniform
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     if (fast) {
-      const float4 a = *reinterpret_cast<const float4 *>(zr + i0 + u * 1024);
-      v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
+      const f32x4_any a = *reinterpret_cast<const f32x4_any *>(zr + i0 + u * 1024);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[u][j] = a[j];
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[u][j] = (i0 + u * 1024 + j < V) ? zr[i0 + u * 1024 + j] : 0.f;
@@ -271,7 +269,7 @@ __global__ __launch_bounds__(256) void k_draft_law(const float *__restrict__ z, 
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[u][j] = __builtin_amdgcn_exp2f((v[u][j] - mx) * k) * inv;
     if (fast) {
-      *reinterpret_cast<float4 *>(qr + i0 + u * 1024) = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+      *reinterpret_cast<f32x4_any *>(qr + i0 + u * 1024) = (f32x4_any){v[u][0], v[u][1], v[u][2], v[u][3]};
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -320,12 +318,11 @@ struct cut_state {
 // thread are issued back to back, without a branch between them (a branch per load makes the wave wait for each load
 // before the next); the U loads of a round lie a U-th of the whole rounds apart, so that the first round is a sample of the
 // vocabulary.  after_round(r, values of the round) is met by every thread of the block after each whole round.
-template <typename LT>
-__device__ __host__ inline int whole_rounds(int V, bool vec) { return vec ? V / (4 * kCutThreads * 8) : 0; }
+__device__ __host__ inline int whole_rounds(int V) { return V / (4 * kCutThreads * 8); }
 template <typename LT, typename F, typename G>
-__device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, G &&after_round) {
+__device__ inline void over_row(const LT *row, int V, int tid, F &&f, G &&after_round) {
   constexpr int U = 4, STEP = kCutThreads * 8;
-  const int R = whole_rounds<LT>(V, vec);
+  const int R = whole_rounds(V);
   for (int r = 0; r < R; ++r) {
     const int base = r * STEP + tid * 8;
     float v[U][8];
@@ -337,7 +334,7 @@ __device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, 
   }
   for (int base = R * U * STEP + tid * 8; base < V; base += STEP) {
     float v[8];
-    loader<LT>::load8(row, base, V, vec, -INFINITY, v);
+    loader<LT>::load8(row, base, V, -INFINITY, v);
     f(base, v);
   }
 }
@@ -350,7 +347,7 @@ __device__ inline void over_row(const LT *row, int V, bool vec, int tid, F &&f, 
 // and highest key of each bin (in hcnt): tied tokens, and a bin of one token, need no further pass.
 // COUNT selects by count and leaves kkey / kmass; by mass, among the keys from lowkey on, leaves cut / kept / acc / total.
 template <typename LT, bool COUNT>
-__device__ inline bool cut_narrow(const LT *row, int V, bool vec, float m, exp_scale k, uint32_t lo, uint32_t hi, bool whole, uint32_t lowkey,
+__device__ inline bool cut_narrow(const LT *row, int V, float m, exp_scale k, uint32_t lo, uint32_t hi, bool whole, uint32_t lowkey,
                                   int tk, float tp, unsigned long long *hist, uint32_t *hcnt, cut_state *st) {
   constexpr int LAST = (sizeof(LT) == 2) ? 16 : 0;   // widest bin that holds one key
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -368,7 +365,7 @@ __device__ inline bool cut_narrow(const LT *row, int V, bool vec, float m, exp_s
     }
     __syncthreads();
     double above = 0.0;   // exact: a whole number below 2^53
-    over_row<LT>(row, V, vec, tid, [&](int i0, const float(&v)[8]) {
+    over_row<LT>(row, V, tid, [&](int i0, const float(&v)[8]) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         if (i0 + j >= V) continue;   // ids beyond the vocabulary are not tokens (they would count for top-k)
@@ -512,7 +509,7 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
                                                       const float *__restrict__ top_p, const int32_t *__restrict__ top_k,
                                                       const float *__restrict__ pmax, const double *__restrict__ psum,
                                                       uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
-                                                      int32_t *__restrict__ nuc_near, int32_t *__restrict__ done, int vec) {
+                                                      int32_t *__restrict__ nuc_near, int32_t *__restrict__ done) {
   constexpr int FB = 32;
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   if ((int)blockIdx.x > off[b + 1] - off[b]) return;
@@ -589,9 +586,9 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   constexpr int U = 4, STEP = 1024 * 8;
   // Most of the first round inside the window (logits far from zero, close together): a top-k that k_cut finds in one pass is
   // left to it.
-  const bool sample = FIRST && use_k && vec && V >= U * STEP && 6l * tk <= kCutList;
+  const bool sample = FIRST && use_k && V >= U * STEP && 6l * tk <= kCutList;
   int base = tid * 8;
-  if (vec) {
+  {
     for (; base + (U - 1) * STEP + 8 <= V; base += U * STEP) {
       float v[U][8];
 #pragma unroll
@@ -613,7 +610,7 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   }
   for (; base < V; base += STEP) {
     float v[8];
-    loader<uint16_t>::load8(row, base, V, vec != 0, -INFINITY, v);
+    loader<uint16_t>::load8(row, base, V, -INFINITY, v);
     add8(base, v, std::false_type{});
   }
   __syncthreads();
@@ -713,18 +710,18 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
 // What k_row_stats leaves for a row, by the waves of one block: the same chunks, the same sums in the same order, but a quarter of a
 // chunk's loads at a time and a second trip (from the cache) for the sums, so that it fits this kernel's registers.
 template <typename LT>
-__device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int V, int nc, bool vec, float T, float *pm, double *ps, int32_t *pa, int w, int lane) {
+__device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int V, int nc, float T, float *pm, double *ps, int32_t *pa, int w, int lane) {
   constexpr int P = FSV_CHUNK / 512;
   for (int c = w; c < nc; c += kCutThreads / 64) {
     const int base = c * FSV_CHUNK + lane * 8;
-    const bool whole = vec && (c + 1) * FSV_CHUNK <= V;   // wave-uniform
+    const bool whole = (c + 1) * FSV_CHUNK <= V;   // wave-uniform
     auto quarter = [&](int p0, float(&v)[P / 4][8]) {
       if (whole) {
 #pragma unroll
         for (int p = 0; p < P / 4; ++p) loader<LT>::load8_fast(row, base + (p0 + p) * 512, v[p]);
       } else {
 #pragma unroll
-        for (int p = 0; p < P / 4; ++p) loader<LT>::load8(row, base + (p0 + p) * 512, V, vec, -INFINITY, v[p]);
+        for (int p = 0; p < P / 4; ++p) loader<LT>::load8(row, base + (p0 + p) * 512, V, -INFINITY, v[p]);
       }
     };
     float mx = -INFINITY, v[P / 4][8];
@@ -778,8 +775,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
                                                      const float *__restrict__ temperature, const float *__restrict__ top_p,
                                                      const int32_t *__restrict__ top_k, float *pmax, double *psum, int32_t *parg,
                                                      uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
-                                                     int32_t *__restrict__ nuc_near, const int32_t *__restrict__ done, int B, int vec,
-                                                     int digits) {
+                                                     int32_t *__restrict__ nuc_near, const int32_t *__restrict__ done, int B, int digits) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x;
   if (done && done[r] == 1) return;   // k_cut_window has settled this row
   int b = -1;   // the row's request: the last one whose first row, off[b] + b, is not beyond r (every wave by itself)
@@ -789,7 +785,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   const bool use_k = T > 0.f && tk > 0 && tk < V, use_p = T > 0.f && tp < 1.f;
   const LT *row = logits + (size_t)r * V;
   if (!use_k && !use_p) {
-    if (STATS) row_stats_by_block(row, V, nc, vec != 0, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
+    if (STATS) row_stats_by_block(row, V, nc, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
     if (tid == 0) { nuc_key[r] = 0u; nuc_S[r] = -1.0; nuc_near[r] = 0; }
     return;
   }
@@ -801,12 +797,12 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
   uint32_t *hist = reinterpret_cast<uint32_t *>(s_raw);
   for (int i = tid; i < kCutBins; i += kCutThreads) hist[i] = 0u;
   if (tid == 0) { st.n = 0; st.found = 0; st.bad = 0; }
-  const bool one_pass = use_k && !digits && cut_takes_one_pass(tk, V) && whole_rounds<LT>(V, vec != 0) > 0;   // block-uniform
+  const bool one_pass = use_k && !digits && cut_takes_one_pass(tk, V) && whole_rounds(V) > 0;   // block-uniform
   float m = 0.f;    // the row's maximum; the one-pass form: first that of its sample, then that of its list, which is the row's
   double S = 0.0;
   auto row_max = [&]() __attribute__((always_inline)) {
     if (STATS) {
-      row_stats_by_block(row, V, nc, vec != 0, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
+      row_stats_by_block(row, V, nc, T, pmax + (size_t)r * nc, psum + (size_t)r * nc, parg + (size_t)r * nc, w, lane);
       __syncthreads();
     }
     if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
@@ -857,7 +853,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       // groups of eight by one branch.
       float vlim = -INFINITY, mx = -INFINITY;
       bool sampled = false;
-      over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+      over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
         if (!sampled) {   // block-uniform
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -912,7 +908,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       // ---- pass 1: bins ----
       const float scale = (float)(2147483648.0 / S), drop = (float)(0.9 * room / 2147483648.0 * S / V);
       if (use_k) {
-        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+        over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             bad |= !(v[j] <= m);
@@ -921,7 +917,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
           }
         }, [](int, const auto &) {});
       } else {   // (a NaN has made the normaliser one, or carries no mass)
-        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+        over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const float e = exp_scaled(v[j] - m, k);
@@ -947,7 +943,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       }
       // ---- pass 2: candidates, and the mass above them ----
       if (fast && !crowded)
-        over_row<LT>(row, V, vec != 0, tid, [&](int, const float(&v)[8]) {
+        over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const uint32_t bin = bin_of(v[j]);
@@ -1082,11 +1078,11 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
     if (one_pass) row_max();
   }
   uint32_t *hcnt = reinterpret_cast<uint32_t *>(s_raw + FSV_NUC_BINS);
-  if (use_k) cut_narrow<LT, true>(row, V, vec != 0, m, k, 0u, ~0u, true, 0u, tk, tp, s_raw, hcnt, &st);
+  if (use_k) cut_narrow<LT, true>(row, V, m, k, 0u, ~0u, true, 0u, tk, tp, s_raw, hcnt, &st);
   const uint32_t kkey = use_k ? st.kkey : 0u;
   if (use_p) {
     // (a second trip over the whole range if the interval the bins left does not hold the cut)
-    while (!cut_narrow<LT, false>(row, V, vec != 0, m, k, crowded ? klo : 0u, crowded ? khi : ~0u, !crowded, kkey, tk, tp, s_raw, hcnt, &st) &&
+    while (!cut_narrow<LT, false>(row, V, m, k, crowded ? klo : 0u, crowded ? khi : ~0u, !crowded, kkey, tk, tp, s_raw, hcnt, &st) &&
            crowded)
       crowded = false;
   }
@@ -1124,11 +1120,11 @@ __device__ inline double masses_of(const float (&lv)[8], const float (&qv)[8], f
 }
 
 template <typename LT>
-__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, bool lvec, bool qvec,
-                                       float m, exp_scale k, double invS, bool residual, uint32_t cutkey, double (&mass)[8]) {
+__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, float m, exp_scale k, double invS, bool residual, uint32_t cutkey,
+                                       double (&mass)[8]) {
   float lv[8], qv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  loader<LT>::load8(lrow, i0, V, lvec, -INFINITY, lv);
-  if (residual) loader<float>::load8(qrow, i0, V, qvec, 0.f, qv);
+  loader<LT>::load8(lrow, i0, V, -INFINITY, lv);
+  if (residual) loader<float>::load8(qrow, i0, V, 0.f, qv);
   return masses_of(lv, qv, m, k, invS, residual, cutkey, mass);
 }
 
@@ -1156,7 +1152,7 @@ __global__ __launch_bounds__(256) void k_decide(
     const double *__restrict__ nuc_S, const int32_t *__restrict__ nuc_near, double *__restrict__ bsum,
     int32_t *__restrict__ ticket, int32_t *__restrict__ accepted_len, int32_t *__restrict__ next_token,
     uint32_t *__restrict__ flags, const int32_t *__restrict__ seq_lens, int32_t *__restrict__ new_seq_lens,
-    int32_t *__restrict__ pages_released, int page_size, int lvec, int qvec) {
+    int32_t *__restrict__ pages_released, int page_size) {
   const int b = blockIdx.y, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int o = off[b], gamma_all = off[b + 1] - o, gamma = min(gamma_all, FSV_MAX_GAMMA), rs = o + b;
   const float T = temperature[b];
@@ -1285,7 +1281,7 @@ __global__ __launch_bounds__(256) void k_decide(
     if (sb < nsb) {
       constexpr int PARTS = FSV_SBK / 512;
       double tot = 0.0, mass[8];
-      if (lvec && qvec && (sb + 1) * FSV_SBK <= V) {   // wave-uniform; all loads of the sub-block before the first use
+      if ((sb + 1) * FSV_SBK <= V) {   // wave-uniform; all loads of the sub-block before the first use
         float lv[PARTS][8], qv[PARTS][8];
 #pragma unroll
         for (int part = 0; part < PARTS; ++part) loader<LT>::load8_fast(lrow, sb * FSV_SBK + part * 512 + lane * 8, lv[part]);
@@ -1298,7 +1294,7 @@ __global__ __launch_bounds__(256) void k_decide(
       } else {
 #pragma unroll 1
         for (int part = 0; part < PARTS; ++part)
-          tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, lvec != 0, qvec != 0, (float)m, k, invS,
+          tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, (float)m, k, invS,
                                    residual, cutkey, mass);
       }
 #pragma unroll
@@ -1381,7 +1377,7 @@ __global__ __launch_bounds__(256) void k_decide(
     qrow = nullptr;
     for (int sb = 0; sb < nsb; ++sb) {
       double mass[8], tot;
-      double t = thread_masses<LT>(lrow, qrow, sb * FSV_SBK + tid * 8, V, lvec != 0, qvec != 0, (float)m, k, invS,
+      double t = thread_masses<LT>(lrow, qrow, sb * FSV_SBK + tid * 8, V, (float)m, k, invS,
                                    false, cutkey, mass);
       block_incl_scan(t, s_w, &tot);
       if (tid == 0) s_sb[sb] = tot;
@@ -1395,7 +1391,7 @@ __global__ __launch_bounds__(256) void k_decide(
   const double lo = s_lo;
   double mass[8];
   const int i0 = sb * FSV_SBK + tid * 8;
-  double t = thread_masses<LT>(lrow, qrow, i0, V, lvec != 0, qvec != 0, (float)m, k, invS, residual, cutkey, mass);
+  double t = thread_masses<LT>(lrow, qrow, i0, V, (float)m, k, invS, residual, cutkey, mass);
   double incl = block_incl_scan(t, s_w, nullptr);
   // the first thread whose running mass crosses, and the last id with mass: a ballot per wave (LDS atomics of all 256 threads
   // on one address cost 3 us here).  Only a thread and an id that hold mass can be taken: lane sums, their scan and the sums
@@ -1455,9 +1451,6 @@ template <typename LT>
 int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv_result *r, int M, bool with_rollback,
                      hipStream_t s) {
   const int V = c->d.vocab, B = b->batch, nc = c->nc, nsb = c->nsb;
-  const int lalign = (sizeof(LT) == 2) ? 8 : 4;
-  const int lvec = (V % lalign == 0 && ((uintptr_t)logits % 16) == 0) ? 1 : 0;
-  const int qvec = (V % 4 == 0 && ((uintptr_t)b->draft_probs % 16) == 0) ? 1 : 0;
   int32_t *acc = r->accepted_len ? r->accepted_len : c->acc_scratch;
   int gmax = 0;
   for (int i = 0; i < B; ++i) gmax = max(gmax, b->draft_offsets_host[i + 1] - b->draft_offsets_host[i]);
@@ -1482,11 +1475,11 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   // 69.6 -> 51.2 us, 5 rows 39.5 -> 33.5, 576 rows 156 -> 116; every second request greedy: 192 rows 57.8 -> 45.1, 576 rows 115 (122 without
   // the statistics); logits rounded to whole numbers, whose lists overflow: 192 rows 68 -> 53.
   const bool skip_stats = sizeof(LT) == 4 && !digits && other_rows == 0 && one_pass_rows > 0 && (M <= 256 ? 2 * one_pass_rows >= M : 3 * one_pass_rows >= 2 * M) &&
-                          whole_rounds<LT>(V, lvec != 0) > 0 && nc <= kCutThreads;
+                          whole_rounds(V) > 0 && nc <= kCutThreads;
   if (!skip_stats) {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_STATS, (double)M * V * sizeof(LT));
     hipLaunchKernelGGL((k_row_stats<LT>), dim3(fsv_ceil_div(nc, 4), gmax + 1, B), dim3(256), 0, s, logits, V, nc,
-                       b->draft_offsets, b->temperature, c->pmax, c->psum, c->parg, lvec, 0);
+                       b->draft_offsets, b->temperature, c->pmax, c->psum, c->parg, 0);
   }
   if (nucleus) {
     // bytes: every row once, what no form can do without; how many passes a row takes is decided on the device
@@ -1495,7 +1488,7 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
     const bool window = sizeof(LT) == 2 && !digits;
 #define FSV_WINDOW(W, FIRST)                                                                                                           \
   hipLaunchKernelGGL((k_cut_window<W, FIRST>), dim3(gmax + 1, B), dim3(1024), 0, s, (const uint16_t *)logits, V, nc, b->draft_offsets, \
-                     b->temperature, b->top_p, b->top_k, c->pmax, c->psum, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, lvec)
+                     b->temperature, b->top_p, b->top_k, c->pmax, c->psum, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done)
     if (window) {
       FSV_WINDOW(4, true);
       FSV_WINDOW(8, false);
@@ -1503,7 +1496,7 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
 #undef FSV_WINDOW
 #define FSV_CUT(ST)                                                                                                                      \
   hipLaunchKernelGGL((k_cut<LT, ST>), dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, \
-                     c->pmax, c->psum, c->parg, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, lvec, digits)
+                     c->pmax, c->psum, c->parg, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, digits)
     if constexpr (sizeof(LT) == 4) {
       if (skip_stats) FSV_CUT(true);
       else FSV_CUT(false);
@@ -1519,7 +1512,7 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
                        nucleus ? c->nuc_key : nullptr, nucleus ? c->nuc_S : nullptr, nucleus ? c->nuc_near : nullptr, c->bsum,
                        c->sel_ticket, acc, r->next_token, r->flags, with_rollback ? b->seq_lens : nullptr,
                        with_rollback ? r->new_seq_lens : nullptr, with_rollback ? r->pages_released : nullptr,
-                       c->d.page_size, lvec, qvec);
+                       c->d.page_size);
   }
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
@@ -1549,12 +1542,10 @@ int fsv_launch_draft_law(fsv_ctx *c, const float *z, const fsv_batch *b, int all
   for (int i = 0; i < B; ++i) gmax = max(gmax, b->draft_offsets_host[i + 1] - b->draft_offsets_host[i]);
   const int rows = gmax + 1 - last;   // widest request
   if (rows < 1) return FSV_OK;
-  const int vec = (V % 4 == 0 && ((uintptr_t)z % 16) == 0 && ((uintptr_t)q % 16) == 0) ? 1 : 0;
-  const int lvec = (V % 4 == 0 && ((uintptr_t)z % 16) == 0) ? 1 : 0;
   hipLaunchKernelGGL((k_row_stats<float, true>), dim3(fsv_ceil_div(c->nc, 4), rows, B), dim3(256), 0, s, z, V, c->nc, b->draft_offsets,
-                     b->temperature, c->pmax, c->psum, c->parg, lvec, last);
+                     b->temperature, c->pmax, c->psum, c->parg, last);
   hipLaunchKernelGGL(k_draft_law, dim3(fsv_ceil_div(V, LAW_IDS), rows, B), dim3(256), 0, s, z, V, c->nc, b->draft_offsets,
-                     b->temperature, c->pmax, c->psum, all_rows, q, vec);
+                     b->temperature, c->pmax, c->psum, all_rows, q);
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
 }
