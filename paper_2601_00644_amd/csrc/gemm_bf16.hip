@@ -7,7 +7,7 @@
 // A block is up to four compute waves (the host picks two to four, so that the launch fills the compute units) and NLD
 // loader waves.  Compute wave w owns 32 output features (one weight
 // tile row) for up to MT*32 batch rows over the block's K range and streams that strip of the re-tiled
-// matrix straight from HBM into MFMA operand registers, D chunks of 128 k (D = 1) ahead of its use.  The loader waves
+// matrix straight from HBM into MFMA operand registers, D chunks of 128 k ahead of its use (weights_ahead).  The loader waves
 // copy the activation chunks of the same K range from global memory (L2) directly into a three-stage LDS
 // ring, two chunks ahead; the compute waves read their B operands from the ring.  Because the activation
 // loads are issued by a wave of their own, the compute waves' load counter tracks the weight stream only
@@ -197,13 +197,18 @@ __global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restric
   store_strip<MT, EPI, F16>(acc, out, nt, mt0, mtc, lane, h, split, M, Mpad, N, KBo, oscale);
 }
 
+// Weight chunks in flight per wave ahead of the one in use.  Measured on MI355X, one is best: with two to four the bytes in flight across
+// the chip approach the size of the L2s they pass through and the achieved bandwidth drops (8B shapes, 71 rows: gate|up 41.7 us, with two
+// 42.8, three 43.5; down 24.8, 25.5, 26.7).  The head with up to 32 rows is the exception: several of its small blocks share a compute
+// unit, their activations hardly compete with the stream, and it runs long enough (128256 x 2048, 5 rows: 87.5 us with one, 81.4 with two).
+template <int MT, int EPI>
+constexpr int weights_ahead = (EPI == EPI_F32 && MT == 1) ? 2 : 1;
+
 template <int MT, int EPI>
 int launch_t(fsv_ctx *c, int cls, dim3 grid, const void *Wp, uint32_t wbytes, const void *Ap, void *out, int N, int KB, int Mt,
              int M, int Mpad, int splits, int nchunks, int KBo, int NB, int mblocks, int f16, float oscale, int ncw, int NT,
              uint32_t strip_bytes, hipStream_t st) {
-  // Weight chunks in flight per wave ahead of the one in use.  Measured on MI355X, one is best: with two to four the
-  // bytes in flight across the chip approach the size of the L2s they pass through and the achieved bandwidth drops.
-  constexpr int D = 1;
+  constexpr int D = weights_ahead<MT, EPI>;
   const size_t ldsb = (size_t)NST * MT * KC * 64 * 16;   // fsv_bf16_gemm_init has raised the kernel's limit to this
   // the profiling events ride on the dispatch itself: they time the kernel, not the gaps around it
   fsv_prof_scope ps(c, st, cls, (double)N * KB * 32.0, true);
@@ -252,7 +257,7 @@ int launch_e(fsv_ctx *c, int cls, const void *Wp, const void *Ap, void *out, int
 template <int MT, int EPI>
 int init_t(fsv_ctx *c) {
 #define FSV_GEMM_ATTR(F16V, NCWV)                                                                          \
-  FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm<MT, EPI, 1, F16V, NCWV>),          \
+  FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm<MT, EPI, weights_ahead<MT, EPI>, F16V, NCWV>),          \
                                  hipFuncAttributeMaxDynamicSharedMemorySize, NST * MT * KC * 64 * 16))
   FSV_GEMM_ATTR(false, 4); FSV_GEMM_ATTR(false, 3); FSV_GEMM_ATTR(false, 2);
   FSV_GEMM_ATTR(true, 4); FSV_GEMM_ATTR(true, 3); FSV_GEMM_ATTR(true, 2);
