@@ -183,7 +183,6 @@ int fsv_verify(fsv_ctx *c, const fsv_batch *b, const fsv_result *r, void *stream
   fsv_attn_plan pl;
   int rc = (c->d.dtype == FSV_F32) ? fsv_f32_check(c, b) : fsv_bf16_attn_plan_host(c, b, &pl);
   if (rc) return rc;
-  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, b, M, s))) return rc;   // (the bf16 path sets its rows up itself)
   rc = (c->d.dtype == FSV_F32) ? fsv_f32_forward(c, b, M, logits, s) : fsv_bf16_forward(c, b, &pl, M, logits, 0, s);
   if (rc) return rc;
   return fsv_launch_sampler(c, logits, FSV_F32, b, r, M, true, s);
@@ -201,7 +200,6 @@ int fsv_prefill(fsv_ctx *c, const fsv_batch *b, float *logits_out, void *stream)
   fsv_attn_plan pl;
   int rc = (c->d.dtype == FSV_F32) ? fsv_f32_check(c, b) : fsv_bf16_attn_plan_host(c, b, &pl);
   if (rc) return rc;
-  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, b, M, s))) return rc;
   return (c->d.dtype == FSV_F32) ? fsv_f32_forward(c, b, M, logits, s) : fsv_bf16_forward(c, b, &pl, M, logits, 0, s);
 }
 

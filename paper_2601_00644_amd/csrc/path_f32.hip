@@ -14,10 +14,29 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-__global__ void k_embed(int d, const float *__restrict__ E, const int32_t *__restrict__ row_tok, float *__restrict__ x) {
-  const int r = blockIdx.x;
-  const float *src = E + (size_t)row_tok[r] * d;
+// The rows of a call, their embeddings and the cos, sin of their rotation angles (fp64 angles; the same in every layer), a block per row: its request is the last one whose first row, off[b] + b, is not beyond it
+// (every wave by itself, 64 requests at a time).  One launch instead of two: 2.2 + 2.4 -> 3.5 us for 5 rows, the angles included.
+__global__ void k_embed_rows(int B, int V, int d, const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ last_token,
+                             const int32_t *__restrict__ off, const int32_t *__restrict__ draft, const float *__restrict__ E,
+                             int32_t *__restrict__ row_req, int32_t *__restrict__ row_pos, float *__restrict__ x, int hd, double theta,
+                             float2 *__restrict__ tab) {
+  const int r = blockIdx.x, lane = threadIdx.x & 63;
+  int b = -1;
+  for (int b0 = 0; b0 < B; b0 += 64) b += __popcll(__ballot(b0 + lane < B && off[min(b0 + lane, B)] + b0 + lane <= r));
+  const int i = r - off[b] - b;
+  const int t = (i == 0) ? (last_token ? last_token[b] : 0) : (draft ? draft[r - b - 1] : 0);
+  const int pos = (seq_lens ? seq_lens[b] : 0) + i;
+  if (threadIdx.x == 0) {
+    row_req[r] = b;
+    row_pos[r] = pos;
+  }
+  const float *src = E + (size_t)min(max(t, 0), V - 1) * d;
   for (int k = threadIdx.x; k < d; k += blockDim.x) x[(size_t)r * d + k] = src[k];
+  const int half = hd / 2;
+  for (int f = threadIdx.x; f < half; f += blockDim.x) {
+    const double ang = (double)pos * pow(theta, -2.0 * (double)f / (double)hd);
+    tab[(size_t)r * half + f] = make_float2((float)cos(ang), (float)sin(ang));
+  }
 }
 
 // y[m][n] (+)= sum_k a[m][k] w[n][k]; one wave per output column and eight rows, lanes stride over k.
@@ -88,37 +107,74 @@ __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, 
   }
 }
 
-// Rotate q and k by their position (half-split pairing), write q to qbuf and k, v into the paged pools.
-__global__ void k_rope_append(int H, int Hkv, int hd, double theta, int num_pages, int max_pages,
-                              const float *__restrict__ qkv, const int32_t *__restrict__ row_req,
-                              const int32_t *__restrict__ row_pos, const int32_t *__restrict__ page_table,
-                              float *__restrict__ qbuf, float *__restrict__ kpool, float *__restrict__ vpool,
-                              size_t layer_off, int page_size) {
-  const int r = blockIdx.x, half = hd / 2, heads = H + 2 * Hkv;
-  const int pos = row_pos[r], b = row_req[r];
-  const float *src = qkv + (size_t)r * heads * hd;
-  // page ids live on the device: an id outside the pool is clamped into it (wrong data, never a wild write)
-  const int page = min(max(page_table[(size_t)b * max_pages + pos / page_size], 0), num_pages - 1), slot = pos % page_size;
-  for (int t = threadIdx.x; t < heads * half; t += blockDim.x) {
-    const int h = t / half, i = t % half;
-    const float a = src[h * hd + i], bb = src[h * hd + i + half];
-    if (h < H + Hkv) {
-      const double ang = (double)pos * pow(theta, -2.0 * (double)i / (double)hd);
-      const float cs = (float)cos(ang), sn = (float)sin(ang);
-      const float ra = a * cs - bb * sn, rb = a * sn + bb * cs;
-      if (h < H) {
-        qbuf[(size_t)r * H * hd + h * hd + i] = ra;
-        qbuf[(size_t)r * H * hd + h * hd + i + half] = rb;
-      } else {
-        float *dst = kpool + layer_off + (((size_t)page * Hkv + (h - H)) * page_size + slot) * hd;
-        dst[i] = ra;
-        dst[i + half] = rb;
+// q|k|v = norm(a) w^T, q and k rotated by their position (half-split pairing), q to qbuf and k, v into the paged pools: k_linear's
+// sums in k_linear's order, a wave per pair of features (i, i + hd / 2) and eight rows, so that the lane that ends up with both turns
+// and stores them.  A launch for the rotation took 4.1 us beside the projection's 3.7 (5 rows, with the angles in fp64 every time); this takes 4.9.
+template <int ROWS>
+__global__ __launch_bounds__(256) void k_qkv_rope(int M, int H, int Hkv, int hd, int K, float eps, const float2 *__restrict__ tab, int num_pages, int max_pages,
+                                                  const float *__restrict__ a, const float *__restrict__ g, const float *__restrict__ w,
+                                                  const int32_t *__restrict__ row_req, const int32_t *__restrict__ row_pos,
+                                                  const int32_t *__restrict__ page_table, float *__restrict__ qbuf, float *__restrict__ kpool,
+                                                  float *__restrict__ vpool, size_t layer_off, int page_size, int vec) {
+  const int pair = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, half = hd / 2;
+  if (pair >= (H + 2 * Hkv) * half) return;
+  const int h = pair / half, f = pair - h * half;
+  auto sums_of = [lane](float(&v)[ROWS]) {
+    if constexpr (ROWS == 1) return wave_sum(v[0]);
+    else return wave_sum8(v, lane);
+  };
+  const float *w0 = w + (size_t)(h * hd + f) * K, *w1 = w0 + (size_t)half * K;
+  for (int m0 = blockIdx.y * ROWS; m0 < M; m0 += gridDim.y * ROWS) {
+    const float *ar[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) ar[i] = a + (size_t)min(m0 + i, M - 1) * K;   // (rows beyond M repeat the last; not stored)
+    const int m = m0 + (ROWS == 1 ? 0 : ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1)), mc = min(m, M - 1);
+    const bool mine = !(lane & (ROWS == 1 ? 63 : 7)) && m < M;
+    const int pos = row_pos[mc], b = row_req[mc];
+    const float2 cs_sn = tab[(size_t)mc * half + f];
+    float lo[ROWS], hi[ROWS], ss[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) lo[i] = hi[i] = ss[i] = 0.f;
+    auto add = [&](int i, float av, float v0, float v1, float gv) {
+      const float x = av * gv;
+      lo[i] = fmaf(x, v0, lo[i]);
+      hi[i] = fmaf(x, v1, hi[i]);
+      ss[i] = fmaf(av, av, ss[i]);
+    };
+    if (vec) {
+      for (int k = lane * 4; k < K; k += 256) {
+        const float4 p4 = *reinterpret_cast<const float4 *>(w0 + k), q4 = *reinterpret_cast<const float4 *>(w1 + k);
+        const float4 g4 = *reinterpret_cast<const float4 *>(g + k);
+        float4 a4[ROWS];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) a4[i] = *reinterpret_cast<const float4 *>(ar[i] + k);
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+          add(i, a4[i].x, p4.x, q4.x, g4.x);
+          add(i, a4[i].y, p4.y, q4.y, g4.y);
+          add(i, a4[i].z, p4.z, q4.z, g4.z);
+          add(i, a4[i].w, p4.w, q4.w, g4.w);
+        }
       }
     } else {
-      float *dst = vpool + layer_off + (((size_t)page * Hkv + (h - H - Hkv)) * page_size + slot) * hd;
-      dst[i] = a;
-      dst[i + half] = bb;
+      for (int k = lane; k < K; k += 64) {
+        const float v0 = w0[k], v1 = w1[k], g1 = g[k];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) add(i, ar[i][k], v0, v1, g1);
+      }
     }
+    // page ids live on the device: an id outside the pool is clamped into it (wrong data, never a wild write)
+    const int page = min(max(page_table[(size_t)b * max_pages + pos / page_size], 0), num_pages - 1), slot = pos % page_size;
+    const float cs = cs_sn.x, sn = cs_sn.y;
+    const float s0 = sums_of(lo), s1 = sums_of(hi), rinv = 1.0f / sqrtf(sums_of(ss) / (float)K + eps);
+    if (!mine) continue;
+    const float x0 = s0 * rinv, x1 = s1 * rinv;
+    float *dst;
+    if (h < H) dst = qbuf + ((size_t)m * H + h) * hd;
+    else if (h < H + Hkv) dst = kpool + layer_off + (((size_t)page * Hkv + (h - H)) * page_size + slot) * hd;
+    else dst = vpool + layer_off + (((size_t)page * Hkv + (h - H - Hkv)) * page_size + slot) * hd;
+    dst[f] = h < H + Hkv ? x0 * cs - x1 * sn : x0;
+    dst[f + half] = h < H + Hkv ? x0 * sn + x1 * cs : x1;
   }
 }
 
@@ -343,8 +399,8 @@ int fsv_f32_create(fsv_ctx *c, const fsv_weights *w) {
     FSV_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_attention<ATT_WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)attention_lds(d, 16384)));
   const size_t R = c->max_rows;
-  FSV_HIP(c, hipMalloc(&c->buf_qkv, f * R * qkvd));
   FSV_HIP(c, hipMalloc(&c->buf_q, f * R * qd));
+  FSV_HIP(c, hipMalloc((void **)&c->rope_tab, f * R * d.head_dim));
   FSV_HIP(c, hipMalloc(&c->buf_att, f * R * qd));
   FSV_HIP(c, hipMalloc(&c->buf_act, f * R * d.d_ffn));
   return FSV_OK;
@@ -369,17 +425,25 @@ int fsv_f32_check(fsv_ctx *c, const fsv_batch *b) {
 int fsv_f32_forward(fsv_ctx *c, const fsv_batch *b, int M, float *logits, hipStream_t s) {
   const fsv_model_desc &d = c->d;
   const int qd = d.n_heads * d.head_dim, qkvd = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
-  float *x = c->x, *qkv = (float *)c->buf_qkv, *qb = (float *)c->buf_q;
+  float *x = c->x, *qb = (float *)c->buf_q;
   float *att = (float *)c->buf_att, *act = (float *)c->buf_act;
   const int keys = max_keys_of(b);   // fsv_f32_check has bounded it
-  hipLaunchKernelGGL(k_embed, dim3(M), dim3(256), 0, s, d.d_model, (const float *)c->embed, c->row_tok, x);
+  hipLaunchKernelGGL(k_embed_rows, dim3(M), dim3(256), 0, s, b->batch, d.vocab, d.d_model, b->seq_lens, b->last_token, b->draft_offsets,
+                     b->draft_tokens, (const float *)c->embed, c->row_req, c->row_pos, x, d.head_dim, (double)d.rope_theta, (float2 *)c->rope_tab);
   for (int l = 0; l < d.n_layers; ++l) {
     const fsv_layer_w &L = c->layers[l];
     const size_t lo = (size_t)l * layer_stride(c, b->num_pages);
-    launch_linear(M, qkvd, d.d_model, x, (const float *)L.w_qkv, qkv, 0, s, (const float *)L.attn_norm, d.rms_eps);
-    hipLaunchKernelGGL(k_rope_append, dim3(M), dim3(256), 0, s, d.n_heads, d.n_kv_heads, d.head_dim,
-                       (double)d.rope_theta, b->num_pages, d.max_pages_per_req, qkv, c->row_req, c->row_pos,
-                       b->page_table, qb, (float *)b->k_pool, (float *)b->v_pool, lo, d.page_size);
+    {
+      const int nb = fsv_ceil_div(qkvd / 2, 4), vec = (d.d_model % 4 == 0 && (((uintptr_t)x | (uintptr_t)L.w_qkv | (uintptr_t)L.attn_norm) % 16) == 0) ? 1 : 0;
+      const dim3 grid(nb, max(1, min(fsv_ceil_div(M, 8), 2048 / nb)));
+#define FSV_F32_QKV(R)                                                                                                               \
+  hipLaunchKernelGGL((k_qkv_rope<R>), grid, dim3(256), 0, s, M, d.n_heads, d.n_kv_heads, d.head_dim, d.d_model, d.rms_eps,              \
+                     (const float2 *)c->rope_tab, b->num_pages, d.max_pages_per_req, x, (const float *)L.attn_norm, (const float *)L.w_qkv,     \
+                     c->row_req, c->row_pos, b->page_table, qb, (float *)b->k_pool, (float *)b->v_pool, lo, d.page_size, vec)
+      if (M == 1) FSV_F32_QKV(1);
+      else FSV_F32_QKV(8);
+#undef FSV_F32_QKV
+    }
     launch_attention(d, c, b, M, keys, qb, lo, att, s);
     launch_linear(M, d.d_model, qd, att, (const float *)L.w_o, x, 1, s);
     launch_linear(M, d.d_ffn, d.d_model, x, (const float *)L.w_gate_up, act, 0, s, (const float *)L.mlp_norm, d.rms_eps, true);

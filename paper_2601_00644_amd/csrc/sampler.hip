@@ -163,8 +163,25 @@ __global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits
 #pragma unroll
     for (int p = 0; p < P; ++p) loader<LT>::load8_fast(row, base + p * 512, v[p]);
   } else {
+    // The ragged last chunk, with its loads issued together like the others': groups of eight beyond the row load its last eight ids
+    // instead and become -inf, and the group the row ends in (V no multiple of eight) is then loaded id by id.
+    if (V >= 8) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) loader<LT>::load8(row, base + p * 512, V, -INFINITY, v[p]);
+      for (int p = 0; p < P; ++p) loader<LT>::load8_fast(row, min(base + p * 512, V - 8), v[p]);
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[p][j] = (base + p * 512 + 8 <= V) ? v[p][j] : -INFINITY;
+    }
+    if (V < 8 || (V & 7)) {
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+        if (base + p * 512 < V && base + p * 512 + 8 > V) loader<LT>::load8(row, base + p * 512, V, -INFINITY, v[p]);
+        else if (V < 8) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[p][j] = -INFINITY;
+        }
+    }
   }
   // A row needs either the argmax (greedy, T = 0) or the sum of exponentials (T > 0), never both; the vocabulary-wide
   // pass is bound by its arithmetic as soon as it carries more than a handful of operations per id.
