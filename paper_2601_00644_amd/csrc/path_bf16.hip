@@ -569,9 +569,21 @@ __global__ void k_head_act(const float *__restrict__ part, int S, int Mpad, int 
     if (r < M) {
       float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       const float *p = part + (size_t)r * N + k0;
-      for (int s = 0; s < S; ++s) {
-        const float4 a = *reinterpret_cast<const float4 *>(p + (size_t)s * Mpad * N), b = *reinterpret_cast<const float4 *>(p + (size_t)s * Mpad * N + 4);
-        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w; v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+      const size_t sstr = (size_t)Mpad * N;
+      for (int s0 = 0; s0 < S; s0 += 8) {   // eight slices in flight; summed in slice order
+        float4 a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (s0 + u >= S) continue;   // (uniform)
+          a[u] = *reinterpret_cast<const float4 *>(p + (s0 + u) * sstr);
+          b[u] = *reinterpret_cast<const float4 *>(p + (s0 + u) * sstr + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (s0 + u >= S) continue;
+          v[0] += a[u].x; v[1] += a[u].y; v[2] += a[u].z; v[3] += a[u].w;
+          v[4] += b[u].x; v[5] += b[u].y; v[6] += b[u].z; v[7] += b[u].w;
+        }
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
