@@ -448,7 +448,11 @@ __global__ __launch_bounds__(256) void k_kv_copy(int Hkv, int num_pages, const i
 // ---------------------------------------------------------------------------------------------
 // rotary embedding + KV append; consumes the split partials of the QKV projection
 // ---------------------------------------------------------------------------------------------
-template <int LORA>
+// SPREAD: a value thread's eight features lie that far apart that the lanes of a wave are side by side.  A page holds the positions of one
+// value feature together, 16 bytes per eight positions, and with neighbouring features in one thread each of its two-byte stores goes
+// to 64 half lines: 2048 rows of 8B 28.8 -> 22.2 us, 1070 rows 20.3 -> 16.0.  The loads are single words then, so with more than two slices to
+// add it does not pay (71 rows, four slices 5.5 and 5.7 us; 1B, eight slices, 5 rows 4.1 and 6.7).
+template <int LORA, bool SPREAD>
 __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, const float *__restrict__ rope_tab,
                                                      const float *__restrict__ part, int S, int Mpad,
                                                      const int32_t *__restrict__ row_req,
@@ -467,18 +471,28 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
   const int item = blockIdx.y * blockDim.x + threadIdx.x;
   if (item >= heads * qpt) return;
   const int hh = item / qpt, i = (item % qpt) * 4;
-  const float *p = part + (size_t)r * qkvd + hh * hd + i;
+  const bool is_v = hh >= H + Hkv, spread = SPREAD && is_v;
+  // a spread thread's first feature (of all value heads) and the step to its next
+  const int vi = item - (H + Hkv) * qpt, vstep = Hkv * qpt;
+  const float *p = part + (size_t)r * qkvd + (spread ? (H + Hkv) * hd + vi : hh * hd + i);
   const size_t sstr = (size_t)Mpad * qkvd;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f), c = a;
+  auto load = [&](int s, float4 &pa, float4 &pc) {
+    const float *q = p + s * sstr;
+    if (spread) {
+      pa = make_float4(q[0], q[vstep], q[2 * vstep], q[3 * vstep]);
+      pc = make_float4(q[4 * vstep], q[5 * vstep], q[6 * vstep], q[7 * vstep]);
+    } else {
+      pa = *reinterpret_cast<const float4 *>(q);
+      pc = *reinterpret_cast<const float4 *>(q + half);
+    }
+  };
   {
     int s = 0;
     for (; s + 4 <= S; s += 4) {  // four slices in flight; summed in slice order
       float4 pa[4], pc[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        pa[u] = *reinterpret_cast<const float4 *>(p + (s + u) * sstr);
-        pc[u] = *reinterpret_cast<const float4 *>(p + (s + u) * sstr + half);
-      }
+      for (int u = 0; u < 4; ++u) load(s + u, pa[u], pc[u]);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         a.x += pa[u].x; a.y += pa[u].y; a.z += pa[u].z; a.w += pa[u].w;
@@ -486,7 +500,8 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
       }
     }
     for (; s < S; ++s) {
-      const float4 pa = *reinterpret_cast<const float4 *>(p + s * sstr), pc = *reinterpret_cast<const float4 *>(p + s * sstr + half);
+      float4 pa, pc;
+      load(s, pa, pc);
       a.x += pa.x; a.y += pa.y; a.z += pa.z; a.w += pa.w;
       c.x += pc.x; c.y += pc.y; c.z += pc.z; c.w += pc.w;
     }
@@ -499,11 +514,11 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
     const int ad = adapter[b];
     if (ad >= 0 && ad < n_adapters) {
       const float sc = lscale[ad];
-      const uint16_t *B = bq + ((size_t)ad * qkvd + hh * hd + i) * rank;
+      const uint16_t *B = bq + ((size_t)ad * qkvd + (spread ? (H + Hkv) * hd + vi : hh * hd + i)) * rank;
       const float *t = tq + (size_t)r * 64;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const uint16_t *brow = B + (size_t)((e < 4) ? e : (half + e - 4)) * rank;
+        const uint16_t *brow = B + (size_t)(spread ? e * vstep : (e < 4) ? e : (half + e - 4)) * rank;
         float acc = 0.f;
         for (int j = 0; j < rank; j += 8) {
           const uint4 raw = *reinterpret_cast<const uint4 *>(brow + j);
@@ -516,7 +531,7 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
       }
     }
   }
-  if (hh < H + Hkv) {
+  if (!is_v) {
     const float4 t0 = *reinterpret_cast<const float4 *>(rope_tab + ((size_t)r * half + i) * 2);      // cos, sin, cos, sin
     const float4 t1 = *reinterpret_cast<const float4 *>(rope_tab + ((size_t)r * half + i) * 2 + 4);
     const float cs[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
@@ -553,16 +568,17 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
     ab[j] = f2bf(av[j]);
     cb[j] = f2bf(cv[j]);
   }
-  if (hh < H + Hkv) {
+  if (!is_v) {
     uint16_t *tile = kpool + layer_off + ((size_t)page * Hkv + (hh - H)) * (16 * hd);
     *reinterpret_cast<uint2 *>(tile + k_tile_off(t, i)) = pack4(ab);          // four consecutive features sit together
     *reinterpret_cast<uint2 *>(tile + k_tile_off(t, i + half)) = pack4(cb);
   } else {
-    uint16_t *tile = vpool + layer_off + ((size_t)page * Hkv + (hh - H - Hkv)) * (16 * hd);
+    uint16_t *tiles = vpool + layer_off + (size_t)page * Hkv * (16 * hd);
+    const int lg = 31 - __builtin_clz(hd);   // 64 or 128
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      tile[v_tile_off(t, i + j)] = ab[j];
-      tile[v_tile_off(t, i + half + j)] = cb[j];
+    for (int e = 0; e < 8; ++e) {
+      const int f = spread ? vi + e * vstep : (hh - H - Hkv) * hd + i + (e < 4 ? e : half + e - 4);
+      tiles[(size_t)(f >> lg) * (16 * hd) + v_tile_off(t, f & (hd - 1))] = e < 4 ? ab[e & 3] : cb[e & 3];
     }
   }
 }
@@ -908,12 +924,14 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
 #define FSV_ROPE_ARGS d.n_heads, d.n_kv_heads, d.head_dim, (const float *)c->rope_tab, part, spq, Mpad, c->row_req, c->row_idx, \
                       c->row_pos, b->page_table, d.max_pages_per_req, b->num_pages, lo, (uint16_t *)c->buf_q,                  \
                       c->q_plane_units * 8, (uint16_t *)b->k_pool, (uint16_t *)b->v_pool
+      const bool spread = spq <= 2;
       if (adapted)
-        hipLaunchKernelGGL(k_rope_append<1>, rg, dim3(256), 0, s, FSV_ROPE_ARGS, b->adapter, c->lora_n, c->lora_rank,
-                           (const float *)c->lora_scale, c->lora_bq + (size_t)l * c->lora_n * qkvd * c->lora_rank,
-                           (const float *)c->lora_t);
+        hipLaunchKernelGGL((spread ? k_rope_append<1, true> : k_rope_append<1, false>), rg, dim3(256), 0, s, FSV_ROPE_ARGS, b->adapter,
+                           c->lora_n, c->lora_rank, (const float *)c->lora_scale,
+                           c->lora_bq + (size_t)l * c->lora_n * qkvd * c->lora_rank, (const float *)c->lora_t);
       else
-        hipLaunchKernelGGL(k_rope_append<0>, rg, dim3(256), 0, s, FSV_ROPE_ARGS, nullptr, 0, 0, nullptr, nullptr, nullptr);
+        hipLaunchKernelGGL((spread ? k_rope_append<0, true> : k_rope_append<0, false>), rg, dim3(256), 0, s, FSV_ROPE_ARGS, nullptr, 0, 0,
+                           nullptr, nullptr, nullptr);
 #undef FSV_ROPE_ARGS
     }
     if ((rc = fsv_bf16_attn_launch(c, b, &pl, lo, nullptr, s))) return rc;
