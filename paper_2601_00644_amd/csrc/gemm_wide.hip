@@ -12,21 +12,21 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Many rows (more than 256): the matrix cores are the bound
 // ---------------------------------------------------------------------------------------------
-// The weight-streaming kernel above stops at 0.36 of the matrix-core peak: its 128 x 128 block has to move 64 bytes per
-// clock into the compute unit to keep the matrix cores busy, all a unit can take.  Here a block is 256 features x 64 MT
-// rows (MT = 2, 3, 4: 128, 192, 256 rows), eight waves of 64 features x 32 MT rows, and both operands arrive through LDS:
-// half to three quarters of the bytes per product.  The contraction advances in stages of 32 (two k blocks); a ring of five or
-// six stages in LDS (140 .. 160 KiB, one block per compute unit) is filled by direct loads, every wave its share of every
-// stage, three to four stages ahead.  The operands being in the order the matrix cores take them, every load, LDS write and
-// LDS read is 1 KiB of consecutive 16-byte units: no bank conflicts, no address arithmetic.
-// Two waves share a SIMD; each interleaves one LDS read of the next k block and at most one load with every product, so the
-// issue slots of these fall into the products' shadow.  Operands of the next k block are read across the barrier: the
-// barrier before stage it certifies that stage it + 1 has landed, too.
-// Measured (fp16 operands, K = 4096, 28672 features): 2048 rows 552 -> 435 us (1.10 PFLOP/s), 1070 rows 292 -> 260 us
-// (0.97); 4096 features, K = 14336, bf16: 2048 rows 252 -> 205 us, 1070 rows 199 -> 130 us with two splits.  The library
-// GEMM takes 402 / 301 / 225 / 146 us for these four, 1.42 PFLOP/s for 8192^3.  What bounds it: the matrix cores are busy 62 %
-// of a full round and the clock falls to 1.9 GHz while they are (2.4 with half the units idle); the rest is the last,
-// partly filled round.  With the loop's tail under the same branch as its body, 2048 rows take 3 % longer.
+// The weight-streaming kernel stops at 0.36 of the matrix-core peak: its 128 x 128 block has to move 64 bytes per clock into the
+// compute unit to keep the matrix cores busy, all a unit can take.  Here a block is 256 features x 64 MT rows (MT = 2, 3, 4: 128,
+// 192, 256 rows) and both operands arrive through LDS: half to three quarters of the bytes per product.  The contraction advances in
+// stages of 32 (two k blocks); a ring of five or six stages in LDS (140 .. 160 KiB, one block per compute unit) is filled by direct
+// loads, every wave its share of every stage, three to four stages ahead.  The operands being in the order the matrix cores take them,
+// every load, LDS write and LDS read is 1 KiB of consecutive 16-byte units: no bank conflicts, no address arithmetic.
+// MT = 3, 4: four waves of 128 features x 32 MT rows, one to a SIMD, with their sums in the accumulation registers: 4 + MT operands
+// read from LDS for 4 MT products, where eight waves of 64 features read 2 + MT for 2 MT.  MT = 2 keeps eight waves
+// of 64 features x 64 rows, two to a SIMD.
+// A wave interleaves the LDS reads of the next k block and its loads with the products, so the issue slots of these fall into their
+// shadow.  Operands of the next k block are read across the barrier: the barrier before stage it certifies that stage it + 1 has
+// landed, too.
+// What bounds it is power: with every unit at work the clock falls from 2.36 to about 1.9 GHz.  2048 x 28672 x 4096: products alone 1.41
+// PFLOP/s, without the direct loads 1.30, without the LDS reads 1.20, whole 1.14.  Fewer LDS reads for a product therefore pay although
+// their slots are free: 192-row blocks 5 .. 7 % faster than with eight waves, 256-row blocks 0 .. 1 %; gate|up, 2048 rows 447 -> 427 us.
 // Direct global -> LDS load of 64 x 16 bytes: lane i of the wave fills the i-th 16-byte unit at LDS byte offset `dst`.  As
 // an opaque statement, because the compiler makes every later LDS read wait for all such loads it knows of; the waits below
 // are explicit.  (One wait state between writing M0 and the load that reads it.)
@@ -41,8 +41,6 @@ __device__ __forceinline__ void wait_loads() {
 
 constexpr int WSB = 2;      // 16-wide k blocks per stage
 constexpr int WSTRIPS = 8;  // weight strips per block: 256 features
-// MT = 3, 4: four waves of 128 features x 32 MT rows, one per SIMD, whose sums fill the accumulation registers; MT = 2: eight waves of
-// 64 x 64.
 template <int MT>
 struct wide_geo {
   static constexpr int NSW = MT >= 3 ? 4 : 2, WF = WSTRIPS / NSW, WR = 2, NW = WF * WR;   // strips per wave; waves along features and rows

@@ -676,12 +676,13 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
 // take.  A block's time is its stages (32 contraction elements) times the time of one plus kWideFixed for its first fills
 // and its result; a stage takes longer the more compute units are busy, because the matrix cores then lower the clock
 // (1.9 GHz with all of them at work against 2.4): base + slope x (busy share)^2, fitted to launches of 16 .. 256 blocks of
-// the 8B projections at 200 .. 2048 rows (4 tiles 0.53 .. 0.89 us, 3 tiles 0.40 .. 0.69, 2 tiles 0.32 .. 0.47).  Of the launches in
-// profiles/gemm_two_kernels_sweep.txt (three tile counts, five projections) 85 % lie within 10 % of it above 700 rows, two thirds
-// at 257 .. 700; the shortest launches run up to 60 % longer than expected.  Every split adds a set of
+// the 8B projections at 200 .. 2048 rows (4 tiles 0.53 .. 0.88 us, 3 tiles 0.39 .. 0.64, 2 tiles 0.32 .. 0.47).  Of the launches in
+// profiles/gemm_two_kernels_sweep.txt (three tile counts, five projections) 83 % lie within 10 % of it from 700 rows, a third
+// at 129 .. 512, where the shortest run up to 77 % longer than expected; from 320 rows the kernel taken is within 10 % of the best one but
+// once (q|k|v, 512 rows 38 and 33 us), at 257 rows q|k|v and down take 32 and 54 us where 27 and 45 would do.  Every split adds a set of
 // partial sums to write and read back at about 5 TB/s.
 // kWideTiles: row tiles from which on the many-row kernel is considered.  Below, the weight-streaming kernel is taken unseen; at
-// 129 .. 224 rows two row tiles would be faster where the matrix fills the chip (gate|up, 129 rows: 67 us and 57).
+// 129 .. 224 rows two row tiles would be faster where the matrix fills the chip (gate|up, 129 rows: 75 us and 70).
 constexpr int kWideTiles = 9;
 constexpr double kWideBase[5] = {0, 0, 0.32, 0.39, 0.53}, kWideSlope[5] = {0, 0, 0.15, 0.25, 0.35}, kWideFixed = 5.0;   // us
 // The weight-streaming kernel's blocks (128 features x 96 or 128 rows) by the same measure: less work per block, so a

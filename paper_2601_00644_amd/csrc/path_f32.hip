@@ -1,7 +1,7 @@
 // FSV_F32 instantiation of the target forward (Alg. 2 step 2: the target model scores the pending
 // token and the draft block on top of the restored KV session, Sec. IV-C).  This is the
-// correctness configuration (a tiny fp32 decoder): plain fp32 kernels, one launch per operation,
-// no matrix cores.  The bf16 path in path_bf16.hip is the one built for throughput.
+// correctness configuration (a tiny fp32 decoder): plain fp32 kernels, no matrix cores; norms, rotation,
+// KV append and SwiGLU are part of the projections' launches.  The bf16 path in path_bf16.hip is the one built for throughput.
 #include <math.h>
 
 #include "fsv_internal.h"
@@ -14,8 +14,8 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// The rows of a call, their embeddings and the cos, sin of their rotation angles (fp64 angles; the same in every layer), a block per row: its request is the last one whose first row, off[b] + b, is not beyond it
-// (every wave by itself, 64 requests at a time).  One launch instead of two: 2.2 + 2.4 -> 3.5 us for 5 rows, the angles included.
+// The rows of a call, their embeddings and the cos, sin of their rotation angles (fp64 angles; the same in every layer), a block per
+// row: its request is the last one whose first row, off[b] + b, is not beyond it (every wave by itself, 64 requests at a time).  One launch instead of two: 2.2 + 2.4 -> 3.5 us for 5 rows, the angles included.
 __global__ void k_embed_rows(int B, int V, int d, const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ last_token,
                              const int32_t *__restrict__ off, const int32_t *__restrict__ draft, const float *__restrict__ E,
                              int32_t *__restrict__ row_req, int32_t *__restrict__ row_pos, float *__restrict__ x, int hd, double theta,
