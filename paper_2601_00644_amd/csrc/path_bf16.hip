@@ -678,8 +678,9 @@ int pick_splits(const fsv_ctx *c, const gemm_shape &s, int Mt, bool allow, int n
 // (1.9 GHz with all of them at work against 2.4): base + slope x (busy share)^2, fitted to launches of 16 .. 256 blocks of
 // the 8B projections at 200 .. 2048 rows (4 tiles 0.53 .. 0.88 us, 3 tiles 0.39 .. 0.64, 2 tiles 0.32 .. 0.47).  Of the launches in
 // profiles/gemm_two_kernels_sweep.txt (three tile counts, five projections) 83 % lie within 10 % of it from 700 rows, a third
-// at 129 .. 512, where the shortest run up to 77 % longer than expected; from 320 rows the kernel taken is within 10 % of the best one but
-// once (q|k|v, 512 rows 38 and 33 us), at 257 rows q|k|v and down take 32 and 54 us where 27 and 45 would do.  Every split adds a set of
+// at 129 .. 512, where the shortest run up to 77 % longer than expected; from 320 rows the kernel taken is within 10 % of the fastest
+// one but once (q|k|v, 512 rows 38 and 33 us).  Where a slower one is taken, it writes fewer partial sums: 257 rows, q|k|v 32 us in one
+// split against 27 in three, down 54 in two against 45 in seven, each split 3 us of traffic for q|k|v and 2 for down.  Every split adds a set of
 // partial sums to write and read back at about 5 TB/s.
 // kWideTiles: row tiles from which on the many-row kernel is considered.  Below, the weight-streaming kernel is taken unseen; at
 // 129 .. 224 rows two row tiles would be faster where the matrix fills the chip (gate|up, 129 rows: 75 us and 70).
