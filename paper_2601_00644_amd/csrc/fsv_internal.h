@@ -89,7 +89,7 @@ struct fsv_ctx {
   int gemm_wide_force = -1;     // bf16 path: FSV_GEMM_WIDE, a measurement and test knob: 0 = never the many-row kernel, 2..4 = always, with that many row tiles per wave
   float os_lm_head = 1.0f;      // bf16 path: inverse of the power of two the fp16 LM-head matrix carries
   uint32_t *absmax = nullptr;   // bf16 path: one word for the largest weight magnitude of the matrix being converted
-  void *buf_a = nullptr, *buf_qkv = nullptr, *buf_q = nullptr, *buf_att = nullptr,
+  void *buf_a = nullptr, *buf_q = nullptr, *buf_att = nullptr,
        *buf_act = nullptr, *buf_part = nullptr;
   size_t part_bytes = 0;
   size_t q_plane_units = 0;     // 16-byte units of one plane of buf_q (bf16 path: plane 0 = hi, plane 1 = lo of the queries)
