@@ -553,9 +553,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   if (nparts == 1) return;
 
   // ---- several parts: the block that draws the last ticket of its (request, kv head) merges them, in part order ----
-  // The parts travel as device-scope accesses, which bypass the non-coherent caches by themselves; what is left to order is
-  // completion: every wave waits for its stores, the barrier collects the waves, and only then is the ticket drawn.
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  wait_own_stores();
   __syncthreads();
   int *const s_last = reinterpret_cast<int *>(lds);
   int32_t *const tk = ticket + (size_t)b * Hkv + kvh;

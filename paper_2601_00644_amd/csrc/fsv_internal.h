@@ -38,6 +38,13 @@ __device__ inline float wave_sum8(float (&v)[8], int lane) {
   return r;
 }
 
+// Waits until every store this wave has issued is complete (stores count in vmcnt here).  Between blocks of one launch results travel as
+// device-scope atomic stores and loads, which bypass the non-coherent caches by themselves; what is left to order is completion.
+// Every wave waits here, a barrier collects the waves of the block, and only then is the ticket drawn that tells the other blocks.
+// Neither the barrier nor a workgroup-scope release does this wait: outside threadgroup-split mode that release is a wait for lgkmcnt
+// alone.  (A device-scope release would also write back the XCD's whole L2 for every block.)
+__device__ __forceinline__ void wait_own_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 struct fsv_prof_rec {
   int cls;
   double bytes;

@@ -1,6 +1,6 @@
 """The attention kernel at the edges of its schedule: parts that end at and beside a multiple of eight key tiles, waves without a
-tile, requests of one to three query-row tiles in one call, as many parts as it takes several batches to merge, and the second
-launch after a merge (the tickets it leaves must be those it found)."""
+tile, requests of one to three query-row tiles in one call, as many parts as it takes several batches to merge, and the
+same launch again after one with other queries (the tickets a merge leaves must be those it found, and no partial result may be the other launch's)."""
 import numpy as np
 import pytest
 import torch
@@ -38,6 +38,7 @@ def test_parts(name, seq_lens, gammas):
                            ptd, kp, vp, npages, L, off)
     qd = q.cuda()
     first = ctx.attention(1, qd, batch)
+    assert not torch.equal(first, ctx.attention(0, -qd, batch))     # other queries: partial results that must not be met again
     assert torch.equal(first, ctx.attention(1, qd, batch))
     out = first.cpu().numpy().astype(np.float64)
     for b in range(len(L)):
