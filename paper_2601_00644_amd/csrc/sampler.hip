@@ -1324,12 +1324,9 @@ __global__ __launch_bounds__(256) void k_decide(
   }
 
   // ---- phase 3: the last block of the request selects the token ----
-  // The masses travel between blocks as device-scope atomics (stores above, loads below), which bypass the non-coherent
-  // caches by themselves; what is left to order is completion: every wave waits for its store (a workgroup-scope
-  // release is a plain wait on the memory counters), the barrier collects the four waves, and only then is the ticket
-  // drawn.  No device-wide fence: that would write back and invalidate the whole L2 of the XCD for every block (measured:
-  // 40 us on top of a 30 us kernel).
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  // The masses travel between blocks as device-scope atomics (stores above, loads below); no device-wide fence, which would write back
+  // and invalidate the whole L2 of the XCD for every block (measured: 40 us on top of a 30 us kernel).
+  wait_own_stores();
   __syncthreads();
   if (tid == 0)
     s_last = (__hip_atomic_fetch_add(&ticket[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) ? 1 : 0;

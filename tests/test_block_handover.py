@@ -34,7 +34,7 @@ def _kernels(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs ROCm's llvm-objdump")
-@pytest.mark.parametrize("kernel,instantiations", [("k_attention", 10)])
+@pytest.mark.parametrize("kernel,instantiations", [("k_attention", 10), ("k_decide", 2)])
 def test_stores_are_complete_before_the_ticket(tmp_path, kernel, instantiations):
     found = 0
     for name, code in _kernels(tmp_path).items():
