@@ -67,10 +67,10 @@ constexpr int kDescInts = 28;
 // takes 4.7 and 6.3.
 constexpr int kSetupThreads = 1024, kSetupB = 2048;   // requests whose prefix sums are kept in LDS (more are searched in memory)
 struct setup_args {
-  int B, tpw, nw, sorted, group, w2, w3, max_pages, num_pages, map_cap, M, half, V;
+  int B, tpw, nw, sorted, group, w2, w3, max_pages, num_pages, grid_parts, tickets, M, half, V;   // grid_parts: records the attention's grid reads
   const int32_t *seq_lens, *off, *page_table, *last_token, *draft;
   const double *inv_freq;
-  int32_t *part_prefix, *part_desc, *row_req, *row_idx, *row_pos, *row_tok;
+  int32_t *part_prefix, *part_desc, *ticket, *row_req, *row_idx, *row_pos, *row_tok;
   float *tab;
   // stand-alone attention: the caller's rotated queries [M][heads][hd] (bf16), to be put into the query operand
   int row_blocks = 0, H = 0, Hkv = 0, hd = 0, q_vec = 0;
@@ -180,7 +180,12 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
   }
   __syncthreads();   // the prefix sums are read back below by other threads of this block
   const int32_t *pre = B <= kSetupB ? s_pre : p.part_prefix;
-  const int total = min(run, p.map_cap);
+  // The grid comes from the host copies of the lengths, the parts from the device's.  Should a caller's two not agree, that call's
+  // result is not defined, but it stays within the grid, records without a part are empty, and every call begins with all tickets
+  // at zero, whatever the one before has left.
+  const int total = min(run, p.grid_parts);
+  for (int q = total + tid; q < p.grid_parts; q += kSetupThreads) *reinterpret_cast<int4 *>(p.part_desc + (size_t)q * kDescInts) = make_int4(0, 0, 0, 0);
+  for (int i = tid; i < p.tickets; i += kSetupThreads) p.ticket[i] = 0;
   // In several rounds the long parts go first, so that the last round is made of short ones: the place of a part is the count of
   // parts in longer classes (128 of them), then as it comes.  What a part computes does not depend on its place.
   __shared__ int32_t s_class[128];
@@ -301,6 +306,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   const int4 d0 = *reinterpret_cast<const int4 *>(desc), d1 = *reinterpret_cast<const int4 *>(desc + 4);
   const int2 d2 = *reinterpret_cast<const int2 *>(desc + 8 + 2 * w);
   const int own = desc[24];
+  if (d0.w == 0) return;   // no part
   const int b = d0.x, t0 = d0.y + w, nparts = d0.w, L = d1.x, gamma = d1.y, rs = d1.z;
   const int cnt = max(0, (d0.z - w + NW - 1) / NW), total = 2 * cnt;   // key tiles t0, t0 + NW, ... of this wave; items
   const int nk = L + gamma + 1, R = group * (gamma + 1);
@@ -561,7 +567,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   __syncthreads();
   if (!*s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  if (tid == 0) __hip_atomic_store(tk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+  if (tid == 0) __hip_atomic_store(tk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next layer's launch
   const size_t base = ((size_t)d1.w * Hkv + kvh) * rows_cap, pstr = (size_t)Hkv * rows_cap;   // d1.w: the request's first part
   // U parts of IT rows are fetched together (two features per access): the time is that of a round trip to memory and back
   constexpr int U = 8, IT = 2, TPM = HD / 4;   // TPM: threads per row, four features each
@@ -672,7 +678,8 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
 int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, const void *q, hipStream_t st) {
   setup_args a;
   a.B = b->batch; a.tpw = pl.tpw; a.nw = pl.nw; a.sorted = pl.sorted; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
-  a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.map_cap = c->attn_wave_cap / c->d.n_kv_heads + 1;
+  a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.grid_parts = pl.waves / c->d.n_kv_heads;
+  a.tickets = b->batch * c->d.n_kv_heads; a.ticket = c->attn_ticket;
   a.M = M; a.half = rope ? c->d.head_dim / 2 : 1; a.V = c->d.vocab;   // without the angles: one thread per row
   a.seq_lens = b->seq_lens; a.off = b->draft_offsets; a.page_table = b->page_table;
   a.last_token = b->last_token; a.draft = b->draft_tokens; a.inv_freq = (const double *)c->inv_freq;

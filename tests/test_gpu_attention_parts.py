@@ -23,6 +23,31 @@ pytestmark = pytest.mark.gpu
     ([3 + 61 * i % 997 for i in range(300)] + [7000], [7] * 300 + [1]),      # several rounds, long parts first
 ])
 def test_parts(name, seq_lens, gammas):
+    ctx, batch, qd, check = _session(name, seq_lens, gammas)
+    first = ctx.attention(1, qd, batch)
+    assert not torch.equal(first, ctx.attention(0, -qd, batch))     # other queries: partial results that must not be met again
+    assert torch.equal(first, ctx.attention(1, qd, batch))
+    check(first)
+    ctx.close()
+
+
+@pytest.mark.parametrize("name", ["mini64", "mini128"])
+def test_a_call_whose_lengths_disagree_spoils_no_later_one(name):
+    """The device's lengths are those of shorter sessions than the host copies say (all pages stay within the table): the grid is
+    larger than the schedule, the surplus blocks find empty records, and the next call is what it was."""
+    ctx, batch, qd, check = _session(name, [5000, 3000, 800], [16, 3, 7])
+    first = ctx.attention(1, qd, batch)
+    lens = batch.seq_lens
+    batch.seq_lens = torch.as_tensor(np.array([700, 300, 20], np.int32)).cuda()
+    ctx.attention(1, qd, batch)
+    batch.seq_lens = lens
+    again = ctx.attention(1, qd, batch)
+    assert torch.equal(first, again)
+    check(again)
+    ctx.close()
+
+
+def _session(name, seq_lens, gammas):
     cfg = synth.MODELS[name]
     L, gm, off, pt, npages, q, ks, vs = _attention_case(cfg, 8, seq_lens, gammas, "permuted")
     fv, ctx, w, wn = _ctx(cfg, 4, max_batch=len(L), max_gamma=16, max_pages=pt.shape[1])
@@ -36,15 +61,14 @@ def test_parts(name, seq_lens, gammas):
         ctx.kv_import(kp, vp, npages, ptd[b], 0, k, v)
     batch = fv.DeviceBatch(torch.as_tensor(L).cuda(), None, torch.as_tensor(off).cuda(), None, None, None, None, None,
                            ptd, kp, vp, npages, L, off)
-    qd = q.cuda()
-    first = ctx.attention(1, qd, batch)
-    assert not torch.equal(first, ctx.attention(0, -qd, batch))     # other queries: partial results that must not be met again
-    assert torch.equal(first, ctx.attention(1, qd, batch))
-    out = first.cpu().numpy().astype(np.float64)
-    for b in range(len(L)):
-        rs, n = int(off[b]) + b, int(gm[b]) + 1
-        ref = oracle.attention(q[rs:rs + n].float().numpy(), ks[b][0].float().numpy(), vs[b][0].float().numpy(), int(L[b]))
-        # the result is stored in fp16 (2^-11), its operands are exact to 2^-16
-        ok, ratio = logits_close(out[rs:rs + n], ref, 2e-3)
-        assert ok, (b, ratio)
-    ctx.close()
+
+    def check(first):
+        out = first.cpu().numpy().astype(np.float64)
+        for b in range(len(L)):
+            rs, n = int(off[b]) + b, int(gm[b]) + 1
+            ref = oracle.attention(q[rs:rs + n].float().numpy(), ks[b][0].float().numpy(), vs[b][0].float().numpy(), int(L[b]))
+            # the result is stored in fp16 (2^-11), its operands are exact to 2^-16
+            ok, ratio = logits_close(out[rs:rs + n], ref, 2e-3)
+            assert ok, (b, ratio)
+
+    return ctx, batch, q.cuda(), check
