@@ -1,6 +1,8 @@
 """The attention kernel at the edges of its schedule: parts that end at and beside a multiple of eight key tiles, waves without a
 tile, requests of one to three query-row tiles in one call, as many parts as it takes several batches to merge, and the
 same launch again after one with other queries (the tickets a merge leaves must be those it found, and no partial result may be the other launch's)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -44,6 +46,33 @@ def test_a_call_whose_lengths_disagree_spoils_no_later_one(name):
     again = ctx.attention(1, qd, batch)
     assert torch.equal(first, again)
     check(again)
+    ctx.close()
+
+
+def test_the_schedule_of_many_long_requests_is_quickly_made():
+    """300 requests of 32 k positions that all read the same pages: more (request, kv head) pairs than blocks, a length that no
+    search for one round can find.  A call returns to its caller in well under the 3 ms that trying every part length took."""
+    from paper_2601_00644_amd import flexverify as fv
+    cfg = synth.MODELS["mini64"]
+    B, L = 300, 32000
+    pages = (L + 1 + 15) // 16
+    _, ctx, w, wn = _ctx(cfg, 4, max_batch=B, max_gamma=1, max_pages=pages)
+    kp, vp = fv.alloc_pools(cfg, pages)
+    kp.zero_()
+    vp.fill_(1.0)
+    t = lambda a: torch.as_tensor(np.ascontiguousarray(a)).cuda()
+    lens, off = np.full(B, L, np.int32), np.zeros(B + 1, np.int32)
+    batch = fv.DeviceBatch(t(lens), None, t(off), None, None, None, None, None,
+                           t(np.tile(np.arange(pages, dtype=np.int32), (B, 1))), kp, vp, pages, lens, off)
+    q = torch.randn((B, cfg.n_heads, cfg.head_dim), generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).cuda()
+    took = []
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        out = ctx.attention(1, q, batch)
+        took.append(time.perf_counter() - t0)
+    assert (out == 1.0).all()       # every value is one
+    assert min(took) < 1e-3, took
     ctx.close()
 
 
