@@ -16,10 +16,10 @@ namespace {
 
 // ---------------------------------------------------------------------------------------------
 // Work decomposition.  The keys of request b are cut into tiles of 32 (two pages); a "part" is a run of
-// tp_b consecutive tiles, s_b parts per request, chosen so that every part of every request has about the
+// tp_b consecutive tiles, s_b runs per request, chosen so that every part of every request has about the
 // same length and parts x kv heads comes to one block per compute unit (see plan_attention).  A block owns its part completely: its
 // waves (eight, or four) take every eighth (fourth) tile each (each byte of the KV stream is read once; all `group` query heads and all gamma+1
-// positions share it).  A wave streams the K and V page tiles of its keys straight from HBM into a ring of its own in LDS, forms
+// positions share it, except in small calls, where every tile of 32 query rows has parts of its own).  A wave streams the K and V page tiles of its keys straight from HBM into a ring of its own in LDS, forms
 // S^T = K Q^T (rows = keys, so a query row's scores sit in two lanes; the queries lie in LDS, shared by the waves), does the
 // online softmax in registers, and feeds the probabilities back as the B operand of O^T += V^T P^T without
 // any shuffle: the V tile is stored in the key order the score accumulators produce.  The waves' shares are merged through
@@ -43,21 +43,23 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 // parts of a request with n key tiles when a part of a request with ONE query-row tile should hold about tpw tiles; *tp = tiles per
-// part (a multiple of the block's waves).  A key tile costs more when the request has more query rows (the score and value
+// part.  A key tile costs more when the request has more query rows (the score and value
 // products and the softmax arithmetic on the same K and V), so such a request is cut into shorter parts, by the
 // cost ratio w16 / 16: 16 requests, 512 .. 4096 positions, 1 .. 9 rows: 35 us with all tiles alike, 30.7 with 20 / 16 for two row tiles
-// and 26 / 16 for three, 31.5 with 26 / 16 and 36 / 16.
+// and 26 / 16 for three, 31.5 with 26 / 16 and 36 / 16.  As many parts as parts of whole rounds of the waves would be, but alike: 1909 ..
+// 2674 positions, 12 requests, 28.8 us a layer with parts of whole rounds, 27.3 like this.  Up to two tiles a wave are one part: two of half
+// of it take 2.0 us longer with one row tile (10 key tiles 11.3 and 9.3 us), 2.4 with two.
 __device__ __host__ inline int attn_parts(int n, int tpw, int w16, int nw, int *tp) {
-  tpw = max(1, tpw * 16 / w16);
-  const int s0 = (n + tpw - 1) / tpw;
-  *tp = ((n + s0 - 1) / s0 + nw - 1) / nw * nw;
-  return (n + *tp - 1) / *tp;
+  tpw = n <= 2 * nw ? n : max(1, tpw * 16 / w16);
+  const int s0 = (n + tpw - 1) / tpw, whole = ((n + s0 - 1) / s0 + nw - 1) / nw * nw, parts = (n + whole - 1) / whole;
+  *tp = (n + parts - 1) / parts;
+  return parts;
 }
 
 // part_prefix[b] = parts of requests before b; part_desc[global part] = everything a wave of
-// the attention kernel needs to start, in one 112-byte record: request, first tile, tiles, parts of the request, cached
-// length, drafts, first row, first part of the request, the physical pages of the part's first eight tiles, its number (records of a
-// schedule of several rounds are not in order) -- a wave fetches it with a few scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
+// the attention kernel needs to start, in one 112-byte record: request, first tile, tiles, parts of the same rows, cached
+// length, drafts, first row, first part of the same rows, the physical pages of the part's first eight tiles, its number (records of a
+// schedule of several rounds are not in order), its first query row, its query rows, the step to the next part of the same rows -- a wave fetches it with a few scalar loads and can issue its first K/V loads at once, instead of after a chain of dependent ones
 constexpr int kDescInts = 28;
 // Everything the forward's kernels look up about a call, in one launch: the attention schedule (block 0), for the stand-alone
 // attention the query operand (the last blocks; 6 us as a launch of its own, two bytes per lane), and for every row
@@ -68,7 +70,7 @@ constexpr int kDescInts = 28;
 // takes 4.7 and 6.3.
 constexpr int kSetupThreads = 1024, kSetupB = 2048;   // requests whose prefix sums are kept in LDS (more are searched in memory)
 struct setup_args {
-  int B, tpw, nw, sorted, group, w2, w3, max_pages, num_pages, grid_parts, tickets, M, half, V;   // grid_parts: records the attention's grid reads
+  int B, tpw, nw, sorted, split, group, w2, w3, max_pages, num_pages, grid_parts, tickets, M, half, V;   // grid_parts: records the attention's grid reads
   const int32_t *seq_lens, *off, *page_table, *last_token, *draft;
   const double *inv_freq;
   int32_t *part_prefix, *part_desc, *ticket, *row_req, *row_idx, *row_pos, *row_tok;
@@ -143,18 +145,19 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     return;
   }
   // ---- attention schedule ----
-  auto parts_of = [&](int b, int &L, int &gamma, int &n, int &tp) {
+  auto parts_of = [&](int b, int &L, int &gamma, int &n, int &tp, int &m) {   // key parts; m: row tiles with parts of their own
     L = p.seq_lens[b];
     gamma = p.off[b + 1] - p.off[b];
     n = (L + gamma + 1 + 31) >> 5;
     const int rtc = (p.group * (gamma + 1) + 31) >> 5;
-    return attn_parts(n, p.tpw, rtc <= 1 ? 16 : rtc == 2 ? p.w2 : p.w3, p.nw, &tp);
+    m = p.split ? rtc : 1;
+    return attn_parts(n, p.tpw, p.split || rtc <= 1 ? 16 : rtc == 2 ? p.w2 : p.w3, p.nw, &tp);
   };
   int run = 0;
   for (int b0 = 0; b0 < B; b0 += kSetupThreads) {
     const int b = b0 + tid;
-    int L, gamma, n, tp;
-    const int s = b < B ? parts_of(b, L, gamma, n, tp) : 0;
+    int L, gamma, n, tp, m;
+    const int s = b < B ? parts_of(b, L, gamma, n, tp, m) * m : 0;
     int incl = s;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -190,12 +193,12 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
   // In several rounds the long parts go first, so that the last round is made of short ones: the place of a part is the count of
   // parts in longer classes (128 of them), then as it comes.  What a part computes does not depend on its place.
   __shared__ int32_t s_class[128];
-  auto part = [&](int q, int &b, int &k, int &s, int &t0, int &cnt, int &L, int &gamma) {
+  auto part = [&](int q, int &b, int &k, int &s, int &t0, int &cnt, int &L, int &gamma, int &m) {   // k: number of the part, row tiles first
     b = find(pre, 0, q);
     int n, tp;
-    s = parts_of(b, L, gamma, n, tp);
+    s = parts_of(b, L, gamma, n, tp, m);
     k = q - pre[b];
-    t0 = k * tp;
+    t0 = k / m * tp;
     cnt = min(n, t0 + tp) - t0;
   };
   auto class_of = [&](int cnt) { return 127 - min(127, cnt * 128 / (p.tpw + p.nw)); };
@@ -203,8 +206,8 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     if (tid < 128) s_class[tid] = 0;
     __syncthreads();
     for (int q = tid; q < total; q += kSetupThreads) {
-      int b, k, s, t0, cnt, L, gamma;
-      part(q, b, k, s, t0, cnt, L, gamma);
+      int b, k, s, t0, cnt, L, gamma, m;
+      part(q, b, k, s, t0, cnt, L, gamma, m);
       atomicAdd(&s_class[class_of(cnt)], 1);
     }
     __syncthreads();
@@ -222,8 +225,8 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     __syncthreads();
   }
   for (int q = tid; q < total; q += kSetupThreads) {
-    int b, k, s, t0, cnt, L, gamma;
-    part(q, b, k, s, t0, cnt, L, gamma);
+    int b, k, s, t0, cnt, L, gamma, m;
+    part(q, b, k, s, t0, cnt, L, gamma, m);
     const int npg = (L + gamma + 1 + 15) >> 4;
     const int32_t *pt = p.page_table + (size_t)b * p.max_pages;
     int pg[16];
@@ -232,10 +235,11 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     const int at = p.sorted ? atomicAdd(&s_class[class_of(cnt)], 1) : q;
     int4 *d = reinterpret_cast<int4 *>(p.part_desc + (size_t)at * kDescInts);
     d[0] = make_int4(b, t0, cnt, s);
-    d[1] = make_int4(L, gamma, p.off[b] + b, pre[b]);
+    d[1] = make_int4(L, gamma, p.off[b] + b, pre[b] + k % m);
 #pragma unroll
     for (int i = 0; i < 4; ++i) d[2 + i] = make_int4(pg[4 * i], pg[4 * i + 1], pg[4 * i + 2], pg[4 * i + 3]);
-    d[6] = make_int4(q, 0, 0, 0);
+    const int R = p.group * (gamma + 1), rb = k % m * 32;
+    d[6] = make_int4(q, rb, m > 1 ? min(32, R - rb) : R, m);
   }
 }
 
@@ -306,11 +310,12 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   const int32_t *desc = part_desc + (size_t)pp * kDescInts;
   const int4 d0 = *reinterpret_cast<const int4 *>(desc), d1 = *reinterpret_cast<const int4 *>(desc + 4);
   const int2 d2 = *reinterpret_cast<const int2 *>(desc + 8 + 2 * w);
-  const int own = desc[24];
+  const int4 d6 = *reinterpret_cast<const int4 *>(desc + 24);
   if (d0.w == 0) return;   // no part
   const int b = d0.x, t0 = d0.y + w, nparts = d0.w, L = d1.x, gamma = d1.y, rs = d1.z;
   const int cnt = max(0, (d0.z - w + NW - 1) / NW), total = 2 * cnt;   // key tiles t0, t0 + NW, ... of this wave; items
-  const int nk = L + gamma + 1, R = group * (gamma + 1);
+  const int own = d6.x, rb = d6.y, R = d6.z, rt0 = rb >> 5;   // the query rows of this part: rb .. rb + R - 1
+  const int nk = L + gamma + 1;
   const int rtc = min(RT, (R + 31) >> 5);
   const int32_t *pt = page_table + (size_t)b * max_pages;
   const int npg = (nk + 15) >> 4;
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   for (int i = 0; i < (RT * KS * 2 + NW - 1) / NW; ++i) {
     const int c = i * NW + w, rt = c / (2 * KS), ks = (c / 2) % KS;   // row c = (rt * KS + ks) * 2 + plane
     if (rt >= rtc) break;
-    const char *src = qp + (size_t)(c & 1) * q_plane_bytes + ((((size_t)b * RTMAX + rt) * Hkv + kvh) * KS + ks) * 1024;
+    const char *src = qp + (size_t)(c & 1) * q_plane_bytes + ((((size_t)b * RTMAX + rt0 + rt) * Hkv + kvh) * KS + ks) * 1024;
     load_to_lds<false>(lds0 + SLOTS * NW * ITEM + c * 1024, lane_off, src);
   }
   int2 pg = d2;   // pages of the next tile to be loaded
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
     mrun[rt] = -INFINITY;
     lrun[rt] = 0.f;
     const int rr = rt * 32 + r;
-    lim[rt] = (rr < R) ? L + rr / group : -1;
+    lim[rt] = (rr < R) ? L + (rb + rr) / group : -1;
   }
   // K operand row = key r (rows 0-15 first page, 16-31 second page); V operand row = feature
   const char *const kl = ldsc + w * SLOTS * ITEM + (r >> 4) * TILEB + (h * 16 + (r & 15)) * 16;
@@ -492,6 +497,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
     uint32_t pk[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) pk[j] = f2h2(acc[2 * j] * inv, acc[2 * j + 1] * inv);
+    rr += rb;
     const int i = (int)(((uint32_t)rr * group_inv) >> 16);   // rr / group (rr < 96: the product is exact)
     const int m = rs + i, col = (kvh * group + rr - i * group) * HD + e0;
     if (out32) {
@@ -503,20 +509,21 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
     }
   };
   auto write_out4 = [&](int rr, int e0, float4 v, float inv) {
+    rr += rb;
     const uint32_t lo = f2h2(v.x * inv, v.y * inv), hi = f2h2(v.z * inv, v.w * inv);
     const int i = (int)(((uint32_t)rr * group_inv) >> 16), m = rs + i, col = (kvh * group + rr - i * group) * HD + e0;
     if (out32) store_row4(out32 + (size_t)m * KBq * 16 + col, lo, hi);
     else *reinterpret_cast<uint2 *>(out + tile_unit(m, col & ~7, KBq) * 8 + (col & 4)) = make_uint2(lo, hi);
   };
 #pragma unroll
-  for (int rt0 = 0; rt0 < RT; rt0 += MS) {
-    if (rt0 >= rtc) continue;
+  for (int m0 = 0; m0 < RT; m0 += MS) {
+    if (m0 >= rtc) continue;
     __syncthreads();   // the rings, or the tiles before, have been read
 #pragma unroll
-    for (int rt = rt0; rt < RT && rt < rt0 + MS; ++rt) {
+    for (int rt = m0; rt < RT && rt < m0 + MS; ++rt) {
       if (rt >= rtc) continue;
       const float ll = lrun[rt] + __shfl_xor(lrun[rt], 32, 64);
-      const int at = (w * MS + rt - rt0) * 32 + r;
+      const int at = (w * MS + rt - m0) * 32 + r;
       float *dst = area + at * OROW + 4 * h;
 #pragma unroll
       for (int c = 0; c < VC; ++c)
@@ -527,9 +534,9 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
       if (h == 0) s_ml[at] = make_float2(mrun[rt], ll);
     }
     __syncthreads();
-    const int rows = min(MS * 32, R - rt0 * 32);
+    const int rows = min(MS * 32, R - m0 * 32);
     for (int it = tid; it < rows * TPR; it += 64 * NW) {
-      const int row = it / TPR, e0 = (it % TPR) * 8, rr = rt0 * 32 + row;
+      const int row = it / TPR, e0 = (it % TPR) * 8, rr = m0 * 32 + row;
       float2 ml[NW];
       float mm = -INFINITY, lsum = 0.f, acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -559,17 +566,17 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
   }
   if (nparts == 1) return;
 
-  // ---- several parts: the block that draws the last ticket of its (request, kv head) merges them, in part order ----
+  // ---- several parts: the block that draws the last ticket of its (request, kv head, rows) merges them, in part order ----
   wait_own_stores();
   __syncthreads();
   int *const s_last = reinterpret_cast<int *>(lds);
-  int32_t *const tk = ticket + (size_t)b * Hkv + kvh;
+  int32_t *const tk = ticket + ((size_t)b * RTMAX + rt0) * Hkv + kvh;
   if (tid == 0) *s_last = (__hip_atomic_fetch_add(tk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nparts - 1) ? 1 : 0;
   __syncthreads();
   if (!*s_last) return;
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   if (tid == 0) __hip_atomic_store(tk, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next layer's launch
-  const size_t base = ((size_t)d1.w * Hkv + kvh) * rows_cap, pstr = (size_t)Hkv * rows_cap;   // d1.w: the request's first part
+  const size_t base = ((size_t)d1.w * Hkv + kvh) * rows_cap, pstr = (size_t)d6.w * Hkv * rows_cap;   // d1.w: the first part of these rows
   // U parts of IT rows are fetched together (two features per access): the time is that of a round trip to memory and back
   constexpr int U = 8, IT = 2, TPM = HD / 4;   // TPM: threads per row, four features each
   for (int i0 = tid; i0 < R * TPM; i0 += IT * 64 * NW) {
@@ -626,20 +633,31 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
 // Size the parts from the host copies of the lengths.
 int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   const fsv_model_desc &d = c->d;
-  int max_rows = 0;
-  long total_tiles = 0;   // in units of the cost of a tile of a request with one query-row tile
+  int max_rows = 0, longest = 0;
+  long total_tiles = 0, row_tiles = 0, items = 0;   // total: in units of the cost of a tile of a request with one query-row tile
+  auto rtc_of = [&](int g) { return fsv_ceil_div(c->group * (g + 1), 32); };
   auto w16_of = [&](int g) {
-    const int rtc = fsv_ceil_div(c->group * (g + 1), 32);
-    return rtc <= 1 ? 16 : rtc == 2 ? c->attn_w2 : c->attn_w3;
+    const int rtc = rtc_of(g);
+    return pl->split || rtc <= 1 ? 16 : rtc == 2 ? c->attn_w2 : c->attn_w3;
   };
   for (int i = 0; i < b->batch; ++i) {
     const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
     const int n = fsv_ceil_div(nk, 32);
     max_rows = max(max_rows, c->group * (g + 1));
+    longest = max(longest, n);
     total_tiles += ((long)n * w16_of(g) + 15) / 16;
+    row_tiles += rtc_of(g);
+    items += (long)n * rtc_of(g);
     pl->kv_tokens += nk;
   }
-  pl->rt = fsv_ceil_div(max_rows, 32);
+  // Row tiles as parts of their own, which read the same keys (neighbouring blocks, on one XCD with eight kv heads), while they leave a wave at most
+  // four (row tile, key tile) pairs: every block then has the short chain of one row tile, and a request's merge is spread over as many
+  // blocks.  Beyond, the row tiles of a request share the keys they read.  Calls of the stand-alone entry in a graph, head size 128, eight kv
+  // heads, shared and split: one request of 1600 positions, two row tiles 23.5 and 18.2 us, three 32.4 and 18.3; 16 of 800 .. 1600, two
+  // 34.2 and 28.4; past the line 16 of 1600 .. 3200 43.4 and 45.9, 48 of 800 .. 1600 55.1 and 57.9.
+  pl->split = max_rows > 32 && items * d.n_kv_heads <= 32l * c->n_cus && row_tiles * d.n_kv_heads <= c->n_cus;
+  if (pl->split) total_tiles = items;
+  pl->rt = pl->split ? 1 : fsv_ceil_div(max_rows, 32);
   // Waves per block.  Eight, one block per compute unit, while requests are few: a part then takes an eighth of its tiles' time.  Four, two blocks per
   // compute unit, from 192 (request, kv head) pairs on, so that a request need not be cut, and one block computes while the other
   // starts or merges; where the queries leave room for it (not with head size 128 and more than one row tile).  Head size 64, whole call
@@ -657,11 +675,14 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
     for (int i = 0; i < b->batch && parts * d.n_kv_heads <= most; ++i) {
       const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
       int tp;
-      parts += attn_parts(fsv_ceil_div(nk, 32), tpw, w16_of(g), pl->nw, &tp);
+      parts += attn_parts(fsv_ceil_div(nk, 32), tpw, w16_of(g), pl->nw, &tp) * (pl->split ? rtc_of(g) : 1);
     }
     return parts * d.n_kv_heads;
   };
-  const int even = (int)max((long)c->attn_min_tpw, (total_tiles * d.n_kv_heads + target - 1) / target);
+  // Fewest key tiles a part is given: two for each of eight waves, or one while that makes no more parts than the merge fetches at once
+  // (1600 positions, head size 128, one row tile 13.9 and 12.5 us; 3200 positions 16.2 and 18.3).
+  const int fewest = pl->nw == 8 && longest <= 64 ? c->attn_min_tpw / 2 : c->attn_min_tpw;
+  const int even = (int)max((long)fewest, (total_tiles * d.n_kv_heads + target - 1) / target);
   int tpw = 0;
   // Every request has a part, so with more pairs than blocks there is nothing to look for; otherwise at most 129 lengths are tried.
   // (Host time of all lengths one by one, before the first launch: 128 requests of 256 .. 8192 positions 0.33 ms, of 8 .. 32 k 2.6 ms.)
@@ -680,9 +701,9 @@ int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
 
 int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M, bool rope, const void *q, hipStream_t st) {
   setup_args a;
-  a.B = b->batch; a.tpw = pl.tpw; a.nw = pl.nw; a.sorted = pl.sorted; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
+  a.B = b->batch; a.tpw = pl.tpw; a.nw = pl.nw; a.sorted = pl.sorted; a.split = pl.split; a.group = c->group; a.w2 = c->attn_w2; a.w3 = c->attn_w3;
   a.max_pages = c->d.max_pages_per_req; a.num_pages = b->num_pages; a.grid_parts = pl.waves / c->d.n_kv_heads;
-  a.tickets = b->batch * c->d.n_kv_heads; a.ticket = c->attn_ticket;
+  a.tickets = b->batch * RTMAX * c->d.n_kv_heads; a.ticket = c->attn_ticket;
   a.M = M; a.half = rope ? c->d.head_dim / 2 : 1; a.V = c->d.vocab;   // without the angles: one thread per row
   a.seq_lens = b->seq_lens; a.off = b->draft_offsets; a.page_table = b->page_table;
   a.last_token = b->last_token; a.draft = b->draft_tokens; a.inv_freq = (const double *)c->inv_freq;
@@ -770,7 +791,7 @@ int fsv_bf16_attn_create(fsv_ctx *c) {
   FSV_ATTN_ATTR(64, 1, 8); FSV_ATTN_ATTR(64, 2, 8); FSV_ATTN_ATTR(64, 3, 8); FSV_ATTN_ATTR(128, 1, 4);
   FSV_ATTN_ATTR(64, 1, 4); FSV_ATTN_ATTR(64, 2, 4); FSV_ATTN_ATTR(64, 3, 4);
 #undef FSV_ATTN_ATTR
-  if ((rc = zalloc((void **)&c->attn_ticket, sizeof(int32_t) * (size_t)d.max_batch * d.n_kv_heads))) return rc;
+  if ((rc = zalloc((void **)&c->attn_ticket, sizeof(int32_t) * (size_t)d.max_batch * RTMAX * d.n_kv_heads))) return rc;
   if ((rc = zalloc(&c->attn_part, c->attn_part_bytes))) return rc;
   if ((rc = zalloc((void **)&c->attn_part_prefix, sizeof(int32_t) * (d.max_batch + 1)))) return rc;
   if ((rc = zalloc((void **)&c->attn_part_map, sizeof(int32_t) * kDescInts * (c->attn_wave_cap / d.n_kv_heads + 1)))) return rc;

@@ -105,7 +105,7 @@ struct fsv_ctx {
   int n_cus = 0;                // compute units of the device the context was created on
   int attn_wave_target = 0;     // compute units: blocks of eight waves the attention schedule aims at
   int attn_wave_cap = 0;        // blocks the partial buffers hold
-  int32_t *attn_ticket = nullptr;  // [max_batch][kv heads] parts of a (request, kv head) that have left their results; zero between the launches of a call
+  int32_t *attn_ticket = nullptr;  // [max_batch][row tiles][kv heads] parts of the same rows that have left their results; zero between the launches of a call
   int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7
   int attn_w2 = 20, attn_w3 = 26;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
   int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 28-int record per part
@@ -197,8 +197,9 @@ int fsv_f32_kv_copy(fsv_ctx *c, void *k_pool, void *v_pool, int num_pages, const
 struct fsv_attn_plan {
   int tpw = 0;          // target key tiles per part
   int waves = 0;        // parts x kv heads: blocks
-  int rt = 1;           // query-row tiles of the widest request
+  int rt = 1;           // query-row tiles of the widest part
   int nw = 8;           // waves per block
+  bool split = false;   // the row tiles of a request are parts of their own
   bool sorted = false;  // the parts run in several rounds, long ones first
   double kv_tokens = 0;
 };

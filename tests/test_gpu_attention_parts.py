@@ -23,6 +23,13 @@ pytestmark = pytest.mark.gpu
     ([9000, 100, 4095], [1, 2, 7]),
     ([40 + 37 * i for i in range(100)], [i % 2 for i in range(100)]),        # two kv heads: four waves per block, one round
     ([3 + 61 * i % 997 for i in range(300)] + [7000], [7] * 300 + [1]),      # several rounds, long parts first
+    ([511, 512, 480, 2047, 1000], [0, 0, 16, 0, 8]),                # 16 and 17 tiles, whole and cut; the longest call of one tile per wave
+    ([511, 512, 480, 2048, 1000], [0, 0, 16, 0, 8]),                # and the next
+    # row tiles that share their keys: two and three of them, four waves (head size 64: 192 pairs and more) and eight, one round and several
+    ([30 + 37 * i for i in range(100)], [8 + i % 8 for i in range(100)]),
+    ([25 + 29 * i for i in range(100)], [16 - i % 9 for i in range(100)]),
+    ([20 + 53 * i for i in range(90)], [2 + 13 * (i % 3 > 0) for i in range(90)]),
+    ([20 + 131 * i % 1999 for i in range(90)] + [9000], [16 - i % 2 for i in range(91)]),
 ])
 def test_parts(name, seq_lens, gammas):
     ctx, batch, qd, check = _session(name, seq_lens, gammas)
