@@ -244,22 +244,11 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
 }
 
 // Four fp16 values as floats, for the stand-alone entry point's row-major result (a 16-byte store at any 4-byte boundary).
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ inline void store_row4(float *p, uint32_t lo, uint32_t hi) {
-  *reinterpret_cast<f32x4_u *>(p) = (f32x4_u){h2f((uint16_t)(lo & 0xffffu)), h2f((uint16_t)(lo >> 16)), h2f((uint16_t)(hi & 0xffffu)),
+  *reinterpret_cast<f32x4_any *>(p) = (f32x4_any){h2f((uint16_t)(lo & 0xffffu)), h2f((uint16_t)(lo >> 16)), h2f((uint16_t)(hi & 0xffffu)),
                                               h2f((uint16_t)(hi >> 16))};
 }
 
-// Direct global -> LDS load of 64 x 16 bytes: lane i of the wave fills the i-th 16-byte unit at LDS byte offset `dst`.  An opaque
-// statement: the compiler makes every later LDS read wait for all such loads it knows of; the waits here are explicit.  (One wait
-// state between writing M0 and the load that reads it.)  NT: bytes that are used once and should not displace others in L2.
-template <bool NT>
-__device__ __forceinline__ void load_to_lds(uint32_t dst, uint32_t lane_off, const char *src) {
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
-}
 // Waits until at most min(n, N) groups of LPG loads of this wave are on their way (n wave-uniform).
 template <int N, int LPG>
 __device__ __forceinline__ void wait_groups(int n) {

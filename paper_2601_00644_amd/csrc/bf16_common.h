@@ -30,6 +30,20 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
+// Direct global -> LDS load of 64 x 16 bytes: lane i of the wave fills the i-th 16-byte unit at LDS byte offset `dst`.  An opaque
+// statement: the compiler makes every later LDS read wait for all such loads it knows of; the waits of these kernels are explicit.  (One
+// wait state between writing M0 and the load that reads it.)  NT: bytes that are used once and should not displace others in L2.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // M0 is named as written although the compiler allocates nothing to it
+template <bool NT>
+__device__ __forceinline__ void load_to_lds(uint32_t dst, uint32_t lane_off, const char *src) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 // offset, in 16-byte units, of the operand unit holding (row r, k .. k+7), k a multiple of 8
 __device__ __host__ inline size_t tile_unit(int r, int k, int KB) {
   return ((size_t)(r >> 5) * KB + (k >> 4)) * 64 + (r & 31) + 32 * ((k >> 3) & 1);

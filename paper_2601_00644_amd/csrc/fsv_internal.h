@@ -14,6 +14,7 @@
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;   // one MFMA A/B operand (8 bf16 per lane)
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;   // one 32x32 MFMA accumulator
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // rows of any length: sixteen bytes at any 4-byte boundary
 
 // ---- sampler geometry -------------------------------------------------------------------------
 // A vocabulary row is cut into sub-blocks of SBK ids and chunks of SPC sub-blocks; the statistics

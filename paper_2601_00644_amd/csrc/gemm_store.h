@@ -7,7 +7,6 @@ namespace fsv_bf16 {
 enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_F32 = 2 };
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // rows of a vocabulary that is no multiple of four
 
 // The barrier as an opaque statement: memory operations do not move across it, and no counter wait is attached.
 #define FSV_BARRIER() asm volatile("s_barrier" ::: "memory")

@@ -27,12 +27,6 @@ namespace {
 // What bounds it is power: with every unit at work the clock falls from 2.36 to about 1.9 GHz.  2048 x 28672 x 4096: products alone 1.41
 // PFLOP/s, without the direct loads 1.30, without the LDS reads 1.20, whole 1.14.  Fewer LDS reads for a product therefore pay although
 // their slots are free: 192-row blocks 5 .. 7 % faster than with eight waves, 256-row blocks 0 .. 1 %; gate|up, 2048 rows 447 -> 427 us.
-// Direct global -> LDS load of 64 x 16 bytes: lane i of the wave fills the i-th 16-byte unit at LDS byte offset `dst`.  As
-// an opaque statement, because the compiler makes every later LDS read wait for all such loads it knows of; the waits below
-// are explicit.  (One wait state between writing M0 and the load that reads it.)
-__device__ __forceinline__ void load_to_lds(uint32_t dst, uint32_t lane_off, const char *src) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(lane_off), "s"(src) : "memory", "m0");
-}
 
 template <int N>
 __device__ __forceinline__ void wait_loads() {
@@ -93,7 +87,7 @@ __global__ __launch_bounds__(64 * wide_geo<MT>::NW) void k_gemm_wide(const char 
     }
   }
   auto issue1 = [&](int j, uint32_t slot_off) {
-    load_to_lds(lds0 + slot_off + (uint32_t)(NW * j + w) * 1024u, lane_off, src[j]);
+    load_to_lds<false>(lds0 + slot_off + (uint32_t)(NW * j + w) * 1024u, lane_off, src[j]);
     src[j] += WSB * 1024;
   };
 
@@ -110,6 +104,7 @@ __global__ __launch_bounds__(64 * wide_geo<MT>::NW) void k_gemm_wide(const char 
   const uint4 *wbase = lds + wf * (NSW * WSB * 64) + lane, *abase = lds + (WSTRIPS + wr * MT) * (WSB * 64) + lane;
   // operand i of a k block, in the order the products need them: the first strip, the row tiles, the other strips
   constexpr int NF = NSW + MT, NM = NSW * MT, EVERY = NM / NF;   // operands, products; an operand is read behind every EVERY-th product
+  static_assert(EVERY >= 1, "");
   auto fetch1 = [&](int set, int i, uint32_t slot_units, int kb) {
     if (i == 0 || i > MT) {
       const int s = i == 0 ? 0 : i - MT;
@@ -152,15 +147,7 @@ __global__ __launch_bounds__(64 * wide_geo<MT>::NW) void k_gemm_wide(const char 
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         mfma1(kb & 1, i);
-        if constexpr (EVERY > 0) {
-          if (i % EVERY == 0 && i / EVERY < NF) fetch1((kb + 1) & 1, i / EVERY, so, (kb + 1) % WSB);
-        } else {   // fewer products than operands
-          fetch1((kb + 1) & 1, i, so, (kb + 1) % WSB);
-          if (i == NM - 1) {
-#pragma unroll
-            for (int f = NM; f < NF; ++f) fetch1((kb + 1) & 1, f, so, (kb + 1) % WSB);
-          }
-        }
+        if (i % EVERY == 0 && i / EVERY < NF) fetch1((kb + 1) & 1, i / EVERY, so, (kb + 1) % WSB);
         constexpr int LEVERY = WSB * NM / LJ;   // and a load behind every LEVERY-th
         const int slot = kb * NM + i;
         if (decltype(more)::value && slot % LEVERY == LEVERY - 1 && slot / LEVERY < LJ) issue1(slot / LEVERY, wrs);

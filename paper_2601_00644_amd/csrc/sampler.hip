@@ -52,7 +52,6 @@ __device__ inline float exp_scaled(float d, exp_scale k) {
 // and a load of four dwords takes those as they come (one element per load instead: 576 rows x 50257 fp32, top-k 50, 267 us a call;
 // 75 like this, bf16 with top-p 0.9 157 and 77).
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename LT>
 struct loader;
@@ -706,24 +705,6 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   nuc_near[r] = (use_p && fmin(target - (double)acc, (double)kept - target) < 1e-6 * total) ? 1 : 0;
 }
 
-// The cut of every row that asks for one: cut key, kept mass, and whether top_p falls within 1e-6 of the row's mass of it.
-// grid = rows, one block each (a block fills its compute unit: blocks that only find they have no row would cost a round).
-//
-// The first pass files the tokens under 8192 bins of the exponent (log2 of the probability relative to the maximum, 192 bins
-// per factor of two): their count for top-k, their mass in 32-bit fixed point for top-p; the bins in which the cut can lie
-// follow from the running sum and a bound of its rounding.  The second collects the tokens of those bins (for top-k: of all
-// bins down to it) and adds up, exactly, what lies above.  The list is sorted by key, and its running sum of exact 2^-40
-// masses decides.  A top-k of a few hundred takes one pass: the first round of loads (32768 ids, sampled across the vocabulary)
-// is filed, the bin at which these already hold top_k tokens bounds the cut, and everything from that bin on goes to the list
-// at once.  For top-p, tokens so improbable that all of them together do not matter to the sums are not filed.
-// When the list cannot hold the candidates (near-flat laws, many ties), top-p goes on with passes that narrow the keys of those
-// bins (cut_narrow).  Rows with NaN or an infinite maximum, a top-k beyond the list, a top-p too close to 1 for the sums of the
-// first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
-// Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
-// arithmetic of a single compute unit with few rows.  Measured on 166 rows x 128256 fp32, N(0, 3), T = 0.8, against passes by
-// digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
-// passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
-// (74); logits rounded to whole numbers, top-p 0.99 110 (110).
 // What k_row_stats leaves for a row, by the waves of one block: the same chunks, the same sums in the same order, but a quarter of a
 // chunk's loads at a time and a second trip (from the cache) for the sums, so that it fits this kernel's registers.
 template <typename LT>
@@ -787,6 +768,24 @@ __device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int 
 // A top-k of this size takes one pass, which needs nothing from the row statistics (4 x top_k candidates are expected in the list).
 __device__ __host__ inline bool cut_takes_one_pass(int top_k, int V) { return top_k > 0 && top_k < V && 6l * top_k <= kCutList; }
 
+// The cut of every row that asks for one: cut key, kept mass, and whether top_p falls within 1e-6 of the row's mass of it.
+// grid = rows, one block each (a block fills its compute unit: blocks that only find they have no row would cost a round).
+//
+// The first pass files the tokens under 8192 bins of the exponent (log2 of the probability relative to the maximum, 192 bins
+// per factor of two): their count for top-k, their mass in 32-bit fixed point for top-p; the bins in which the cut can lie
+// follow from the running sum and a bound of its rounding.  The second collects the tokens of those bins (for top-k: of all
+// bins down to it) and adds up, exactly, what lies above.  The list is sorted by key, and its running sum of exact 2^-40
+// masses decides.  A top-k of a few hundred takes one pass: the first round of loads (32768 ids, sampled across the vocabulary)
+// is filed, the bin at which these already hold top_k tokens bounds the cut, and everything from that bin on goes to the list
+// at once.  For top-p, tokens so improbable that all of them together do not matter to the sums are not filed.
+// When the list cannot hold the candidates (near-flat laws, many ties), top-p goes on with passes that narrow the keys of those
+// bins (cut_narrow).  Rows with NaN or an infinite maximum, a top-k beyond the list, a top-p too close to 1 for the sums of the
+// first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
+// Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
+// arithmetic of a single compute unit with few rows.  Measured on 166 rows x 128256 fp32, N(0, 3), T = 0.8, against passes by
+// digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
+// passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
+// (74); logits rounded to whole numbers, top-p 0.99 110 (110).
 template <typename LT, bool STATS>
 __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logits, int V, int nc, const int32_t *__restrict__ off,
                                                      const float *__restrict__ temperature, const float *__restrict__ top_p,
