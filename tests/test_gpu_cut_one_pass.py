@@ -56,3 +56,33 @@ def test_without_statistics(kind, V, monkeypatch):
             out.append(torch.stack([res.accepted_len, res.next_token, res.flags]).cpu().numpy())
         assert (out[0] == out[1]).all(), top_k
     ctx.close()
+
+
+@pytest.mark.parametrize("sampled", [60, 59])
+def test_more_rows_than_compute_units(sampled, monkeypatch):
+    """270 rows: two thirds of them sampled, which leaves the statistics to k_cut, and one request less, which does not."""
+    from paper_2601_00644_amd import flexverify as fv
+    B, gam, V = 90, 2, 32772
+    off = (np.arange(B + 1) * gam).astype(np.int32)
+    g = torch.Generator().manual_seed(7)
+    lg = (torch.randn((B * (gam + 1), V), generator=g) * 3.0).cuda()
+    q = torch.softmax(torch.randn((B * gam, V), generator=g), -1).cuda()
+    T = np.zeros(B, np.float32)
+    T[np.random.default_rng(3).permutation(B)[:sampled]] = 0.8
+    t = lambda a: torch.as_tensor(a).cuda()
+    d = np.random.default_rng(5).integers(0, V, B * gam).astype(np.int32)
+    d[::2] = lg[::gam + 1].argmax(-1).cpu().numpy()     # first drafts: likely tokens
+    ctx = fv.Context(synth.ModelCfg("sampler", 0, 0, 0, 0, 0, 0, V, "bf16"), None, B, 16, sampler_only=True)
+    batch = fv.DeviceBatch(None, None, t(off), t(d), q, t(synth.uniforms24(B * gam, V, 1)), t(synth.uniforms24(B, V, 2)), t(T), None,
+                           None, None, 0, None, off, T)
+    batch.top_k_host, batch.top_p_host = np.full(B, 50, np.int32), np.full(B, 0.9, np.float32)
+    batch.top_k, batch.top_p = t(batch.top_k_host), t(batch.top_p_host)
+    out = []
+    for full in ("0", "1"):
+        monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
+        res = fv.DeviceResult.alloc(B)
+        ctx.sample(lg, batch, res)
+        out.append(torch.stack([res.accepted_len, res.next_token, res.flags]).cpu().numpy())
+    assert (out[0] == out[1]).all()
+    assert 0 < out[0][0].sum() < B * gam
+    ctx.close()
