@@ -314,7 +314,8 @@ int fsv_attention(fsv_ctx *ctx, int32_t layer, const void *q, const fsv_batch *b
  * rides on the dispatch itself (start and stop of the kernel); for the other classes it is recorded on
  * the stream before and after the launches and so includes the dispatch gaps.  FSV_K_SAMPLE_NUCLEUS covers
  * the launches that find the top-k / top-p cuts of a call (one, or three on bf16 logits), its bytes every
- * logits row once.  fsv_profile_read() waits for the recorded
+ * logits row once. FSV_K_ATTN_COMBINE has no launches any more: the merge of the parts belongs to
+ * FSV_K_ATTENTION.  fsv_profile_read() waits for the recorded
  * events and returns, per class, the number of launches, their summed duration and the algorithmic
  * bytes the host computed for them (weights for a GEMM, K and V for attention, logits and draft law
  * for the sampling kernels), then clears the records.  Returns the number of classes written (<= cap).

@@ -107,7 +107,7 @@ struct fsv_ctx {
   int attn_wave_target = 0;     // compute units: blocks of eight waves the attention schedule aims at
   int attn_wave_cap = 0;        // blocks the partial buffers hold
   int32_t *attn_ticket = nullptr;  // [max_batch][row tiles][kv heads] parts of the same rows that have left their results; zero between the launches of a call
-  int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7
+  int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7 (half of it in short requests: plan_attention)
   int attn_w2 = 20, attn_w3 = 26;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
   int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 28-int record per part
 

@@ -24,9 +24,12 @@ namespace {
 // A wave interleaves the LDS reads of the next k block and its loads with the products, so the issue slots of these fall into their
 // shadow.  Operands of the next k block are read across the barrier: the barrier before stage it certifies that stage it + 1 has
 // landed, too.
-// What bounds it is power: with every unit at work the clock falls from 2.36 to about 1.9 GHz.  2048 x 28672 x 4096: products alone 1.41
-// PFLOP/s, without the direct loads 1.30, without the LDS reads 1.20, whole 1.14.  Fewer LDS reads for a product therefore pay although
+// With every unit at work the clock falls from 2.36 to about 1.9 GHz.  2048 x 28672 x 4096: products alone 1.41 PFLOP/s, without the direct
+// loads 1.30, without the LDS reads 1.20, whole 1.14; the library's fp16 product of 8192^3 reaches 1.42 with all of its loads, so that
+// power alone is not the bound: every block fills its ring from nothing and stores its result with no load in flight (kWideFixed, 5 us in
+// each of three to five rounds), and the last round is partly filled.  Fewer LDS reads for a product pay although
 // their slots are free: 192-row blocks 5 .. 7 % faster than with eight waves, 256-row blocks 0 .. 1 %; gate|up, 2048 rows 447 -> 427 us.
+// MT = 4 with bf16 operands fills all 512 registers; sixteen are spilled and read back once, in the epilogue.
 
 template <int N>
 __device__ __forceinline__ void wait_loads() {

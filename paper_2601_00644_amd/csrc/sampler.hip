@@ -706,7 +706,9 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
 }
 
 // What k_row_stats leaves for a row, by the waves of one block: the same chunks, the same sums in the same order, but a quarter of a
-// chunk's loads at a time and a second trip (from the cache) for the sums, so that it fits this kernel's registers.
+// chunk's loads at a time and a second trip (from the cache) for the sums, so that it fits this kernel's registers.  A function of its own:
+// inlined it spilled 295 registers; called, k_cut<float, true> saves four registers and has a stack of 384 bytes a lane for it (112, unused,
+// are set aside in k_cut<float, false>).
 template <typename LT>
 __device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int V, int nc, float T, float *pm, double *ps, int32_t *pa, int w, int lane) {
   constexpr int P = FSV_CHUNK / 512;
