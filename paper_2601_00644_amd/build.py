@@ -13,9 +13,11 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, os.environ.get("FSV_LIB_NAME", "libflexverify.so"))
 OBJ = os.path.join(HERE, "_build")
 
+# Kernel arguments preloaded into registers (the first 14 words): a wave does not begin with a trip to memory for them.  A chain of
+# launches of 256 blocks that each read 8 KB takes 2.45 us a launch instead of 2.97, 32 KB more 3.16 instead of 3.46.
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
-         "-fno-gpu-rdc"]
+         "-fno-gpu-rdc", "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 # per-file flags: the attention kernels keep their MFMA accumulators in architectural registers

@@ -297,10 +297,9 @@ struct attn_geo {
 
 template <int HD, int RT, int NW>
 __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_attention(
-    int Hkv, int group, int rows_cap, const char *__restrict__ qp, size_t q_plane_bytes, const int32_t *__restrict__ part_desc,
-    const int32_t *__restrict__ page_table, int max_pages, int num_pages,
-    const char *__restrict__ kpool, const char *__restrict__ vpool, float *part_o, float *part_ml, int32_t *__restrict__ ticket,
-    uint16_t *__restrict__ out, int KBq, float *__restrict__ out32) {
+    const int32_t *__restrict__ part_desc, int Hkv, int group, const char *__restrict__ qp, size_t q_plane_bytes,
+    const char *__restrict__ kpool, const char *__restrict__ vpool, int max_pages, int num_pages, const int32_t *__restrict__ page_table,
+    int rows_cap, float *part_o, float *part_ml, int32_t *__restrict__ ticket, uint16_t *__restrict__ out, int KBq, float *__restrict__ out32) {
   using G = attn_geo<HD, RT, NW>;
   constexpr int KS = G::KS, VC = G::VC, TILEB = G::TILEB, ITEM = G::ITEM, LPI = G::LPI, SLOTS = G::SLOTS, LOOK = G::LOOK;
   extern __shared__ uint4 lds[];
@@ -736,9 +735,8 @@ int launch_attention(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, si
     fsv_prof_scope ps(c, st, FSV_K_ATTENTION, pl.kv_tokens * d.n_kv_heads * d.head_dim * 4.0, true);
 #define FSV_ATTN_LAUNCH(HDV, RTV, NWV)                                                                                            \
   hipExtLaunchKernelGGL((k_attention<HDV, RTV, NWV>), dim3(pl.waves), dim3(64 * NWV), (attn_geo<HDV, RTV, NWV>::LDS), st, ps.start(), \
-                        ps.stop(), 0, d.n_kv_heads, group, rows_cap, (const char *)c->buf_q, c->q_plane_units * 16, c->attn_part_map, \
-                        b->page_table, d.max_pages_per_req, b->num_pages, (const char *)kl, (const char *)vl, po, pml, c->attn_ticket, \
-                        out, KBq, out32)
+                        ps.stop(), 0, c->attn_part_map, d.n_kv_heads, group, (const char *)c->buf_q, c->q_plane_units * 16, (const char *)kl, \
+                        (const char *)vl, d.max_pages_per_req, b->num_pages, b->page_table, rows_cap, po, pml, c->attn_ticket, out, KBq, out32)
     if (d.head_dim == 128) {
       if (pl.rt <= 1) { if (pl.nw == 8) FSV_ATTN_LAUNCH(128, 1, 8); else FSV_ATTN_LAUNCH(128, 1, 4); }
       else if (pl.rt == 2) FSV_ATTN_LAUNCH(128, 2, 8);

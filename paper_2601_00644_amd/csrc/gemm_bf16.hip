@@ -82,9 +82,10 @@ __device__ __forceinline__ void loader_wave(uint4 *lds, const uint4 *__restrict_
 }
 
 template <int MT, int EPI, int D, bool F16, int NCW>
-__global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restrict__ Wp, uint32_t wbytes, const uint4 *__restrict__ Ap,
-                                              void *__restrict__ out, int N, int KB, int Mt_total, int M, int Mpad,
-                                              int S, int nchunks, int KBo, int NBv, int MB, float oscale, int NT, uint32_t strip_bytes) {
+__global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restrict__ Wp, const uint4 *__restrict__ Ap, uint32_t wbytes,
+                                              uint32_t strip_bytes, int KB, int nchunks, int S, int MB, int NBv, int NT, int Mt_total,
+                                              int Mpad, void *__restrict__ out, int N, int M, int KBo, float oscale) {
+  // (the arguments a wave needs before its first load come first: the first 14 words are in registers when it starts)
   // strip_bytes: distance between the weight strips of consecutive 32-feature tiles (K / 16 KiB of operands plus padding)
   // NCW: compute waves of the block (the block has NCW + NLD waves); NT: weight strips the matrix holds
   extern __shared__ uint4 lds[];
@@ -214,7 +215,7 @@ int launch_t(fsv_ctx *c, int cls, dim3 grid, const void *Wp, uint32_t wbytes, co
   fsv_prof_scope ps(c, st, cls, (double)N * KB * 32.0, true);
 #define FSV_GEMM_GO(F16V, NCWV, OSC)                                                                                          \
   hipExtLaunchKernelGGL((k_gemm<MT, EPI, D, F16V, NCWV>), grid, dim3(64 * (NCWV + NLD)), ldsb, st, ps.start(), ps.stop(), 0, Wp, \
-                        wbytes, (const uint4 *)Ap, out, N, KB, Mt, M, Mpad, splits, nchunks, KBo, NB, mblocks, OSC, NT, strip_bytes)
+                        (const uint4 *)Ap, wbytes, strip_bytes, KB, nchunks, splits, mblocks, NB, NT, Mt, Mpad, out, N, M, KBo, OSC)
   if (f16) {
     if (ncw == 4) FSV_GEMM_GO(true, 4, oscale);
     else if (ncw == 3) FSV_GEMM_GO(true, 3, oscale);

@@ -173,13 +173,16 @@ __device__ inline void lora_shrink(const uint16_t *__restrict__ A, int rank, int
   __syncthreads();
 }
 
+// Threads per row of k_resid_norm: one 8-wide slice each, up to 1024.
+__host__ __device__ inline int norm_threads(int d) { return min(1024, max(64, (d / 8 + 63) / 64 * 64)); }
+
 template <int EMBED, int LQ, int LO, int RAW = 0>
-__global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, float eps, const int32_t *__restrict__ row_tok,
-                                                     const uint16_t *__restrict__ E, const float *__restrict__ part,
-                                                     int S, int Mpad, float *__restrict__ x,
+__global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, int S, int Mpad, float *__restrict__ x, const float *__restrict__ part,
                                                      const uint16_t *__restrict__ gain, uint4 *__restrict__ a_out,
+                                                     const int32_t *__restrict__ row_tok, const uint16_t *__restrict__ E, float eps,
                                                      lora_args lo) {
-  const int r = row_of_block(), tid = threadIdx.x, KB = d / 16, stride = blockDim.x * 8, nw = blockDim.x >> 6;
+  // (blockDim.x is not asked for: unlike the first arguments, it would have to be fetched)
+  const int nthr = norm_threads(d), r = row_of_block(), tid = threadIdx.x, KB = d / 16, stride = nthr * 8, nw = nthr >> 6;
   if (r >= M) {
     for (int k0 = tid * 8; k0 < d; k0 += stride) a_out[tile_unit(r, k0, KB)] = make_uint4(0, 0, 0, 0);
     return;
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, float eps, co
           xv[2 * u + 1] = h2f((uint16_t)(w4[u] >> 16));
         }
       };
-      lora_shrink(lo.ao + (size_t)ad * lo.rank * lo.qd, lo.rank, lo.qd, tid, (int)blockDim.x, att_slice, s_part, s_t);
+      lora_shrink(lo.ao + (size_t)ad * lo.rank * lo.qd, lo.rank, lo.qd, tid, nthr, att_slice, s_part, s_t);
       if (live) {
         const float sc = lo.scale[ad];
         const uint16_t *B = lo.bo + ((size_t)ad * d + k0) * lo.rank;
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, float eps, co
           xv[2 * u + 1] = h2f((uint16_t)(w4[u] >> 16));
         }
       };
-      lora_shrink(lo.aq + (size_t)ad * lo.rank * d, lo.rank, d, tid, (int)blockDim.x, own_slice, s_part, s_t);
+      lora_shrink(lo.aq + (size_t)ad * lo.rank * d, lo.rank, d, tid, nthr, own_slice, s_part, s_t);
       if (tid < lo.rank) lo.t_out[(size_t)r * 64 + tid] = s_t[tid];
     }
     return;
@@ -453,11 +456,10 @@ __global__ __launch_bounds__(256) void k_kv_copy(int Hkv, int num_pages, const i
 // to 64 half lines: 2048 rows of 8B 28.8 -> 22.2 us, 1070 rows 20.3 -> 16.0.  The loads are single words then, so with more than two slices to
 // add it does not pay (71 rows, four slices 5.5 and 5.7 us; 1B, eight slices, 5 rows 4.1 and 6.7).
 template <int LORA, bool SPREAD>
-__global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, const float *__restrict__ rope_tab,
-                                                     const float *__restrict__ part, int S, int Mpad,
+__global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, int S, int Mpad, const float *__restrict__ part,
                                                      const int32_t *__restrict__ row_req,
                                                      const int32_t *__restrict__ row_idx,
-                                                     const int32_t *__restrict__ row_pos,
+                                                     const int32_t *__restrict__ row_pos, const float *__restrict__ rope_tab,
                                                      const int32_t *__restrict__ page_table, int max_pages,
                                                      int num_pages, size_t layer_off, uint16_t *__restrict__ qp,
                                                      size_t q_plane, uint16_t *__restrict__ kpool,
@@ -468,7 +470,7 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, con
   // rotation pairs (i .. i+3, i+half .. i+half+3) of one head.  The partial sums and the rotation table only need the
   // row index, so their loads are issued first, next to the row's request / position / page lookups.
   const int r = row_of_block(), half = hd / 2, qpt = half / 4, heads = H + 2 * Hkv, qkvd = heads * hd, group = H / Hkv;
-  const int item = blockIdx.y * blockDim.x + threadIdx.x;
+  const int item = blockIdx.y * 256 + threadIdx.x;
   if (item >= heads * qpt) return;
   const int hh = item / qpt, i = (item % qpt) * 4;
   const bool is_v = hh >= H + Hkv, spread = SPREAD && is_v;
@@ -882,7 +884,7 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
                     glg = pick_launch(c, sg, Mt, false), gll = pick_launch(c, sl, Mt, false);
   const int spq = glq.splits, spo = glo.splits, spd = gld.splits;
   float *part = (float *)c->buf_part;
-  const int nthr = min(1024, max(64, fsv_ceil_div(d.d_model / 8, 64) * 64));  // one 8-wide slice per thread
+  const int nthr = norm_threads(d.d_model);
   int rc;
   const fsv_attn_plan &pl = *plan;
   if ((rc = fsv_bf16_setup_launch(c, b, plan, M, true, nullptr, s))) return rc;
@@ -906,13 +908,11 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
   {
     fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
     if (lq0)
-      hipLaunchKernelGGL((k_resid_norm<1, 1, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok,
-                         (const uint16_t *)c->embed, nullptr, 0, Mpad, c->x, (const uint16_t *)c->layers[l_first].attn_norm,
-                         (uint4 *)c->buf_a, lora_for(0, true, false));
+      hipLaunchKernelGGL((k_resid_norm<1, 1, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, 0, Mpad, c->x, nullptr,
+                         (const uint16_t *)c->layers[l_first].attn_norm, (uint4 *)c->buf_a, c->row_tok, (const uint16_t *)c->embed, d.rms_eps, lora_for(0, true, false));
     else
-      hipLaunchKernelGGL((k_resid_norm<1, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok,
-                         (const uint16_t *)c->embed, nullptr, 0, Mpad, c->x, (const uint16_t *)c->layers[l_first].attn_norm,
-                         (uint4 *)c->buf_a, lora_args{});
+      hipLaunchKernelGGL((k_resid_norm<1, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, 0, Mpad, c->x, nullptr,
+                         (const uint16_t *)c->layers[l_first].attn_norm, (uint4 *)c->buf_a, c->row_tok, (const uint16_t *)c->embed, d.rms_eps, lora_args{});
   }
   for (int l = l_first; l < d.n_layers; ++l) {
     const fsv_layer_w &L = c->layers[l];
@@ -923,8 +923,8 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
     {
       fsv_prof_scope ps(c, s, FSV_K_ROPE_APPEND, 0.0);
       const dim3 rg(M, fsv_ceil_div((d.n_heads + 2 * d.n_kv_heads) * (d.head_dim / 8), 256));
-#define FSV_ROPE_ARGS d.n_heads, d.n_kv_heads, d.head_dim, (const float *)c->rope_tab, part, spq, Mpad, c->row_req, c->row_idx, \
-                      c->row_pos, b->page_table, d.max_pages_per_req, b->num_pages, lo, (uint16_t *)c->buf_q,                  \
+#define FSV_ROPE_ARGS d.n_heads, d.n_kv_heads, d.head_dim, spq, Mpad, part, c->row_req, c->row_idx, c->row_pos, \
+                      (const float *)c->rope_tab, b->page_table, d.max_pages_per_req, b->num_pages, lo, (uint16_t *)c->buf_q,                  \
                       c->q_plane_units * 8, (uint16_t *)b->k_pool, (uint16_t *)b->v_pool
       const bool spread = spq <= 2;
       if (adapted)
@@ -941,11 +941,11 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
     {
       fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
       if (adapted)
-        hipLaunchKernelGGL((k_resid_norm<0, 0, 1>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok, nullptr,
-                           part, spo, Mpad, c->x, (const uint16_t *)L.mlp_norm, (uint4 *)c->buf_a, lora_for(l, false, true));
+        hipLaunchKernelGGL((k_resid_norm<0, 0, 1>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, spo, Mpad, c->x, part,
+                           (const uint16_t *)L.mlp_norm, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_for(l, false, true));
       else
-        hipLaunchKernelGGL((k_resid_norm<0, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok, nullptr,
-                           part, spo, Mpad, c->x, (const uint16_t *)L.mlp_norm, (uint4 *)c->buf_a, lora_args{});
+        hipLaunchKernelGGL((k_resid_norm<0, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, spo, Mpad, c->x, part,
+                           (const uint16_t *)L.mlp_norm, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_args{});
     }
     if ((rc = launch_gemm<EPI_SWIGLU>(c, FSV_K_GEMM_GATE_UP, L.w_gate_up, c->buf_a, c->buf_act, sg, M, glg, s, L.os_gate_up))) return rc;
     if ((rc = launch_gemm<EPI_PARTIAL>(c, FSV_K_GEMM_DOWN, L.w_down, c->buf_act, part, sd, M, gld, s))) return rc;
@@ -953,14 +953,14 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
       fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
       const void *gain = (l + 1 < d.n_layers) ? c->layers[l + 1].attn_norm : c->final_norm;
       if (draft)
-        hipLaunchKernelGGL((k_resid_norm<0, 0, 0, 1>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok, nullptr,
-                           part, spd, Mpad, c->x, (const uint16_t *)gain, (uint4 *)c->buf_a, lora_args{});
+        hipLaunchKernelGGL((k_resid_norm<0, 0, 0, 1>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, spd, Mpad, c->x, part,
+                           (const uint16_t *)gain, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_args{});
       else if (next_adapted)
-        hipLaunchKernelGGL((k_resid_norm<0, 1, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok, nullptr,
-                           part, spd, Mpad, c->x, (const uint16_t *)gain, (uint4 *)c->buf_a, lora_for(l + 1, true, false));
+        hipLaunchKernelGGL((k_resid_norm<0, 1, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, spd, Mpad, c->x, part,
+                           (const uint16_t *)gain, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_for(l + 1, true, false));
       else
-        hipLaunchKernelGGL((k_resid_norm<0, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, d.rms_eps, c->row_tok, nullptr,
-                           part, spd, Mpad, c->x, (const uint16_t *)gain, (uint4 *)c->buf_a, lora_args{});
+        hipLaunchKernelGGL((k_resid_norm<0, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, spd, Mpad, c->x, part,
+                           (const uint16_t *)gain, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_args{});
     }
   }
   if (draft) {
