@@ -98,7 +98,7 @@ void fsv_destroy(fsv_ctx *c) {
   if (!c) return;
   for (auto &r : c->prof) { (void)hipEventDestroy(r.e0); (void)hipEventDestroy(r.e1); }
   for (hipEvent_t e : c->prof_pool) (void)hipEventDestroy(e);
-  void *ptrs[] = {c->embed, c->final_norm, c->lm_head, c->inv_freq, c->rope_tab, c->row_req, c->row_idx, c->row_pos, c->row_tok,
+  void *ptrs[] = {c->embed, c->final_norm, c->lm_head, c->inv_freq, c->rope_tab, c->row_req, c->row_idx, c->row_pos, c->row_tok, c->row_place,
                   c->pmax, c->psum, c->parg, c->bsum, c->acc_scratch, c->sel_ticket, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, c->x, c->logits,
                   c->absmax, c->buf_a, c->buf_q, c->buf_att, c->buf_act, c->buf_part, c->attn_part, c->attn_part_prefix, c->attn_part_map, c->attn_ticket,
                   c->lora_aq, c->lora_bq, c->lora_ao, c->lora_bo, c->lora_scale, c->lora_t,

@@ -74,7 +74,7 @@ struct setup_args {
   int B, tpw, nw, sorted, split, group, w2, w3, max_pages, num_pages, grid_parts, tickets, M, half, V;   // grid_parts: records the attention's grid reads
   const int32_t *seq_lens, *off, *page_table, *last_token, *draft;
   const double *inv_freq;
-  int32_t *part_prefix, *part_desc, *ticket, *row_req, *row_idx, *row_pos, *row_tok;
+  int32_t *part_prefix, *part_desc, *ticket, *row_req, *row_place, *row_tok;
   float *tab;
   // stand-alone attention: the caller's rotated queries [M][heads][hd] (bf16), to be put into the query operand
   int row_blocks = 0, H = 0, Hkv = 0, hd = 0, q_vec = 0;
@@ -133,8 +133,8 @@ __global__ __launch_bounds__(kSetupThreads) void k_setup(setup_args p) {
     const int b = find(off, 1, r), idx = r - off[b] - b, pos = p.seq_lens[b] + idx;
     if (i == 0) {
       p.row_req[r] = b;
-      p.row_idx[r] = idx;
-      p.row_pos[r] = pos;
+      const int page = p.page_table[(size_t)b * p.max_pages + min(pos >> 4, p.max_pages - 1)];
+      reinterpret_cast<int4 *>(p.row_place)[r] = make_int4(b, idx, pos, min(max(page, 0), p.num_pages - 1));
       const int tok = (idx == 0) ? (p.last_token ? p.last_token[b] : 0) : (p.draft ? p.draft[r - b - 1] : 0);
       p.row_tok[r] = min(max(tok, 0), p.V - 1);
     }
@@ -709,7 +709,7 @@ int launch_setup(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan &pl, int M,
   a.seq_lens = b->seq_lens; a.off = b->draft_offsets; a.page_table = b->page_table;
   a.last_token = b->last_token; a.draft = b->draft_tokens; a.inv_freq = (const double *)c->inv_freq;
   a.part_prefix = c->attn_part_prefix; a.part_desc = c->attn_part_map;
-  a.row_req = c->row_req; a.row_idx = c->row_idx; a.row_pos = c->row_pos; a.row_tok = c->row_tok;
+  a.row_req = c->row_req; a.row_place = c->row_place; a.row_tok = c->row_tok;
   a.tab = rope ? (float *)c->rope_tab : nullptr;
   a.row_blocks = fsv_ceil_div(M * a.half, kSetupThreads);
   int q_blocks = 0;

@@ -76,6 +76,7 @@ struct fsv_ctx {
 
   // row map, built per call on the device
   int32_t *row_req = nullptr, *row_idx = nullptr, *row_pos = nullptr, *row_tok = nullptr;
+  int32_t *row_place = nullptr;     // bf16 path: [max_rows][4] request, index, position, physical page of the position
 
   // sampler workspace
   float *pmax = nullptr;    // [max_rows][nc]
@@ -220,6 +221,15 @@ int fsv_bf16_gemm(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, 
 int fsv_bf16_gemm_wide_init(fsv_ctx *c);
 int fsv_bf16_gemm_wide(fsv_ctx *c, int cls, int epi, const void *Wp, const void *Ap, void *out, int N, int K, int NTpad, int M, int splits,
                        int KBo, int f16, float oscale, int mt, hipStream_t st);
+// few_rows.hip: the projections of a layer for calls of up to 16 rows, with what precedes and follows them.  strip_bytes, wbytes: distance
+// between the weight strips, size of the re-tiled matrix
+bool fsv_bf16_few_rows(const fsv_ctx *c, int M);
+int fsv_bf16_few_qkv(fsv_ctx *c, const fsv_batch *b, const void *Wp, const void *gain, uint32_t strip_bytes, uint32_t wbytes, int N, int M,
+                     float oscale, size_t layer_off, hipStream_t st);   // norm of x, q|k|v, rotation, query operand, KV append
+int fsv_bf16_few_gate_up(fsv_ctx *c, const void *Wp, const void *gain, uint32_t strip_bytes, uint32_t wbytes, int N, int M, float oscale,
+                         hipStream_t st);                                // norm of x, gate|up, SwiGLU
+int fsv_bf16_few_add(fsv_ctx *c, int cls, const void *Wp, const void *Ap, uint32_t strip_bytes, uint32_t wbytes, int N, int K, int M, int f16,
+                     float oscale, hipStream_t st);                      // x += W a
 // path_bf16.hip
 int fsv_bf16_create(fsv_ctx *c, const fsv_weights *w);
 int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *pl, int M, float *logits, int draft, hipStream_t s);

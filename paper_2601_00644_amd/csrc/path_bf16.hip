@@ -457,12 +457,8 @@ __global__ __launch_bounds__(256) void k_kv_copy(int Hkv, int num_pages, const i
 // add it does not pay (71 rows, four slices 5.5 and 5.7 us; 1B, eight slices, 5 rows 4.1 and 6.7).
 template <int LORA, bool SPREAD>
 __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, int S, int Mpad, const float *__restrict__ part,
-                                                     const int32_t *__restrict__ row_req,
-                                                     const int32_t *__restrict__ row_idx,
-                                                     const int32_t *__restrict__ row_pos, const float *__restrict__ rope_tab,
-                                                     const int32_t *__restrict__ page_table, int max_pages,
-                                                     int num_pages, size_t layer_off, uint16_t *__restrict__ qp,
-                                                     size_t q_plane, uint16_t *__restrict__ kpool,
+                                                     const int4 *__restrict__ row_place, const float *__restrict__ rope_tab,
+                                                     uint16_t *__restrict__ qp, size_t q_plane, uint16_t *__restrict__ kpool,
                                                      uint16_t *__restrict__ vpool, const int32_t *__restrict__ adapter,
                                                      int n_adapters, int rank, const float *__restrict__ lscale,
                                                      const uint16_t *__restrict__ bq, const float *__restrict__ tq) {
@@ -508,7 +504,8 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, int
       c.x += pc.x; c.y += pc.y; c.z += pc.z; c.w += pc.w;
     }
   }
-  const int b = row_req[r], i_row = row_idx[r], pos = row_pos[r];
+  const int4 place = row_place[r];
+  const int b = place.x, i_row = place.y;
   float av[4] = {a.x, a.y, a.z, a.w}, cv[4] = {c.x, c.y, c.z, c.w};
   if (LORA) {
     // adapted request: qkv += s B_qkv t, t = A_qkv a left by the norm kernel (before the rotation: it is part of the
@@ -563,7 +560,7 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, int
     *reinterpret_cast<uint2 *>(qp + q_plane + o1) = pack4(cl);
     return;
   }
-  const int page = min(max(page_table[(size_t)b * max_pages + (pos >> 4)], 0), num_pages - 1), t = pos & 15;
+  const int page = place.w, t = place.z & 15;
   uint16_t ab[4], cb[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -571,11 +568,11 @@ __global__ __launch_bounds__(256) void k_rope_append(int H, int Hkv, int hd, int
     cb[j] = f2bf(cv[j]);
   }
   if (!is_v) {
-    uint16_t *tile = kpool + layer_off + ((size_t)page * Hkv + (hh - H)) * (16 * hd);
+    uint16_t *tile = kpool + ((size_t)page * Hkv + (hh - H)) * (16 * hd);
     *reinterpret_cast<uint2 *>(tile + k_tile_off(t, i)) = pack4(ab);          // four consecutive features sit together
     *reinterpret_cast<uint2 *>(tile + k_tile_off(t, i + half)) = pack4(cb);
   } else {
-    uint16_t *tiles = vpool + layer_off + (size_t)page * Hkv * (16 * hd);
+    uint16_t *tiles = vpool + (size_t)page * Hkv * (16 * hd);
     const int lg = 31 - __builtin_clz(hd);   // 64 or 128
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -846,6 +843,7 @@ int fsv_bf16_create(fsv_ctx *c, const fsv_weights *w) {
     FSV_HIP(c, hipMemcpy(c->inv_freq, f.data(), sizeof(double) * f.size(), hipMemcpyHostToDevice));
   }
   FSV_HIP(c, hipMalloc((void **)&c->rope_tab, sizeof(float) * (size_t)c->max_rows * d.head_dim));
+  FSV_HIP(c, hipMalloc((void **)&c->row_place, sizeof(int32_t) * 4 * (size_t)c->max_rows));
   const int MtMax = fsv_ceil_div(c->max_rows, 32);
   const size_t rows_pad = (size_t)MtMax * 32;
   auto zalloc = [&](void **p, size_t bytes) -> int {
@@ -905,6 +903,8 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
     return la;
   };
   const bool lq0 = lora && d.n_layers > 1;
+  // Few rows: five launches a layer, see few_rows.hip (the measurement knobs ask for the kernels they name)
+  const bool few = !lora && c->gemm_wide_force < 0 && !c->gemm_ncw_force && fsv_bf16_few_rows(c, M);
   {
     fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
     if (lq0)
@@ -919,13 +919,26 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
     const size_t lo = (size_t)(draft ? 0 : l) * layer_stride(c, b->num_pages);
     const bool adapted = lora && l < d.n_layers - 1;         // the last block belongs to the invariant head
     const bool next_adapted = lora && l + 1 < d.n_layers - 1;
+    if (few) {
+      auto strip = [&](const gemm_shape &sh) { return (uint32_t)(sh.K / 16 * 1024 + c->strip_pad_bytes); };
+      if ((rc = fsv_bf16_few_qkv(c, b, L.w_qkv, L.attn_norm, strip(sq), sq.NTpad * strip(sq), sq.N, M, L.os_qkv, lo, s))) return rc;
+      if ((rc = fsv_bf16_attn_launch(c, b, &pl, lo, nullptr, s))) return rc;
+      if ((rc = fsv_bf16_few_add(c, FSV_K_GEMM_O, L.w_o, c->buf_att, strip(so), so.NTpad * strip(so), so.N, so.K, M, so.f16, L.os_o, s))) return rc;
+      if ((rc = fsv_bf16_few_gate_up(c, L.w_gate_up, L.mlp_norm, strip(sg), sg.NTpad * strip(sg), sg.N, M, L.os_gate_up, s))) return rc;
+      if ((rc = fsv_bf16_few_add(c, FSV_K_GEMM_DOWN, L.w_down, c->buf_act, strip(sd), sd.NTpad * strip(sd), sd.N, sd.K, M, sd.f16, 1.0f, s))) return rc;
+      if (l + 1 < d.n_layers) continue;
+      // the head reads the normalised rows (the draft model's: the rows themselves) as an operand
+      fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
+      hipLaunchKernelGGL((draft ? k_resid_norm<0, 0, 0, 1> : k_resid_norm<0, 0, 0>), dim3(Mpad), dim3(nthr), 0, s, M, d.d_model, 0, Mpad, c->x,
+                         nullptr, (const uint16_t *)c->final_norm, (uint4 *)c->buf_a, nullptr, nullptr, d.rms_eps, lora_args{});
+      continue;
+    }
     if ((rc = launch_gemm<EPI_PARTIAL>(c, FSV_K_GEMM_QKV, L.w_qkv, c->buf_a, part, sq, M, glq, s, L.os_qkv))) return rc;
     {
       fsv_prof_scope ps(c, s, FSV_K_ROPE_APPEND, 0.0);
       const dim3 rg(M, fsv_ceil_div((d.n_heads + 2 * d.n_kv_heads) * (d.head_dim / 8), 256));
-#define FSV_ROPE_ARGS d.n_heads, d.n_kv_heads, d.head_dim, spq, Mpad, part, c->row_req, c->row_idx, c->row_pos, \
-                      (const float *)c->rope_tab, b->page_table, d.max_pages_per_req, b->num_pages, lo, (uint16_t *)c->buf_q,                  \
-                      c->q_plane_units * 8, (uint16_t *)b->k_pool, (uint16_t *)b->v_pool
+#define FSV_ROPE_ARGS d.n_heads, d.n_kv_heads, d.head_dim, spq, Mpad, part, (const int4 *)c->row_place, (const float *)c->rope_tab, \
+                      (uint16_t *)c->buf_q, c->q_plane_units * 8, (uint16_t *)b->k_pool + lo, (uint16_t *)b->v_pool + lo
       const bool spread = spq <= 2;
       if (adapted)
         hipLaunchKernelGGL((spread ? k_rope_append<1, true> : k_rope_append<1, false>), rg, dim3(256), 0, s, FSV_ROPE_ARGS, b->adapter,

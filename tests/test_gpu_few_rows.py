@@ -1,0 +1,45 @@
+"""Calls of up to 16 rows, whose projections carry the normalisation, the rotation, the append and the residual sum (few_rows.hip): one layer
+against the oracle at the edges of its row counts and of the blocks its rules choose, and on the first row count past it.
+
+Bars as everywhere: logits within 2e-2 of the fp64 oracle, layer-0 cache rows against the oracle with the bf16 storage points rounded.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_00644_amd import synth
+from tests.helpers import STORED_BF16, check_bf16_kv, check_bf16_logits
+from tests.test_gpu_prefill import _oracle, _setup
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,heads,kv_heads,hd,ffn,sessions", [
+    (256, 4, 1, 64, 256, [(7, 1)]),                  # one row; shares of one step, the second half of a pair empty
+    (256, 4, 2, 128, 768, [(15, 8)]),                # eight rows; shares of three steps
+    (768, 6, 3, 128, 512, [(15, 2), (30, 7)]),       # nine rows of two requests; three steps of the normalised rows
+    (256, 64, 16, 64, 8192, [(9, 5)]),               # q|k|v in pairs of tiles, gate|up in fours
+    (256, 4, 4, 64, 14336, [(0, 16)]),               # gate|up in sevens, 56 steps in down
+    (2304, 4, 2, 64, 256, [(40, 11)]),               # more than eight steps a wave
+    (4096, 4, 1, 128, 14336, [(33, 3), (2, 5)]),     # the widest row, whole tiles added, eight rows
+    (4096, 4, 1, 128, 512, [(3, 16)]),               # and sixteen
+    (256, 4, 4, 64, 256, [(0, 17)]),                 # seventeen rows: the kernels of more rows
+])
+def test_one_layer_matches_the_oracle(monkeypatch, d, heads, kv_heads, hd, ffn, sessions):
+    name = f"few_{d}_{heads}_{kv_heads}_{hd}_{ffn}"
+    monkeypatch.setitem(synth.MODELS, name, synth.ModelCfg(name, 1, d, heads, kv_heads, hd, ffn, 640, "bf16", 500000.0))
+    fv, cfg, wn, chunks, ctxs, ctx, kp, vp, pt, page_rows, num_pages = _setup(name, sessions, 5, 15)
+    batch = fv.prefill_pieces(chunks, page_rows, kp, vp, num_pages, 16)
+    lg = ctx.prefill(batch, want_logits=True)
+    again = ctx.prefill(batch, want_logits=True)
+    assert torch.equal(lg, again)
+    lg = lg.cpu().numpy().astype(np.float64)
+    row = 0
+    for (s_, L0, tokens), (r64, _, _), (rst, kst, vst) in zip(chunks, _oracle(cfg, wn, ctxs, chunks, 0), _oracle(cfg, wn, ctxs, chunks, STORED_BF16)):
+        n = len(tokens)
+        check_bf16_logits(lg[row:row + n], r64, rst, f"{name} session {s_}")
+        row += n
+        gk, gv = ctx.kv_export(kp, vp, num_pages, pt[s_], L0, n)
+        for nm, got, want in (("k", gk, kst[:, L0:L0 + n]), ("v", gv, vst[:, L0:L0 + n])):
+            check_bf16_kv(got.float().cpu().numpy().astype(np.float64).reshape(1, n, -1), want.reshape(1, n, -1), True, (s_, nm))
+    ctx.close()
