@@ -45,7 +45,7 @@ __device__ inline exp_scale make_exp_scale(double k) {
 }
 __device__ inline float exp_scaled(float d, exp_scale k) {
   const float z = fmaf(d, k.lo, d * k.hi);
-  return (z > -150.f) ? __builtin_amdgcn_exp2f(z) : 0.f;  // also catches -inf and NaN (a chunk that is all -inf)
+  return __builtin_amdgcn_exp2f(fmaxf(z, -160.f));  // 0 from there on; -inf and NaN (a chunk that is all -inf) end there too
 }
 
 // Sixteen bytes at a time from any row: a vocabulary that is no multiple of four or eight leaves the rows at 4- or 2-byte boundaries,
@@ -143,9 +143,8 @@ __global__ void k_build_rows(int B, int V, const int32_t *seq_lens, const int32_
 // grid = (chunks / 4, largest gamma of the batch + 1, requests): row i of request b is logits row off[b] + b + i.
 // LAW: the statistics feed k_draft_law: greedy requests need none, and with drafts_only neither does a request's last row.
 template <typename LT, bool LAW = false>
-__global__ __launch_bounds__(256) void k_row_stats(const LT *__restrict__ logits, int V, int nc,
-                                                   const int32_t *__restrict__ off,
-                                                   const float *__restrict__ temperature, float *__restrict__ pmax,
+__global__ __launch_bounds__(256) void k_row_stats(const int32_t *__restrict__ off, const float *__restrict__ temperature,
+                                                   const LT *__restrict__ logits, int V, int nc, float *__restrict__ pmax,
                                                    double *__restrict__ psum, int32_t *__restrict__ parg, int drafts_only = 0) {
   constexpr int P = FSV_CHUNK / 512;  // passes of 64 lanes x 8 ids
   const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.x * 4 + (tid >> 6), bq = blockIdx.z;
@@ -318,6 +317,7 @@ __device__ inline unsigned long long nuc_mass(float d, exp_scale k) {
 // What the passes over a row hand to each other, in LDS.
 struct cut_state {
   float m;                                   // row maximum
+  float vlow, vtop;                          // smallest candidate, smallest value above them
   int n, found, bad;                         // candidates, selection done, a NaN in the row
   uint32_t bin_lo, bin_hi, before, upto;     // bins the cut can lie in, running sum before the first and up to the last
   uint32_t kkey, cut;
@@ -348,10 +348,20 @@ __device__ inline void over_row(const LT *row, int V, int tid, F &&f, G &&after_
     for (int u = 0; u < U; ++u) f(base + u * R * STEP, v[u]);
     after_round(r, v);
   }
-  for (int base = R * U * STEP + tid * 8; base < V; base += STEP) {
-    float v[8];
-    loader<LT>::load8(row, base, V, -INFINITY, v);
-    f(base, v);
+  // the rest, less than a round, with its loads issued together too: groups beyond the row load its last eight ids and are left out
+  const int rest = R * U * STEP + tid * 8;
+  if (R * U * STEP >= V) return;
+  float v[U][8];
+  if (V >= 8) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) loader<LT>::load8_fast(row, min(rest + u * STEP, V - 8), v[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i0 = rest + u * STEP;
+    if (i0 >= V) continue;
+    if (i0 + 8 > V) loader<LT>::load8(row, i0, V, -INFINITY, v[u]);
+    f(i0, v[u]);
   }
 }
 
@@ -624,10 +634,19 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
       for (int u = 0; u < U; ++u) add8(base + u * STEP, v[u], std::true_type{});
     }
   }
-  for (; base < V; base += STEP) {
-    float v[8];
-    loader<uint16_t>::load8(row, base, V, -INFINITY, v);
-    add8(base, v, std::false_type{});
+  if (base < V) {   // the rest, at most a round: as in over_row
+    float v[U][8];
+    if (V >= 8) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) loader<uint16_t>::load8_fast(row, min(base + u * STEP, V - 8), v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i0 = base + u * STEP;
+      if (i0 >= V) continue;
+      if (i0 + 8 > V) loader<uint16_t>::load8(row, i0, V, -INFINITY, v[u]);
+      add8(i0, v[u], std::false_type{});
+    }
   }
   __syncthreads();
   if (tid >= 64) return;
@@ -784,16 +803,17 @@ __device__ __host__ inline bool cut_takes_one_pass(int top_k, int V) { return to
 // bins (cut_narrow).  Rows with NaN or an infinite maximum, a top-k beyond the list, a top-p too close to 1 for the sums of the
 // first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
 // Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
-// arithmetic of a single compute unit with few rows.  Measured on 166 rows x 128256 fp32, N(0, 3), T = 0.8, against passes by
-// digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
+// arithmetic of a single compute unit with few rows (71 rows of a flat law, top-p 0.9: two passes of about 19 us, 47.6 in all).  204 rows, top-k 50
+// and top-p 0.9, 29.5 us: 16 of them the stream, 4.5 the bound from the first round, 6 the list.  Measured on 166 rows x 128256 fp32,
+// N(0, 3), T = 0.8, against passes by digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
 // passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
 // (74); logits rounded to whole numbers, top-p 0.99 110 (110).
 template <typename LT, bool STATS>
-__global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logits, int V, int nc, const int32_t *__restrict__ off,
-                                                     const float *__restrict__ temperature, const float *__restrict__ top_p,
-                                                     const int32_t *__restrict__ top_k, float *pmax, double *psum, int32_t *parg,
+__global__ __launch_bounds__(kCutThreads) void k_cut(const int32_t *__restrict__ off, int B, int V, const int32_t *__restrict__ done,
+                                                     const LT *__restrict__ logits, const float *__restrict__ temperature,
+                                                     const float *__restrict__ top_p, const int32_t *__restrict__ top_k, int nc, int digits, float *pmax, double *psum, int32_t *parg,
                                                      uint32_t *__restrict__ nuc_key, double *__restrict__ nuc_S,
-                                                     int32_t *__restrict__ nuc_near, const int32_t *__restrict__ done, int B, int digits) {
+                                                     int32_t *__restrict__ nuc_near) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x;
   if (done && done[r] == 1) return;   // k_cut_window has settled this row
   int b = -1;   // the row's request: the last one whose first row, off[b] + b, is not beyond r (every wave by itself)
@@ -874,10 +894,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
       over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
         if (!sampled) {   // block-uniform
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            bad |= v[j] != v[j];
-            mx = fmaxf(mx, v[j]);
-          }
+          for (int j = 0; j < 8; ++j) bad |= v[j] != v[j];
           return;
         }
         bool any = false;
@@ -892,6 +909,14 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         }
       }, [&](int round, const auto &v) {
         if (round != 0) return;
+        float own[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          own[u] = v[u][0];
+#pragma unroll
+          for (int j = 1; j < 8; ++j) own[u] = fmaxf(own[u], v[u][j]);
+          mx = fmaxf(mx, own[u]);
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
         if (lane == 0) st.w32[w] = __float_as_uint(mx);
@@ -899,14 +924,14 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         for (int i = 0; i < kCutThreads / 64; ++i) mx = fmaxf(mx, __uint_as_float(st.w32[i]));
         m = mx;
         bad |= !(fabsf(m) < INFINITY);
+        // Of every eight tokens the largest is filed: where these reach top_k, so do the tokens.  (All of them took 4 us longer; for the
+        // largest top_k of this form 1.04 times as many tokens lie above the bound.)
         if (fabsf(m) < INFINITY) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const uint32_t bin = bin_of(v[u][j]);
-              if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
-            }
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t bin = bin_of(own[u]);
+            if (bin < kCutBins - 1) atomicAdd(&hist[bin], 1u);
+          }
         }
         __syncthreads();   // (the bins are complete, and w32 has been read)
         cut_find_bins(hist, (uint32_t)tk, (uint32_t)tk, &st);
@@ -960,28 +985,56 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         crowded = (float)(st.upto - st.before) * __builtin_amdgcn_exp2f((float)lo / kCutBinsPerLog2) > scale * (float)kCutList;
       }
       // ---- pass 2: candidates, and the mass above them ----
-      if (fast && !crowded)
+      if (fast && !crowded) {
+        // The values at the bins' edges, exactly: the smallest whose bin is at most `bin`, found by a wave among the keys from -inf to the
+        // maximum (64 a step), so that two comparisons place a token.  The pass is bound by the instructions a single compute unit
+        // issues for its row: a flat law has most of its mass above the cut, so the mass is summed without a branch per token.
+        auto edge = [&](uint32_t bin) {
+          uint32_t below = okey(-INFINITY), at = okey(m);
+          while (at - below > 1u) {
+            const uint64_t d = at - below;
+            const uint32_t key = below + (uint32_t)((d * (uint32_t)(lane + 1)) >> 6);
+            const int f = (int)__builtin_ctzll(__ballot(bin_of(okey_value(key)) <= bin));   // (lane 63 holds `at`)
+            at = below + (uint32_t)((d * (uint32_t)(f + 1)) >> 6);
+            below += (uint32_t)((d * (uint32_t)f) >> 6);
+          }
+          return okey_value(at);
+        };
+        if (w == 0) st.vlow = edge(hi);
+        if (w == 1) st.vtop = lo ? edge(lo - 1) : INFINITY;
+        __syncthreads();
+        const float vlow = st.vlow, vtop = st.vtop;
         over_row<LT>(row, V, tid, [&](int, const float(&v)[8]) {
+          uint32_t mask = 0u;   // candidates are few: noted, and put afterwards
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            const uint32_t bin = bin_of(v[j]);
-            if (bin > hi) continue;
-            if (bin < lo) above += floor((double)exp_scaled(v[j] - m, k) * kNucScale + 0.5);
-            else put(v[j]);
+            const float d = v[j] - m, e = __builtin_amdgcn_exp2f(fmaf(d, k.lo, d * k.hi));   // (of a token above the candidates: not small)
+            above += floor((double)(v[j] >= vtop ? e : 0.f) * kNucScale + 0.5);
+            mask |= v[j] >= vlow && !(v[j] >= vtop) ? 1u << j : 0u;
+          }
+          while (mask) {
+            const int j = __builtin_ctz(mask);
+            mask &= mask - 1u;
+            const float a0 = (j & 1) ? v[1] : v[0], a1 = (j & 1) ? v[3] : v[2], a2 = (j & 1) ? v[5] : v[4], a3 = (j & 1) ? v[7] : v[6];
+            const float b0 = (j & 2) ? a1 : a0, b1 = (j & 2) ? a3 : a2;
+            put((j & 4) ? b1 : b0);
           }
         }, [](int, const auto &) {});
+      }
     }
     // sums over the block: the mass above, and the total
-    unsigned long long ta = (unsigned long long)above, tt = (unsigned long long)tot;
+    unsigned long long A = 0ull, all = 0ull;   // (the one-pass form has neither)
+    if (!one_pass) {
+      unsigned long long ta = (unsigned long long)above, tt = (unsigned long long)tot;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      ta += __shfl_xor(ta, o, 64);
-      tt += __shfl_xor(tt, o, 64);
+      for (int o = 32; o > 0; o >>= 1) {
+        ta += __shfl_xor(ta, o, 64);
+        tt += __shfl_xor(tt, o, 64);
+      }
+      if (lane == 0) { st.w64[w] = ta; st.t64[w] = tt; }
+      __syncthreads();
+      for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
     }
-    if (lane == 0) { st.w64[w] = ta; st.t64[w] = tt; }
-    __syncthreads();
-    unsigned long long A = 0ull, all = 0ull;
-    for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
     double total = (double)all;
     const int n = st.n;
     crowded |= n > kCutList && fast && !use_k;   // block-uniform
@@ -998,8 +1051,9 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
         __syncthreads();
         const uint32_t mine = lkey[i];
         uint32_t rank = 0u;
-#pragma unroll 4
-        for (int x = part * 64; x < part * 64 + 64; x += 4) {
+#pragma unroll
+        for (int y = 0; y < 64; y += 4) {
+          const int x = part * 64 + y;
           const uint4 kx = *reinterpret_cast<const uint4 *>(lkey + x);
           rank += (kx.x > mine || (kx.x == mine && x < i)) + (kx.y > mine || (kx.y == mine && x + 1 < i)) +
                   (kx.z > mine || (kx.z == mine && x + 2 < i)) + (kx.w > mine || (kx.w == mine && x + 3 < i));
@@ -1120,30 +1174,46 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const LT *__restrict__ logi
 
 #define FSV_MAX_GAMMA 16
 
-// Eight ids' masses from their logits and draft probabilities: p, or (residual) max(0, p - q); their sum in id order.
-__device__ inline double masses_of(const float (&lv)[8], const float (&qv)[8], float m, exp_scale k, double invS, bool residual,
-                                   uint32_t cutkey, double (&mass)[8]) {
+// The tokens a cut key keeps: those whose logit is not below the value the key stands for.  Only where that value is a zero (the keys tell
+// -0 from +0) or no number are the keys themselves compared.
+struct cut_test {
+  float value;
+  uint32_t key;   // 0: `value` decides
+};
+__device__ inline cut_test make_cut_test(uint32_t key) {   // 0: nothing is cut
+  const float v = okey_value(key);
+  if (key && !(v < 0.f) && !(v > 0.f)) return cut_test{-INFINITY, key};
+  return cut_test{key ? v : -INFINITY, 0u};
+}
+
+// Eight ids' masses from their logits and draft probabilities: p, or (RES) max(0, p - q); their sum in id order.  This is what the
+// vocabulary-wide part of k_decide consists of besides its loads: 12 instructions an id.
+template <bool RES>
+__device__ inline double masses_of(float (&lv)[8], const float (&qv)[8], float m, exp_scale k, double invS, cut_test cut, double (&mass)[8]) {
+  if (cut.key) {   // (uniform)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) lv[j] = okey(lv[j]) >= cut.key ? lv[j] : -INFINITY;
+  }
   double t = 0.0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    double p = (okey(lv[j]) >= cutkey) ? (double)exp_scaled(lv[j] - m, k) * invS : 0.0;  // cutkey 0: nothing is cut
-    if (residual) {
-      p -= (double)qv[j];
-      p = p > 0.0 ? p : 0.0;
-    }
-    mass[j] = p;
-    t += p;
+    const float d = lv[j] - m, z = fmaxf(fmaf(d, k.lo, d * k.hi), -160.f);   // exp_scaled; a NaN and -inf end as 0 here, too
+    const double e = (double)(lv[j] >= cut.value ? __builtin_amdgcn_exp2f(z) : 0.f);
+    const double p = RES ? fma(e, invS, -(double)qv[j]) : e * invS;
+    mass[j] = RES ? fmax(p, 0.0) : p;
+    t += mass[j];
   }
   return t;
 }
 
 template <typename LT>
-__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, float m, exp_scale k, double invS, bool residual, uint32_t cutkey,
+__device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0, int V, float m, exp_scale k, double invS, bool residual, cut_test cut,
                                        double (&mass)[8]) {
   float lv[8], qv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   loader<LT>::load8(lrow, i0, V, -INFINITY, lv);
-  if (residual) loader<float>::load8(qrow, i0, V, 0.f, qv);
-  return masses_of(lv, qv, m, k, invS, residual, cutkey, mass);
+  if (!residual) return masses_of<false>(lv, qv, m, k, invS, cut, mass);
+  loader<float>::load8(qrow, i0, V, 0.f, qv);
+  return masses_of<true>(lv, qv, m, k, invS, cut, mass);
 }
 
 #define FSV_MAX_NSB 160
@@ -1161,13 +1231,15 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
 // Phase 3: the blocks of a request take a ticket; the one that draws the last ticket adds the sub-block masses up (lane sums
 //   and their scan), finds the sub-block and the id by inverse CDF, writes every output of the request (accepted length,
 //   token, flags, rollback) and clears the ticket for the next call.
+// Bound by its chain of round trips (3.5 us to the accepted prefix, 6 from the last mass to the token) around a stream of two rows.  Five waves on
+// a SIMD, so that a call of 64 requests x 152064 ids (1216 blocks) is resident at once; with 193 registers two were, and the second half of the
+// blocks began 10 us late.  That and the shorter arithmetic of masses_of: 23.9 -> 20 us.
 template <typename LT>
-__global__ __launch_bounds__(256) void k_decide(
-    const LT *__restrict__ logits, int V, int nc, int nsb, const int32_t *__restrict__ off,
-    const int32_t *__restrict__ draft, const float *__restrict__ q, const float *__restrict__ u_acc,
-    const float *__restrict__ u_smp, const float *__restrict__ temperature, const float *__restrict__ pmax,
-    const double *__restrict__ psum, const int32_t *__restrict__ parg, const uint32_t *__restrict__ nuc_key,
-    const double *__restrict__ nuc_S, const int32_t *__restrict__ nuc_near, double *__restrict__ bsum,
+__global__ __launch_bounds__(256, 5) void k_decide(
+    const int32_t *__restrict__ off, const float *__restrict__ temperature, const float *__restrict__ pmax,
+    const double *__restrict__ psum, const int32_t *__restrict__ parg, const int32_t *__restrict__ draft, int V, int nc, int nsb,
+    const LT *__restrict__ logits, const float *__restrict__ q, const float *__restrict__ u_acc,
+    const float *__restrict__ u_smp, const uint32_t *__restrict__ nuc_key, const double *__restrict__ nuc_S, const int32_t *__restrict__ nuc_near, double *__restrict__ bsum,
     int32_t *__restrict__ ticket, int32_t *__restrict__ accepted_len, int32_t *__restrict__ next_token,
     uint32_t *__restrict__ flags, const int32_t *__restrict__ seq_lens, int32_t *__restrict__ new_seq_lens,
     int32_t *__restrict__ pages_released, int page_size) {
@@ -1288,7 +1360,7 @@ __global__ __launch_bounds__(256) void k_decide(
   const int tau = s_tau;
   bool residual = tau < gamma;
   const double m = s_m[tau], invS = 1.0 / s_S[tau];
-  const uint32_t cutkey = nuc_key ? nuc_key[rs + tau] : 0u;
+  const cut_test cut = make_cut_test(nuc_key ? nuc_key[rs + tau] : 0u);
   const exp_scale k = make_exp_scale(kLog2e / (double)T);
   const LT *lrow = logits + (size_t)(rs + tau) * V;
   const float *qrow = residual ? q + (size_t)(o + tau) * V : nullptr;
@@ -1306,14 +1378,17 @@ __global__ __launch_bounds__(256) void k_decide(
         if (residual) {
 #pragma unroll
           for (int part = 0; part < PARTS; ++part) loader<float>::load8_fast(qrow, sb * FSV_SBK + part * 512 + lane * 8, qv[part]);
-        }
 #pragma unroll
-        for (int part = 0; part < PARTS; ++part) tot += masses_of(lv[part], qv[part], (float)m, k, invS, residual, cutkey, mass);
+          for (int part = 0; part < PARTS; ++part) tot += masses_of<true>(lv[part], qv[part], (float)m, k, invS, cut, mass);
+        } else {
+#pragma unroll
+          for (int part = 0; part < PARTS; ++part) tot += masses_of<false>(lv[part], qv[part], (float)m, k, invS, cut, mass);
+        }
       } else {
 #pragma unroll 1
         for (int part = 0; part < PARTS; ++part)
           tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, (float)m, k, invS,
-                                   residual, cutkey, mass);
+                                   residual, cut, mass);
       }
 #pragma unroll
       for (int sh = 32; sh > 0; sh >>= 1) tot += __shfl_xor(tot, sh, 64);
@@ -1393,7 +1468,7 @@ __global__ __launch_bounds__(256) void k_decide(
     for (int sb = 0; sb < nsb; ++sb) {
       double mass[8], tot;
       double t = thread_masses<LT>(lrow, qrow, sb * FSV_SBK + tid * 8, V, (float)m, k, invS,
-                                   false, cutkey, mass);
+                                   false, cut, mass);
       block_incl_scan(t, s_w, &tot);
       if (tid == 0) s_sb[sb] = tot;
     }
@@ -1406,7 +1481,7 @@ __global__ __launch_bounds__(256) void k_decide(
   const double lo = s_lo;
   double mass[8];
   const int i0 = sb * FSV_SBK + tid * 8;
-  double t = thread_masses<LT>(lrow, qrow, i0, V, (float)m, k, invS, residual, cutkey, mass);
+  double t = thread_masses<LT>(lrow, qrow, i0, V, (float)m, k, invS, residual, cut, mass);
   double incl = block_incl_scan(t, s_w, nullptr);
   // the first thread whose running mass crosses, and the last id with mass: a ballot per wave (LDS atomics of all 256 threads
   // on one address cost 3 us here).  Only a thread and an id that hold mass can be taken: lane sums, their scan and the sums
@@ -1493,8 +1568,8 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
                           whole_rounds(V) > 0 && nc <= kCutThreads;
   if (!skip_stats) {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_STATS, (double)M * V * sizeof(LT));
-    hipLaunchKernelGGL((k_row_stats<LT>), dim3(fsv_ceil_div(nc, 4), gmax + 1, B), dim3(256), 0, s, logits, V, nc,
-                       b->draft_offsets, b->temperature, c->pmax, c->psum, c->parg, 0);
+    hipLaunchKernelGGL((k_row_stats<LT>), dim3(fsv_ceil_div(nc, 4), gmax + 1, B), dim3(256), 0, s, b->draft_offsets,
+                       b->temperature, logits, V, nc, c->pmax, c->psum, c->parg, 0);
   }
   if (nucleus) {
     // bytes: every row once, what no form can do without; how many passes a row takes is decided on the device
@@ -1510,8 +1585,8 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
     }
 #undef FSV_WINDOW
 #define FSV_CUT(ST)                                                                                                                      \
-  hipLaunchKernelGGL((k_cut<LT, ST>), dim3(M), dim3(kCutThreads), 0, s, logits, V, nc, b->draft_offsets, b->temperature, b->top_p, b->top_k, \
-                     c->pmax, c->psum, c->parg, c->nuc_key, c->nuc_S, c->nuc_near, window ? c->nuc_done : nullptr, B, digits)
+  hipLaunchKernelGGL((k_cut<LT, ST>), dim3(M), dim3(kCutThreads), 0, s, b->draft_offsets, B, V, window ? c->nuc_done : nullptr, logits, \
+                     b->temperature, b->top_p, b->top_k, nc, digits, c->pmax, c->psum, c->parg, c->nuc_key, c->nuc_S, c->nuc_near)
     if constexpr (sizeof(LT) == 4) {
       if (skip_stats) FSV_CUT(true);
       else FSV_CUT(false);
@@ -1522,9 +1597,8 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
   }
   {
     fsv_prof_scope ps(c, s, FSV_K_SAMPLE_DECIDE, (double)B * V * (sizeof(LT) + 4));
-    hipLaunchKernelGGL(k_decide<LT>, dim3(fsv_ceil_div(nsb, 4), B), dim3(256), 0, s, logits, V, nc, nsb, b->draft_offsets,
-                       b->draft_tokens, b->draft_probs, b->u_accept, b->u_sample, b->temperature, c->pmax, c->psum, c->parg,
-                       nucleus ? c->nuc_key : nullptr, nucleus ? c->nuc_S : nullptr, nucleus ? c->nuc_near : nullptr, c->bsum,
+    hipLaunchKernelGGL(k_decide<LT>, dim3(fsv_ceil_div(nsb, 4), B), dim3(256), 0, s, b->draft_offsets, b->temperature, c->pmax,
+                       c->psum, c->parg, b->draft_tokens, V, nc, nsb, logits, b->draft_probs, b->u_accept, b->u_sample, nucleus ? c->nuc_key : nullptr, nucleus ? c->nuc_S : nullptr, nucleus ? c->nuc_near : nullptr, c->bsum,
                        c->sel_ticket, acc, r->next_token, r->flags, with_rollback ? b->seq_lens : nullptr,
                        with_rollback ? r->new_seq_lens : nullptr, with_rollback ? r->pages_released : nullptr,
                        c->d.page_size);
@@ -1557,8 +1631,8 @@ int fsv_launch_draft_law(fsv_ctx *c, const float *z, const fsv_batch *b, int all
   for (int i = 0; i < B; ++i) gmax = max(gmax, b->draft_offsets_host[i + 1] - b->draft_offsets_host[i]);
   const int rows = gmax + 1 - last;   // widest request
   if (rows < 1) return FSV_OK;
-  hipLaunchKernelGGL((k_row_stats<float, true>), dim3(fsv_ceil_div(c->nc, 4), rows, B), dim3(256), 0, s, z, V, c->nc, b->draft_offsets,
-                     b->temperature, c->pmax, c->psum, c->parg, last);
+  hipLaunchKernelGGL((k_row_stats<float, true>), dim3(fsv_ceil_div(c->nc, 4), rows, B), dim3(256), 0, s, b->draft_offsets, b->temperature,
+                     z, V, c->nc, c->pmax, c->psum, c->parg, last);
   hipLaunchKernelGGL(k_draft_law, dim3(fsv_ceil_div(V, LAW_IDS), rows, B), dim3(256), 0, s, z, V, c->nc, b->draft_offsets,
                      b->temperature, c->pmax, c->psum, all_rows, q);
   FSV_HIP(c, hipGetLastError());

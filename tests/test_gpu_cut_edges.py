@@ -1,0 +1,59 @@
+"""What the cut keeps where a comparison of values, or of the largest of eight tokens, could differ from the order of the keys: a cut at a
+zero (the keys tell -0 from +0), and the most probable tokens side by side in a few groups of eight."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_00644_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _sample(lg, off, T, u, top_k, top_p=None):
+    from paper_2601_00644_amd import flexverify as fv
+    B, V = len(T), lg.shape[1]
+    t = lambda a: torch.as_tensor(a).cuda()
+    ctx = fv.Context(synth.ModelCfg("sampler", 0, 0, 0, 0, 0, 0, V, "bf16"), None, B, 16, sampler_only=True)
+    batch = fv.DeviceBatch(None, None, t(off), t(np.zeros(1, np.int32)), torch.zeros((1, V), device="cuda"), t(np.zeros(1, np.float32)), t(u), t(T),
+                           None, None, None, 0, None, off, T)
+    batch.top_k_host = np.full(B, top_k, np.int32)
+    batch.top_k = t(batch.top_k_host)
+    if top_p is not None:
+        batch.top_p_host = np.full(B, top_p, np.float32)
+        batch.top_p = t(batch.top_p_host)
+    res = fv.DeviceResult.alloc(B)
+    ctx.sample(lg, batch, res)
+    out = res.next_token.cpu().numpy(), res.flags.cpu().numpy()
+    ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("V", [512, 40004])
+@pytest.mark.parametrize("top_k,kept", [(3, [5, 10, 20]), (4, [5, 10, 20, 30, 40])])
+def test_a_cut_at_zero(top_k, kept, V, dtype):
+    B = 32
+    row = torch.full((V,), -3.0)
+    row[5], row[10], row[20], row[30], row[40] = 1.0, 0.0, 0.0, -0.0, -0.0
+    u = ((np.arange(B) + 0.5) / B).astype(np.float32)
+    tok, _ = _sample(row.to(dtype).cuda().expand(B, V).contiguous(), np.zeros(B + 1, np.int32), np.ones(B, np.float32), u, top_k)
+    p = np.exp(row.double().numpy()[kept])
+    c = np.cumsum(p) / p.sum()
+    want = np.asarray(kept)[(c[None, :] > u[:, None]).argmax(1)]
+    assert (tok == want).all()
+
+
+@pytest.mark.parametrize("V", [32776, 98307, 152064])
+@pytest.mark.parametrize("top_k", [50, 341])
+def test_top_tokens_side_by_side(V, top_k, monkeypatch):
+    B = 16
+    g = torch.Generator().manual_seed(V)
+    lg = torch.randn((B, V), generator=g)
+    for i in range(7):                                   # 56 tokens in seven groups
+        lg[:, 4096 * i + 8 * i:4096 * i + 8 * i + 8] += 8.0
+    u = ((np.arange(B) + 0.5) / B).astype(np.float32)
+    out = []
+    for full in ("0", "1"):
+        monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
+        out.append(_sample(lg.cuda(), np.zeros(B + 1, np.int32), np.full(B, 0.8, np.float32), u, top_k, 0.95))
+    assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
