@@ -40,7 +40,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 constexpr int KC = 8;     // 16-wide k blocks per chunk (128 contraction elements)
 constexpr int NST = 3;    // LDS stages of the activation ring
-constexpr int GRAN = 2;   // chunks per 256-element granule of the K cut
+constexpr int GRAN = 2;   // chunks per 256-element granule of the K cut: a split has an even number of chunks
 constexpr int NLD = 2;    // loader waves per block: two halve the time of the first fills, which matters for the short split-K blocks
 
 // Loader wave lw of a block: activation chunk `it` -> LDS stage it % NST, one 1 KiB row of units per instruction; loader
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restric
   constexpr uint32_t OOB = 0xFFFF0000u;  // a chunk beyond the K range: the descriptor returns zeros, no memory traffic
   bf16x8_t wb[D + 1][KC];   // sixteen bytes of operand per lane; the element type only matters to the MFMA below
   auto issue = [&](int it, bf16x8_t(&dst)[KC]) {
-    const uint32_t off = (it < per) ? wbase + (uint32_t)(cb0 + it) * (KC * 1024u) : OOB;
+    const uint32_t off = (D == 1 || it < per) ? wbase + (uint32_t)(cb0 + it) * (KC * 1024u) : OOB;
 #pragma unroll
     for (int kb = 0; kb < KC; ++kb)
       dst[kb] = __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(wrs, off + kb * 1024u, 0, 2));
@@ -180,18 +180,38 @@ __global__ __launch_bounds__(64 * (NCW + NLD)) void k_gemm(const void *__restric
     }
   };
   // Step s of an unrolled round consumes buffer s and refills the buffer consumed just before it with the chunk D
-  // ahead; buffers rotate by name.  Steps past the K range are skipped whole, so that every wave of the block meets
-  // exactly 1 + per barriers.
-  for (int it = 0; it < per; it += D + 1) {
+  // ahead; buffers rotate by name.
+  auto step = [&](int it, bool refill, bf16x8_t(&use)[KC], bf16x8_t(&next)[KC]) __attribute__((always_inline)) {
+    if (refill) issue(it + D, next);
+    __builtin_amdgcn_sched_barrier(0);
+    consume(it, use);
+    FSV_BARRIER();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (D == 1) {
+    // The last two chunks (a split has an even number of them) follow apart, so that nothing is loaded beyond the K range: loads that
+    // return zeros hold the unit's load path as long as any others, and with a branch around them the compiler would wait for more
+    // than it uses.
+    int it = 0;
+    for (; it + 2 < per; it += 2) {
+      step(it, true, wb[0], wb[1]);
+      step(it + 1, true, wb[1], wb[0]);
+    }
+    step(it, true, wb[0], wb[1]);
+    step(it + 1, false, wb[1], wb[0]);
+  } else {
+    // Steps past the K range are skipped whole, so that every wave of the block meets exactly 1 + per barriers.
+    for (int it = 0; it < per; it += D + 1) {
 #pragma unroll
-    for (int s = 0; s <= D; ++s) {
-      issue(it + s + D, wb[(s + D) % (D + 1)]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (it + s < per) {
-        consume(it + s, wb[s]);
-        FSV_BARRIER();
+      for (int s = 0; s <= D; ++s) {
+        issue(it + s + D, wb[(s + D) % (D + 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (it + s < per) {
+          consume(it + s, wb[s]);
+          FSV_BARRIER();
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
