@@ -635,65 +635,94 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
 int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   const fsv_model_desc &d = c->d;
   int max_rows = 0, longest = 0;
-  long total_tiles = 0, row_tiles = 0, items = 0;   // total: in units of the cost of a tile of a request with one query-row tile
+  long row_tiles = 0, items = 0;
   auto rtc_of = [&](int g) { return fsv_ceil_div(c->group * (g + 1), 32); };
-  auto w16_of = [&](int g) {
-    const int rtc = rtc_of(g);
-    return pl->split || rtc <= 1 ? 16 : rtc == 2 ? c->attn_w2 : c->attn_w3;
-  };
   for (int i = 0; i < b->batch; ++i) {
     const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
     const int n = fsv_ceil_div(nk, 32);
     max_rows = max(max_rows, c->group * (g + 1));
     longest = max(longest, n);
-    total_tiles += ((long)n * w16_of(g) + 15) / 16;
     row_tiles += rtc_of(g);
     items += (long)n * rtc_of(g);
     pl->kv_tokens += nk;
   }
-  // Row tiles as parts of their own, which read the same keys (neighbouring blocks, on one XCD with eight kv heads), while they leave a wave at most
-  // four (row tile, key tile) pairs: every block then has the short chain of one row tile, and a request's merge is spread over as many
-  // blocks.  Beyond, the row tiles of a request share the keys they read.  Calls of the stand-alone entry in a graph, head size 128, eight kv
-  // heads, shared and split: one request of 1600 positions, two row tiles 23.5 and 18.2 us, three 32.4 and 18.3; 16 of 800 .. 1600, two
-  // 34.2 and 28.4; past the line 16 of 1600 .. 3200 43.4 and 45.9, 48 of 800 .. 1600 55.1 and 57.9.
-  pl->split = max_rows > 32 && items * d.n_kv_heads <= 32l * c->n_cus && row_tiles * d.n_kv_heads <= c->n_cus;
-  if (pl->split) total_tiles = items;
-  pl->rt = pl->split ? 1 : fsv_ceil_div(max_rows, 32);
-  // Waves per block.  Eight, one block per compute unit, while requests are few: a part then takes an eighth of its tiles' time.  Four, two blocks per
-  // compute unit, from 192 (request, kv head) pairs on, so that a request need not be cut, and one block computes while the other
-  // starts or merges; where the queries leave room for it (not with head size 128 and more than one row tile).  Head size 64, whole call
-  // of the stand-alone entry: 8 requests of 2000 .. 6000 positions 24.8 us with eight, 28.6 with four; 24 of 200 .. 1000 16.6 and 16.6; 54 of 1000
-  // 36.8 and 28.5.  Three row tiles of head size 128: four waves, one block (eight waves' rings and the queries exceed the LDS).
-  const bool two_blocks = d.head_dim == 64 || pl->rt == 1, wide_q = d.head_dim == 128 && pl->rt > 2;
-  pl->nw = wide_q || (two_blocks && b->batch * d.n_kv_heads >= 192) ? 4 : 8;
-  // One round if it can be had: the smallest part length, up to twice the even share, for which parts x kv heads fit the
-  // compute units.  Otherwise parts of up to five quarters of the even share in several rounds, the long ones first (a block costs 6 us besides
-  // its tiles, so few and long is right as long as the last round is short).  In the order of the requests, and in parts of half the share:
-  // 128 requests of 256 .. 8192 positions 240 us instead of 207, 2048 prefill rows 127 and 119.
-  const int target = c->attn_wave_target * (pl->nw == 4 && !wide_q ? 2 : 1);
-  auto count = [&](int tpw, int most) {   // parts x kv heads; counted no further than `most`
-    int parts = 0;
-    for (int i = 0; i < b->batch && parts * d.n_kv_heads <= most; ++i) {
-      const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
-      int tp;
-      parts += attn_parts(fsv_ceil_div(nk, 32), tpw, w16_of(g), pl->nw, &tp) * (pl->split ? rtc_of(g) : 1);
+  // The schedule with the row tiles of a request together or (split) as parts of their own; cost16: of its longest part, in 1/16 of a tile of
+  // a request with one row tile.
+  struct cut { int rt, nw, tpw, blocks, cost16; bool sorted; };
+  auto cut_for = [&](bool split) {
+    cut k{};
+    auto w16_of = [&](int g) {
+      const int rtc = rtc_of(g);
+      return split || rtc <= 1 ? 16 : rtc == 2 ? c->attn_w2 : c->attn_w3;
+    };
+    k.rt = split ? 1 : fsv_ceil_div(max_rows, 32);
+    // Waves per block.  Eight, one block per compute unit, while requests are few: a part then takes an eighth of its tiles' time.  Four, two blocks per
+    // compute unit, from 192 (request, kv head) pairs on, so that a request need not be cut, and one block computes while the other
+    // starts or merges; where the queries leave room for it (not with head size 128 and more than one row tile).  Head size 64, whole call
+    // of the stand-alone entry: 8 requests of 2000 .. 6000 positions 24.8 us with eight, 28.6 with four; 24 of 200 .. 1000 16.6 and 16.6; 54 of 1000
+    // 36.8 and 28.5.  Three row tiles of head size 128: four waves, one block (eight waves' rings and the queries exceed the LDS).
+    const bool two_blocks = d.head_dim == 64 || k.rt == 1, wide_q = d.head_dim == 128 && k.rt > 2;
+    k.nw = wide_q || (two_blocks && b->batch * d.n_kv_heads >= 192) ? 4 : 8;
+    // One round if it can be had: the smallest part length, up to twice the even share, for which parts x kv heads fit the
+    // compute units.  Otherwise parts of up to five quarters of the even share in several rounds, the long ones first (a block costs 6 us besides
+    // its tiles, so few and long is right as long as the last round is short).  In the order of the requests, and in parts of half the share:
+    // 128 requests of 256 .. 8192 positions 240 us instead of 207, 2048 prefill rows 127 and 119.
+    const int target = c->attn_wave_target * (k.nw == 4 && !wide_q ? 2 : 1);
+    auto count = [&](int tpw, int most) {   // parts x kv heads; counted no further than `most`
+      int parts = 0;
+      k.cost16 = 0;
+      for (int i = 0; i < b->batch && parts * d.n_kv_heads <= most; ++i) {
+        const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
+        int tp;
+        parts += attn_parts(fsv_ceil_div(nk, 32), tpw, w16_of(g), k.nw, &tp) * (split ? rtc_of(g) : 1);
+        k.cost16 = max(k.cost16, tp * w16_of(g));
+      }
+      return parts * d.n_kv_heads;
+    };
+    long total_tiles = 0;   // in units of the cost of a tile of a request with one query-row tile
+    for (int i = 0; i < b->batch; ++i) {
+      const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], n = fsv_ceil_div(b->seq_lens_host[i] + g + 1, 32);
+      total_tiles += ((long)n * w16_of(g) + 15) / 16;
     }
-    return parts * d.n_kv_heads;
+    if (split) total_tiles = items;
+    // Fewest key tiles a part is given: two for each of eight waves, or one while that makes no more parts than the merge fetches at once
+    // (1600 positions, head size 128, one row tile 13.9 and 12.5 us; 3200 positions 16.2 and 18.3).
+    const int fewest = k.nw == 8 && longest <= 64 ? c->attn_min_tpw / 2 : c->attn_min_tpw;
+    const int even = (int)max((long)fewest, (total_tiles * d.n_kv_heads + target - 1) / target);
+    // Every request has a part, so with more pairs than blocks there is nothing to look for; otherwise at most 129 lengths are tried.
+    // (Host time of all lengths one by one, before the first launch: 128 requests of 256 .. 8192 positions 0.33 ms, of 8 .. 32 k 2.6 ms.)
+    for (int t = even; b->batch * d.n_kv_heads <= target && t <= 2 * even; t += max(1, even / 128)) {
+      if (count(t, target) <= target) { k.tpw = t; break; }
+    }
+    k.sorted = k.tpw == 0;
+    if (!k.tpw) k.tpw = max(8, even * 5 / 4);
+    k.blocks = count(k.tpw, INT_MAX);
+    return k;
   };
-  // Fewest key tiles a part is given: two for each of eight waves, or one while that makes no more parts than the merge fetches at once
-  // (1600 positions, head size 128, one row tile 13.9 and 12.5 us; 3200 positions 16.2 and 18.3).
-  const int fewest = pl->nw == 8 && longest <= 64 ? c->attn_min_tpw / 2 : c->attn_min_tpw;
-  const int even = (int)max((long)fewest, (total_tiles * d.n_kv_heads + target - 1) / target);
-  int tpw = 0;
-  // Every request has a part, so with more pairs than blocks there is nothing to look for; otherwise at most 129 lengths are tried.
-  // (Host time of all lengths one by one, before the first launch: 128 requests of 256 .. 8192 positions 0.33 ms, of 8 .. 32 k 2.6 ms.)
-  for (int t = even; b->batch * d.n_kv_heads <= target && t <= 2 * even; t += max(1, even / 128)) {
-    if (count(t, target) <= target) { tpw = t; break; }
+  // Row tiles as parts of their own, which read the same keys (neighbouring blocks, on one XCD with eight kv heads), while all fit the compute units
+  // at once and leave a wave at most four (row tile, key tile) pairs: every block then has the short chain of one row tile, and a request's merge
+  // is spread over as many blocks.  Beyond, the row tiles of a request share the keys they read.  Calls of the stand-alone entry in a graph, head
+  // size 128, eight kv heads, shared and split: one request of 1600 positions, two row tiles 23.5 and 18.2 us, three 32.4 and 18.3; 16 of 800 .. 1600, two
+  // 34.2 and 28.4; past the line 16 of 1600 .. 3200 43.4 and 45.9, 48 of 800 .. 1600 55.1 and 57.9.
+  // Past it the longest parts of both schedules decide, while they are short enough for the merge to show: split if the shared one's is at
+  // least 0.625 (head size 64) or 0.7 (128) of the split one's.  44 calls that this takes (drawn; in a graph): head size 64 0.99 .. 1.23 x as fast
+  // split, mean 1.05, head size 128 0.98 .. 1.15, mean 1.06 (16 requests of 512 .. 4096 positions, one of them with two row tiles, 34.7 and
+  // 32.8 us).  Of 50 calls it does not take all but six are slower split, down to 0.75 x.
+  const bool may = max_rows > 32 && row_tiles * d.n_kv_heads <= c->n_cus;
+  pl->split = may && items * d.n_kv_heads <= 32l * c->n_cus;
+  cut k = cut_for(pl->split);
+  if (may && !pl->split && !k.sorted && k.nw == 8 && k.cost16 <= 16 * (d.head_dim == 64 ? 66 : 42)) {
+    const cut s = cut_for(true);
+    if (!s.sorted && s.nw == 8 && (d.head_dim == 64 ? 8 * k.cost16 >= 5 * s.cost16 : 10 * k.cost16 >= 7 * s.cost16)) {
+      pl->split = true;
+      k = s;
+    }
   }
-  pl->sorted = tpw == 0;
-  if (!tpw) tpw = max(8, even * 5 / 4);
-  pl->tpw = tpw;
-  pl->waves = count(tpw, INT_MAX);
+  pl->rt = k.rt;
+  pl->nw = k.nw;
+  pl->tpw = k.tpw;
+  pl->sorted = k.sorted;
+  pl->waves = k.blocks;
   if (pl->waves > c->attn_wave_cap) FSV_FAIL(c, FSV_E_CAPACITY, "%d attention parts > %d the workspace holds", pl->waves, c->attn_wave_cap);
   if ((size_t)b->num_pages * d.n_kv_heads * 16 * d.head_dim * 2 > 0xFFFF0000ull)
     FSV_FAIL(c, FSV_E_UNSUPPORTED, "one layer of a KV pool must stay below 4 GiB (%d pages given)", b->num_pages);
