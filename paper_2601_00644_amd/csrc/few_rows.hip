@@ -9,7 +9,7 @@
 // block that reads the whole residual row can normalise it on the way in.  Five launches a layer instead of eight, and no split
 // sums in memory.
 //
-// One 1B request of five rows (2048 wide), per layer: q|k|v 6.3, o 3.9, gate|up 13.5 (67 MB: 5.0 TB/s), down 8.1 us (33.6 MB) against
+// One 1B request of five rows (2048 wide), per layer: q|k|v 6.0, o 3.9, gate|up 13.5 (67 MB: 5.0 TB/s), down 8.1 us (33.6 MB) against
 // 5.3 + 4.0 (rotation and append), 4.0 + 3.7 (sum and norm), 13.6 and 8.1 + 3.7; the call of 16 layers 914 -> 749 us.  8B, five rows, four
 // layers 473 -> 433: down 19.9 us (117 MB: 5.9 TB/s), o 7.0, gate|up 37, q|k|v 12.4.
 // Why up to 16 rows: every block reads and normalises all rows, which takes as long as a launch by then (16 rows: 1B 483 -> 426 us over
@@ -24,6 +24,8 @@
 using namespace fsv_bf16;
 
 namespace {
+
+typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 
 constexpr int FW = 8;                      // waves of a block
 constexpr uint32_t OOB = 0xFFFF0000u;      // beyond every descriptor: the load returns zeros and moves nothing
@@ -107,12 +109,14 @@ __global__ __launch_bounds__(64 * FW, 2) void k_few_norm(const void *__restrict_
   const int eft = tid >> 5, em = tid & 15, eg = (tid >> 4) & 1;
   const bool fin = tid < FT * 32 && em < M;
   const int eT = blockIdx.x * FT + eft, ehh = eT / tph, ei0 = (eT - ehh * tph) * 8 + 4 * eg;   // the thread's head and first pair
-  int4 place = make_int4(0, 0, 0, 0);
-  float4 t0 = make_float4(0.f, 0.f, 0.f, 0.f), t1 = t0;
+  // (Undefined in threads that finish nothing: any value there would have to be merged in behind a wait for all loads, and wave 0 would come to
+  // the barrier with its weights only: q|k|v of 1B, five rows, 6.3 -> 5.95 us.)
+  i32x4_t place;
+  f32x4_t t0, t1;
   if (KIND == FEW_QKV && fin) {
-    place = e.row_place[em];
-    t0 = *reinterpret_cast<const float4 *>(e.rope_tab + ((size_t)em * half + ei0) * 2);      // cos, sin, cos, sin
-    t1 = *reinterpret_cast<const float4 *>(e.rope_tab + ((size_t)em * half + ei0) * 2 + 4);
+    place = *reinterpret_cast<const i32x4_t *>(e.row_place + em);
+    t0 = *reinterpret_cast<const f32x4_t *>(e.rope_tab + ((size_t)em * half + ei0) * 2);      // cos, sin, cos, sin
+    t1 = *reinterpret_cast<const f32x4_t *>(e.rope_tab + ((size_t)em * half + ei0) * 2 + 4);
   }
 
   // ---- the rows' sums of squares ----
