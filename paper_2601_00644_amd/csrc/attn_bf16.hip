@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
         float tmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64)) * sc;
+        tmax = fmaxf(tmax, lane_xor<32>(tmax)) * sc;
         // Lazy reference: the running reference m only moves when the tile maximum exceeds it by more than 2^8
         // (probabilities then stay below 256, exact enough in fp32 / bf16), so the accumulators are almost never
         // rescaled; the first tile of a row needs no rescale either (its accumulators are still zero).
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
 #pragma unroll
     for (int rt = m0; rt < RT && rt < m0 + MS; ++rt) {
       if (rt >= rtc) continue;
-      const float ll = lrun[rt] + __shfl_xor(lrun[rt], 32, 64);
+      const float ll = lane_pair_sum<32>(lrun[rt]);
       const int at = (w * MS + rt - m0) * 32 + r;
       float *dst = area + at * OROW + 4 * h;
 #pragma unroll

@@ -24,11 +24,6 @@ __device__ inline uint16_t f2h(float f) {
 }
 __device__ inline float h2f(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
 __device__ inline uint32_t f2h2(float lo, float hi) { return (uint32_t)f2h(lo) | ((uint32_t)f2h(hi) << 16); }
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // Direct global -> LDS load of 64 x 16 bytes: lane i of the wave fills the i-th 16-byte unit at LDS byte offset `dst`.  An opaque
 // statement: the compiler makes every later LDS read wait for all such loads it knows of; the waits of these kernels are explicit.  (One

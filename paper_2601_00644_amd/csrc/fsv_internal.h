@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "flexverify.h"
+#include "wave_ops.h"
 
 #define FSV_WAVE 64
 
@@ -26,16 +27,12 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // ro
 #define FSV_CHUNK (FSV_SBK * FSV_SPC)
 
 // Sum of eight values over the wave, all eight at once: every exchange halves the values a lane still carries, so it takes
-// ten shuffles instead of forty-eight.  Lane l ends with the sum of value 4 l5 + 2 l4 + l3 (l5 .. l3: bits of l).
+// ten exchanges instead of forty-eight.  Lane l ends with the sum of value 4 l5 + 2 l4 + l3 (l5 .. l3: bits of l).
 __device__ inline float wave_sum8(float (&v)[8], int lane) {
-  auto fold = [lane](float lo, float hi, int off) {   // every index a constant: an array indexed by a loop would leave the registers
-    const float send = (lane & off) ? lo : hi, keep = (lane & off) ? hi : lo;
-    return keep + __shfl_xor(send, off, 64);
-  };
-  const float a0 = fold(v[0], v[4], 32), a1 = fold(v[1], v[5], 32), a2 = fold(v[2], v[6], 32), a3 = fold(v[3], v[7], 32);
-  float r = fold(fold(a0, a2, 16), fold(a1, a3, 16), 8);
-#pragma unroll
-  for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+  const float a0 = lane_fold<32>(v[0], v[4], lane), a1 = lane_fold<32>(v[1], v[5], lane);
+  const float a2 = lane_fold<32>(v[2], v[6], lane), a3 = lane_fold<32>(v[3], v[7], lane);
+  float r = lane_fold<8>(lane_fold<16>(a0, a2, lane), lane_fold<16>(a1, a3, lane), lane);
+  r = lanes_sum<4>(r);
   return r;
 }
 

@@ -8,12 +8,6 @@
 
 namespace {
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // The rows of a call, their embeddings and the cos, sin of their rotation angles (fp64 angles; the same in every layer), a block per
 // row: its request is the last one whose first row, off[b] + b, is not beyond it (every wave by itself, 64 requests at a time).  One launch instead of two: 2.2 + 2.4 -> 3.5 us for 5 rows, the angles included.
 __global__ void k_embed_rows(int B, int V, int d, const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ last_token,
@@ -44,7 +38,7 @@ __global__ void k_embed_rows(int B, int V, int d, const int32_t *__restrict__ se
 // the sum of squares costs an operation per element and saves a launch and a pass.  SWIGLU: columns n and n + N of w are gate
 // and up, y = silu(gate) up, for the same reason.  ROWS = 1 for a call of one row: seven repeated rows cost nothing on a small
 // matrix, but 131 MB of head take 34 us with them and 19 without (26 before rows were taken by eight).
-// Bound by latency at the sizes this path is for (5 rows, 256 .. 4096 columns): one round of loads and ten shuffles per eight
+// Bound by latency at the sizes this path is for (5 rows, 256 .. 4096 columns): one round of loads and ten exchanges per eight
 // rows.  Measured there: 3.4 .. 5.0 us per projection against 7.6 .. 15.3 us row by row plus 4.2 us per norm and 3.4 for SwiGLU.
 template <bool NORM, bool SWIGLU, int ROWS>
 __global__ __launch_bounds__(256) void k_linear(int M, int N, int K, float eps, const float *__restrict__ a, const float *__restrict__ g,
@@ -209,8 +203,7 @@ __global__ __launch_bounds__(ATT) void k_attention(int H, int Hkv, int hd, int m
   const int l16 = tid & 15;
   float mx = -INFINITY;
   auto score = [&](int j, float s) {   // all sixteen lanes of a key
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 16);
+    s = lanes_sum<8>(s);
     s *= scale;
     if (j < nkeys) {
       if (l16 == 0) sc[j] = s;
@@ -261,8 +254,7 @@ __global__ __launch_bounds__(ATT) void k_attention(int H, int Hkv, int hd, int m
       score(j, s);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  mx = lanes_max(mx);
   if (lane == 0) s_red[w] = mx;
   __syncthreads();
 #pragma unroll

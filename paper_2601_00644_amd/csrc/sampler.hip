@@ -138,7 +138,7 @@ __global__ void k_build_rows(int B, int V, const int32_t *seq_lens, const int32_
 }
 
 // One wave per 8192-id chunk of a row: all of the chunk's loads are issued before the first use (sixteen 16-byte loads
-// per lane for bf16), the maximum and the sum are reduced over the wave with shuffles, and no LDS or barrier is
+// per lane for bf16), the maximum and the sum are reduced over the wave, and no LDS or barrier is
 // involved; waves are independent, so a compute unit keeps a dozen of them streaming.
 // grid = (chunks / 4, largest gamma of the batch + 1, requests): row i of request b is logits row off[b] + b + i.
 // LAW: the statistics feed k_draft_law: greedy requests need none, and with drafts_only neither does a request's last row.
@@ -191,8 +191,7 @@ __global__ __launch_bounds__(256) void k_row_stats(const int32_t *__restrict__ o
     for (int p = 0; p < P; ++p)
 #pragma unroll
       for (int j = 0; j < 8; ++j) mx = fmaxf(mx, v[p][j]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    mx = lanes_max(mx);
     if (mx > -INFINITY) {  // wave-uniform; an all -inf chunk carries no mass
       // 2^{(l - max) k} with k in fp32: its rounding moves a term by 6e-8 of its own exponent, nothing for the terms
       // that carry the sum; ids beyond the vocabulary were loaded as -inf and come out as 0
@@ -204,8 +203,7 @@ __global__ __launch_bounds__(256) void k_row_stats(const int32_t *__restrict__ o
         for (int j = 0; j < 8; ++j) part += __builtin_amdgcn_exp2f((v[p][j] - mx) * k);
         sum += (double)part;
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      sum = lanes_sum(sum);
     } else if (LAW) {   // a NaN makes the whole law NaN, also where nothing else in its chunk carries mass
       bool nan = false;
 #pragma unroll
@@ -221,12 +219,7 @@ __global__ __launch_bounds__(256) void k_row_stats(const int32_t *__restrict__ o
       for (int j = 0; j < 8; ++j)
         if (v[p][j] > mx) { mx = v[p][j]; ai = base + p * 512 + j; }   // ids ascend with (p, j): the first maximum stays
     // wave (max, lowest id attaining it)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      float om = __shfl_xor(mx, off, 64);
-      int oi = __shfl_xor(ai, off, 64);
-      if (om > mx || (om == mx && oi < ai)) { mx = om; ai = oi; }
-    }
+    lanes_argmax(mx, ai);
   }
   if (lane == 0) {
     pmax[(size_t)r * nc + c] = mx;
@@ -236,7 +229,7 @@ __global__ __launch_bounds__(256) void k_row_stats(const int32_t *__restrict__ o
 }
 
 // The draft model's laws q = softmax(z / T_b), fp32, from its logits z and the chunk statistics k_row_stats left: every
-// block combines the row's chunks by itself (a few hundred bytes; chunks in lanes, fixed shuffle tree) and writes the law
+// block combines the row's chunks by itself (a few hundred bytes; chunks in lanes, fixed tree) and writes the law
 // of its LAW_IDS ids.  Two streaming passes over z (the second finds most of it in the memory-side cache) and one over q is
 // the bound.  Measured for 71 rows x 128256 (8B vocabulary, 55 drafts): 10 us for the statistics and 11 us here, against
 // 359 us for one block per row that went over the row three times, one value per load.
@@ -268,16 +261,14 @@ __global__ __launch_bounds__(256) void k_draft_law(const float *__restrict__ z, 
   }
   float mx = -INFINITY;
   for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
-#pragma unroll
-  for (int sh = 32; sh > 0; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh, 64));
+  mx = lanes_max(mx);
   const double invT = 1.0 / (double)T;
   double sum = 0.0;
   for (int c = lane; c < nc; c += 64) {
     const float pm = pmax[(size_t)r * nc + c];
     sum += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
   }
-#pragma unroll
-  for (int sh = 32; sh > 0; sh >>= 1) sum += __shfl_xor(sum, sh, 64);
+  sum = lanes_sum(sum);
   const float k = (float)(kLog2e / (double)T), inv = (float)(1.0 / sum);
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -410,8 +401,7 @@ __device__ inline bool cut_narrow(const LT *row, int V, float m, exp_scale k, ui
     }, [](int, const auto &) {});
     if (sum_above) {
       unsigned long long ta = (unsigned long long)above;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ta += __shfl_xor(ta, o, 64);
+      ta = lanes_sum(ta);
       if (lane == 0) st->w64[w] = ta;
     }
     __syncthreads();
@@ -559,16 +549,14 @@ __global__ __launch_bounds__(1024) void k_cut_window(const uint16_t *__restrict_
   if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
     float mx = -INFINITY;
     for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
-#pragma unroll
-    for (int o2 = 32; o2 > 0; o2 >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o2, 64));
+    mx = lanes_max(mx);
     double term = 0.0;
     const double invT = 1.0 / (double)T;
     for (int c = lane; c < nc; c += 64) {
       const float pm = pmax[(size_t)r * nc + c];
       term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
     }
-#pragma unroll
-    for (int o2 = 32; o2 > 0; o2 >>= 1) term += __shfl_xor(term, o2, 64);
+    term = lanes_sum(term);
     if (lane == 0) {
       s_m = mx;
       s_total = term * kNucScale;
@@ -757,8 +745,7 @@ __device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int 
         }
     }
     if (T > 0.f) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      mx = lanes_max(mx);
       if (mx > -INFINITY) {
         const float k = (float)(kLog2e / (double)T);
         for (int p0 = 0; p0 < P; p0 += P / 4) {
@@ -771,16 +758,10 @@ __device__ __attribute__((noinline)) void row_stats_by_block(const LT *row, int 
             sum += (double)part;
           }
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        sum = lanes_sum(sum);
       }
     } else {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float om = __shfl_xor(mx, o, 64);
-        const int oi = __shfl_xor(ai, o, 64);
-        if (om > mx || (om == mx && oi < ai)) { mx = om; ai = oi; }
-      }
+      lanes_argmax(mx, ai);
     }
     if (lane == 0) { pm[c] = mx; ps[c] = sum; pa[c] = ai; }
   }
@@ -846,16 +827,14 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const int32_t *__restrict__
     if (tid < 64) {   // the row's maximum and normaliser from the per-chunk statistics (chunks in lanes, 64 at a time)
       float mx = -INFINITY;
       for (int c = lane; c < nc; c += 64) mx = fmaxf(mx, pmax[(size_t)r * nc + c]);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      mx = lanes_max(mx);
       const double invT = 1.0 / (double)T;
       double term = 0.0;
       for (int c = lane; c < nc; c += 64) {
         const float pm = pmax[(size_t)r * nc + c];
         term += psum[(size_t)r * nc + c] * ((pm == mx) ? 1.0 : exp(((double)pm - (double)mx) * invT));
       }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
+      term = lanes_sum(term);
       if (lane == 0) { st.m = mx; st.S = term; }
     }
     __syncthreads();
@@ -917,8 +896,7 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const int32_t *__restrict__
           for (int j = 1; j < 8; ++j) own[u] = fmaxf(own[u], v[u][j]);
           mx = fmaxf(mx, own[u]);
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        mx = lanes_max(mx);
         if (lane == 0) st.w32[w] = __float_as_uint(mx);
         __syncthreads();
         for (int i = 0; i < kCutThreads / 64; ++i) mx = fmaxf(mx, __uint_as_float(st.w32[i]));
@@ -1026,11 +1004,8 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const int32_t *__restrict__
     unsigned long long A = 0ull, all = 0ull;   // (the one-pass form has neither)
     if (!one_pass) {
       unsigned long long ta = (unsigned long long)above, tt = (unsigned long long)tot;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        ta += __shfl_xor(ta, o, 64);
-        tt += __shfl_xor(tt, o, 64);
-      }
+      ta = lanes_sum(ta);
+      tt = lanes_sum(tt);
       if (lane == 0) { st.w64[w] = ta; st.t64[w] = tt; }
       __syncthreads();
       for (int i = 0; i < kCutThreads / 64; ++i) { A += st.w64[i]; all += st.t64[i]; }
@@ -1221,7 +1196,7 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
 // Acceptance tests, masses and token selection of one request.  grid = (ceil(sub-blocks / 4), requests).
 //
 // Phase 1, every block: the acceptance tests.  Sixteen lanes combine the per-chunk statistics of a row (up to three chunks per
-//   lane: row max with the lowest id attaining it, then the sum of the rescaled chunk sums over a fixed shuffle tree), all rows
+//   lane: row max with the lowest id attaining it, then the sum of the rescaled chunk sums over a fixed tree), all rows
 //   of the request side by side (four rows per wave one after the other took 3 us longer at 16 drafts); then thread i tests
 //   draft i+1 from two gathered scalars, and
 //   thread 0 takes the accepted prefix.  Every block of the request repeats this (a few KB from L2) instead of waiting
@@ -1297,20 +1272,14 @@ __global__ __launch_bounds__(256, 5) void k_decide(
 #pragma unroll
       for (int j = 1; j < CPL; ++j)
         if (pm[j] > mx || (pm[j] == mx && pa[j] < ai)) { mx = pm[j]; ai = pa[j]; }
-#pragma unroll
-      for (int sh = 8; sh > 0; sh >>= 1) {
-        const float om = __shfl_xor(mx, sh, 16);
-        const int oi = __shfl_xor(ai, sh, 16);
-        if (om > mx || (om == mx && oi < ai)) { mx = om; ai = oi; }
-      }
+      lanes_argmax<8>(mx, ai);
       double term = 0.0;
       if (T > 0.f) {
 #pragma unroll
         for (int j = 0; j < CPL; ++j)
           if (l16 + 16 * j < nc) term += ps[j] * ((pm[j] == mx) ? 1.0 : exp(((double)pm[j] - (double)mx) * invT));
       }
-#pragma unroll
-      for (int sh = 8; sh > 0; sh >>= 1) term += __shfl_xor(term, sh, 16);
+      term = lanes_sum<8>(term);
       if (l16 == 0) {
         s_m[i] = (double)mx;
         // a row cut to its most probable tokens is normalised by the kept mass; its cut key masks the tokens outside
@@ -1390,8 +1359,7 @@ __global__ __launch_bounds__(256, 5) void k_decide(
           tot += thread_masses<LT>(lrow, qrow, sb * FSV_SBK + part * 512 + lane * 8, V, (float)m, k, invS,
                                    residual, cut, mass);
       }
-#pragma unroll
-      for (int sh = 32; sh > 0; sh >>= 1) tot += __shfl_xor(tot, sh, 64);
+      tot = lanes_sum(tot);
       // a device-scope atomic store: written through to where every XCD sees it (a plain store would stay in this XCD's L2)
       if (lane == 0)
         __hip_atomic_store(reinterpret_cast<unsigned long long *>(bsum) + (size_t)b * nsb + sb,
