@@ -57,3 +57,18 @@ def test_top_tokens_side_by_side(V, top_k, monkeypatch):
         monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
         out.append(_sample(lg.cuda(), np.zeros(B + 1, np.int32), np.full(B, 0.8, np.float32), u, top_k, 0.95))
     assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
+
+
+@pytest.mark.parametrize("V", [8193, 16380, 24581, 32760, 40963])   # one to four groups of loads in the last round, the last ids on their own
+@pytest.mark.parametrize("T", [0.25, 1.0, 8.0])                     # few, some and nearly all tokens above the cut
+def test_top_p_of_peaked_and_flat_rows(V, T, monkeypatch):
+    B = 12
+    g = torch.Generator().manual_seed(V)
+    lg = 3.0 * torch.randn((B, V), generator=g)
+    lg[1::2, V - 3:] = 11.0                              # half the rows end in their most probable tokens
+    u = ((np.arange(B) + 0.5) / B).astype(np.float32)
+    out = []
+    for full in ("0", "1"):
+        monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
+        out.append(_sample(lg.cuda(), np.zeros(B + 1, np.int32), np.full(B, T, np.float32), u, 0, 0.9))
+    assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
