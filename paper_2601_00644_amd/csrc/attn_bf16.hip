@@ -30,7 +30,7 @@ namespace {
 // SIMD one's arithmetic runs under the other's matrix products; the loads cost no registers and 64 .. 128 KiB per compute unit are on
 // their way.  One wave per SIMD with K and V in registers, one tile ahead, and the merge as a launch of its own (16 requests of
 // 512 .. 4096 positions, head size 128: 27.3 + 5.9 us; 128 requests of 256 .. 8192: 230 + 14; 2048 prefill rows 128 + 22; 8 requests
-// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 31.6, 207, 118, 39 (33.2, 207, 119, 38 before the partial results were stored in
+// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 27.9 (31.6 with the row tiles of a request together), 207, 118, 39 (33.2, 207, 119, 38 before the partial results were stored in
 // whole lines, and when the following were measured).  Measured and dropped: four waves per block with the
 // queries in registers (33, 249, 141, 46); two blocks per compute unit whose waves share the tiles, one row tile each, a barrier per
 // item (40, 249, 148, 54: a tile is a chain of 1.2 us and too few are in work); one block per compute unit that goes through the

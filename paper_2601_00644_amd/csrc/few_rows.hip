@@ -9,8 +9,8 @@
 // block that reads the whole residual row can normalise it on the way in.  Five launches a layer instead of eight, and no split
 // sums in memory.
 //
-// One 1B request of five rows (2048 wide), per layer: q|k|v 6.0, o 3.9, gate|up 13.5 (67 MB: 5.0 TB/s), down 8.1 us (33.6 MB) against
-// 5.3 + 4.0 (rotation and append), 4.0 + 3.7 (sum and norm), 13.6 and 8.1 + 3.7; the call of 16 layers 914 -> 749 us.  8B, five rows, four
+// One 1B request of five rows (2048 wide), per layer: q|k|v 5.5, o 3.9, gate|up 13.2 (67 MB: 5.1 TB/s), down 8.2 us (33.6 MB) against
+// 5.3 + 4.0 (rotation and append), 4.0 + 3.7 (sum and norm), 13.6 and 8.1 + 3.7; the call of 16 layers 914 -> 738 us.  8B, five rows, four
 // layers 473 -> 433: down 19.9 us (117 MB: 5.9 TB/s), o 7.0, gate|up 37, q|k|v 12.4.
 // Why up to 16 rows: every block reads and normalises all rows, which takes as long as a launch by then (16 rows: 1B 483 -> 426 us over
 // eight layers, 8B 487 -> 481), and a matrix instruction has 16.

@@ -786,7 +786,7 @@ __device__ __host__ inline bool cut_takes_one_pass(int top_k, int V) { return to
 // first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
 // Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
 // arithmetic of a single compute unit with few rows (71 rows of a flat law, top-p 0.9: two passes of about 19 us, 47.6 in all).  204 rows, top-k 50
-// and top-p 0.9, 29.5 us: 16 of them the stream, 4.5 the bound from the first round, 6 the list.  Measured on 166 rows x 128256 fp32,
+// and top-p 0.9, 30 us: 16 of them the stream, 4.5 the bound from the first round, 6 the list.  Measured on 166 rows x 128256 fp32,
 // N(0, 3), T = 0.8, against passes by digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
 // passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
 // (74); logits rounded to whole numbers, top-p 0.99 110 (110).
@@ -1398,7 +1398,7 @@ __global__ __launch_bounds__(256, 5) void k_decide(
     rollback(tau);
   }
   // Wave 0 takes the sub-block masses, PER consecutive ones per lane, and finds the first sub-block whose running mass exceeds
-  // u times the total (lane sums and their shuffle scan: a fixed order).  One thread adding and comparing them one after the
+  // u times the total (lane sums and their scan: a fixed order).  One thread adding and comparing them one after the
   // other cost 3 us of this kernel's serial tail.
   auto pick_sb = [&](auto mass_of) {
     constexpr int PER = (FSV_MAX_NSB + 63) / 64;
