@@ -1,8 +1,7 @@
 // Exchanges between the lanes of a wave without LDS (gfx950): data-parallel moves within rows of 16 lanes, row and half swaps beyond.
-// An exchange through LDS (__shfl_xor) is a round trip of some 60 ns, and the kernels whose launches are short chains of dependent
+// An exchange through LDS (__shfl_xor) is a round trip to LDS, and the kernels whose launches are short chains of dependent
 // steps go through a dozen of them; these take a few cycles.  The sums they form are the same, in the same order.  One fp32 request
-// through two layers 66.8 -> 60.7 us (k_linear 3.8 -> 3.4, k_decide 9.3 -> 7.8), one request on 16 layers 744 -> 738, sampling from
-// 152064 bf16 logits 54.4 -> 53.3.
+// through two layers 66.8 -> 60.7 us, one 1B request on 16 layers 744 -> 738, sampling from 152064 bf16 logits 54.4 -> 53.3.
 // All lanes of the rows (1 .. 8) or of the wave (16, 32) that take part must be active.
 #pragma once
 #include <hip/hip_runtime.h>
