@@ -903,8 +903,9 @@ int fsv_bf16_forward(fsv_ctx *c, const fsv_batch *b, const fsv_attn_plan *plan, 
     return la;
   };
   const bool lq0 = lora && d.n_layers > 1;
-  // Few rows: five launches a layer, see few_rows.hip (the measurement knobs ask for the kernels they name)
-  const bool few = !lora && c->gemm_wide_force < 0 && !c->gemm_ncw_force && fsv_bf16_few_rows(c, M);
+  // Few rows: five launches a layer, see few_rows.hip (the measurement knobs ask for the kernels they name).  Not where adapters are loaded,
+  // whether or not this call uses them: its sums run in another order, and a base request keeps its bits beside adapted ones.
+  const bool few = (draft || c->lora_n == 0) && c->gemm_wide_force < 0 && !c->gemm_ncw_force && fsv_bf16_few_rows(c, M);
   {
     fsv_prof_scope ps(c, s, FSV_K_NORM, 0.0);
     if (lq0)

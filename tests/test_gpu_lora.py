@@ -111,3 +111,31 @@ def test_lora_load_refusals():
     ctx.lora_load([synth.make_lora(cfg, 8, 1, 0, device="cuda")])
     ctx.lora_load(None)            # removing the adapters again is fine
     ctx.close()
+
+
+def test_a_base_request_of_a_short_call_is_untouched_by_the_others_adapters():
+    """Up to 16 rows: the base request's logits and appended rows keep their bits whether or not the call carries adapter ids."""
+    from paper_2601_00644_amd import flexverify as fv
+    cfg = synth.MODELS["mini64"]
+    wl = synth.Workload("t", "mini64", 3, 20, 90, "uniform", 3, 4, "uniform", 0.7, 0.8, "permuted")
+    case = build_case(cfg, wl, seed=54, weight_std=0.04, run_oracle=False)
+    req = case.req
+    assert int(req.draft_offsets[-1]) + req.batch <= 16
+    ctx = fv.Context(cfg, {k: v.cuda() for k, v in case.weights.items()}, max_batch=3, max_gamma=16, max_pages_per_req=req.page_table.shape[1])
+    ctx.lora_load([synth.make_lora(cfg, 16, 54, a, device="cuda") for a in range(2)])
+    pt = torch.as_tensor(req.page_table, device="cuda")
+    got = []
+    for ids in ([1, -1, 0], [-1, -1, -1], None):
+        kp, vp = fv.alloc_pools(cfg, req.num_pages, "cuda")
+        for b in range(3):
+            ctx.kv_import(kp, vp, req.num_pages, pt[b], 0, case.ctx_k[b].cuda(), case.ctx_v[b].cuda())
+        bt = fv.device_batch(req, case.draft_tokens, case.draft_probs.cuda(), kp, vp, "cuda")
+        bt.adapter = None if ids is None else torch.tensor(ids, dtype=torch.int32, device="cuda")
+        res = fv.DeviceResult.alloc(3, bt.rows, cfg.vocab, want_logits=True)
+        ctx.verify(bt, res)
+        o, g, L = int(req.draft_offsets[1]), int(req.gammas[1]), int(req.seq_lens[1])
+        got.append((res.logits_out[o + 1:o + 1 + g + 1].clone(), *ctx.kv_export(kp, vp, req.num_pages, pt[1], L, g + 1)))
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)
+    ctx.close()
