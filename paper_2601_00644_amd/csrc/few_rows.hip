@@ -12,8 +12,13 @@
 // One 1B request of five rows (2048 wide), per layer: q|k|v 5.5, o 3.9, gate|up 13.2 (67 MB: 5.1 TB/s), down 8.2 us (33.6 MB) against
 // 5.3 + 4.0 (rotation and append), 4.0 + 3.7 (sum and norm), 13.6 and 8.1 + 3.7; the call of 16 layers 914 -> 738 us.  8B, five rows, four
 // layers 473 -> 433: down 19.9 us (117 MB: 5.9 TB/s), o 7.0, gate|up 37, q|k|v 12.4.
-// Why up to 16 rows: every block reads and normalises all rows, which takes as long as a launch by then (16 rows: 1B 483 -> 426 us over
-// eight layers, 8B 487 -> 481), and a matrix instruction has 16.
+// Which calls (fsv_bf16_few_rows): every block reads and normalises all rows, and a matrix instruction has 16.  39 shapes of 256 .. 4096 features,
+// whole calls of four or eight layers, through the eight launches and through these: up to eight rows 1.01 .. 1.4 x at all but one (3072, ffn 16384, eight
+// rows 0.98).  From nine rows there is room for 16: twice the loads and LDS (128 KiB beyond 2048 features: one block per compute unit).  That pays
+// where a wave's share is whole pieces of 256 elements and the projections are not so long that the launches no longer count: up to 2048 features (16
+// rows: 256 wide with ffn 4096 1.03 x, 8192 0.98; 512 / 8192 1.01, 14336 0.95; 1024 / 4096 1.11, 14336 0.95; 1536 / 16384 1.00; 2048 / 8192 1.10,
+// 16384 1.04, 28672 0.98) and at 4096 (4096 / 8192 1.04, 14336 1.02, 16384 0.99, 22016 0.94).  In between the last piece is partly empty and the
+// normalisation takes as long as at 4096: 2304 .. 3840 features 0.85 .. 0.95.
 //
 // The matrix instruction is 16 x 16 x 32: lane l holds feature (or row) l % 16 and the eight contraction elements 8 (l / 16) .. of
 // a step of 32; a lane's accumulator v is feature 4 (l / 16) + v of row l % 16.
@@ -340,7 +345,10 @@ void launch_norm(fsv_ctx *c, int cls, const void *Wp, const void *gain, uint32_t
 }  // namespace
 
 bool fsv_bf16_few_rows(const fsv_ctx *c, int M) {
-  return M <= 16 && c->d.d_model <= 4096 && c->d.d_model % 256 == 0;
+  const int d = c->d.d_model, ffn = c->d.d_ffn;
+  if (M > 16 || d > 4096 || d % 256) return false;
+  if (M <= 8) return true;   // (nine and more: see the head of this file)
+  return d <= 2048 ? ffn <= min(16 * d, max(8192, 8 * d)) : d == 4096 && ffn <= 14336;
 }
 
 int fsv_bf16_few_qkv(fsv_ctx *c, const fsv_batch *b, const void *Wp, const void *gain, uint32_t strip_bytes, uint32_t wbytes, int N, int M,

@@ -43,3 +43,24 @@ def test_one_layer_matches_the_oracle(monkeypatch, d, heads, kv_heads, hd, ffn, 
         for nm, got, want in (("k", gk, kst[:, L0:L0 + n]), ("v", gv, vst[:, L0:L0 + n])):
             check_bf16_kv(got.float().cpu().numpy().astype(np.float64).reshape(1, n, -1), want.reshape(1, n, -1), True, (s_, nm))
     ctx.close()
+
+
+@pytest.mark.parametrize("d,ffn,rows,few", [
+    (256, 4096, 16, True), (256, 4352, 8, True), (256, 4352, 9, False), (768, 8192, 9, True), (768, 8448, 9, False),
+    (2048, 512, 16, True), (2304, 512, 8, True), (2304, 512, 9, False), (3840, 512, 16, False),
+    (4096, 512, 8, True), (4096, 14336, 16, True), (4096, 14592, 8, True), (4096, 14592, 9, False),
+    (2048, 512, 17, False),
+])
+def test_which_calls_take_the_layers_of_few_rows(monkeypatch, d, ffn, rows, few):
+    """The rotation is a launch of its own where the layers of more rows are taken: from nine rows at widths whose normalisation costs more
+    than the launches it saves."""
+    from paper_2601_00644_amd import flexverify as fv
+    cfg = synth.ModelCfg("route", 1, d, 4, 2, 64, ffn, 256, "bf16", 500000.0)
+    ctx = fv.Context(cfg, synth.make_weights(cfg, 1, device="cuda"), max_batch=1, max_gamma=16, max_pages_per_req=2)
+    kp, vp = fv.alloc_pools(cfg, 2)
+    batch = fv.prefill_pieces([(0, 0, np.arange(rows, dtype=np.int32))], np.array([[0, 1]], np.int32), kp, vp, 2, 17)
+    ctx.profile_enable(True)
+    ctx.prefill(batch)
+    launched = ctx.profile_read()
+    assert ("rope_append" not in launched) == few, sorted(launched)
+    ctx.close()
