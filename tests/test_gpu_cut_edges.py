@@ -9,7 +9,7 @@ from paper_2601_00644_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-def _sample(lg, off, T, u, top_k, top_p=None):
+def _sample(lg, off, T, u, top_k, top_p=None, timed=False):
     from paper_2601_00644_amd import flexverify as fv
     B, V = len(T), lg.shape[1]
     t = lambda a: torch.as_tensor(a).cuda()
@@ -24,8 +24,20 @@ def _sample(lg, off, T, u, top_k, top_p=None):
     res = fv.DeviceResult.alloc(B)
     ctx.sample(lg, batch, res)
     out = res.next_token.cpu().numpy(), res.flags.cpu().numpy()
+    if timed:   # the shortest of five runs of ten calls, in ms a call
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        out += (min(_run(ctx, lg, batch, res, a, b) for _ in range(5)),)
     ctx.close()
     return out
+
+
+def _run(ctx, lg, batch, res, a, b):
+    a.record()
+    for _ in range(10):
+        ctx.sample(lg, batch, res)
+    b.record()
+    b.synchronize()
+    return a.elapsed_time(b) / 10
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
@@ -57,6 +69,24 @@ def test_top_tokens_side_by_side(V, top_k, monkeypatch):
         monkeypatch.setenv("FSV_NUCLEUS_FULL", full)
         out.append(_sample(lg.cuda(), np.zeros(B + 1, np.int32), np.full(B, 0.8, np.float32), u, top_k, 0.95))
     assert (out[0][0] == out[1][0]).all() and (out[0][1] == out[1][1]).all()
+
+
+@pytest.mark.parametrize("run,top_k", [(8, 64), (8, 341), (4, 200), (2, 341)])
+def test_likely_tokens_in_runs(run, top_k, monkeypatch):
+    """All likely ids side by side in runs: the same tokens as through the general passes, and the list holds its candidates (general passes
+    would take about four times as long; a factor of two is asked for)."""
+    B, V = 64, 128256
+    g = torch.Generator(device="cuda").manual_seed(run)
+    z = 3.0 * torch.randn((B, V), generator=g, device="cuda")
+    lg = z[:, :V // run].repeat_interleave(run, 1) + 0.05 * torch.randn((B, V), generator=g, device="cuda")
+    u = ((np.arange(B) + 0.5) / B).astype(np.float32)
+    args = (np.zeros(B + 1, np.int32), np.full(B, 0.8, np.float32), u, top_k, 0.95)
+    monkeypatch.setenv("FSV_NUCLEUS_FULL", "1")
+    want = _sample(lg, *args)
+    monkeypatch.setenv("FSV_NUCLEUS_FULL", "0")
+    tok, flags, ms = _sample(lg, *args, timed=True)
+    assert (tok == want[0]).all() and (flags == want[1]).all()
+    assert ms < 2.0 * _sample(z, *args, timed=True)[2]
 
 
 @pytest.mark.parametrize("V", [8193, 16380, 24581, 32760, 40963])   # one to four groups of loads in the last round, the last ids on their own
