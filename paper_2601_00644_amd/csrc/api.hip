@@ -98,7 +98,7 @@ void fsv_destroy(fsv_ctx *c) {
   if (!c) return;
   for (auto &r : c->prof) { (void)hipEventDestroy(r.e0); (void)hipEventDestroy(r.e1); }
   for (hipEvent_t e : c->prof_pool) (void)hipEventDestroy(e);
-  void *ptrs[] = {c->embed, c->final_norm, c->lm_head, c->inv_freq, c->rope_tab, c->row_req, c->row_idx, c->row_pos, c->row_tok, c->row_place,
+  void *ptrs[] = {c->embed, c->final_norm, c->lm_head, c->inv_freq, c->rope_tab, c->row_req, c->row_pos, c->row_tok, c->row_place,
                   c->pmax, c->psum, c->parg, c->bsum, c->acc_scratch, c->sel_ticket, c->nuc_key, c->nuc_S, c->nuc_near, c->nuc_done, c->x, c->logits,
                   c->absmax, c->buf_a, c->buf_q, c->buf_att, c->buf_act, c->buf_part, c->attn_part, c->attn_part_prefix, c->attn_part_map, c->attn_ticket,
                   c->lora_aq, c->lora_bq, c->lora_ao, c->lora_bo, c->lora_scale, c->lora_t,
@@ -145,8 +145,6 @@ int fsv_create(const fsv_model_desc *desc, const fsv_weights *w, fsv_ctx **out) 
   const size_t R = c->max_rows, B = d.max_batch;
   int rc = FSV_OK;
   auto A = [&](int r) { if (rc == FSV_OK) rc = r; };
-  A(dev_alloc(c, &c->row_req, R)); A(dev_alloc(c, &c->row_idx, R)); A(dev_alloc(c, &c->row_pos, R));
-  A(dev_alloc(c, &c->row_tok, R));
   A(dev_alloc(c, &c->pmax, R * c->nc)); A(dev_alloc(c, &c->psum, R * c->nc)); A(dev_alloc(c, &c->parg, R * c->nc));
   A(dev_alloc(c, &c->bsum, B * c->nsb));
   A(dev_alloc(c, &c->acc_scratch, B));
@@ -156,6 +154,8 @@ int fsv_create(const fsv_model_desc *desc, const fsv_weights *w, fsv_ctx **out) 
   A(dev_alloc(c, &c->nuc_done, R));
   if (rc == FSV_OK && d.n_layers > 0) {
     const size_t rows_pad = (R + 31) / 32 * 32;
+    A(dev_alloc(c, &c->row_req, R));
+    A(d.dtype == FSV_F32 ? dev_alloc(c, &c->row_pos, R) : dev_alloc(c, &c->row_tok, R));
     A(dev_alloc(c, &c->x, rows_pad * d.d_model));
     A(dev_alloc(c, &c->logits, R * (size_t)d.vocab));
     if (rc == FSV_OK) rc = (d.dtype == FSV_F32) ? fsv_f32_create(c, w) : fsv_bf16_create(c, w);
@@ -329,7 +329,7 @@ int fsv_attention(fsv_ctx *c, int32_t layer, const void *q, const fsv_batch *b, 
   fsv_batch bb = *b;
   bb.last_token = nullptr;
   bb.draft_tokens = nullptr;
-  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, &bb, M, s))) return rc;
+  if (c->d.dtype == FSV_F32 && (rc = fsv_launch_build_rows(c, &bb, s))) return rc;
   return (c->d.dtype == FSV_F32) ? fsv_f32_attention(c, layer, q, b, M, out, s)
                                  : fsv_bf16_attention(c, layer, q, &bb, &pl, M, out, s);
 }

@@ -72,7 +72,9 @@ struct fsv_ctx {
   float *rope_tab = nullptr;        // [max_rows][head_dim/2][2] cos, sin of the rows of the current call
 
   // row map, built per call on the device
-  int32_t *row_req = nullptr, *row_idx = nullptr, *row_pos = nullptr, *row_tok = nullptr;
+  int32_t *row_req = nullptr;       // request
+  int32_t *row_pos = nullptr;       // fp32 path: position
+  int32_t *row_tok = nullptr;       // bf16 path: token
   int32_t *row_place = nullptr;     // bf16 path: [max_rows][4] request, index, position, physical page of the position
 
   // sampler workspace
@@ -179,7 +181,7 @@ static inline int fsv_ceil_div(int a, int b) { return (a + b - 1) / b; }
 // api.hip: CSR shape, capacity and pointer checks shared by the entry points.  Returns the number of rows or a status < 0.
 int fsv_check_batch(fsv_ctx *c, const fsv_batch *b, bool need_kv, bool need_sampling);
 // sampler.hip
-int fsv_launch_build_rows(fsv_ctx *c, const fsv_batch *b, int M, hipStream_t s);
+int fsv_launch_build_rows(fsv_ctx *c, const fsv_batch *b, hipStream_t s);
 int fsv_launch_sampler(fsv_ctx *c, const void *logits, int logits_dtype, const fsv_batch *b, const fsv_result *r,
                        int M, bool with_rollback, hipStream_t s);
 int fsv_launch_draft_law(fsv_ctx *c, const float *z, const fsv_batch *b, int all_rows, float *q, hipStream_t s);

@@ -119,21 +119,14 @@ __device__ inline double block_incl_scan(double v, double *s_w, double *total) {
   return v + pre;
 }
 
-__global__ void k_build_rows(int B, int V, const int32_t *seq_lens, const int32_t *last_token, const int32_t *off,
-                             const int32_t *draft, int32_t *row_req, int32_t *row_idx, int32_t *row_pos,
-                             int32_t *row_tok) {
+__global__ void k_build_rows(int B, const int32_t *seq_lens, const int32_t *off, int32_t *row_req, int32_t *row_pos) {
   int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   int o = off[b], g = off[b + 1] - o, rs = o + b;
   int L = seq_lens ? seq_lens[b] : 0;
   for (int i = 0; i <= g; ++i) {
     row_req[rs + i] = b;
-    row_idx[rs + i] = i;
     row_pos[rs + i] = L + i;
-    if (row_tok) {
-      int t = (i == 0) ? (last_token ? last_token[b] : 0) : (draft ? draft[o + i - 1] : 0);
-      row_tok[rs + i] = min(max(t, 0), V - 1);
-    }
   }
 }
 
@@ -1588,11 +1581,9 @@ int launch_sampler_t(fsv_ctx *c, const LT *logits, const fsv_batch *b, const fsv
 
 }  // namespace
 
-int fsv_launch_build_rows(fsv_ctx *c, const fsv_batch *b, int M, hipStream_t s) {
-  (void)M;
-  hipLaunchKernelGGL(k_build_rows, dim3(fsv_ceil_div(b->batch, 256)), dim3(256), 0, s, b->batch, c->d.vocab,
-                     b->seq_lens, b->last_token, b->draft_offsets, b->draft_tokens, c->row_req, c->row_idx,
-                     c->row_pos, c->row_tok);
+int fsv_launch_build_rows(fsv_ctx *c, const fsv_batch *b, hipStream_t s) {
+  hipLaunchKernelGGL(k_build_rows, dim3(fsv_ceil_div(b->batch, 256)), dim3(256), 0, s, b->batch, b->seq_lens, b->draft_offsets, c->row_req,
+                     c->row_pos);
   FSV_HIP(c, hipGetLastError());
   return FSV_OK;
 }
@@ -1660,8 +1651,6 @@ bool carve_static(fsv_ctx &c, unsigned char *base) {
     return p;
   };
   const size_t R = FSV_STATIC_MAX_ROWS, B = FSV_STATIC_MAX_BATCH, NC = FSV_STATIC_MAX_NC, NSB = FSV_STATIC_MAX_NSB;
-  c.row_req = (int32_t *)take(4 * R); c.row_idx = (int32_t *)take(4 * R); c.row_pos = (int32_t *)take(4 * R);
-  c.row_tok = (int32_t *)take(4 * R);
   c.pmax = (float *)take(4 * R * NC); c.psum = (double *)take(8 * R * NC); c.parg = (int32_t *)take(4 * R * NC);
   c.bsum = (double *)take(8 * B * NSB);
   c.acc_scratch = (int32_t *)take(4 * B);
