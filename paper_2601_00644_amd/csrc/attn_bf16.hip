@@ -17,7 +17,7 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Work decomposition.  The keys of request b are cut into tiles of 32 (two pages); a "part" is a run of
 // tp_b consecutive tiles, s_b runs per request, chosen so that every part of every request has about the
-// same length and parts x kv heads comes to one block per compute unit (see plan_attention).  A block owns its part completely: its
+// same length and parts x kv heads comes to one block per compute unit (attn_schedule.h).  A block owns its part completely: its
 // waves (eight, or four) take every eighth (fourth) tile each (each byte of the KV stream is read once; all `group` query heads and all gamma+1
 // positions share it, except in small calls, where every tile of 32 query rows has parts of its own).  A wave streams the K and V page tiles of its keys straight from HBM into a ring of its own in LDS, forms
 // S^T = K Q^T (rows = keys, so a query row's scores sit in two lanes; the queries lie in LDS, shared by the waves), does the
@@ -30,7 +30,7 @@ namespace {
 // SIMD one's arithmetic runs under the other's matrix products; the loads cost no registers and 64 .. 128 KiB per compute unit are on
 // their way.  One wave per SIMD with K and V in registers, one tile ahead, and the merge as a launch of its own (16 requests of
 // 512 .. 4096 positions, head size 128: 27.3 + 5.9 us; 128 requests of 256 .. 8192: 230 + 14; 2048 prefill rows 128 + 22; 8 requests
-// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 27.9 (31.6 with the row tiles of a request together), 207, 118, 39 (33.2, 207, 119, 38 before the partial results were stored in
+// of 4 .. 16 k, head size 64: 37.9 + 7.8) against this: 31.6 (27.9 where the schedule takes the row tiles of such a call apart, which few of that range do), 207, 118, 39 (33.2, 207, 119, 38 before the partial results were stored in
 // whole lines, and when the following were measured).  Measured and dropped: four waves per block with the
 // queries in registers (33, 249, 141, 46); two blocks per compute unit whose waves share the tiles, one row tile each, a barrier per
 // item (40, 249, 148, 54: a tile is a chain of 1.2 us and too few are in work); one block per compute unit that goes through the
@@ -42,20 +42,6 @@ namespace {
 // probabilities.  The result then differs from exact arithmetic on the stored K / V only by fp32 accumulation.
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
-
-// parts of a request with n key tiles when a part of a request with ONE query-row tile should hold about tpw tiles; *tp = tiles per
-// part.  A key tile costs more when the request has more query rows (the score and value
-// products and the softmax arithmetic on the same K and V), so such a request is cut into shorter parts, by the
-// cost ratio w16 / 16: 16 requests, 512 .. 4096 positions, 1 .. 9 rows: 35 us with all tiles alike, 30.7 with 20 / 16 for two row tiles
-// and 26 / 16 for three, 31.5 with 26 / 16 and 36 / 16.  As many parts as parts of whole rounds of the waves would be, but alike: 1909 ..
-// 2674 positions, 12 requests, 28.8 us a layer with parts of whole rounds, 27.3 like this.  Up to two tiles a wave are one part: two of half
-// of it take 2.0 us longer with one row tile (10 key tiles 11.3 and 9.3 us), 2.4 with two.
-__device__ __host__ inline int attn_parts(int n, int tpw, int w16, int nw, int *tp) {
-  tpw = n <= 2 * nw ? n : max(1, tpw * 16 / w16);
-  const int s0 = (n + tpw - 1) / tpw, whole = ((n + s0 - 1) / s0 + nw - 1) / nw * nw, parts = (n + whole - 1) / whole;
-  *tp = (n + parts - 1) / parts;
-  return parts;
-}
 
 // part_prefix[b] = parts of requests before b; part_desc[global part] = everything a wave of
 // the attention kernel needs to start, in one 112-byte record: request, first tile, tiles, parts of the same rows, cached
@@ -634,95 +620,8 @@ __global__ __launch_bounds__(64 * NW, (RT == 3 && HD == 128) ? 1 : 2) void k_att
 // Size the parts from the host copies of the lengths.
 int plan_attention(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl) {
   const fsv_model_desc &d = c->d;
-  int max_rows = 0, longest = 0;
-  long row_tiles = 0, items = 0;
-  auto rtc_of = [&](int g) { return fsv_ceil_div(c->group * (g + 1), 32); };
-  for (int i = 0; i < b->batch; ++i) {
-    const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
-    const int n = fsv_ceil_div(nk, 32);
-    max_rows = max(max_rows, c->group * (g + 1));
-    longest = max(longest, n);
-    row_tiles += rtc_of(g);
-    items += (long)n * rtc_of(g);
-    pl->kv_tokens += nk;
-  }
-  // The schedule with the row tiles of a request together or (split) as parts of their own; cost16: of its longest part, in 1/16 of a tile of
-  // a request with one row tile.
-  struct cut { int rt, nw, tpw, blocks, cost16; bool sorted; };
-  auto cut_for = [&](bool split) {
-    cut k{};
-    auto w16_of = [&](int g) {
-      const int rtc = rtc_of(g);
-      return split || rtc <= 1 ? 16 : rtc == 2 ? c->attn_w2 : c->attn_w3;
-    };
-    k.rt = split ? 1 : fsv_ceil_div(max_rows, 32);
-    // Waves per block.  Eight, one block per compute unit, while requests are few: a part then takes an eighth of its tiles' time.  Four, two blocks per
-    // compute unit, from 192 (request, kv head) pairs on, so that a request need not be cut, and one block computes while the other
-    // starts or merges; where the queries leave room for it (not with head size 128 and more than one row tile).  Head size 64, whole call
-    // of the stand-alone entry: 8 requests of 2000 .. 6000 positions 24.8 us with eight, 28.6 with four; 24 of 200 .. 1000 16.6 and 16.6; 54 of 1000
-    // 36.8 and 28.5.  Three row tiles of head size 128: four waves, one block (eight waves' rings and the queries exceed the LDS).
-    const bool two_blocks = d.head_dim == 64 || k.rt == 1, wide_q = d.head_dim == 128 && k.rt > 2;
-    k.nw = wide_q || (two_blocks && b->batch * d.n_kv_heads >= 192) ? 4 : 8;
-    // One round if it can be had: the smallest part length, up to twice the even share, for which parts x kv heads fit the
-    // compute units.  Otherwise parts of up to five quarters of the even share in several rounds, the long ones first (a block costs 6 us besides
-    // its tiles, so few and long is right as long as the last round is short).  In the order of the requests, and in parts of half the share:
-    // 128 requests of 256 .. 8192 positions 240 us instead of 207, 2048 prefill rows 127 and 119.
-    const int target = c->attn_wave_target * (k.nw == 4 && !wide_q ? 2 : 1);
-    auto count = [&](int tpw, int most) {   // parts x kv heads; counted no further than `most`
-      int parts = 0;
-      k.cost16 = 0;
-      for (int i = 0; i < b->batch && parts * d.n_kv_heads <= most; ++i) {
-        const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], nk = b->seq_lens_host[i] + g + 1;
-        int tp;
-        parts += attn_parts(fsv_ceil_div(nk, 32), tpw, w16_of(g), k.nw, &tp) * (split ? rtc_of(g) : 1);
-        k.cost16 = max(k.cost16, tp * w16_of(g));
-      }
-      return parts * d.n_kv_heads;
-    };
-    long total_tiles = 0;   // in units of the cost of a tile of a request with one query-row tile
-    for (int i = 0; i < b->batch; ++i) {
-      const int g = b->draft_offsets_host[i + 1] - b->draft_offsets_host[i], n = fsv_ceil_div(b->seq_lens_host[i] + g + 1, 32);
-      total_tiles += ((long)n * w16_of(g) + 15) / 16;
-    }
-    if (split) total_tiles = items;
-    // Fewest key tiles a part is given: two for each of eight waves, or one while that makes no more parts than the merge fetches at once
-    // (1600 positions, head size 128, one row tile 13.9 and 12.5 us; 3200 positions 16.2 and 18.3).
-    const int fewest = k.nw == 8 && longest <= 64 ? c->attn_min_tpw / 2 : c->attn_min_tpw;
-    const int even = (int)max((long)fewest, (total_tiles * d.n_kv_heads + target - 1) / target);
-    // Every request has a part, so with more pairs than blocks there is nothing to look for; otherwise at most 129 lengths are tried.
-    // (Host time of all lengths one by one, before the first launch: 128 requests of 256 .. 8192 positions 0.33 ms, of 8 .. 32 k 2.6 ms.)
-    for (int t = even; b->batch * d.n_kv_heads <= target && t <= 2 * even; t += max(1, even / 128)) {
-      if (count(t, target) <= target) { k.tpw = t; break; }
-    }
-    k.sorted = k.tpw == 0;
-    if (!k.tpw) k.tpw = max(8, even * 5 / 4);
-    k.blocks = count(k.tpw, INT_MAX);
-    return k;
-  };
-  // Row tiles as parts of their own, which read the same keys (neighbouring blocks, on one XCD with eight kv heads), while all fit the compute units
-  // at once and leave a wave at most four (row tile, key tile) pairs: every block then has the short chain of one row tile, and a request's merge
-  // is spread over as many blocks.  Beyond, the row tiles of a request share the keys they read.  Calls of the stand-alone entry in a graph, head
-  // size 128, eight kv heads, shared and split: one request of 1600 positions, two row tiles 23.5 and 18.2 us, three 32.4 and 18.3; 16 of 800 .. 1600, two
-  // 34.2 and 28.4; past the line 16 of 1600 .. 3200 43.4 and 45.9, 48 of 800 .. 1600 55.1 and 57.9.
-  // Past it the longest parts of both schedules decide, while they are short enough for the merge to show: split if the shared one's is at
-  // least 0.625 (head size 64) or 0.7 (128) of the split one's.  44 calls that this takes (drawn; in a graph): head size 64 0.99 .. 1.23 x as fast
-  // split, mean 1.05, head size 128 0.98 .. 1.15, mean 1.06 (16 requests of 512 .. 4096 positions, one of them with two row tiles, 34.7 and
-  // 32.8 us).  Of 50 calls it does not take all but six are slower split, down to 0.75 x.
-  const bool may = max_rows > 32 && row_tiles * d.n_kv_heads <= c->n_cus;
-  pl->split = may && items * d.n_kv_heads <= 32l * c->n_cus;
-  cut k = cut_for(pl->split);
-  if (may && !pl->split && !k.sorted && k.nw == 8 && k.cost16 <= 16 * (d.head_dim == 64 ? 66 : 42)) {
-    const cut s = cut_for(true);
-    if (!s.sorted && s.nw == 8 && (d.head_dim == 64 ? 8 * k.cost16 >= 5 * s.cost16 : 10 * k.cost16 >= 7 * s.cost16)) {
-      pl->split = true;
-      k = s;
-    }
-  }
-  pl->rt = k.rt;
-  pl->nw = k.nw;
-  pl->tpw = k.tpw;
-  pl->sorted = k.sorted;
-  pl->waves = k.blocks;
+  const attn_shape sh{d.head_dim, d.n_kv_heads, c->group, c->n_cus, c->attn_wave_target, c->attn_min_tpw, c->attn_w2, c->attn_w3};
+  *pl = attn_schedule(sh, b->batch, b->seq_lens_host, b->draft_offsets_host);
   if (pl->waves > c->attn_wave_cap) FSV_FAIL(c, FSV_E_CAPACITY, "%d attention parts > %d the workspace holds", pl->waves, c->attn_wave_cap);
   if ((size_t)b->num_pages * d.n_kv_heads * 16 * d.head_dim * 2 > 0xFFFF0000ull)
     FSV_FAIL(c, FSV_E_UNSUPPORTED, "one layer of a KV pool must stay below 4 GiB (%d pages given)", b->num_pages);
@@ -804,7 +703,7 @@ int fsv_bf16_attn_create(fsv_ctx *c) {
     if (n == 3 && w2 >= 16 && w2 <= 64 && w3 >= w2 && w3 <= 96) { c->attn_w2 = w2; c->attn_w3 = w3; }
   }
   c->attn_wave_target = c->n_cus;
-  c->attn_wave_cap = 4 * c->attn_wave_target + 2 * d.max_batch * d.n_kv_heads;  // multi-round schedules: see plan_attention
+  c->attn_wave_cap = 4 * c->attn_wave_target + 2 * d.max_batch * d.n_kv_heads;  // multi-round schedules: see attn_schedule.h
   const int rows_cap = c->group * (d.max_gamma + 1);
   c->attn_part_bytes = (size_t)c->attn_wave_cap * rows_cap * (d.head_dim + 2) * 4;
   auto zalloc = [&](void **p, size_t bytes) -> int {

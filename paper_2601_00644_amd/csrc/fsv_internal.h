@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "attn_schedule.h"
 #include "flexverify.h"
 #include "wave_ops.h"
 
@@ -107,8 +108,7 @@ struct fsv_ctx {
   int attn_wave_target = 0;     // compute units: blocks of eight waves the attention schedule aims at
   int attn_wave_cap = 0;        // blocks the partial buffers hold
   int32_t *attn_ticket = nullptr;  // [max_batch][row tiles][kv heads] parts of the same rows that have left their results; zero between the launches of a call
-  int attn_min_tpw = 16;        // fewest key tiles a part is given, two per wave: one 2048-position request 11.2 us, with 24 tiles 11.7 (half of it in short requests: plan_attention)
-  int attn_w2 = 20, attn_w3 = 26;  // cost of a key tile for a request with two / three query-row tiles, in 1/16 of one with one
+  int attn_min_tpw = 16, attn_w2 = 20, attn_w3 = 26;   // see attn_shape
   int32_t *attn_part_prefix = nullptr, *attn_part_map = nullptr;   // parts before each request; 28-int record per part
 
   // LoRA adapters of the evolved target (bf16 path): tables [layer < n_layers - 1][adapter][...], library-owned
@@ -175,8 +175,6 @@ struct fsv_prof_scope {
   }
 };
 
-static inline int fsv_ceil_div(int a, int b) { return (a + b - 1) / b; }
-
 // ---- entry points of the other translation units ----------------------------------------------
 // api.hip: CSR shape, capacity and pointer checks shared by the entry points.  Returns the number of rows or a status < 0.
 int fsv_check_batch(fsv_ctx *c, const fsv_batch *b, bool need_kv, bool need_sampling);
@@ -195,15 +193,6 @@ int fsv_f32_attention(fsv_ctx *c, int layer, const void *q, const fsv_batch *b, 
 int fsv_f32_kv_copy(fsv_ctx *c, void *k_pool, void *v_pool, int num_pages, const int32_t *pt_row, int pos0, int n,
                     void *k_lin, void *v_lin, bool import, hipStream_t s);
 // attn_bf16.hip
-struct fsv_attn_plan {
-  int tpw = 0;          // target key tiles per part
-  int waves = 0;        // parts x kv heads: blocks
-  int rt = 1;           // query-row tiles of the widest part
-  int nw = 8;           // waves per block
-  bool split = false;   // the row tiles of a request are parts of their own
-  bool sorted = false;  // the parts run in several rounds, long ones first
-  double kv_tokens = 0;
-};
 int fsv_bf16_attn_create(fsv_ctx *c);
 int fsv_bf16_attn_plan_host(fsv_ctx *c, const fsv_batch *b, fsv_attn_plan *pl);          // host only; may fail
 // row map, attention schedule and (rope) rotation angles of a call, on the device; q: rotated queries to put into the query
