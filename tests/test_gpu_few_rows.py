@@ -19,10 +19,16 @@ pytestmark = pytest.mark.gpu
     (256, 4, 2, 128, 768, [(15, 8)]),                # eight rows; shares of three steps
     (768, 6, 3, 128, 512, [(15, 2), (30, 7)]),       # nine rows of two requests; three steps of the normalised rows
     (256, 64, 16, 64, 8192, [(9, 5)]),               # q|k|v in pairs of tiles, gate|up in fours
-    (256, 4, 4, 64, 14336, [(0, 16)]),               # gate|up in sevens, 56 steps in down
+    (256, 64, 16, 128, 512, [(20, 13)]),             # q|k|v in fours
+    (256, 128, 32, 128, 256, [(9, 5)]),              # and in sevens
+    (256, 4, 4, 64, 14336, [(0, 8)]),                # gate|up in sevens, 56 steps in down
+    (256, 4, 4, 64, 14336, [(0, 16)]),               # sixteen rows and an ffn too long for the width: the kernels of more rows
+    (1280, 4, 4, 64, 8448, [(0, 16)]),               # gate|up in sevens, sixteen rows, five steps of the normalised rows
     (2304, 4, 2, 64, 256, [(40, 11)]),               # more than eight steps a wave
     (4096, 4, 1, 128, 14336, [(33, 3), (2, 5)]),     # the widest row, whole tiles added, eight rows
     (4096, 4, 1, 128, 512, [(3, 16)]),               # and sixteen
+    (4096, 32, 8, 128, 8448, [(33, 3), (2, 5)]),     # the widest row, q|k|v in pairs of tiles and gate|up in sevens: eight rows
+    (4096, 32, 8, 128, 8448, [(3, 16)]),             # and sixteen
     (256, 4, 4, 64, 256, [(0, 17)]),                 # seventeen rows: the kernels of more rows
 ])
 def test_one_layer_matches_the_oracle(monkeypatch, d, heads, kv_heads, hd, ffn, sessions):
