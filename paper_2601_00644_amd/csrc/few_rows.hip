@@ -13,12 +13,11 @@
 // 5.3 + 4.0 (rotation and append), 4.0 + 3.7 (sum and norm), 13.6 and 8.1 + 3.7; the call of 16 layers 914 -> 738 us.  8B, five rows, four
 // layers 473 -> 433: down 19.9 us (117 MB: 5.9 TB/s), o 7.0, gate|up 37, q|k|v 12.4.
 // Which calls (fsv_bf16_few_rows): every block reads and normalises all rows, and a matrix instruction has 16.  39 shapes of 256 .. 4096 features,
-// whole calls of four or eight layers, through the eight launches and through these: up to eight rows 1.01 .. 1.4 x at all but one (3072, ffn 16384, eight
-// rows 0.98).  From nine rows there is room for 16: twice the loads and LDS (128 KiB beyond 2048 features: one block per compute unit).  That pays
+// whole calls of four or eight layers, through the eight launches and through these: up to eight rows 1.01 .. 1.4 x.  From nine rows there is room for 16: twice the loads and LDS (128 KiB beyond 2048 features: one block per compute unit).  That pays
 // where a wave's share is whole pieces of 256 elements and the projections are not so long that the launches no longer count: up to 2048 features (16
 // rows: 256 wide with ffn 4096 1.03 x, 8192 0.98; 512 / 8192 1.01, 14336 0.95; 1024 / 4096 1.11, 14336 0.95; 1536 / 16384 1.00; 2048 / 8192 1.10,
 // 16384 1.04, 28672 0.98) and at 4096 (4096 / 8192 1.04, 14336 1.02, 16384 0.99, 22016 0.94).  In between the last piece is partly empty and the
-// normalisation takes as long as at 4096: 2304 .. 3840 features 0.85 .. 0.95.
+// normalisation takes as long as at 4096: 2304 .. 3840 features 0.92 .. 1.06 with sixteen rows, 0.98 .. 1.10 with nine.
 //
 // The matrix instruction is 16 x 16 x 32: lane l holds feature (or row) l % 16 and the eight contraction elements 8 (l / 16) .. of
 // a step of 32; a lane's accumulator v is feature 4 (l / 16) + v of row l % 16.
@@ -318,7 +317,9 @@ __global__ __launch_bounds__(64 * FW, 2) void k_few_add(const void *__restrict__
 }
 
 // Tiles of 16 features per block (1, 2, 4 or 7): the least work per compute unit, rounds x (tiles + what a block costs besides, about
-// one).  Seven are for gate|up of the 8B shape: 256 blocks.
+// one).  Seven are for gate|up of the 8B shape: 256 blocks.  22 shapes with 5, 8 and 16 rows, each projection with all four: the rule's is within
+// 3 % of the best at 121 of 124, 9 % off at worst (37888 x 3584, five rows: 49.8 us with seven, 45.7 with two); the wrong one costs up to 2 x (22016 x 4096, 16
+// rows: 1, 2, 4, 7 tiles 68, 41, 41, 33 us).  All timings: profiles/few_rows_tiles.txt.
 int pick_tiles(const fsv_ctx *c, int tiles) {
   int best = 1, cost = 0;
   for (int ft : {7, 4, 2, 1}) {
@@ -387,7 +388,10 @@ int fsv_bf16_few_gate_up(fsv_ctx *c, const void *Wp, const void *gain, uint32_t 
 int fsv_bf16_few_add(fsv_ctx *c, int cls, const void *Wp, const void *Ap, uint32_t strip_bytes, uint32_t wbytes, int N, int K, int M, int f16,
                      float oscale, hipStream_t st) {
   fsv_prof_scope ps(c, st, cls, (double)N * K * 2.0, true);
-  const bool half = N / 16 < c->n_cus;
+  // Tiles of eight where they still fit the compute units at once: down of 2048 features, ffn 8192, five rows 7.8 us and 9.1 with tiles of 16; of
+  // 2304, ffn 6144, eight rows 9.6 and 7.3 (288 blocks are a second round), of 3584, ffn 18944 28.5 and 23.0.  Steps in flight, P 4 or 8: within 3 % of
+  // each other at 4096 features; at 2048 four 8 .. 12 % faster with ffn 5632, eight 6 % with 16384.
+  const bool half = N / 8 <= c->n_cus;
 #define FSV_FEW_GO(F16V, HV, RGV, PV, OSC)                                                                                           \
   hipExtLaunchKernelGGL((k_few_add<F16V, HV, RGV, PV>), dim3(N / (HV ? 8 : 16)), dim3(64 * FW), 0, st, ps.start(), ps.stop(), 0, Wp, Ap, c->x, \
                         strip_bytes, wbytes, K, M, N, OSC)

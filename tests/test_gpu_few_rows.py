@@ -25,6 +25,9 @@ pytestmark = pytest.mark.gpu
     (256, 4, 4, 64, 14336, [(0, 16)]),               # sixteen rows and an ffn too long for the width: the kernels of more rows
     (1280, 4, 4, 64, 8448, [(0, 16)]),               # gate|up in sevens, sixteen rows, five steps of the normalised rows
     (2304, 4, 2, 64, 256, [(40, 11)]),               # more than eight steps a wave
+    (2048, 4, 2, 64, 768, [(40, 7)]),                # o and down in tiles of eight features, the most blocks of them
+    (2304, 4, 2, 64, 768, [(40, 7)]),                # and in tiles of sixteen, the fewest
+    (3840, 4, 2, 128, 512, [(11, 2), (3, 6)]),
     (4096, 4, 1, 128, 14336, [(33, 3), (2, 5)]),     # the widest row, whole tiles added, eight rows
     (4096, 4, 1, 128, 512, [(3, 16)]),               # and sixteen
     (4096, 32, 8, 128, 8448, [(33, 3), (2, 5)]),     # the widest row, q|k|v in pairs of tiles and gate|up in sevens: eight rows
