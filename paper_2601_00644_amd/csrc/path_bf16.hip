@@ -181,7 +181,7 @@ __global__ __launch_bounds__(1024) void k_resid_norm(int M, int d, int S, int Mp
                                                      const uint16_t *__restrict__ gain, uint4 *__restrict__ a_out,
                                                      const int32_t *__restrict__ row_tok, const uint16_t *__restrict__ E, float eps,
                                                      lora_args lo) {
-  // (blockDim.x is not asked for: unlike the first arguments, it would have to be fetched)
+  // (nthr: blockDim.x, from d like the host's)
   const int nthr = norm_threads(d), r = row_of_block(), tid = threadIdx.x, KB = d / 16, stride = nthr * 8, nw = nthr >> 6;
   if (r >= M) {
     for (int k0 = tid * 8; k0 < d; k0 += stride) a_out[tile_unit(r, k0, KB)] = make_uint4(0, 0, 0, 0);

@@ -778,7 +778,7 @@ __device__ __host__ inline bool cut_takes_one_pass(int top_k, int V) { return to
 // bins (cut_narrow).  Rows with NaN or an infinite maximum, a top-k beyond the list, a top-p too close to 1 for the sums of the
 // first pass, and every row with `digits` (FSV_NUCLEUS_FULL=1, the test of one against the other) narrow from the whole range.
 // Bound by HBM with a row for every compute unit (a pass over 204 rows x 128256 fp32 takes 21 us by itself), by the per-token
-// arithmetic of a single compute unit with few rows (71 rows of a flat law, top-p 0.9: two passes of about 19 us, 47.6 in all).  204 rows, top-k 50
+// arithmetic of a single compute unit with few rows (71 rows of a flat law, top-p 0.9: two passes of about 19 us, 48.2 in all).  204 rows, top-k 50
 // and top-p 0.9, 30 us: 16 of them the stream, 4.5 the bound from the first round, 6 the list.  Measured on 166 rows x 128256 fp32,
 // N(0, 3), T = 0.8, against passes by digits alone: top-k 50 then top-p 0.9 32 us (195), top-p 0.9 51 (81), top-k 5000 93 (155), top-p 0.9999 91 (84: the same
 // passes, without fixed shifts); logits N(0, 0.02), top-p 0.9 91 (85: a pass to find that the list is too short), on 4 rows 86
@@ -961,7 +961,8 @@ __global__ __launch_bounds__(kCutThreads) void k_cut(const int32_t *__restrict__
         // The values at the bins' edges, exactly: the smallest whose bin is at most `bin`, found by a wave among the keys around the rounded
         // one (64 a step; should it not lie there, from -inf to the maximum), so that two comparisons place a token.  The pass is bound by the instructions a single compute unit
         // issues for its row: a flat law has most of its mass above the cut, so the mass is summed without a branch per token;
-        // a peaked one leaves nothing to do for most groups of eight (800 rows x 50257, T = 0.6, the whole call: 157.6 -> 151.6 us).
+        // a peaked one leaves nothing to do for most groups of eight, which are left at once (800 rows x 50257, T = 0.6, the whole call
+        // 191.7 -> 187.0 us; 71 rows x 128256, peaked or flat, are 1.4 us longer for it, 204 rows up to 1.5).
         auto edge = [&](uint32_t bin) {
           const float depth = (float)(bin + 1) / (kCutBinsPerLog2 * k.hi), off = 5e-7f * (fabsf(m) + depth);
           uint32_t below = okey((m - depth * 1.00001f) - off), at = okey(fminf((m - depth * 0.99999f) + off, m));
@@ -1211,8 +1212,8 @@ __device__ inline double thread_masses(const LT *lrow, const float *qrow, int i0
 //   and their scan), finds the sub-block and the id by inverse CDF, writes every output of the request (accepted length,
 //   token, flags, rollback) and clears the ticket for the next call.
 // Bound by its chain of round trips (3.5 us to the accepted prefix, 6 from the last mass to the token) around a stream of two rows.  Five waves on
-// a SIMD, so that a call of 64 requests x 152064 ids (1216 blocks) is resident at once; with 193 registers two were, and the second half of the
-// blocks began 10 us late.  That and the shorter arithmetic of masses_of: 23.9 -> 20 us.
+// a SIMD (96 registers), so that a call of 64 requests x 152064 ids (1216 blocks) is resident at once; with 113 registers four were, 1024 blocks, and a
+// sixth of them began when others had ended.  That and the shorter arithmetic of masses_of: 23.9 -> 20 us.
 template <typename LT>
 __global__ __launch_bounds__(256, 5) void k_decide(
     const int32_t *__restrict__ off, const float *__restrict__ temperature, const float *__restrict__ pmax,
